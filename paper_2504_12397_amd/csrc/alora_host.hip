@@ -26,6 +26,7 @@ static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 namespace {
 
 constexpr int N_SLOTS = 8;
+constexpr int QKV_STREAM_ROWS = 256;
 
 // per-sequence records travel to the device as kernel arguments (no staging buffer, no copy from host memory)
 constexpr int STAGE_SEQS = 32;
@@ -97,7 +98,7 @@ struct alora_ctx {
   int opt_splits = 0;
   int opt_gemm_splits = 0;
   int opt_gemm_tile = 0;
-  int opt_prep_split = 1;        // calls without adapters: 1: many rows take the row-per-wave RMSNorm kernel; 0: never; 2: always
+  int opt_prep_split = 1;        // calls with adapters: RMSNorm and down projection in one kernel (1: few rows; 0: never; 2: always)
   int opt_attn_waves = 0;
   int opt_lora_split = 0;        // 0 = automatic, 1 = always, 2 = never: low-rank term in workgroups of its own
   int opt_stage_copy = 0;        // 1: the staged metadata travels by hipMemcpyAsync instead of a copy kernel
@@ -227,6 +228,9 @@ struct Plan {
   bool any_adapter = false;
   bool any_prefix = false;   // some sequence reads a shared prefix
   std::vector<SeqMeta> seqs;
+  int n_used = 0;            // adapters that a row of the call may use (at most 64 listed), and their scales
+  uint8_t used[64] = {};
+  float used_scale[64] = {};
 };
 
 alora_status check_layer(alora_ctx *ctx, const alora_layer_desc *ly, bool need_tail, LayerDims *L) {
@@ -282,6 +286,8 @@ alora_status check_batch(alora_ctx *ctx, const alora_layer_desc *ly, const alora
   pl->max_len = 0;
   pl->any_adapter = false;
   pl->any_prefix = false;
+  pl->n_used = 0;
+  uint64_t listed = 0;
   for (int b = 0; b < B; ++b) {
     const int S = cu[b + 1] - cu[b];
     if (S < 0) return fail(ctx, ALORA_EINVAL, "cu_seqlens decreases at sequence %d", b);
@@ -316,7 +322,14 @@ alora_status check_batch(alora_ctx *ctx, const alora_layer_desc *ly, const alora
     m.prefix_len = plen;
     m.pad_ = 0;
     if (plen > 0) pl->any_prefix = true;
-    if (aps[b] >= 0 && S > 0 && grown > kps[b]) pl->any_adapter = true;
+    if (aps[b] >= 0 && S > 0 && grown > kps[b]) {
+      pl->any_adapter = true;
+      if (aps[b] < 64 && !((listed >> aps[b]) & 1)) {
+        listed |= 1ull << aps[b];
+        pl->used[pl->n_used] = (uint8_t)aps[b];
+        pl->used_scale[pl->n_used++] = m.scale;
+      }
+    }
     pl->max_len = std::max(pl->max_len, (int)grown);
   }
   pl->T = cu[B];
@@ -414,7 +427,7 @@ Workspace layout_workspace(char *base, const LayerDims &L, int T, size_t esz, in
   w.rm.adapter = b.take<int32_t>(T);
   w.rm.slot = b.take<int64_t>(T);
   w.rm.present16 = b.take<unsigned long long>((T + 15) / 16);
-  w.xh = b.take<char>((size_t)T * L.d * esz);
+  w.xh = b.take<char>((size_t)((T + 31) & ~31) * L.d * esz);      // (operand order comes in blocks of 32 rows)
   w.tlow = b.take<float>((size_t)T * 3 * std::max(L.rank, 1));
   w.y_floats = (size_t)T * L.n_qkv * (std::max(k_splits, 1) + 1);
   if (stack) {      // split-K partials of W_o / W_down and of the down-projections of their adapters
@@ -450,6 +463,17 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
   const bool mfma = w.mfma && std::is_same<T, bf16>::value;
   const int rank_used = pl.any_adapter ? L.rank : 0;
   const bool prep_mfma = mfma && prep_rows_mfma_supported(L.d, rank_used);      // it also leaves the adapter masks
+  // the MFMA attention kernels (prefill and decode) take their queries as fp16 (every operand of its matrix products is fp16),
+  // in its folded-softmax form premultiplied by sm_scale * log2(e)
+  // (the plain attention kernel reads them as fp32: the Q buffer holds four bytes per element)
+  const bool q_half = (w.attn_mfma || w.decode_mfma) && std::is_same<T, bf16>::value;
+  const int q_mode = q_half ? 1 : 2;
+  const float q_scale = (w.attn_mfma && q_half) ? attn_prefill_mfma_q_scale(L, ctx->opt_attn_fold != 0) : 1.0f;
+  // The projection rotates and appends by itself where a head is 128 columns.  Up to QKV_STREAM_ROWS rows the kernel that streams
+  // the weights past all rows, beyond that the one whose tiles are large in both directions; both add in one order.
+  const bool fuse = mfma && q_half && ctx->opt_rope_fuse && ctx->opt_gemm_splits <= 1 && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
+  const bool stream = fuse && prep_mfma && ctx->opt_gemm_tile == 0 && pl.T <= QKV_STREAM_ROWS &&
+                      qkv_stream_supported(pl.T, L.n_qkv, L.d, L.n_q, L.n_kv, L.head_dim);
   {
     ProfScope p(ctx, K_PREP, s);
     if (prep_mfma) {
@@ -458,29 +482,21 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       pa.T = pl.T; pa.d = L.d; pa.seqs = seqs_dev; pa.n_seqs = pl.B; pa.pos_shift = pos_shift;
       pa.one = pl.seqs[0];
       pa.A = rank_used ? (const bf16 *)ly->A : nullptr; pa.rank = rank_used;
-      pa.n_adapters = L.n_adapters;
+      if (rank_used) {
+        pa.n_used = pl.n_used;
+        memcpy(pa.used, pl.used, sizeof pa.used);
+        memcpy(pa.used_scale, pl.used_scale, sizeof pa.used_scale);
+      }
+      pa.few = ctx->opt_prep_split;
       pa.write_meta = write_meta ? 1 : 0;
-      pa.xh = (bf16 *)w.xh; pa.tlow16 = (bf16 *)w.tlow; pa.rm = w.rm;
-      // Many rows and no adapter in the call (a base-model prefill): the kernel that holds 16 rows per workgroup
-      // in registers runs one workgroup per compute unit and needs several rounds; a row-per-wave kernel does
-      // metadata and RMSNorm at streaming rate, with the same bits.
-      if (rank_used == 0 && ctx->opt_prep_split != 0 && norm_rows_mfma_supported(L.d) &&
-          (pl.T >= 512 || ctx->opt_prep_split == 2))
-        launch_norm_rows_mfma(pa, s);
-      else
-        launch_prep_rows_mfma(pa, s);
+      pa.xh = (bf16 *)w.xh; pa.packed = stream ? 1 : 0; pa.tlow16 = (bf16 *)w.tlow; pa.rm = w.rm;
+      launch_prep_rows_mfma(pa, s);
     } else {
       launch_prep_rows<T>(x, (const T *)ly->rms_gain, ly->rms_eps, pl.T, L.d, seqs_dev, pl.B, pos_shift,
                           (const T *)ly->A, rank_used, write_meta, (T *)w.xh, w.tlow, mfma ? (bf16 *)w.tlow : nullptr, w.rm, s);
     }
   }
   if (w.rope_by_row) launch_rope_rows(w.rope_rows, w.rm.pos, pl.T, L.head_dim / 2, ly->rope_theta, s);
-  // the MFMA attention kernels (prefill and decode) take their queries as fp16 (every operand of its matrix products is fp16),
-  // in its folded-softmax form premultiplied by sm_scale * log2(e)
-  // (the plain attention kernel reads them as fp32: the Q buffer holds four bytes per element)
-  const bool q_half = (w.attn_mfma || w.decode_mfma) && std::is_same<T, bf16>::value;
-  const int q_mode = q_half ? 1 : 2;
-  const float q_scale = (w.attn_mfma && q_half) ? attn_prefill_mfma_q_scale(L, ctx->opt_attn_fold != 0) : 1.0f;
   bool rope_fused = false;
   {
     ProfScope p(ctx, K_QKV, s);
@@ -501,14 +517,14 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       g.n_q = L.n_q; g.n_kv = L.n_kv;
       g.row_adapter = w.rm.adapter;
       g.present16 = prep_mfma ? w.rm.present16 : nullptr;
-      // many rows, unsplit reduction, one head per column tile: rotation and cache append happen in the
-      // projection's epilogue and the fp32 projection never goes to memory
-      if (ctx->opt_gemm_tile == 0 && ctx->opt_rope_fuse && q_half && !w.rope_by_row &&
-          gemm_mfma_rope_supported(g, L.head_dim)) {
-        g.rope_pos = w.rm.pos; g.rope_slot = w.rm.slot; g.rope_table = w.rope; g.q_scale = q_scale;
-        g.Qout = (bf16 *)w.Q; g.cacheK = (bf16 *)cache->k; g.cacheV = (bf16 *)cache->v;
-        g.q_half = q_half ? 1 : 0;
-        launch_gemm_mfma(g, GEMM_EPI_ROPE, s);
+      g.rope_pos = w.rm.pos; g.rope_slot = w.rm.slot; g.rope_table = w.rope; g.q_scale = q_scale;
+      g.rope_by_row = w.rope_by_row ? 1 : 0;
+      g.Qout = (bf16 *)w.Q; g.cacheK = (bf16 *)cache->k; g.cacheV = (bf16 *)cache->v;
+      if (stream) {
+        launch_qkv_stream(g, ctx->n_cu, s);
+        rope_fused = true;
+      } else if (fuse && !w.rope_by_row && pl.T > 256 && gemm_mfma_rope_supported(g, L.head_dim)) {
+        launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, GEMM_EPI_ROPE, ctx->n_cu, 1).rows, s);
         rope_fused = true;
       } else {
         launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
@@ -605,6 +621,20 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     if (ctx->opt_gemm_splits > 0) return K % (64 * ctx->opt_gemm_splits) == 0 ? ctx->opt_gemm_splits : 1;
     return gemm_mfma_fixed_segments(N, K, ctx->n_cu);
   };
+  // Many rows with default splits: the large-tile kernel, whose partial sums (when it takes several workgroups per output tile)
+  // land in Y.  Returns their number, 0: not this way, 1: C is written.
+  auto large = [&](GemmArgs &g) -> int {
+    if (T_rows <= 256 || ctx->opt_gemm_splits != 0 || g.tile_hint == 1 || g.tile_hint >= 4) return 0;
+    int most = 4;
+    while (most > 1 && ((size_t)most * T_rows * g.N > w.y_floats || (uint64_t)T_rows * g.lda * 2 >= (1ull << 31))) most /= 2;
+    const GemmLargePlan pn = gemm_large_plan(g.tile_hint, g, GEMM_EPI_BF16, ctx->n_cu, most);
+    g.k_splits = pn.splits;
+    const int epi = pn.splits > 1 ? GEMM_EPI_PARTIAL : GEMM_EPI_BF16;
+    if (!gemm_large_supported(g, epi)) return 0;
+    g.Cpart = w.Y;
+    launch_gemm_large(g, epi, pn.rows, s);
+    return pn.splits;
+  };
   // C = A W^T (+ R), with the gated low-rank term of (Al, Bl) when given
   auto dense = [&](const void *A, const void *W, const void *R, void *C, int N, int K, const void *Al, const void *Bl,
                    int parts = 1, int part = 0) {
@@ -615,8 +645,13 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
       g.A = (const bf16 *)A; g.lda = K;
       g.B = (const bf16 *)W; g.ldb = K;
       g.M = T_rows; g.N = N; g.K = K;
-      g.tile_hint = (ctx->opt_gemm_tile >= 4 || ctx->opt_gemm_tile == 1) ? ctx->opt_gemm_tile : 0;
+      g.tile_hint = ctx->opt_gemm_tile;
       if (lr) set_lowrank(g, Bl, nullptr, 1, N);
+      g.C = (bf16 *)C; g.ldc = N; g.R = (const bf16 *)R;
+      if (const int n = large(g)) {
+        if (n > 1) launch_splitk_reduce(w.Y, n, (int64_t)T_rows * N, (const bf16 *)R, (bf16 *)C, s);
+        return;
+      }
       // few row tiles: every segment gets workgroups of its own to fill the chip, the segment sums go through
       // the Y buffer; otherwise one workgroup adds them itself, in the same order
       const int segs = segments_of(N, K);
@@ -629,7 +664,6 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
         launch_splitk_reduce(w.Y, segs, (int64_t)T_rows * N, (const bf16 *)R, (bf16 *)C, s);
       } else {
         g.k_splits = 1;
-        g.C = (bf16 *)C; g.ldc = N; g.R = (const bf16 *)R;
         launch_gemm_mfma(g, GEMM_EPI_BF16, s);
       }
     } else if (w.f0 != nullptr) {
@@ -652,24 +686,34 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
   {
     ProfScope p(ctx, K_OPROJ, s);
     const int splits = mfma ? segments_of(L.d, L.n_q) : 1;
-    if (mfma && splits > 1 && gemm_mfma_split_segments(T_rows, L.d, ctx->n_cu) &&
-        (size_t)splits * T_rows * L.d <= w.y_floats && splitk_reduce_norm_supported(L.d)) {
+    const bool few = splits > 1 && gemm_mfma_split_segments(T_rows, L.d, ctx->n_cu) && (size_t)splits * T_rows * L.d <= w.y_floats;
+    if (mfma && splitk_reduce_norm_supported(L.d) && (few || T_rows > 256)) {
       GemmArgs g{};
       g.A = (const bf16 *)w.attn; g.lda = L.n_q;
       g.B = (const bf16 *)ly->W_o; g.ldb = L.n_q;
       g.M = T_rows; g.N = L.d; g.K = L.n_q;
-      g.tile_hint = (ctx->opt_gemm_tile >= 4 || ctx->opt_gemm_tile == 1) ? ctx->opt_gemm_tile : 0;
+      g.tile_hint = ctx->opt_gemm_tile;
       if (ly->A_o && w.any_adapter) {
         lowrank_t(w.attn, L.n_q, ly->A_o, 1);
         set_lowrank(g, ly->B_o, nullptr, 1, L.d);
       }
-      g.k_splits = splits;
-      g.k_segments = splits;
-      g.Cpart = w.Y;
-      launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
-      launch_splitk_reduce_norm(w.Y, splits, T_rows, L.d, (const bf16 *)x, (const bf16 *)ly->rms2_gain, ly->rms_eps,
-                                (bf16 *)w.h1, (bf16 *)w.hn, s);
-      normed = true;
+      g.C = (bf16 *)w.h1; g.ldc = L.d; g.R = (const bf16 *)x;
+      int parts = large(g);
+      if (parts == 0 && few) {
+        g.k_splits = parts = splits;
+        g.k_segments = splits;
+        g.Cpart = w.Y;
+        launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
+      }
+      if (parts > 1) {
+        launch_splitk_reduce_norm(w.Y, parts, T_rows, L.d, (const bf16 *)x, (const bf16 *)ly->rms2_gain, ly->rms_eps,
+                                  (bf16 *)w.h1, (bf16 *)w.hn, s);
+        normed = true;
+      } else if (parts == 0) {
+        g.k_splits = 1;
+        g.k_segments = splits;
+        launch_gemm_mfma(g, GEMM_EPI_BF16, s);
+      }
     } else {
       dense(w.attn, ly->W_o, x, w.h1, L.d, L.n_q, ly->A_o, ly->B_o);
     }
@@ -692,7 +736,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     g.A = (const bf16 *)w.hn; g.lda = L.d;
     g.B = (const bf16 *)ly->W_gate; g.B2 = (const bf16 *)ly->W_up; g.ldb = L.d;
     g.M = T_rows; g.N = 2 * ly->intermediate; g.K = L.d; g.k_splits = 1; g.k_segments = 1;
-    g.tile_hint = (ctx->opt_gemm_tile >= 4 || ctx->opt_gemm_tile == 1) ? ctx->opt_gemm_tile : 0;
+    g.tile_hint = ctx->opt_gemm_tile;
     if (ly->A_gu && w.any_adapter) {
       lowrank_t(w.hn, L.d, ly->A_gu, 2);
       set_lowrank(g, ly->B_gate, ly->B_up, 2, ly->intermediate);
@@ -1032,12 +1076,11 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   const int dec_hw = dp.hw, dec_kr = dp.kr, dec_groups = dp.groups, dec_cols_max = dp.cols_max;
   // kernel family: MFMA for bf16 shapes it covers, plain otherwise
   const bool mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && L.d % 64 == 0 &&
-                    (L.n_adapters == 0 || (L.rank % 16 == 0 && L.n_adapters <= 64)) && L.n_q % 32 == 0 &&
+                    (L.n_adapters == 0 || (L.rank % 8 == 0 && L.n_adapters <= 64)) && L.n_q % 32 == 0 &&
                     L.n_kv % 32 == 0 && (!stack || (layers[0].intermediate % 64 == 0 && L.n_q % 64 == 0));
-  // The reduction axis of the QKV projection is cut into segments fixed by the weight shape (or by the
-  // gemm_splits option); whether they run in workgroups of their own or one after the other inside one
-  // is a scheduling choice that does not change a single bit of the result.
-  int k_segments = mfma ? gemm_mfma_fixed_segments(L.n_qkv, L.d, ctx->n_cu) : 1;
+  // The reduction axis of the QKV projection is one running sum (or gemm_splits segments, added in order: whether they run in
+  // workgroups of their own or one after the other inside one does not change a bit of the result).
+  int k_segments = 1;
   if (mfma && ctx->opt_gemm_splits > 0) k_segments = L.d % (64 * ctx->opt_gemm_splits) == 0 ? ctx->opt_gemm_splits : 1;
   const int k_splits = (k_segments > 1 && gemm_mfma_split_segments(pl.T, L.n_qkv, ctx->n_cu)) ? k_segments : 1;
   const bool f32_tail = stack && !mfma && layers[0].dtype == ALORA_BF16;

@@ -1,7 +1,7 @@
 // Plain kernels: every step of the path in straightforward fp32-FMA HIP, for any dtype and
 // any shape.  They are the fp32 path (small single-block configuration) and the fallback
 // for shapes the MFMA kernels do not cover.
-#include "common.h"
+#include "lds_dma.h"
 
 namespace alora {
 
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void rope_append_kernel(const float *__restric
     for (int c = lane; c < h2; c += 64) {
       const float u = ysum(y + base + c), w = ysum(y + base + c + h2);
       const float2 cs = tab[c];
-      const float lo = (u * cs.x - w * cs.y) * qs, hi = (w * cs.x + u * cs.y) * qs;
+      const float lo = rope_lo(u, w, cs.x, cs.y) * qs, hi = rope_hi(u, w, cs.x, cs.y) * qs;
       if (is_q && q_half == 1) {
         // the MFMA attention kernels want their queries as fp16
         _Float16 *dq = reinterpret_cast<_Float16 *>(Q) + (int64_t)row * L.n_q + head * h;

@@ -1,12 +1,13 @@
-// Row preparation with MFMA (bf16): per-row metadata, RMSNorm, and the low-rank down projection
-// t = s_a * A_a x_hat (Eq.6, Delta applied right to left) for 16 packed rows per workgroup.
+// Row preparation (bf16): per-row metadata, RMSNorm, and the low-rank down projection t = s_a * A_a x_hat (Eq.6, Delta applied
+// right to left).
 //
-// Eight waves split the hidden dimension (d = 512, 1024, 2048 or 4096); each lane owns 8 consecutive
-// elements of one row at a time, which is both the 16-byte global access and the A-operand layout of
-// v_mfma_f32_16x16x32_bf16 (lane l: row l%16, k = 8*(l/16)..+7), so the normalised row goes from
-// registers straight into the MFMA and into the x_hat store; LDS is used only for the row
-// statistics and the fixed-order sum of the eight partial accumulators.
-#include "mfma_kernels.h"
+// Three kernels.  norm_rows: metadata and RMSNorm, a wave per row (or four), for calls without adapters and for many
+// rows.  t_rows: t for many rows, from the normalised rows (which the caches still hold).  prep_few: both in one launch for few
+// rows, where every round trip and every launch counts: the workgroups of a row tile each normalise it again (registers
+// to matrix operand, no memory between) and compute 16 columns of one adapter's t.
+// With T rows of four rank-32 adapters at d = 4096 the one kernel that used to do it all (16 rows per workgroup, all columns)
+// took 41 us at T = 512 and 81 us at T = 4458.
+#include "lds_dma.h"
 
 namespace alora {
 
@@ -16,10 +17,11 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int PREP_ROWS = 16;
 constexpr int PREP_WAVES = 8;
+constexpr int PREP_FEW = 512;      // workgroups
 
 // Sum of squares of a row, in ONE order for every kernel that normalises rows (a row's x_hat must not depend on
 // which of them ran -- the base rows of a long prefill and of a decode step are compared bit for bit): the
-// row is cut into 16-byte chunks, chunk index c = 64 w + 4 u + g (w < 8, u < d / 256, g < 4); a chunk's eight
+// row is cut into 16-byte chunks, chunk index c = 4 CH w + 4 u + g (w < 8, u < CH = d / 256, g < 4); a chunk's eight
 // squares are added in order starting from zero; the chunk sums of one (w, g) go through a balanced tree over u
 // (neighbours first), the four g of a w through a tree (g ^ 1, then g ^ 2), the eight w are added in order.
 __device__ __forceinline__ float chunk_ssq(u32x4 c) {
@@ -36,6 +38,10 @@ __device__ __forceinline__ u32x4 norm_chunk(u32x4 x, u32x4 g, float rinv) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) xh[e] = (bf16)((float)xv[e] * (float)gv[e] * rinv);
   return __builtin_bit_cast(u32x4, xh);
+}
+// 16-byte chunk c of a row in x_hat: row-major, or in the order of the matrix operand (PrepArgs::packed)
+__device__ __forceinline__ int64_t xh_chunk(int row, int c, int d, int packed) {
+  return packed ? ((int64_t)(row >> 5) * (d >> 4) + (c >> 1)) * 64 + (row & 31) + 32 * (c & 1) : (int64_t)row * (d >> 3) + c;
 }
 // Metadata of the rows [row0, tile_end) of one tile: a thread takes a sequence, fetches its record once and fills
 // in the rows of the tile that belong to it -- one memory round trip, where a search over the sequence table
@@ -56,85 +62,59 @@ __device__ __forceinline__ void fill_row_meta(const PrepArgs &a, const SeqMeta &
   if (adapter >= 0) atomicOr(s_present, 1ull << adapter);
 }
 
-// NF = 16-column fragments of t this workgroup computes (0: no adapter work).  The 3*rank columns
-// of t are spread over gridDim.y workgroups so that short batches still fill the chip; group 0
-// also writes x_hat and the row metadata.  CH = d / 256: 16-byte chunks of its row each lane
-// holds.  x is read from memory once: the chunks stay in registers from the sum of squares to the
-// normalised store and the MFMAs, and every phase issues all its loads before the first use, so
-// the kernel pays about three memory round trips in total.
-// EARLY (single-sequence batches with NF == 1): the sequence record comes with the kernel arguments, so the
-// adapter of the tile is known at once and its A fragments are requested together with x instead of after
-// the metadata and normalisation phases -- one dependent memory round trip less on a kernel that is nothing
-// but round trips at these sizes.
-template <int NF, int CH, bool EARLY = false>
-__global__ __launch_bounds__(512, 2) void prep_rows_mfma_kernel(PrepArgs a) {
+// Few rows with adapters (up to PREP_FEW workgroups): workgroup (x, y, z) takes row tile x (16 rows), columns 16 y .. of the 3 * rank columns of t and
+// adapter used[z]; the first of a tile also writes x_hat and the row metadata.  Eight waves split the hidden dimension; a lane
+// owns 8 consecutive elements of one row at a time, which is both the 16-byte global access and the operand layout of
+// v_mfma_f32_16x16x32_bf16 (lane l: row l % 16, k = 8 * (l / 16) ..).  CH = d / 256: chunks of its row a lane holds.
+// The kernel is memory round trips and little else, so everything is requested at once: x, the gain, the sequences' records
+// and this adapter's down matrix, before anybody knows whether a row of the tile uses it.
+template <int CH>
+__global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   __shared__ float s_ssq[PREP_WAVES][PREP_ROWS];
   __shared__ int s_adapter[PREP_ROWS];
   __shared__ float s_scale[PREP_ROWS];
   __shared__ unsigned long long s_present;
   __shared__ u32x4 s_gain[CH * 32];          // d / 8 chunks of the gain
-  extern __shared__ float s_part[];          // [PREP_WAVES][PREP_ROWS][16 * NF]
+  __shared__ float s_part[PREP_WAVES][PREP_ROWS][17];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kg = lane >> 4;
   const int row0 = blockIdx.x * PREP_ROWS;
-  const int d = a.d;                            // = CH * 256
-  const int col0 = blockIdx.y * 16 * NF;       // first column of t handled here
-  // gridDim.z > 1 (short batches of several sequences): workgroup z does the pass of adapter z only -- the passes
-  // of the adapters present in a row tile, each a memory round trip of its own, then run side by side
-  const int only = gridDim.z > 1 ? (int)blockIdx.z : -1;
+  constexpr int d = CH * 256;
+  const int rank = a.rank, col0 = blockIdx.y * 16, ad = a.used[blockIdx.z];
   const bool lead = blockIdx.y == 0 && blockIdx.z == 0;
   const int row = min(row0 + r16, a.T - 1);
   const bool row_ok = row0 + r16 < a.T;
   const int k_lo = wave * (CH * 32) + kg * 8;  // this lane's first element; chunk u is at k_lo + 32 u
 
-  // ---- all of this lane's x (and gain) chunks, issued at once ----------------------------------
-  // (the gain goes through LDS: one 16-byte chunk per thread instead of CH of them in every lane's registers)
-  u32x4 xr[CH], gown = u32x4{0, 0, 0, 0};
+  u32x4 xr[CH], br[CH], gown = u32x4{0, 0, 0, 0};
   const bf16 *xrow = a.x + (int64_t)row * d + k_lo;
 #pragma unroll
   for (int u = 0; u < CH; ++u) xr[u] = *reinterpret_cast<const u32x4 *>(xrow + 32 * u);
+  // (the gain goes through LDS: one 16-byte chunk per thread instead of CH of them in every lane's registers)
   if (a.gain != nullptr && tid < d / 8) gown = *reinterpret_cast<const u32x4 *>(a.gain + tid * 8);
-
-  // EARLY: A fragments of the sequence's adapter, if any row of the tile is adapted
-  u32x4 bpre[EARLY ? CH : 1][EARLY && NF > 0 ? NF : 1];
-  bool pre_loaded = false;
-  if constexpr (EARLY && NF > 0) {
-    const SeqMeta &o = a.one;
-    const int last = min(row0 + PREP_ROWS, a.T) - 1;
-    pre_loaded = o.adapter >= 0 && o.P + a.pos_shift + (last - o.row_start) >= o.k;
-    if (pre_loaded) {
-      const bf16 *Ab = a.A + ((int64_t)o.adapter * 3 * a.rank + col0 + r16) * d + k_lo;
+  const int my_col = min(col0 + r16, 3 * rank - 1);      // (3 * rank need not be a multiple of 16)
+  const bf16 *Ab = a.A + ((int64_t)ad * 3 * rank + my_col) * d + k_lo;
 #pragma unroll
-      for (int u = 0; u < CH; ++u)
-#pragma unroll
-        for (int j = 0; j < NF; ++j) bpre[u][j] = *reinterpret_cast<const u32x4 *>(Ab + (int64_t)j * 16 * d + 32 * u);
-    }
-  }
+  for (int u = 0; u < CH; ++u) br[u] = *reinterpret_cast<const u32x4 *>(Ab + 32 * u);
 
   if (tid == 0) s_present = 0ull;
   if (tid < PREP_ROWS) { s_adapter[tid] = -1; s_scale[tid] = 0.f; }
   __syncthreads();
-  // Row metadata.  With one sequence (EARLY: its record came with the arguments) a thread takes a row.
-  // Otherwise a thread takes a sequence: it fetches the sequence record once and fills in the rows of this
-  // tile that belong to it -- one memory round trip, where a search over the sequence table per row costs
-  // log2(n_seqs) dependent ones.
   const int tile_end = min(row0 + PREP_ROWS, a.T);
   auto fill_row = [&](const SeqMeta &sm, int sq, int mrow) {
     fill_row_meta(a, sm, sq, mrow, row0, a.write_meta && lead, s_adapter, s_scale, &s_present);
   };
-  if constexpr (EARLY) {
+  if (a.n_seqs == 1) {      // (the record came with the kernel arguments)
     if (tid < PREP_ROWS && row0 + tid < tile_end) fill_row(a.one, 0, row0 + tid);
   } else {
-    for (int sq = tid; sq < (a.seqs != nullptr ? a.n_seqs : 0); sq += 512) {
+    for (int sq = tid; sq < a.n_seqs; sq += 512) {
       const SeqMeta sm = a.seqs[sq];
       const int lo = max(sm.row_start, row0), hi = min(sm.row_start + sm.n_new, tile_end);
       for (int mrow = lo; mrow < hi; ++mrow) fill_row(sm, sq, mrow);
     }
   }
 
-  // ---- sum of squares: lane -> the 4 lanes of a row -> the 8 waves (fixed order) ------------------
-  float rinv = 1.f;
   if (a.gain != nullptr) {
     float cs[CH];
 #pragma unroll
@@ -155,123 +135,34 @@ __global__ __launch_bounds__(512, 2) void prep_rows_mfma_kernel(PrepArgs a) {
     float t = 0.f;
 #pragma unroll
     for (int w = 0; w < PREP_WAVES; ++w) t += s_ssq[w][r16];
-    rinv = row_rinv(t, d, a.eps);
-    // normalise in place: x_hat = bf16(x * g * rinv)
+    const float rinv = row_rinv(t, d, a.eps);
 #pragma unroll
     for (int u = 0; u < CH; ++u) xr[u] = norm_chunk(xr[u], s_gain[(k_lo >> 3) + 4 * u], rinv);
   }
   if (lead && row_ok) {
-    bf16 *dst = a.xh + (int64_t)row * d + k_lo;
+    u32x4 *dst = reinterpret_cast<u32x4 *>(a.xh);
 #pragma unroll
-    for (int u = 0; u < CH; ++u) *reinterpret_cast<u32x4 *>(dst + 32 * u) = xr[u];
+    for (int u = 0; u < CH; ++u) dst[xh_chunk(row, (k_lo >> 3) + 4 * u, d, a.packed)] = xr[u];
   }
+  if (!((s_present >> ad) & 1)) return;
 
-  // ---- t partials over this wave's slice of d, one pass per adapter present in the row tile -------
-  const int my_adapter = s_adapter[r16];
-  const unsigned long long present = NF > 0 ? (only >= 0 ? s_present & (1ull << only) : s_present) : 0ull;
-  const int rank = a.rank;
-  f32x4 acc[NF > 0 ? NF : 1];
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool mine = s_adapter[r16] == ad;
 #pragma unroll
-  for (int j = 0; j < (NF > 0 ? NF : 1); ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (NF > 0) {
-    constexpr int NFX = NF > 0 ? NF : 1;
-    // chunks per load batch: about 16 fragments, a power of two so that it divides CH
-    constexpr int UBN = NFX >= 9 ? 1 : NFX >= 5 ? 2 : NFX >= 3 ? 4 : NFX == 2 ? 8 : 16;
-    constexpr int UB0 = UBN > CH ? CH : UBN;
-    constexpr int UB = UB0;
-    if constexpr (EARLY) {
-      if (pre_loaded) {
-        const bool mine = my_adapter == a.one.adapter;
-#pragma unroll
-        for (int u = 0; u < CH; ++u) {
-          const u32x4 au = mine ? xr[u] : u32x4{0, 0, 0, 0};
-#pragma unroll
-          for (int j = 0; j < NFX; ++j)
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, au),
-                                                             __builtin_bit_cast(bf16x8, bpre[u][j]), acc[j], 0, 0, 0);
-        }
-      }
-    }
-    // One pass over the lane's chunks per adapter present in the tile, in batches of UB chunks.  Every batch
-    // of A fragments is a memory round trip, so two register buffers alternate: the next batch -- the next
-    // adapter's first one at the end of a pass -- is requested before the current one is multiplied.
-    unsigned long long todo = EARLY ? 0ull : present;
-    auto next_adapter = [&]() {
-      if (!todo) return -1;
-      const int ad = __builtin_ctzll(todo);
-      todo &= todo - 1;
-      return ad;
-    };
-    auto load_batch = [&](int ad, int u0, u32x4 (&br)[UB][NFX]) {
-      const bf16 *Ab = a.A + ((int64_t)ad * 3 * rank + col0 + r16) * d + k_lo;     // row col0 + 16 j + r16
-#pragma unroll
-      for (int u = 0; u < UB; ++u)
-#pragma unroll
-        for (int j = 0; j < NFX; ++j)
-          br[u][j] = *reinterpret_cast<const u32x4 *>(Ab + (int64_t)j * 16 * d + 32 * (u0 + u));
-    };
-    auto mma_batch = [&](int ad, int u0, const u32x4 (&br)[UB][NFX]) {
-      const bool mine = my_adapter == ad;
-#pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        const u32x4 au = mine ? xr[u0 + u] : u32x4{0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < NFX; ++j)
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, au),
-                                                           __builtin_bit_cast(bf16x8, br[u][j]), acc[j], 0, 0, 0);
-      }
-    };
-    constexpr int NB = CH / UB;        // batches per pass
-    static_assert(CH % UB == 0, "batches cover the lane's chunks exactly");
-    if constexpr (NB % 2 == 0) {
-      u32x4 br0[UB][NFX], br1[UB][NFX];
-      int ad = next_adapter();
-      if (ad >= 0) load_batch(ad, 0, br0);
-      while (ad >= 0) {
-        const int nx = next_adapter();
-#pragma unroll
-        for (int u0 = 0; u0 < CH; u0 += 2 * UB) {
-          load_batch(ad, u0 + UB, br1);
-          mma_batch(ad, u0, br0);
-          if (u0 + 2 * UB < CH) load_batch(ad, u0 + 2 * UB, br0);
-          else if (nx >= 0) load_batch(nx, 0, br0);
-          mma_batch(ad, u0 + UB, br1);
-        }
-        ad = nx;
-      }
-    } else {
-      static_assert(NB == 1, "batches per pass: one or an even number");
-      u32x4 br0[UB][NFX], br1[UB][NFX];      // one batch per pass: adapters alternate between the buffers
-      int ad = next_adapter();
-      if (ad >= 0) load_batch(ad, 0, br0);
-      while (ad >= 0) {
-        const int nx = next_adapter();
-        if (nx >= 0) load_batch(nx, 0, br1);
-        mma_batch(ad, 0, br0);
-        if (nx < 0) break;
-        ad = next_adapter();
-        if (ad >= 0) load_batch(ad, 0, br0);
-        mma_batch(nx, 0, br1);
-      }
-    }
+  for (int u = 0; u < CH; ++u) {
+    const u32x4 au = mine ? xr[u] : u32x4{0, 0, 0, 0};
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, au), __builtin_bit_cast(bf16x8, br[u]), acc, 0, 0, 0);
   }
-
-  if (NF > 0 && present) {
-    // accumulator register v of lane l is T[row 4*(l/16) + v][column 16*j + l%16]
-    float *mine = s_part + (size_t)wave * PREP_ROWS * 16 * NF;
+  // accumulator register v of lane l is T[row 4*(l/16) + v][column l%16]
 #pragma unroll
-    for (int j = 0; j < NF; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) mine[(4 * kg + v) * 16 * NF + j * 16 + r16] = acc[j][v];
-    __syncthreads();
-    const int n_out = PREP_ROWS * 16 * NF;       // 16 rows x 3*rank columns
-    for (int i = tid; i < n_out; i += 512) {
-      const int lr = i / (16 * NF), col = i % (16 * NF);
-      const int orow = row0 + lr;
-      if (orow >= a.T || s_adapter[lr] < 0 || (only >= 0 && s_adapter[lr] != only)) continue;
+  for (int v = 0; v < 4; ++v) s_part[wave][4 * kg + v][r16] = acc[v];
+  __syncthreads();
+  if (tid < PREP_ROWS * 16) {
+    const int lr = tid >> 4, col = tid & 15, orow = row0 + lr;
+    if (orow < a.T && s_adapter[lr] == ad && col0 + col < 3 * rank) {
       float t = 0.f;
 #pragma unroll
-      for (int w = 0; w < PREP_WAVES; ++w) t += s_part[(size_t)w * n_out + i];
+      for (int w = 0; w < PREP_WAVES; ++w) t += s_part[w][lr][col];
       t *= s_scale[lr];
       const int p = (col0 + col) / rank, jj = (col0 + col) % rank;
       const bf16 hi = (bf16)t;
@@ -282,17 +173,17 @@ __global__ __launch_bounds__(512, 2) void prep_rows_mfma_kernel(PrepArgs a) {
   }
 }
 
-// Many rows at d = 4096 and no adapter in the call (a base-model prefill): metadata and RMSNorm only.  A wave takes
-// four consecutive rows whole -- every load and store instruction covers 1 KB of one row, 32 KB are in flight per
-// wave -- sixteen rows per workgroup of four waves, several workgroups per compute unit; the 16-rows-per-tile
-// kernel above holds a whole tile in registers, runs one workgroup per compute unit and needs a second round of
-// workgroups from 4097 rows on.  Same arithmetic in the same order: lane l holds the chunks c = l + 64 j, so
-// l = 4 u + g and j = w in the terms of chunk_ssq's order.
-__global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
+// Metadata and RMSNorm, 16 rows per workgroup of 16 / RW waves, RW rows per wave.  A wave takes its rows whole -- every load and
+// store instruction covers 1 KB of one row -- and the only wait besides the rows themselves is the sequences' records.  One row
+// per wave while that still fills the chip, four rows (32 KB in flight) for long calls.  Memory-bound: 21 us at 4096 rows of 4096.
+// Lane l holds the chunks c = l + 64 j: in the terms of chunk_ssq's order, a lane group of 4 CH lanes is one w.
+template <int CH, int RW>
+__global__ __launch_bounds__(64 * (PREP_ROWS / RW)) void norm_rows_kernel(PrepArgs a) {
   __shared__ unsigned long long s_present;
+  constexpr int NT = 64 * (PREP_ROWS / RW);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row0 = blockIdx.x * PREP_ROWS;
-  constexpr int D = 4096, NJ = D / 512, RW = PREP_ROWS / 4;      // rows per wave
+  constexpr int D = CH * 256, NJ = D / 512;
   const int wrow0 = row0 + wave * RW;
   u32x4 xr[RW][NJ], gr[NJ];
 #pragma unroll
@@ -306,16 +197,23 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) gr[j] = *reinterpret_cast<const u32x4 *>(a.gain + lane * 8 + 512 * j);
   }
-  if (tid == 0) s_present = 0ull;
-  __syncthreads();
-  const int tile_end = min(row0 + PREP_ROWS, a.T);
-  for (int sq = tid; sq < (a.seqs != nullptr ? a.n_seqs : 0); sq += 256) {
-    const SeqMeta sm = a.seqs[sq];
-    const int lo = max(sm.row_start, row0), hi = min(sm.row_start + sm.n_new, tile_end);
-    for (int mrow = lo; mrow < hi; ++mrow) fill_row_meta(a, sm, sq, mrow, row0, a.write_meta != 0, nullptr, nullptr, &s_present);
+  if (a.seqs != nullptr && a.write_meta) {
+    if (tid == 0) s_present = 0ull;
+    __syncthreads();
+    const int tile_end = min(row0 + PREP_ROWS, a.T);
+    if (a.n_seqs == 1) {
+      if (tid < PREP_ROWS && row0 + tid < tile_end) fill_row_meta(a, a.one, 0, row0 + tid, row0, true, nullptr, nullptr, &s_present);
+    } else {
+      for (int sq = tid; sq < a.n_seqs; sq += NT) {
+        const SeqMeta sm = a.seqs[sq];
+        const int lo = max(sm.row_start, row0), hi = min(sm.row_start + sm.n_new, tile_end);
+        for (int mrow = lo; mrow < hi; ++mrow) fill_row_meta(a, sm, sq, mrow, row0, true, nullptr, nullptr, &s_present);
+      }
+    }
+    __syncthreads();
+    if (tid == 0 && a.rm.present16 != nullptr) a.rm.present16[blockIdx.x] = s_present;
   }
-  __syncthreads();
-  if (tid == 0 && a.rm.present16 != nullptr) a.rm.present16[blockIdx.x] = s_present;
+  constexpr int GL = 4 * CH, GW = 64 / GL;      // lanes of one w, and how many w a chunk row j of the wave covers
 #pragma unroll
   for (int i = 0; i < RW; ++i) {
     if (a.gain != nullptr) {
@@ -323,87 +221,141 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         float v = chunk_ssq(xr[i][j]);
-        v += __shfl_xor(v, 4, 64);       // tree over u (lane bits 2..5), neighbours first
-        v += __shfl_xor(v, 8, 64);
-        v += __shfl_xor(v, 16, 64);
-        v += __shfl_xor(v, 32, 64);
-        v += __shfl_xor(v, 1, 64);       // tree over g (lane bits 0, 1)
+#pragma unroll
+        for (int o = 4; o < GL; o *= 2) v += __shfl_xor(v, o, 64);      // tree over u, neighbours first
+        v += __shfl_xor(v, 1, 64);                                     // tree over g
         v += __shfl_xor(v, 2, 64);
-        t += v;                          // the eight w in order
+#pragma unroll
+        for (int w = 0; w < GW; ++w) t += GW == 1 ? v : __shfl(v, w * GL, 64);      // the eight w in order
       }
       const float rinv = row_rinv(t, D, a.eps);
 #pragma unroll
       for (int j = 0; j < NJ; ++j) xr[i][j] = norm_chunk(xr[i][j], gr[j], rinv);
     }
     if (wrow0 + i < a.T) {
-      bf16 *dst = a.xh + (int64_t)(wrow0 + i) * D + lane * 8;
+      u32x4 *dst = reinterpret_cast<u32x4 *>(a.xh);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) *reinterpret_cast<u32x4 *>(dst + 512 * j) = xr[i][j];
+      for (int j = 0; j < NJ; ++j) dst[xh_chunk(wrow0 + i, lane + 64 * j, D, a.packed)] = xr[i][j];
     }
   }
 }
 
-bool norm_rows_mfma_supported(int d) { return d == 4096; }
-void launch_norm_rows_mfma(const PrepArgs &a, hipStream_t s) {
-  if (a.T == 0) return;
-  hipLaunchKernelGGL(norm_rows_kernel, dim3((a.T + PREP_ROWS - 1) / PREP_ROWS), dim3(256), 0, s, a);
+// t of many rows from x_hat: workgroup (x, y, z) takes 32 rows, columns 96 y .. of the 3 * rank and adapter used[z]; it leaves at
+// once when no row of its tile uses that adapter.  What bounds it: 1 MB (down matrix and rows) through one compute unit, which
+// loads to registers in operand order brought in at 28 bytes per ns (36 us); requests to LDS arrive at 130.  128 values of k per
+// step, four steps in the ring; wave w multiplies the 16 values 16 w .. of a step, the eight sums are added in wave order.
+// LDS rows are 256 bytes, chunk c of row i at c ^ (i & 15); x_hat in operand order needs no rows (1 KB per 16 values of k).
+constexpr int T_STEP = 32 * 1024;
+__global__ __launch_bounds__(512) void t_rows_kernel(PrepArgs a) {
+  extern __shared__ u32x4 smem[];
+  char *lds = reinterpret_cast<char *>(smem);
+  typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, lhi = lane >> 5;
+  const int row0 = blockIdx.x * 32, ad = a.used[blockIdx.z], cols = 3 * a.rank, d = a.d;
+  const int col0 = blockIdx.y * 96, nb = min(3, (cols - col0 + 31) / 32);
+  const int my_row = row0 + (tid >> 4), mine = a.rm.adapter[min(my_row, a.T - 1)];      // (of the row this thread finishes)
+  const int g0 = row0 / 16, g1 = min(g0 + 1, (a.T - 1) / 16);
+  if (!(((a.rm.present16[g0] | a.rm.present16[g1]) >> ad) & 1)) return;
+
+  const i32x4 rx = make_rsrc(a.xh, (uint64_t)((a.T + 31) & ~31) * d * 2);
+  const i32x4 rw = make_rsrc(a.A + ((int64_t)ad * cols + col0) * d, (uint64_t)(cols - col0) * d * 2);      // rows past the end: zeros
+  const int r4 = lane >> 4, pos = lane & 15;
+  int vx, vw[3];
+  if (a.packed) vx = (row0 >> 5) * (d >> 4) * 1024 + wave * 1024 + lane * 16;
+  else vx = min(row0 + 4 * wave + r4, a.T - 1) * d * 2 + (pos ^ ((4 * wave + r4) & 15)) * 16;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const int i = 4 * (3 * wave + j) + r4;
+    vw[j] = i * d * 2 + (pos ^ (i & 15)) * 16;
+  }
+  const int steps = d / 128, x_step = a.packed ? 8 * 1024 : 256;
+  auto req = [&](int s) {
+    const int t = min(s, steps - 1), dst = (s & 3) * T_STEP;      // (past the end: the last step again, which nobody reads)
+    load_to_lds(rx, vx, t * x_step, dst + wave * 1024);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) load_to_lds(rw, vw[j], t * 256, dst + 8192 + (3 * wave + j) * 1024);
+  };
+  f32x16 acc[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+  const int at = ((2 * wave + lhi) ^ (l32 & 15)) * 16, xa = a.packed ? wave * 1024 + lane * 16 : l32 * 256 + at;
+  for (int s = 0; s < 3; ++s) req(s);
+  for (int s = 0; s < steps; ++s) {
+    wait_vm<8>();
+    wave_barrier();      // step s is there, step s - 1 used up
+    const char *b = lds + (s & 3) * T_STEP;
+    const bf16x8 x = *reinterpret_cast<const bf16x8 *>(b + xa);
+    bf16x8 w[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) w[j] = *reinterpret_cast<const bf16x8 *>(b + 8192 + (32 * j + l32) * 256 + at);
+    req(s + 3);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[j], x, acc[j], 0, 0, 0);
+  }
+  wait_vm<0>();
+  wave_barrier();      // the ring becomes the place of the eight sums: [wave][row][100]
+  // weights first: register v of lane l is column 8 (v / 4) + 4 (l / 32) + v % 4 of row l % 32
+  float *part = reinterpret_cast<float *>(lds);
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<float4 *>(part + (wave * 32 + l32) * 100 + 32 * j + 8 * q + 4 * lhi) =
+          make_float4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
+  __syncthreads();
+  const float scale = a.used_scale[blockIdx.z];
+  const int rank = a.rank;
+  for (int i = 0; i < 2 * nb; ++i) {
+    const int lc = 16 * i + (tid & 15), col = col0 + lc;
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < PREP_WAVES; ++w) t += part[(w * 32 + (tid >> 4)) * 100 + lc];
+    t *= scale;
+    if (my_row < a.T && col < cols && mine == ad) {
+      const int p = col / rank, jj = col % rank;
+      const bf16 hi = (bf16)t;
+      bf16 *dst = a.tlow16 + (((int64_t)my_row * 3 + p) * 2) * rank + jj;
+      dst[0] = hi;
+      dst[rank] = (bf16)(t - (float)hi);
+    }
+  }
 }
 
 bool prep_rows_mfma_supported(int d, int rank) {
-  return (d == 4096 || d == 2048 || d == 1024 || d == 512) && (rank == 0 || rank == 16 || rank == 32 || rank == 64);
+  return (d == 4096 || d == 2048 || d == 1024 || d == 512) && rank % 8 == 0;
 }
 
-template <int NF, int CH, bool EARLY = false>
-static void launch_prep_cfg(const PrepArgs &a, int groups, hipStream_t s) {
+template <int CH>
+static void launch_norm(const PrepArgs &a, hipStream_t s) {
+  const dim3 grid((a.T + PREP_ROWS - 1) / PREP_ROWS);
+  if (a.T <= 2048) hipLaunchKernelGGL((norm_rows_kernel<CH, 1>), grid, dim3(1024), 0, s, a);
+  else hipLaunchKernelGGL((norm_rows_kernel<CH, 4>), grid, dim3(256), 0, s, a);
+}
+
+template <int CH>
+static void launch_prep_ch(const PrepArgs &a, hipStream_t s) {
   const int row_tiles = (a.T + PREP_ROWS - 1) / PREP_ROWS;
-  // few row tiles, several sequences, several adapters: one workgroup per (row tile, column group, adapter)
-  const int per_adapter = (!EARLY && NF > 0 && a.n_adapters > 1 && a.n_adapters <= 16 && a.n_seqs > 1 &&
-                           row_tiles * groups * a.n_adapters <= 1024) ? a.n_adapters : 1;
-  const dim3 grid(row_tiles, groups, per_adapter);
-  const size_t smem = (size_t)PREP_WAVES * PREP_ROWS * 16 * NF * sizeof(float);
-  auto kern = prep_rows_mfma_kernel<NF, CH, EARLY>;
-  // set on every launch that needs it: a host-side attribute write, safe from any thread and on any device
-  if (smem > 48 * 1024)
-    (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  hipLaunchKernelGGL(kern, grid, dim3(512), smem, s, a);
-}
-
-template <int NF>
-static void launch_prep_nf(const PrepArgs &a, int groups, hipStream_t s) {
-  if (NF == 1 && a.seqs != nullptr && a.n_seqs == 1) {
-    switch (a.d) {
-      case 4096: launch_prep_cfg<1, 16, true>(a, groups, s); return;
-      case 2048: launch_prep_cfg<1, 8, true>(a, groups, s); return;
-      case 1024: launch_prep_cfg<1, 4, true>(a, groups, s); return;
-      case 512: launch_prep_cfg<1, 2, true>(a, groups, s); return;
-      default: break;
-    }
-  }
-  switch (a.d) {
-    case 4096: launch_prep_cfg<NF, 16>(a, groups, s); break;
-    case 2048: launch_prep_cfg<NF, 8>(a, groups, s); break;
-    case 1024: launch_prep_cfg<NF, 4>(a, groups, s); break;
-    case 512: launch_prep_cfg<NF, 2>(a, groups, s); break;
-    default: break;
+  if (a.rank == 0 || a.A == nullptr || a.n_used == 0) {
+    launch_norm<CH>(a, s);
+  } else if (a.few == 2 || (a.few == 1 && row_tiles * ((3 * a.rank + 15) / 16) * a.n_used <= PREP_FEW)) {
+    hipLaunchKernelGGL(prep_few_kernel<CH>, dim3(row_tiles, (3 * a.rank + 15) / 16, a.n_used), dim3(512), 0, s, a);
+  } else {
+    launch_norm<CH>(a, s);
+    (void)hipFuncSetAttribute((const void *)t_rows_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * T_STEP);
+    hipLaunchKernelGGL(t_rows_kernel, dim3((a.T + 31) / 32, (3 * a.rank + 95) / 96, a.n_used), dim3(512), 4 * T_STEP, s, a);
   }
 }
 
 void launch_prep_rows_mfma(const PrepArgs &a, hipStream_t s) {
   if (a.T == 0) return;
-  const int nf = (a.rank > 0 && a.A != nullptr) ? 3 * a.rank / 16 : 0;     // 3, 6 or 12
-  if (nf == 0) { launch_prep_nf<0>(a, 1, s); return; }
-  // fragments per workgroup: as few as it takes to reach ~256 workgroups, out of {nf, nf/2, 3, 1}
-  const int row_tiles = (a.T + PREP_ROWS - 1) / PREP_ROWS;
-  int per = nf;
-  if (row_tiles * (nf / per) < 256 && per % 2 == 0 && per > 3) per /= 2;      // 12 -> 6, 6 -> 3
-  if (row_tiles * (nf / per) < 256 && per % 2 == 0 && per > 3) per /= 2;      // 6 -> 3
-  if (row_tiles * (nf / per) < 256 && per == 3) per = 1;
-  const int groups = nf / per;
-  switch (per) {
-    case 1: launch_prep_nf<1>(a, groups, s); break;
-    case 3: launch_prep_nf<3>(a, groups, s); break;
-    case 6: launch_prep_nf<6>(a, groups, s); break;
-    case 12: launch_prep_nf<12>(a, groups, s); break;
+  switch (a.d) {
+    case 4096: launch_prep_ch<16>(a, s); break;
+    case 2048: launch_prep_ch<8>(a, s); break;
+    case 1024: launch_prep_ch<4>(a, s); break;
+    case 512: launch_prep_ch<2>(a, s); break;
     default: break;
   }
 }

@@ -41,6 +41,7 @@ struct GemmArgs {
   const int64_t *rope_slot;    // [M] pool rows
   const float2 *rope_table;    // [positions, 64] (cos, sin)
   float q_scale;               // multiplies the rotated queries
+  int rope_by_row;             // 1: rope_table has a line per row instead of one per position (few-row kernel only)
   int q_half;                  // 1: Qout receives fp16 (the MFMA prefill attention kernel's operand type) instead of bf16
   bf16 *Qout, *cacheK, *cacheV;
 };
@@ -59,19 +60,18 @@ struct PrepArgs {
   int pos_shift;            // added to every position (step index of a multi-step decode)
   const bf16 *A;            // [n_adapters, 3, rank, d] or nullptr
   int rank;
-  int n_adapters;           // adapters stored in A (a short batch gives every adapter workgroups of its own)
+  int n_used;               // the adapters that rows of this call may use ...
+  uint8_t used[64];         // ... their ids and their scales s_a
+  float used_scale[64];
+  int few;                  // one kernel for normalisation and t: 0 never, 1 few rows, 2 always
   int write_meta;
   bf16 *xh;                 // [T, d]
+  int packed;               // 1: xh in operand order: [T / 32][d / 16][lane of 64][8] with lane = row % 32 + 32 (k % 16 / 8)
   bf16 *tlow16;             // [T, 3, 2, rank]
   RowMeta rm;
 };
 bool prep_rows_mfma_supported(int d, int rank);
 void launch_prep_rows_mfma(const PrepArgs &a, hipStream_t s);
-// metadata and RMSNorm only (A, rank, tlow16 unused), for many rows of a call without adapters: x_hat and
-// metadata bit-identical to launch_prep_rows_mfma's
-bool norm_rows_mfma_supported(int d);
-void launch_norm_rows_mfma(const PrepArgs &a, hipStream_t s);
-
 // One workgroup of the prefill attention kernel: up to 256/G consecutive packed rows (tokens) against the key
 // positions [kbeg, kend) of one kv head, counted from pool row key_row0.  Own rows of one sequence: key_row0 is
 // its first own row, pos0 the position of the first token counted from there, and the causal mask applies.
@@ -148,6 +148,14 @@ int gemm_mfma_pick_splits(int M, int N, int K, int n_cu);
 int gemm_mfma_fixed_segments(int N, int K, int n_cu);      // reduction segments of a linear: from the weight shape alone
 bool gemm_mfma_split_segments(int M, int N, int n_cu);     // one workgroup per segment (few row tiles) or one for all
 void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s);
+// many rows: 256 x 256 or 128 x 256 tiles (rows = 256 / 128), one running sum over K; BF16, SWIGLU and ROPE epilogues
+// few rows: the whole QKV projection with rotation and append, A packed (PrepArgs::packed)
+bool qkv_stream_supported(int M, int N, int K, int n_q, int n_kv, int head_dim);
+void launch_qkv_stream(const GemmArgs &g, int n_cu, hipStream_t s);
+struct GemmLargePlan { int rows, splits; };      // tile rows (128 / 256); workgroups per output tile (> 1: PARTIAL)
+GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits);      // hint 2 / 3: 128 / 256 rows
+bool gemm_large_supported(const GemmArgs &g, int epi);
+void launch_gemm_large(GemmArgs g, int epi, int rows, hipStream_t s);
 // tlow[row, p, {hi, lo}, j] = s_a * sum over splits of Y[split, row, (a * parts + p) * rank + j] for adapted rows
 // (a = row_adapter[row] >= 0): picks each row's adapter out of a projection on all adapters' down-matrices
 void launch_tlow_select(const float *Y, int splits, int M, int n_adapters, int parts, int rank,
