@@ -403,6 +403,9 @@ struct Workspace {
   const DecItem *ditems = nullptr;   // work list of the MFMA decode kernel
   int n_ditems = 0;
   const float *scale_dev = nullptr;  // [n_adapters] s_a on the device (adapters of W_o / the MLP)
+  const uint4 *stage_src = nullptr;  // staged metadata that the first kernel of the call carries to the device (n16 > 0)
+  uint4 *stage_dst = nullptr;
+  int stage_n16 = 0;
   bool any_adapter = false;
   const float2 *rope = nullptr;      // rotary table: one line per position, or (rope_by_row) one per packed row
   bool rope_by_row = false;
@@ -474,13 +477,22 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
   const bool fuse = mfma && q_half && ctx->opt_rope_fuse && ctx->opt_gemm_splits <= 1 && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
   const bool stream = fuse && prep_mfma && ctx->opt_gemm_tile == 0 && pl.T <= QKV_STREAM_ROWS &&
                       qkv_stream_supported(pl.T, L.n_qkv, L.d, L.n_q, L.n_kv, L.head_dim);
+  auto stage_of = [&](bool first) {
+    StagedCall st{};
+    if (w.stage_n16 > 0) {
+      st.n_few = pl.B;
+      memcpy(st.few, pl.seqs.data(), (size_t)pl.B * sizeof(SeqMeta));
+      if (first) { st.src = w.stage_src; st.dst = w.stage_dst; st.n16 = w.stage_n16; }
+    }
+    return st;
+  };
   {
     ProfScope p(ctx, K_PREP, s);
     if (prep_mfma) {
       PrepArgs pa{};
       pa.x = (const bf16 *)x; pa.gain = (const bf16 *)ly->rms_gain; pa.eps = ly->rms_eps;
       pa.T = pl.T; pa.d = L.d; pa.seqs = seqs_dev; pa.n_seqs = pl.B; pa.pos_shift = pos_shift;
-      pa.one = pl.seqs[0];
+      pa.st = stage_of(write_meta && pos_shift == 0);
       pa.A = rank_used ? (const bf16 *)ly->A : nullptr; pa.rank = rank_used;
       if (rank_used) {
         pa.n_used = pl.n_used;
@@ -493,7 +505,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       launch_prep_rows_mfma(pa, s);
     } else {
       launch_prep_rows<T>(x, (const T *)ly->rms_gain, ly->rms_eps, pl.T, L.d, seqs_dev, pl.B, pos_shift,
-                          (const T *)ly->A, rank_used, write_meta, (T *)w.xh, w.tlow, mfma ? (bf16 *)w.tlow : nullptr, w.rm, s);
+                          (const T *)ly->A, rank_used, write_meta, (T *)w.xh, w.tlow, mfma ? (bf16 *)w.tlow : nullptr, w.rm, stage_of(write_meta && pos_shift == 0), s);
     }
   }
   if (w.rope_by_row) launch_rope_rows(w.rope_rows, w.rm.pos, pl.T, L.head_dim / 2, ly->rope_theta, s);
@@ -529,6 +541,10 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       } else {
         launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
       }
+    } else if (qkv_small_plain_wanted(pl.T, L.n_qkv, ctx->n_cu)) {
+      launch_qkv_small_plain<T>((const T *)w.xh, (const T *)ly->W_qkv, w.tlow, (const T *)ly->B_q, (const T *)ly->B_k, (const T *)ly->B_v,
+                                L, w.rm, pl.T, w.rope, w.rope_by_row, q_scale, q_mode, w.Q, (T *)cache->k, (T *)cache->v, s);
+      rope_fused = true;
     } else {
       launch_qkv_gemm_plain<T>((const T *)w.xh, (const T *)ly->W_qkv, w.tlow, (const T *)ly->B_q,
                                (const T *)ly->B_k, (const T *)ly->B_v, L, w.rm, pl.T, w.Y, s);
@@ -539,7 +555,8 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
     launch_rope_append<T>(w.Y, mfma ? w.k_splits + ((pl.any_adapter && w.lora_split) ? 1 : 0) : 1, L, w.rm, pl.T, w.rope, w.rope_by_row, q_scale, q_mode, w.Q,
                           (T *)cache->k, (T *)cache->v, s);
   }
-  const bool direct = w.attn_mfma && std::is_same<T, bf16>::value && n_splits == 1;
+  const bool mfma_attn = std::is_same<T, bf16>::value && (w.attn_mfma || w.decode_mfma);
+  const bool direct = n_splits == 1 && (mfma_attn ? w.attn_mfma : true);
   // split prefill attention on the MFMA path: partial results travel in the compact record
   const bool compact16 = w.attn_mfma && std::is_same<T, bf16>::value && !direct && ctx->opt_attn_partials16;
   {
@@ -575,7 +592,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       launch_attn_decode_mfma(a, w.n_ditems, s);
     } else {
       launch_attn_plain<T>((const float *)w.Q, (const T *)cache->k, (const T *)cache->v, seqs_dev, w.rm, L, pl.T,
-                           n_splits, w.partials, s);
+                           n_splits, w.partials, direct ? out : nullptr, s);
     }
   }
   if (!direct) {
@@ -727,7 +744,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
       launch_prep_rows_mfma(pa, s);
     } else {
       launch_prep_rows<T>((const T *)w.h1, (const T *)ly->rms2_gain, ly->rms_eps, T_rows, L.d, nullptr, 0, 0,
-                          (const T *)nullptr, 0, false, (T *)w.hn, nullptr, nullptr, none, s);
+                          (const T *)nullptr, 0, false, (T *)w.hn, nullptr, nullptr, none, StagedCall{}, s);
     }
   }
   if (mfma) {   // act = silu(hn W_gate^T) * (hn W_up^T) in one pass
@@ -1156,10 +1173,12 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   if (!qtiles.empty()) memcpy(slot->host + seq_bytes, qtiles.data(), qtiles.size() * sizeof(AttnItem));
   if (!ditems.empty()) memcpy(slot->host + seq_bytes, ditems.data(), ditems.size() * sizeof(DecItem));
   if (scale_bytes) memcpy(slot->host + seq_bytes + work_bytes, layers[0].scale, (size_t)L.n_adapters * sizeof(float));
-  if (ctx->opt_stage_copy) {
+  const int n16 = (int)((meta_bytes + 15) / 16);
+  const bool carried = B <= FEW_SEQS && n16 <= STAGE_N16 && !ctx->opt_stage_copy;      // by the call's first kernel
+  if (carried) {
+  } else if (ctx->opt_stage_copy) {
     HIP_TRY(ctx, hipMemcpyAsync(slot->dev, slot->host, meta_bytes, hipMemcpyHostToDevice, s));
   } else {
-    const int n16 = (int)((meta_bytes + 15) / 16);
     hipLaunchKernelGGL(stage_meta_kernel, dim3((n16 + 255) / 256), dim3(256), 0, s, (const uint4 *)slot->host,
                        (uint4 *)slot->dev, n16);
   }
@@ -1181,6 +1200,11 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   w.scale_dev = scale_bytes ? (const float *)(slot->dev + seq_bytes + work_bytes) : nullptr;
   w.any_adapter = pl.any_adapter;
   w.rope = ctx->rope;
+  if (carried) {
+    w.stage_src = (const uint4 *)slot->host;
+    w.stage_dst = (uint4 *)slot->dev;
+    w.stage_n16 = n16;
+  }
 
   const bool bf = layers[0].dtype == ALORA_BF16;
   if (!stack) {
@@ -1419,10 +1443,10 @@ alora_status alora_lm_head(alora_ctx *ctx, alora_dtype dtype, int32_t d, int32_t
       launch_prep_rows_mfma(pa, s);
     } else if (bf) {
       launch_prep_rows<bf16>((const bf16 *)x_last, (const bf16 *)final_gain, rms_eps, B, d, nullptr, 0, 0, nullptr, 0,
-                             false, (bf16 *)xh, nullptr, nullptr, none, s);
+                             false, (bf16 *)xh, nullptr, nullptr, none, StagedCall{}, s);
     } else {
       launch_prep_rows<float>((const float *)x_last, (const float *)final_gain, rms_eps, B, d, nullptr, 0, 0, nullptr,
-                              0, false, (float *)xh, nullptr, nullptr, none, s);
+                              0, false, (float *)xh, nullptr, nullptr, none, StagedCall{}, s);
     }
     rows = xh;
   }

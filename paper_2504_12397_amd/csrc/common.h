@@ -22,6 +22,18 @@ struct SeqMeta {
   int32_t pad_;
 };
 
+// The records of a call with few sequences as kernel arguments, for the kernel that prepares its rows.  That kernel, the first of
+// the call, also carries the staged metadata (records and work lists, `n16` pieces of 16 bytes) from the pinned host buffer to
+// where the kernels after it read them: a copy kernel of its own is 4 us of a call that may take 30.
+constexpr int FEW_SEQS = 16, STAGE_N16 = 256;
+struct StagedCall {
+  int n_few;                 // 0: the records are in device memory already
+  const uint4 *src;          // nullptr: nothing to carry
+  uint4 *dst;
+  int n16;                   // <= STAGE_N16
+  SeqMeta few[FEW_SEQS];
+};
+
 // pool row of cached position j of a sequence
 __device__ __forceinline__ int64_t seq_pool_row(const SeqMeta &sm, int j) {
   return (j < sm.prefix_len ? sm.prefix_off : sm.pool_off) + j;
@@ -70,13 +82,20 @@ void launch_rope_rows(float2 *table, const int32_t *pos, int n_rows, int half_di
 template <typename T>
 void launch_prep_rows(const T *x, const T *gain, float eps, int T_rows, int d, const SeqMeta *seqs,
                       int n_seqs, int pos_shift, const T *A, int rank, bool write_meta, T *xh, float *tlow,
-                      bf16 *tlow16, RowMeta rm, hipStream_t s);
+                      bf16 *tlow16, RowMeta rm, const StagedCall &st, hipStream_t s);
 
 // Y[T, n_qkv] (fp32) = xh W^T + gated low-rank term (Eq.6)
 template <typename T>
 void launch_qkv_gemm_plain(const T *xh, const T *W, const float *tlow, const T *Bq, const T *Bk,
                            const T *Bv, const LayerDims &L, RowMeta rm, int T_rows, float *Y,
                            hipStream_t s);
+
+// the same projection with rotation and append, for calls that the tiled kernel leaves most of the chip idle with
+bool qkv_small_plain_wanted(int T_rows, int n_qkv, int n_cu);
+template <typename T>
+void launch_qkv_small_plain(const T *xh, const T *W, const float *tlow, const T *Bq, const T *Bk, const T *Bv, const LayerDims &L,
+                            RowMeta rm, int T_rows, const float2 *table, bool by_row, float q_scale, int q_mode, void *Q, T *cacheK,
+                            T *cacheV, hipStream_t s);
 
 // C[M,N] (T) = A[M,K] B[N,K]^T (+ R[M,N])
 template <typename T>
@@ -110,10 +129,10 @@ void launch_lm_logits_plain(const T *xh, const T *W, int B, int V, int d, float 
 int argmax_slabs(int V);
 void launch_argmax(const float *logits, int B, int V, float *pv, int *pi, int32_t *token, hipStream_t s);
 
-// split-KV attention with plain fp32 arithmetic: partial pass + merge
+// split-KV attention with plain fp32 arithmetic: partial pass (+ merge); out: the result itself, with n_splits == 1 only
 template <typename T>
 void launch_attn_plain(const float *Q, const T *cacheK, const T *cacheV, const SeqMeta *seqs, RowMeta rm,
-                       const LayerDims &L, int T_rows, int n_splits, float *partials, hipStream_t s);
+                       const LayerDims &L, int T_rows, int n_splits, float *partials, T *out, hipStream_t s);
 // merge of the per-split partials (log-sum-exp weights); partial layout per (row, q head, split):
 // head_dim accumulators, running max, running sum
 template <typename T>

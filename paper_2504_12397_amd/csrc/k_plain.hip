@@ -59,22 +59,29 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const T *__restrict__ x,
                                                         int n_seqs, int pos_shift, const T *__restrict__ A, int rank,
                                                         int write_meta, T *__restrict__ xh,
                                                         float *__restrict__ tlow, bf16 *__restrict__ tlow16,
-                                                        RowMeta rm) {
+                                                        RowMeta rm, StagedCall st) {
   extern __shared__ float xs[];
   __shared__ float red[4];
   __shared__ int s_adapter;
   __shared__ float s_scale;
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint4 staged{};
+  const bool carry = row == 0 && st.src != nullptr && tid < st.n16;
+  if (carry) staged = st.src[tid];
   if (tid == 0) {
     int adapter = -1;
     float scale = 0.f;
     if (seqs != nullptr) {
       int lo = 0, hi = n_seqs - 1;   // last sequence whose first row is <= row
-      while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (seqs[mid].row_start <= row) lo = mid; else hi = mid - 1;
+      if (st.n_few) {
+        while (lo < hi && st.few[lo + 1].row_start <= row) ++lo;
+      } else {
+        while (lo < hi) {
+          int mid = (lo + hi + 1) >> 1;
+          if (seqs[mid].row_start <= row) lo = mid; else hi = mid - 1;
+        }
       }
-      SeqMeta sm = seqs[lo];
+      SeqMeta sm = st.n_few ? st.few[lo] : seqs[lo];
       int pos = sm.P + pos_shift + (row - sm.row_start);
       if (sm.adapter >= 0 && pos >= sm.k) { adapter = sm.adapter; scale = sm.scale; }
       if (write_meta) {
@@ -106,6 +113,7 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const T *__restrict__ x,
     xh[(int64_t)row * d + c] = stored;
     xs[c] = to_f32<T>(stored);      // the projections consume the stored (rounded) value
   }
+  if (carry) st.dst[tid] = staged;
   __syncthreads();
   const int a = s_adapter;
   if (a < 0 || rank == 0) return;
@@ -135,15 +143,15 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const T *__restrict__ x,
 template <typename T>
 void launch_prep_rows(const T *x, const T *gain, float eps, int T_rows, int d, const SeqMeta *seqs,
                       int n_seqs, int pos_shift, const T *A, int rank, bool write_meta, T *xh, float *tlow,
-                      bf16 *tlow16, RowMeta rm, hipStream_t s) {
+                      bf16 *tlow16, RowMeta rm, const StagedCall &st, hipStream_t s) {
   if (T_rows == 0) return;
   hipLaunchKernelGGL((prep_rows_kernel<T>), dim3(T_rows), dim3(256), (size_t)d * sizeof(float), s, x, gain,
-                     eps, d, seqs, n_seqs, pos_shift, A, rank, write_meta ? 1 : 0, xh, tlow, tlow16, rm);
+                     eps, d, seqs, n_seqs, pos_shift, A, rank, write_meta ? 1 : 0, xh, tlow, tlow16, rm, st);
 }
 template void launch_prep_rows<float>(const float *, const float *, float, int, int, const SeqMeta *, int, int,
-                                      const float *, int, bool, float *, float *, bf16 *, RowMeta, hipStream_t);
+                                      const float *, int, bool, float *, float *, bf16 *, RowMeta, const StagedCall &, hipStream_t);
 template void launch_prep_rows<bf16>(const bf16 *, const bf16 *, float, int, int, const SeqMeta *, int, int,
-                                     const bf16 *, int, bool, bf16 *, float *, bf16 *, RowMeta, hipStream_t);
+                                     const bf16 *, int, bool, bf16 *, float *, bf16 *, RowMeta, const StagedCall &, hipStream_t);
 
 // ---------------------------------------------------------------------------------------
 // plain tiled GEMM  C[M,N] = A[M,K] B[N,K]^T, 64x64 tile, 16-deep, 4x4 outputs per thread
@@ -183,7 +191,7 @@ __global__ __launch_bounds__(256) void gemm_plain_kernel(const T *__restrict__ A
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
+        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
     }
     __syncthreads();
   }
@@ -221,6 +229,96 @@ __global__ __launch_bounds__(256) void gemm_plain_kernel(const T *__restrict__ A
     }
   }
 }
+
+// The QKV projection of a call too small to fill the chip with 64 x 64 tiles, rotated and appended where it is computed: 16 rows x 8
+// rotation pairs (c, c + h/2) per workgroup, a thread per output, 256 values of k at a time through LDS with the next 256 on their
+// way.  A thread adds its products in ascending k, as the tiled kernel does (same bits).  16 rows x 768 columns x 256: 40 us in
+// 12 workgroups of 16 dependent k-steps each, plus the rotation's own launch.
+template <typename T>
+__global__ __launch_bounds__(256) void qkv_small_plain_kernel(const T *__restrict__ X, const T *__restrict__ W, LayerDims L, int M,
+                                                              LoraEpi epi, const int32_t *__restrict__ pos,
+                                                              const int64_t *__restrict__ slot, const float2 *__restrict__ table,
+                                                              int table_by_row, float q_scale, int q_mode, void *__restrict__ Q,
+                                                              T *__restrict__ cacheK, T *__restrict__ cacheV) {
+  constexpr int KC = 256, LD = KC + 4;
+  __shared__ float xs[16][LD], ws[16][LD];
+  const int tid = threadIdx.x, r = tid >> 4, c = tid & 15;
+  const int h = L.head_dim, h2 = h >> 1, n_pairs = L.n_qkv >> 1, K = L.d;
+  const int m0 = blockIdx.y * 16, p0 = blockIdx.x * 8;
+  auto col_of = [&](int i) {      // column i of the tile: the pairs' first columns, then their partners
+    const int p = min(p0 + (i & 7), n_pairs - 1);
+    return (p / h2) * h + p % h2 + (i >> 3) * h2;
+  };
+  const int row = m0 + r, rc = min(row, M - 1), col = col_of(c);
+  const int kind = col < L.n_q ? 0 : (col < L.n_q + L.n_kv ? 1 : 2);
+  const int a = epi.row_adapter[rc];
+  const int64_t sl = slot[rc];
+  const float2 cs = table[(int64_t)(table_by_row ? rc : pos[rc]) * h2 + (col % h) % h2];
+  const T *xrow = X + (int64_t)rc * K, *wrow = W + (int64_t)col_of(r) * K;      // (thread r, c loads row r of both, k from 16 c)
+  float xv[16], wv[16];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int k = k0 + c + 16 * i;
+      xv[i] = k < K ? to_f32<T>(xrow[k]) : 0.f;
+      wv[i] = k < K ? to_f32<T>(wrow[k]) : 0.f;
+    }
+  };
+  float acc = 0.f;
+  fetch(0);
+  for (int k0 = 0; k0 < K; k0 += KC) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { xs[r][c + 16 * i] = xv[i]; ws[r][c + 16 * i] = wv[i]; }
+    __syncthreads();
+    if (k0 + KC < K) fetch(k0 + KC);
+#pragma unroll 8
+    for (int k = 0; k < KC; k += 4) {
+      const float4 x4 = *reinterpret_cast<const float4 *>(&xs[r][k]), w4 = *reinterpret_cast<const float4 *>(&ws[c][k]);
+      acc = __builtin_fmaf(x4.x, w4.x, acc);
+      acc = __builtin_fmaf(x4.y, w4.y, acc);
+      acc = __builtin_fmaf(x4.z, w4.z, acc);
+      acc = __builtin_fmaf(x4.w, w4.w, acc);
+    }
+    __syncthreads();
+  }
+  if (a >= 0) {
+    const int rk = epi.rank;
+    const T *bp = kind == 0 ? (const T *)epi.Bq + ((int64_t)a * L.n_q + col) * rk
+                            : (kind == 1 ? (const T *)epi.Bk + ((int64_t)a * L.n_kv + col - L.n_q) * rk
+                                         : (const T *)epi.Bv + ((int64_t)a * L.n_kv + col - L.n_q - L.n_kv) * rk);
+    const float *t = epi.tlow + (int64_t)rc * 3 * rk + kind * rk;
+    float lo = 0.f;
+    for (int jj = 0; jj < rk; ++jj) lo += t[jj] * to_f32<T>(bp[jj]);
+    acc += lo;
+  }
+  const float other = __shfl_xor(acc, 8, 64);      // the rotation partner
+  if (row >= M || p0 + (c & 7) >= n_pairs) return;
+  const float u = c < 8 ? acc : other, w = c < 8 ? other : acc;
+  const int hcol = kind == 0 ? col : (kind == 1 ? col - L.n_q : col - L.n_q - L.n_kv);
+  if (kind == 2) { cacheV[sl * L.n_kv + hcol] = from_f32<T>(acc); return; }
+  const float y = (c < 8 ? rope_lo(u, w, cs.x, cs.y) : rope_hi(u, w, cs.x, cs.y)) * (kind == 0 ? q_scale : 1.0f);
+  if (kind == 1) cacheK[sl * L.n_kv + hcol] = from_f32<T>(y);
+  else if (q_mode == 1) reinterpret_cast<_Float16 *>(Q)[(int64_t)row * L.n_q + hcol] = (_Float16)y;
+  else reinterpret_cast<float *>(Q)[(int64_t)row * L.n_q + hcol] = y;
+}
+
+// where the 64 x 64 tiles of the projection would leave most of the chip idle
+bool qkv_small_plain_wanted(int T_rows, int n_qkv, int n_cu) { return ((T_rows + 63) / 64) * ((n_qkv + 63) / 64) * 2 <= n_cu; }
+
+template <typename T>
+void launch_qkv_small_plain(const T *xh, const T *W, const float *tlow, const T *Bq, const T *Bk, const T *Bv, const LayerDims &L,
+                            RowMeta rm, int T_rows, const float2 *table, bool by_row, float q_scale, int q_mode, void *Q, T *cacheK,
+                            T *cacheV, hipStream_t s) {
+  if (T_rows == 0) return;
+  LoraEpi epi{tlow, Bq, Bk, Bv, rm.adapter, L.rank, L.n_q, L.n_kv};
+  dim3 grid((L.n_qkv / 2 + 7) / 8, (T_rows + 15) / 16);
+  hipLaunchKernelGGL((qkv_small_plain_kernel<T>), grid, dim3(256), 0, s, xh, W, L, T_rows, epi, rm.pos, rm.slot, table, by_row ? 1 : 0,
+                     q_scale, q_mode, Q, cacheK, cacheV);
+}
+template void launch_qkv_small_plain<float>(const float *, const float *, const float *, const float *, const float *, const float *,
+                                            const LayerDims &, RowMeta, int, const float2 *, bool, float, int, void *, float *, float *, hipStream_t);
+template void launch_qkv_small_plain<bf16>(const bf16 *, const bf16 *, const float *, const bf16 *, const bf16 *, const bf16 *,
+                                           const LayerDims &, RowMeta, int, const float2 *, bool, float, int, void *, bf16 *, bf16 *, hipStream_t);
 
 template <typename T>
 void launch_qkv_gemm_plain(const T *xh, const T *W, const float *tlow, const T *Bq, const T *Bk,
@@ -353,20 +451,33 @@ template void launch_rope_append<bf16>(const float *, int, const LayerDims &, Ro
                                        void *, bf16 *, bf16 *, hipStream_t);
 
 // ---------------------------------------------------------------------------------------
-// plain split-KV attention (Eq.1 / Eq.4, causal, GQA).  One wave per (row, kv head, chunk of
-// up to 8 query heads, key split).  Scores: one key per lane; values: lanes across head_dim.
-// Partial layout: part[(((row*Hq + hq) * n_splits) + split) * (h + 2)] = acc[h], m, l.
+// plain split-KV attention (Eq.1 / Eq.4, causal, GQA).  One workgroup of four waves per (row, kv head, chunk of
+// up to 8 query heads, key split), 64 keys at a time: four threads to a key for the scores, a wave to a head for the
+// softmax, every fourth key to a wave for the values (lanes across head_dim), the four waves' sums added at the end.  Latency is
+// what it costs (16 rows over 80 keys: one wave per workgroup with a key per lane took 44 us), so every phase has its loads
+// together.  out != nullptr (one split): the result itself; otherwise
+// partial layout: part[(((row*Hq + hq) * n_splits) + split) * (h + 2)] = acc[h], m, l.
 // ---------------------------------------------------------------------------------------
 #define ATT_GMAX 8
 #define ATT_DMAX 4     // head_dim <= 256
 
-template <typename T>
-__global__ __launch_bounds__(64) void attn_partial_kernel(const float *__restrict__ Q, const T *__restrict__ cacheK,
+template <typename T> __device__ __forceinline__ float4 load4(const T *p);
+template <> __device__ __forceinline__ float4 load4<float>(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+template <> __device__ __forceinline__ float4 load4<bf16>(const bf16 *p) {
+  const uint2 w = *reinterpret_cast<const uint2 *>(p);
+  return make_float4(__builtin_bit_cast(float, w.x << 16), __builtin_bit_cast(float, w.x & 0xffff0000u),
+                     __builtin_bit_cast(float, w.y << 16), __builtin_bit_cast(float, w.y & 0xffff0000u));
+}
+
+template <typename T, bool VEC>      // VEC: head_dim is a multiple of 16
+__global__ __launch_bounds__(256) void attn_partial_kernel(const float *__restrict__ Q, const T *__restrict__ cacheK,
                                                           const T *__restrict__ cacheV,
                                                           const SeqMeta *__restrict__ seqs, RowMeta rm,
-                                                          LayerDims L, int n_splits, float *__restrict__ part) {
-  extern __shared__ float smem[];       // qs[GMAX][h] then ps[GMAX][64]
-  const int lane = threadIdx.x;
+                                                          LayerDims L, int n_splits, float *__restrict__ part,
+                                                          T *__restrict__ out) {
+  extern __shared__ float smem[];       // qs[GMAX][h], ps[GMAX][64]; the waves' sums at the end: [4][GMAX][h]
+  __shared__ float s_corr[ATT_GMAX], s_m[ATT_GMAX], s_l[ATT_GMAX];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int h = L.head_dim;
   const int G = L.n_q_heads / L.n_kv_heads;
   const int row = blockIdx.x / L.n_kv_heads, g = blockIdx.x % L.n_kv_heads;
@@ -374,81 +485,112 @@ __global__ __launch_bounds__(64) void attn_partial_kernel(const float *__restric
   const int g0 = blockIdx.z * ATT_GMAX;
   const int ng = min(ATT_GMAX, G - g0);
   float *qs = smem, *ps = smem + ATT_GMAX * h;
+  const SeqMeta sm = seqs[rm.seq[row]];
   const int n_keys = rm.pos[row] + 1;
   int chunk = (n_keys + n_splits - 1) / n_splits;
   chunk = (chunk + 63) & ~63;
   const int begin = split * chunk, end = min(n_keys, begin + chunk);
-  const SeqMeta sm = seqs[rm.seq[row]];
   const float sm_scale = 1.0f / sqrtf((float)h);
-  for (int i = lane; i < ng * h; i += 64) {
-    int gi = i / h, c = i % h;
-    qs[gi * h + c] = Q[(int64_t)row * L.n_q + (g * G + g0 + gi) * h + c] * sm_scale;
-  }
-  __syncthreads();
-  float m[ATT_GMAX], l[ATT_GMAX], acc[ATT_GMAX][ATT_DMAX];
+  for (int i = tid; i < ng * h; i += 256) qs[i] = Q[(int64_t)row * L.n_q + (g * G + g0) * h + i] * sm_scale;
+  float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};      // of heads wave and wave + 4
+  float acc[ATT_GMAX][ATT_DMAX];
 #pragma unroll
-  for (int gi = 0; gi < ATT_GMAX; ++gi) {
-    m[gi] = -INFINITY; l[gi] = 0.f;
+  for (int gi = 0; gi < ATT_GMAX; ++gi)
 #pragma unroll
     for (int dd = 0; dd < ATT_DMAX; ++dd) acc[gi][dd] = 0.f;
-  }
+  __syncthreads();
   for (int t0 = begin; t0 < end; t0 += 64) {
-    const int key = t0 + lane;
-    const bool valid = key < end;
-    float sc[ATT_GMAX];
+    {
+      const int key = t0 + (tid >> 2), q4 = tid & 3;
+      const T *kr = cacheK + seq_pool_row(sm, min(key, end - 1)) * L.n_kv + g * h;
+      float sc[ATT_GMAX];
 #pragma unroll
-    for (int gi = 0; gi < ATT_GMAX; ++gi) sc[gi] = 0.f;
-    if (valid) {
-      const T *kr = cacheK + seq_pool_row(sm, key) * L.n_kv + g * h;
-      for (int c = 0; c < h; ++c) {
-        float kv = to_f32<T>(kr[c]);
+      for (int gi = 0; gi < ATT_GMAX; ++gi) sc[gi] = 0.f;
+      if constexpr (VEC) {
+#pragma unroll 4
+        for (int c = 4 * q4; c < h; c += 16) {
+          const float4 kv = load4<T>(kr + c);
 #pragma unroll
-        for (int gi = 0; gi < ATT_GMAX; ++gi)
-          if (gi < ng) sc[gi] += qs[gi * h + c] * kv;
+          for (int gi = 0; gi < ATT_GMAX; ++gi)
+            if (gi < ng) {
+              const float4 qv = *reinterpret_cast<const float4 *>(qs + gi * h + c);
+              sc[gi] += qv.x * kv.x + qv.y * kv.y + qv.z * kv.z + qv.w * kv.w;
+            }
+        }
+      } else {
+        for (int c = q4; c < h; c += 4) {
+          const float kv = to_f32<T>(kr[c]);
+#pragma unroll
+          for (int gi = 0; gi < ATT_GMAX; ++gi)
+            if (gi < ng) sc[gi] += qs[gi * h + c] * kv;
+        }
       }
+#pragma unroll
+      for (int gi = 0; gi < ATT_GMAX; ++gi)
+        if (gi < ng) {
+          float v = sc[gi] + __shfl_xor(sc[gi], 1, 64);
+          v += __shfl_xor(v, 2, 64);
+          if (q4 == 0) ps[gi * 64 + (tid >> 2)] = key < end ? v : -INFINITY;
+        }
     }
-    __syncthreads();      // previous tile's ps fully consumed
+    __syncthreads();
 #pragma unroll
-    for (int gi = 0; gi < ATT_GMAX; ++gi) {
+    for (int u = 0; u < 2; ++u) {
+      const int gi = wave + 4 * u;
       if (gi < ng) {
-        float s = valid ? sc[gi] : -INFINITY;
-        float mn = fmaxf(m[gi], wave_max(s));
-        float p = valid ? __expf(s - mn) : 0.f;
-        float corr = __expf(m[gi] - mn);
-        l[gi] = l[gi] * corr + wave_sum(p);
-        m[gi] = mn;
-#pragma unroll
-        for (int dd = 0; dd < ATT_DMAX; ++dd) acc[gi][dd] *= corr;
+        const float s = ps[gi * 64 + lane];
+        const float mn = fmaxf(m[u], wave_max(s));
+        const float p = __expf(s - mn), corr = __expf(m[u] - mn);      // (every tile holds a valid key: mn is finite)
+        l[u] = l[u] * corr + wave_sum(p);
+        m[u] = mn;
         ps[gi * 64 + lane] = p;
+        if (lane == 0) s_corr[gi] = corr;
       }
     }
     __syncthreads();
+#pragma unroll
+    for (int gi = 0; gi < ATT_GMAX; ++gi)
+      if (gi < ng)
+#pragma unroll
+        for (int dd = 0; dd < ATT_DMAX; ++dd) acc[gi][dd] *= s_corr[gi];
     const int nk = min(64, end - t0);
-    for (int j = 0; j < nk; ++j) {
+#pragma unroll 8
+    for (int j = wave; j < nk; j += 4) {
       const T *vr = cacheV + seq_pool_row(sm, t0 + j) * L.n_kv + g * h;
 #pragma unroll
       for (int dd = 0; dd < ATT_DMAX; ++dd) {
-        int c = lane + 64 * dd;
+        const int c = lane + 64 * dd;
         if (c < h) {
-          float vv = to_f32<T>(vr[c]);
+          const float vv = to_f32<T>(vr[c]);
 #pragma unroll
           for (int gi = 0; gi < ATT_GMAX; ++gi)
             if (gi < ng) acc[gi][dd] += ps[gi * 64 + j] * vv;
         }
       }
     }
+    __syncthreads();      // the probabilities are used up
   }
 #pragma unroll
-  for (int gi = 0; gi < ATT_GMAX; ++gi) {
-    if (gi < ng) {
-      float *o = part + (((int64_t)row * L.n_q_heads + (g * G + g0 + gi)) * n_splits + split) * (h + 2);
+  for (int u = 0; u < 2; ++u)
+    if (wave + 4 * u < ng && lane == 0) { s_m[wave + 4 * u] = m[u]; s_l[wave + 4 * u] = l[u]; }
 #pragma unroll
-      for (int dd = 0; dd < ATT_DMAX; ++dd) {
-        int c = lane + 64 * dd;
-        if (c < h) o[c] = acc[gi][dd];
-      }
-      if (lane == 0) { o[h] = m[gi]; o[h + 1] = l[gi]; }
-    }
+  for (int gi = 0; gi < ATT_GMAX; ++gi)
+    if (gi < ng)
+#pragma unroll
+      for (int dd = 0; dd < ATT_DMAX; ++dd)
+        if (lane + 64 * dd < h) smem[(wave * ng + gi) * h + lane + 64 * dd] = acc[gi][dd];
+  __syncthreads();
+  for (int i = tid; i < ng * h; i += 256) {
+    const float v = ((smem[i] + smem[ng * h + i]) + smem[2 * ng * h + i]) + smem[3 * ng * h + i];
+    const int gi = i / h, c = i - gi * h;
+    const int64_t rh = (int64_t)row * L.n_q_heads + g * G + g0 + gi;
+    if (out != nullptr) out[rh * h + c] = from_f32<T>(v * (1.0f / s_l[gi]));
+    else part[(rh * n_splits + split) * (h + 2) + c] = v;
+  }
+  if (out == nullptr && tid < ng) {
+    float *o = part + (((int64_t)row * L.n_q_heads + g * G + g0 + tid) * n_splits + split) * (h + 2);
+    o[h] = s_m[tid];
+    o[h + 1] = s_l[tid];
   }
 }
 
@@ -559,18 +701,21 @@ size_t attn_plain_partial_floats(const LayerDims &L, int T_rows, int n_splits) {
 
 template <typename T>
 void launch_attn_plain(const float *Q, const T *cacheK, const T *cacheV, const SeqMeta *seqs, RowMeta rm,
-                       const LayerDims &L, int T_rows, int n_splits, float *partials, hipStream_t s) {
+                       const LayerDims &L, int T_rows, int n_splits, float *partials, T *out, hipStream_t s) {
   if (T_rows == 0) return;
-  const int G = L.n_q_heads / L.n_kv_heads;
+  const int G = L.n_q_heads / L.n_kv_heads, ng = G < ATT_GMAX ? G : ATT_GMAX;
   dim3 grid(T_rows * L.n_kv_heads, n_splits, (G + ATT_GMAX - 1) / ATT_GMAX);
-  size_t smem = (size_t)(ATT_GMAX * L.head_dim + ATT_GMAX * 64) * sizeof(float);
-  hipLaunchKernelGGL((attn_partial_kernel<T>), grid, dim3(64), smem, s, Q, cacheK, cacheV, seqs, rm, L, n_splits,
-                     partials);
+  const size_t tile = (size_t)(ATT_GMAX * L.head_dim + ATT_GMAX * 64), sums = (size_t)4 * ng * L.head_dim;
+  const size_t smem = (tile > sums ? tile : sums) * sizeof(float);
+  if (L.head_dim % 16 == 0)
+    hipLaunchKernelGGL((attn_partial_kernel<T, true>), grid, dim3(256), smem, s, Q, cacheK, cacheV, seqs, rm, L, n_splits, partials, out);
+  else
+    hipLaunchKernelGGL((attn_partial_kernel<T, false>), grid, dim3(256), smem, s, Q, cacheK, cacheV, seqs, rm, L, n_splits, partials, out);
 }
 template void launch_attn_plain<float>(const float *, const float *, const float *, const SeqMeta *, RowMeta,
-                                       const LayerDims &, int, int, float *, hipStream_t);
+                                       const LayerDims &, int, int, float *, float *, hipStream_t);
 template void launch_attn_plain<bf16>(const float *, const bf16 *, const bf16 *, const SeqMeta *, RowMeta,
-                                      const LayerDims &, int, int, float *, hipStream_t);
+                                      const LayerDims &, int, int, float *, bf16 *, hipStream_t);
 
 template <typename T>
 void launch_attn_merge(const float *partials, const LayerDims &L, int T_rows, int n_splits, T *out, hipStream_t s) {

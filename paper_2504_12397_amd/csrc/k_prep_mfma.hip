@@ -66,7 +66,7 @@ __device__ __forceinline__ void fill_row_meta(const PrepArgs &a, const SeqMeta &
 // adapter used[z]; the first of a tile also writes x_hat and the row metadata.  Eight waves split the hidden dimension; a lane
 // owns 8 consecutive elements of one row at a time, which is both the 16-byte global access and the operand layout of
 // v_mfma_f32_16x16x32_bf16 (lane l: row l % 16, k = 8 * (l / 16) ..).  CH = d / 256: chunks of its row a lane holds.
-// The kernel is memory round trips and little else, so everything is requested at once: x, the gain, the sequences' records
+// The kernel is memory round trips and little else, so everything is requested at once: x, the gain, the sequences' records (in the kernel arguments when they are few)
 // and this adapter's down matrix, before anybody knows whether a row of the tile uses it.
 template <int CH>
 __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
@@ -87,6 +87,9 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   const bool row_ok = row0 + r16 < a.T;
   const int k_lo = wave * (CH * 32) + kg * 8;  // this lane's first element; chunk u is at k_lo + 32 u
 
+  uint4 staged{};
+  const bool carry = blockIdx.x == 0 && lead && a.st.src != nullptr && tid < a.st.n16;
+  if (carry) staged = a.st.src[tid];
   u32x4 xr[CH], br[CH], gown = u32x4{0, 0, 0, 0};
   const bf16 *xrow = a.x + (int64_t)row * d + k_lo;
 #pragma unroll
@@ -105,11 +108,9 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   auto fill_row = [&](const SeqMeta &sm, int sq, int mrow) {
     fill_row_meta(a, sm, sq, mrow, row0, a.write_meta && lead, s_adapter, s_scale, &s_present);
   };
-  if (a.n_seqs == 1) {      // (the record came with the kernel arguments)
-    if (tid < PREP_ROWS && row0 + tid < tile_end) fill_row(a.one, 0, row0 + tid);
-  } else {
+  {
     for (int sq = tid; sq < a.n_seqs; sq += 512) {
-      const SeqMeta sm = a.seqs[sq];
+      const SeqMeta sm = a.st.n_few ? a.st.few[sq] : a.seqs[sq];
       const int lo = max(sm.row_start, row0), hi = min(sm.row_start + sm.n_new, tile_end);
       for (int mrow = lo; mrow < hi; ++mrow) fill_row(sm, sq, mrow);
     }
@@ -144,6 +145,7 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
 #pragma unroll
     for (int u = 0; u < CH; ++u) dst[xh_chunk(row, (k_lo >> 3) + 4 * u, d, a.packed)] = xr[u];
   }
+  if (carry) a.st.dst[tid] = staged;
   if (!((s_present >> ad) & 1)) return;
 
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -185,6 +187,9 @@ __global__ __launch_bounds__(64 * (PREP_ROWS / RW)) void norm_rows_kernel(PrepAr
   const int row0 = blockIdx.x * PREP_ROWS;
   constexpr int D = CH * 256, NJ = D / 512;
   const int wrow0 = row0 + wave * RW;
+  uint4 staged{};
+  const bool carry = blockIdx.x == 0 && a.st.src != nullptr && tid < a.st.n16;
+  if (carry) staged = a.st.src[tid];
   u32x4 xr[RW][NJ], gr[NJ];
 #pragma unroll
   for (int i = 0; i < RW; ++i) {
@@ -201,14 +206,10 @@ __global__ __launch_bounds__(64 * (PREP_ROWS / RW)) void norm_rows_kernel(PrepAr
     if (tid == 0) s_present = 0ull;
     __syncthreads();
     const int tile_end = min(row0 + PREP_ROWS, a.T);
-    if (a.n_seqs == 1) {
-      if (tid < PREP_ROWS && row0 + tid < tile_end) fill_row_meta(a, a.one, 0, row0 + tid, row0, true, nullptr, nullptr, &s_present);
-    } else {
-      for (int sq = tid; sq < a.n_seqs; sq += NT) {
-        const SeqMeta sm = a.seqs[sq];
-        const int lo = max(sm.row_start, row0), hi = min(sm.row_start + sm.n_new, tile_end);
-        for (int mrow = lo; mrow < hi; ++mrow) fill_row_meta(a, sm, sq, mrow, row0, true, nullptr, nullptr, &s_present);
-      }
+    for (int sq = tid; sq < a.n_seqs; sq += NT) {
+      const SeqMeta sm = a.st.n_few ? a.st.few[sq] : a.seqs[sq];
+      const int lo = max(sm.row_start, row0), hi = min(sm.row_start + sm.n_new, tile_end);
+      for (int mrow = lo; mrow < hi; ++mrow) fill_row_meta(a, sm, sq, mrow, row0, true, nullptr, nullptr, &s_present);
     }
     __syncthreads();
     if (tid == 0 && a.rm.present16 != nullptr) a.rm.present16[blockIdx.x] = s_present;
@@ -238,6 +239,7 @@ __global__ __launch_bounds__(64 * (PREP_ROWS / RW)) void norm_rows_kernel(PrepAr
       for (int j = 0; j < NJ; ++j) dst[xh_chunk(wrow0 + i, lane + 64 * j, D, a.packed)] = xr[i][j];
     }
   }
+  if (carry) a.st.dst[tid] = staged;
 }
 
 // t of many rows from x_hat: workgroup (x, y, z) takes 32 rows, columns 96 y .. of the 3 * rank and adapter used[z]; it leaves at
