@@ -34,20 +34,28 @@ struct SeqChunk { SeqMeta m[STAGE_SEQS]; };
 __global__ void stage_seqs_kernel(SeqChunk c, int n, SeqMeta *dst) {
   if ((int)threadIdx.x < n) dst[threadIdx.x] = c.m[threadIdx.x];
 }
-// the work list of the decode attention kernel for sequences without shared prefixes, in the order the host
-// builds it: item ((row * n_groups) + gb) * n_own + split covers split `split` of row `row`, kv heads gb * heads_per_wg ...
-__global__ void make_decode_items_kernel(DecItem *items, int n_items, int n_groups, int heads_per_wg, int n_own) {
+// the work list of the decode attention kernel for sequences without shared prefixes, from the sequences' records: item
+// ((row * n_groups) + gb) * n_own + part covers range `part` of row `row`, kv heads gb * heads_per_wg ...  The ranges are the host
+// list's (dec_cut); a row with fewer of them than n_own leaves empty items.  Every sequence has one new row here.
+__global__ void make_decode_items_kernel(const SeqMeta *seqs, int n_seqs, DecItem *items, int32_t *counts, int n_groups, int heads_per_wg,
+                                         int n_own, int range, int splits) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_items) return;
+  const int row = i / (n_own * n_groups);
+  if (row >= n_seqs) return;
+  const SeqMeta sm = seqs[row];
+  const int n_keys = sm.P + 1, part = i % n_own;
+  const DecCut c = dec_cut(n_keys, splits > 0 ? max(1, (n_keys + splits - 1) / splits) : range);
   DecItem it{};
-  it.n_rows = 1;
-  it.split = i % n_own;
-  it.g = ((i / n_own) % n_groups) * heads_per_wg;
-  it.n_splits = n_own;
-  it.part = it.split;
-  it.shared = 0;
-  it.rows[0] = i / (n_own * n_groups);
+  it.key_row0 = sm.pool_off;
+  it.row = row;
+  it.kbeg = part * c.len;
+  it.kend = min(n_keys, it.kbeg + c.len);
+  it.n_rows = part < c.parts ? 1 : 0;
+  it.g = (int16_t)(((i / n_own) % n_groups) * heads_per_wg);
+  it.part = (int16_t)part;
+  it.grows = part == c.parts - 1;
   items[i] = it;
+  if (i % (n_own * n_groups) == 0) { counts[2 * row] = c.parts; counts[2 * row + 1] = 0; }
 }
 
 // copies the staged metadata from the pinned host buffer (which the GPU can read directly) into device memory: as a
@@ -371,13 +379,6 @@ alora_status check_batch(alora_ctx *ctx, const alora_layer_desc *ly, const alora
   return ALORA_OK;
 }
 
-// decode batches have one row per sequence: the sequence whose new token is packed row `row`
-static int a_seq_of_row(const Plan &pl, int row) {
-  for (int b = 0; b < pl.B; ++b)
-    if (pl.seqs[b].n_new > 0 && pl.seqs[b].row_start == row) return b;
-  return 0;
-}
-
 struct Workspace {
   RowMeta rm;
   void *xh;        // [T, d]
@@ -402,6 +403,8 @@ struct Workspace {
   int n_qtiles = 0;
   const DecItem *ditems = nullptr;   // work list of the MFMA decode kernel
   int n_ditems = 0;
+  const int32_t *drows = nullptr;    // rows of its shared items
+  MergeCounts merge{nullptr, 0};     // records per row (decode)
   const float *scale_dev = nullptr;  // [n_adapters] s_a on the device (adapters of W_o / the MLP)
   const uint4 *stage_src = nullptr;  // staged metadata that the first kernel of the call carries to the device (n16 > 0)
   uint4 *stage_dst = nullptr;
@@ -582,9 +585,8 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
     } else if (w.decode_mfma && std::is_same<T, bf16>::value) {
       DecodeArgs a{};
       a.Q = (const _Float16 *)w.Q; a.K = (const bf16 *)cache->k; a.V = (const bf16 *)cache->v;
-      a.seqs = seqs_dev; a.rm = w.rm;
       a.n_q = L.n_q; a.n_kv = L.n_kv; a.n_q_heads = L.n_q_heads; a.n_kv_heads = L.n_kv_heads;
-      a.items = w.ditems;
+      a.items = w.ditems; a.rows = w.drows; a.pos_shift = pos_shift;
       a.n_parts = n_splits;
       a.heads_per_wg = w.dec_hw; a.ranges_per_wg = w.dec_kr; a.cols_max = w.dec_cols_max;
       a.sm_scale = 1.0f / sqrtf((float)L.head_dim);
@@ -598,7 +600,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
   if (!direct) {
     ProfScope p(ctx, K_ATTN_MERGE, s);
     if (compact16) launch_attn_merge16(w.partials, L, pl.T, n_splits, (bf16 *)out, s);
-    else launch_attn_merge<T>(w.partials, L, pl.T, n_splits, out, s);
+    else launch_attn_merge<T>(w.partials, L, pl.T, n_splits, w.merge, out, s);
   }
 }
 
@@ -795,41 +797,26 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
   }
 }
 
-// Work list of the MFMA decode kernel: per (row, group of up to eight kv heads) n_own items over the row's own
-// cache rows, and -- when sequences name shared prefixes -- per (group of up to 16 / G rows with the same prefix,
-// group of kv heads) n_shared items over that prefix.  Every (row, head) ends up with n_own + n_shared partial
-// records.  A workgroup's eight waves are hw kv heads x kr sub-ranges of the item's keys.
+// Work list of the MFMA decode kernel: per (row, group of kv heads) items over ranges of the row's own cache rows, and -- when
+// sequences name shared prefixes -- per (group of up to 32 / G rows with the same prefix, group of kv heads) items over
+// ranges of that prefix.  A workgroup's eight waves are hw kv heads x kr sub-ranges of the item's keys.
 struct DecodePlan {
   std::vector<DecItem> items;      // empty when the list is built on the device (the static entry point)
-  int n_own = 1, n_shared = 0;
+  std::vector<int32_t> rows;       // rows of the shared items
+  std::vector<int32_t> counts;     // records per row: own, shared
+  int n_own = 1, n_shared = 0;     // most own and shared records of a row
+  int range = 0;                   // keys per own range, before it is evened out (dec_cut)
   int n_device_items = 0;          // size of the device-built list: rows x head groups x n_own
   int hw = 1, kr = 1, groups = 1, cols_max = 1;
 };
 DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, int B, int n_steps, bool on_device) {
   DecodePlan dp;
   const int G = L.n_q_heads / L.n_kv_heads;
-  const int pack = std::max(1, 16 / G);
-  decode_mfma_shape(L.n_kv_heads, &dp.hw, &dp.kr);
-  dp.groups = (L.n_kv_heads + dp.hw - 1) / dp.hw;
+  const int pack = std::max(1, 32 / G);
+  // rows that share one prefix, at most `pack` each
+  struct Chunk { int64_t off; int len; int first, n; };
+  std::vector<Chunk> chunks;
   dp.cols_max = G;
-  int max_own = 1, max_pfx = 0;
-  for (int b = 0; b < B; ++b) {
-    max_own = std::max(max_own, pl.seqs[b].P + n_steps - pl.seqs[b].prefix_len);
-    max_pfx = std::max(max_pfx, pl.seqs[b].prefix_len);
-  }
-  // 16 waves per compute unit (two rounds of workgroups), each over a key range of at least 1024 keys (every range
-  // of a head costs a partial record unless it shares its workgroup): `items` (row, kv head) pairs need so many
-  // ranges each, kr of which share a workgroup (and a partial record).  A handful of sequences over long caches
-  // cannot fill the chip with ranges that long: down to 256 keys then, up to 128 records per head.
-  auto splits_for = [&](int64_t items, int longest) {
-    if (ctx->opt_splits > 0) return ctx->opt_splits;
-    const bool few = 2 * items < ctx->n_cu;
-    const int64_t ranges = std::max<int64_t>(1, std::min<int64_t>((16 * (int64_t)ctx->n_cu + items - 1) / std::max<int64_t>(items, 1),
-                                                                  std::max(1, longest / (few ? 256 : 1024))));
-    return (int)std::max<int64_t>(1, std::min<int64_t>(few ? 128 : 64, (ranges + dp.kr - 1) / dp.kr));
-  };
-  dp.n_own = splits_for((int64_t)pl.T * L.n_kv_heads, max_own);
-  std::vector<std::vector<int>> chunks;      // rows that share one prefix, at most `pack` each
   if (pl.any_prefix) {
     std::vector<int> order(B);
     for (int b = 0; b < B; ++b) order[b] = b;
@@ -839,42 +826,76 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
     });
     for (int i = 0; i < B; ++i) {
       const SeqMeta &m = pl.seqs[order[i]];
-      if (m.n_new <= 0 || m.prefix_len <= 0) continue;     // nothing to read: its records are zero-filled below
-      const bool same = !chunks.empty() && (int)chunks.back().size() < pack &&
-                        pl.seqs[order[i - 1]].prefix_off == m.prefix_off && pl.seqs[order[i - 1]].prefix_len == m.prefix_len &&
-                        pl.seqs[order[i - 1]].prefix_len > 0 && pl.seqs[order[i - 1]].n_new > 0;
-      if (!same) chunks.emplace_back();
-      chunks.back().push_back(m.row_start);
+      if (m.n_new <= 0 || m.prefix_len <= 0) continue;
+      if (chunks.empty() || chunks.back().n >= pack || chunks.back().off != m.prefix_off || chunks.back().len != m.prefix_len)
+        chunks.push_back(Chunk{m.prefix_off, m.prefix_len, (int)dp.rows.size(), 0});
+      dp.rows.push_back(m.row_start);
+      dp.cols_max = std::max(dp.cols_max, ++chunks.back().n * G);
     }
-    // rows without a prefix still need their shared-part records: empty items (no keys) write them
-    for (int b = 0; b < B; ++b) {
-      const SeqMeta &m = pl.seqs[b];
-      if (m.n_new <= 0 || m.prefix_len > 0) continue;
-      if (chunks.empty() || (int)chunks.back().size() >= pack ||
-          pl.seqs[a_seq_of_row(pl, chunks.back()[0])].prefix_len > 0) chunks.emplace_back();
-      chunks.back().push_back(m.row_start);
-    }
-    dp.n_shared = splits_for((int64_t)chunks.size() * L.n_kv_heads, max_pfx);
   }
+  auto own_keys = [&](const SeqMeta &m) { return m.P + 1 - m.prefix_len; };      // of the first step, the new key included
+  int64_t keys = 0;
+  int longest = 1;
+  for (const SeqMeta &m : pl.seqs)
+    if (m.n_new > 0) { keys += own_keys(m); longest = std::max(longest, own_keys(m)); }
+  for (const Chunk &c : chunks) { keys += c.len; longest = std::max(longest, c.len); }
+  // Short work: spread over one wave per SIMD slot (2048 of them) a wave has fewer than 384 keys of one kv head.  Then a workgroup is
+  // two kv heads x four sub-ranges and the ranges are as long as one round of workgroups allows, but no shorter than the four
+  // sub-ranges' steps.  Otherwise eight kv heads side by side, two rounds of workgroups (every range of a head costs a
+  // partial record), at least 512 keys each.
+  const bool short_work = keys * L.n_kv_heads < 384 * 8 * (int64_t)ctx->n_cu && ctx->opt_splits == 0;
+  decode_mfma_shape(L.n_kv_heads, short_work, &dp.hw, &dp.kr);
+  dp.groups = (L.n_kv_heads + dp.hw - 1) / dp.hw;
+  auto workgroups = [&](int range) {
+    int64_t n = 0;
+    for (const SeqMeta &m : pl.seqs)
+      if (m.n_new > 0) n += dec_cut(own_keys(m), range).parts;
+    for (const Chunk &c : chunks) n += dec_cut(c.len, range).parts;
+    return n * dp.groups;
+  };
+  const int64_t most = short_work ? ctx->n_cu : 2 * ctx->n_cu;
+  int range = short_work ? 32 * dp.kr : 512;
+  range = std::max<int64_t>(range, keys * dp.groups / most);
+  if (ctx->opt_splits == 0)
+    for (int i = 0; i < 12 && workgroups(range) > most && range < longest; ++i) range += std::max(32, range / 16);
+  const int cap = pl.T <= 16 ? 256 : 64;      // most records of either kind a row may have (every row's place is that large)
+  range = std::max(range, (longest + cap - 1) / cap);
+  auto cut_of = [&](int n) {
+    if (ctx->opt_splits > 0) return dec_cut(n, std::max(1, (n + ctx->opt_splits - 1) / ctx->opt_splits));
+    return dec_cut(n, range);
+  };
+  dp.range = range;
+  for (const SeqMeta &m : pl.seqs)
+    if (m.n_new > 0) dp.n_own = std::max(dp.n_own, cut_of(own_keys(m)).parts);
+  for (const Chunk &c : chunks) dp.n_shared = std::max(dp.n_shared, cut_of(c.len).parts);
   dp.n_device_items = pl.T * dp.groups * dp.n_own;
-  for (const auto &rows : chunks) dp.cols_max = std::max(dp.cols_max, (int)rows.size() * G);
   if (on_device) return dp;
-  for (const auto &rows : chunks)
-    for (int gb = 0; gb < dp.groups; ++gb)
-      for (int sp = 0; sp < dp.n_shared; ++sp) {
+  dp.counts.assign((size_t)2 * pl.T, 0);
+  for (const Chunk &c : chunks) {
+    const DecCut cut = cut_of(c.len);
+    for (int i = 0; i < c.n; ++i) dp.counts[2 * dp.rows[c.first + i] + 1] = cut.parts;
+    for (int sp = 0; sp < cut.parts; ++sp)
+      for (int gb = 0; gb < dp.groups; ++gb) {
         DecItem it{};
-        it.n_rows = (int)rows.size(); it.g = gb * dp.hw; it.split = sp; it.n_splits = dp.n_shared; it.part = dp.n_own + sp; it.shared = 1;
-        for (size_t i = 0; i < rows.size(); ++i) it.rows[i] = rows[i];
+        it.key_row0 = c.off; it.row = c.first; it.kbeg = sp * cut.len; it.kend = std::min(c.len, it.kbeg + cut.len);
+        it.n_rows = (int16_t)c.n; it.g = (int16_t)(gb * dp.hw); it.part = (int16_t)(dp.n_own + sp); it.shared = 1;
         dp.items.push_back(it);
       }
-  for (int row = 0; row < pl.T; ++row)
+  }
+  for (const SeqMeta &m : pl.seqs) {
+    if (m.n_new <= 0) continue;
+    const DecCut cut = cut_of(own_keys(m));
+    dp.counts[2 * m.row_start] = cut.parts;
     for (int gb = 0; gb < dp.groups; ++gb)
-      for (int sp = 0; sp < dp.n_own; ++sp) {
+      for (int sp = 0; sp < cut.parts; ++sp) {
         DecItem it{};
-        it.n_rows = 1; it.g = gb * dp.hw; it.split = sp; it.n_splits = dp.n_own; it.part = sp; it.shared = 0;
-        it.rows[0] = row;
+        it.key_row0 = m.pool_off + m.prefix_len; it.row = m.row_start; it.kbeg = sp * cut.len; it.kend = std::min(own_keys(m), it.kbeg + cut.len);
+        it.n_rows = 1; it.g = (int16_t)(gb * dp.hw); it.part = (int16_t)sp; it.grows = sp == cut.parts - 1;
         dp.items.push_back(it);
       }
+  }
+  // longest first, so that the short ones even out the end
+  std::stable_sort(dp.items.begin(), dp.items.end(), [](const DecItem &x, const DecItem &y) { return x.kend - x.kbeg > y.kend - y.kbeg; });
   return dp;
 }
 
@@ -1089,7 +1110,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
     n_splits = pp.n_own + pp.n_sh;
   }
   const std::vector<DecItem> &ditems = dp.items;
-  const int n_static_items = dp.n_device_items, n_static_n_own = dp.n_own;
+  const int n_static_items = dp.n_device_items;
   const int dec_hw = dp.hw, dec_kr = dp.kr, dec_groups = dp.groups, dec_cols_max = dp.cols_max;
   // kernel family: MFMA for bf16 shapes it covers, plain otherwise
   const bool mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && L.d % 64 == 0 &&
@@ -1112,7 +1133,8 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
     const size_t seq_b = ((size_t)B * sizeof(SeqMeta) + 255) & ~(size_t)255;
     const size_t item_b = ((size_t)n_static_items * sizeof(DecItem) + 255) & ~(size_t)255;
     const size_t rope_b = (size_t)pl.T * (L.head_dim / 2) * sizeof(float2);
-    const size_t need = ws_bytes + seq_b + item_b + rope_b;
+    const size_t count_b = ((size_t)2 * pl.T * sizeof(int32_t) + 255) & ~(size_t)255;
+    const size_t need = ws_bytes + seq_b + item_b + count_b + rope_b;
     if (need > SCRATCH_BYTES)
       return fail(ctx, ALORA_ECAPACITY, "alora_decode_static: this call needs %zu bytes of scratch, the static buffer holds %zu",
                   need, SCRATCH_BYTES);
@@ -1120,6 +1142,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
     char *base = (char *)ctx->scratch_dev;
     SeqMeta *seqs_dev = (SeqMeta *)(base + ws_bytes);
     DecItem *items_dev = (DecItem *)(base + ws_bytes + seq_b);
+    int32_t *counts_dev = (int32_t *)(base + ws_bytes + seq_b + item_b);
     for (int b0 = 0; b0 < B; b0 += STAGE_SEQS) {
       SeqChunk c;
       const int n = std::min(STAGE_SEQS, B - b0);
@@ -1127,8 +1150,8 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
       hipLaunchKernelGGL(stage_seqs_kernel, dim3(1), dim3(64), 0, s, c, n, seqs_dev + b0);
     }
     if (decode_mfma && n_static_items > 0)
-      hipLaunchKernelGGL(make_decode_items_kernel, dim3((n_static_items + 255) / 256), dim3(256), 0, s, items_dev,
-                         n_static_items, dec_groups, dec_hw, n_static_n_own);
+      hipLaunchKernelGGL(make_decode_items_kernel, dim3((n_static_items + 255) / 256), dim3(256), 0, s, seqs_dev, B, items_dev,
+                         counts_dev, dec_groups, dec_hw, dp.n_own, dp.range, ctx->opt_splits);
     Workspace w = layout_workspace(base, L, pl.T, esz, n_splits, k_splits, 0, false);
     w.mfma = mfma;
     w.k_splits = k_splits;
@@ -1142,7 +1165,8 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
     w.dec_hw = dec_hw; w.dec_kr = dec_kr; w.dec_cols_max = dec_cols_max;
     w.any_adapter = pl.any_adapter;
     w.rope_by_row = true;
-    w.rope_rows = (float2 *)(base + ws_bytes + seq_b + item_b);
+    if (decode_mfma) w.merge = MergeCounts{counts_dev, dp.n_own};
+    w.rope_rows = (float2 *)(base + ws_bytes + seq_b + item_b + count_b);
     w.rope = w.rope_rows;
     const int saved_profile = ctx->opt_profile;
     ctx->opt_profile = 0;             // the event brackets of the profiling option create events: not here
@@ -1163,7 +1187,9 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   std::vector<AttnItem> qtiles;
   if (attn_mfma) qtiles = build_prefill_items(pl, L, B, attn_waves, pp);
   const size_t seq_bytes = ((size_t)B * sizeof(SeqMeta) + 15) & ~(size_t)15;
-  const size_t work_bytes = (qtiles.size() * sizeof(AttnItem) + ditems.size() * sizeof(DecItem) + 15) & ~(size_t)15;   // one of the two lists
+  const size_t list_bytes = (qtiles.size() * sizeof(AttnItem) + ditems.size() * sizeof(DecItem) + 15) & ~(size_t)15;   // one of the two lists
+  const size_t row_bytes = ((dp.rows.size() + dp.counts.size()) * sizeof(int32_t) + 15) & ~(size_t)15;                // decode: shared items' rows, records per row
+  const size_t work_bytes = list_bytes + row_bytes;
   const size_t scale_bytes = stack ? (((size_t)L.n_adapters * sizeof(float) + 15) & ~(size_t)15) : 0;
   const size_t meta_bytes = seq_bytes + work_bytes + scale_bytes;
   MetaSlot *slot = nullptr;
@@ -1172,6 +1198,8 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   memcpy(slot->host, pl.seqs.data(), (size_t)B * sizeof(SeqMeta));
   if (!qtiles.empty()) memcpy(slot->host + seq_bytes, qtiles.data(), qtiles.size() * sizeof(AttnItem));
   if (!ditems.empty()) memcpy(slot->host + seq_bytes, ditems.data(), ditems.size() * sizeof(DecItem));
+  if (!dp.counts.empty()) memcpy(slot->host + seq_bytes + list_bytes, dp.counts.data(), dp.counts.size() * sizeof(int32_t));
+  if (!dp.rows.empty()) memcpy(slot->host + seq_bytes + list_bytes + dp.counts.size() * sizeof(int32_t), dp.rows.data(), dp.rows.size() * sizeof(int32_t));
   if (scale_bytes) memcpy(slot->host + seq_bytes + work_bytes, layers[0].scale, (size_t)L.n_adapters * sizeof(float));
   const int n16 = (int)((meta_bytes + 15) / 16);
   const bool carried = B <= FEW_SEQS && n16 <= STAGE_N16 && !ctx->opt_stage_copy;      // by the call's first kernel
@@ -1196,6 +1224,10 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   w.n_qtiles = (int)qtiles.size();
   w.ditems = (const DecItem *)(slot->dev + seq_bytes);
   w.n_ditems = (int)ditems.size();
+  if (!dp.counts.empty()) {
+    w.merge = MergeCounts{(const int32_t *)(slot->dev + seq_bytes + list_bytes), dp.n_own};
+    w.drows = w.merge.counts + dp.counts.size();
+  }
   w.dec_hw = dec_hw; w.dec_kr = dec_kr; w.dec_cols_max = dec_cols_max;
   w.scale_dev = scale_bytes ? (const float *)(slot->dev + seq_bytes + work_bytes) : nullptr;
   w.any_adapter = pl.any_adapter;

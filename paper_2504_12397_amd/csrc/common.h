@@ -135,8 +135,18 @@ void launch_attn_plain(const float *Q, const T *cacheK, const T *cacheV, const S
                        const LayerDims &L, int T_rows, int n_splits, float *partials, T *out, hipStream_t s);
 // merge of the per-split partials (log-sum-exp weights); partial layout per (row, q head, split):
 // head_dim accumulators, running max, running sum
+// counts == nullptr: every record is there; otherwise row r has counts[2 r] records from 0 on and counts[2 r + 1] from first_shared on
+struct MergeCounts {
+  const int32_t *counts;
+  int first_shared;
+  __device__ __forceinline__ void of_row(int row, int n_parts, int &own, int &all) const {
+    if (counts == nullptr) { own = all = n_parts; return; }
+    own = counts[2 * row];
+    all = own + counts[2 * row + 1];
+  }
+};
 template <typename T>
-void launch_attn_merge(const float *partials, const LayerDims &L, int T_rows, int n_splits, T *out, hipStream_t s);
+void launch_attn_merge(const float *partials, const LayerDims &L, int T_rows, int n_splits, MergeCounts mc, T *out, hipStream_t s);
 
 template <typename T>
 void launch_silu_mul(const T *gate, const T *up, T *out, int64_t n, hipStream_t s);

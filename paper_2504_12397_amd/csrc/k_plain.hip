@@ -599,16 +599,19 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float *__restri
 // MU is: a short batch over a long cache has few (row, head) pairs and a hundred records each, and every group
 // of records is a memory round trip).
 template <typename T, int MU>
-__global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict__ part, LayerDims L, int n_splits,
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict__ part, LayerDims L, int n_parts, MergeCounts mc,
                                                          int64_t n_rh, T *__restrict__ out) {
   const int lane = threadIdx.x & 63, h = L.head_dim;
   const int64_t rh = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);       // row * Hq + hq
   if (rh >= n_rh) return;
-  const float *p = part + rh * n_splits * (h + 2);
+  const float *p0 = part + rh * n_parts * (h + 2);
+  int own, n_splits;
+  mc.of_row((int)(rh / L.n_q_heads), n_parts, own, n_splits);
+  auto rec = [&](int s) { return p0 + (int64_t)(s < own ? s : s + mc.first_shared - own) * (h + 2); };
   float M = -INFINITY;
   for (int s0 = 0; s0 < n_splits; s0 += 64) {
     const int s = s0 + lane;
-    M = fmaxf(M, s < n_splits ? p[s * (h + 2) + h] : -INFINITY);
+    M = fmaxf(M, s < n_splits ? rec(s)[h] : -INFINITY);
   }
   M = wave_max(M);
   float denom = 0.f;
@@ -617,8 +620,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict
     float ms[MU], ls[MU], v[MU][ATT_DMAX];
 #pragma unroll
     for (int u = 0; u < MU; ++u) {
-      const int s = min(s0 + u, n_splits - 1);
-      const float *ps = p + s * (h + 2);
+      const float *ps = rec(min(s0 + u, n_splits - 1));
       ms[u] = ps[h];
       ls[u] = ps[h + 1];
 #pragma unroll
@@ -647,16 +649,19 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict
 // caches): one workgroup per pair, its four waves take the records w, w + 4, w + 8, ... (eight in flight each, two
 // columns per lane and load), and their sums are added in wave order.  head_dim <= 128.
 template <typename T>
-__global__ __launch_bounds__(256) void attn_merge_wide_kernel(const float *__restrict__ part, LayerDims L, int n_splits,
+__global__ __launch_bounds__(256) void attn_merge_wide_kernel(const float *__restrict__ part, LayerDims L, int n_parts, MergeCounts mc,
                                                               T *__restrict__ out) {
   __shared__ float s_acc[4][130];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = L.head_dim;
   const int64_t rh = blockIdx.x;
-  const float *p = part + rh * n_splits * (h + 2);
+  const float *p0 = part + rh * n_parts * (h + 2);
+  int own, n_splits;
+  mc.of_row((int)(rh / L.n_q_heads), n_parts, own, n_splits);
+  auto rec = [&](int s) { return p0 + (int64_t)(s < own ? s : s + mc.first_shared - own) * (h + 2); };
   float M = -INFINITY;
   for (int s0 = 0; s0 < n_splits; s0 += 64) {
     const int s = s0 + lane;
-    M = fmaxf(M, s < n_splits ? p[s * (h + 2) + h] : -INFINITY);
+    M = fmaxf(M, s < n_splits ? rec(s)[h] : -INFINITY);
   }
   M = wave_max(M);
   float denom = 0.f;
@@ -668,8 +673,7 @@ __global__ __launch_bounds__(256) void attn_merge_wide_kernel(const float *__res
     float2 v[MU];
 #pragma unroll
     for (int u = 0; u < MU; ++u) {
-      const int s = min(s0 + 4 * u, n_splits - 1);
-      const float *ps = p + s * (h + 2);
+      const float *ps = rec(min(s0 + 4 * u, n_splits - 1));
       ms[u] = ps[h];
       ls[u] = ps[h + 1];
       v[u] = col_ok ? *reinterpret_cast<const float2 *>(ps + 2 * lane) : make_float2(0.f, 0.f);
@@ -718,20 +722,20 @@ template void launch_attn_plain<bf16>(const float *, const bf16 *, const bf16 *,
                                       const LayerDims &, int, int, float *, bf16 *, hipStream_t);
 
 template <typename T>
-void launch_attn_merge(const float *partials, const LayerDims &L, int T_rows, int n_splits, T *out, hipStream_t s) {
+void launch_attn_merge(const float *partials, const LayerDims &L, int T_rows, int n_splits, MergeCounts mc, T *out, hipStream_t s) {
   if (T_rows == 0) return;
   const int64_t n_rh = (int64_t)T_rows * L.n_q_heads;
   if (n_splits >= 16 && n_rh <= 512 && L.head_dim <= 128 && L.head_dim % 2 == 0)
-    hipLaunchKernelGGL((attn_merge_wide_kernel<T>), dim3((unsigned)n_rh), dim3(256), 0, s, partials, L, n_splits, out);
+    hipLaunchKernelGGL((attn_merge_wide_kernel<T>), dim3((unsigned)n_rh), dim3(256), 0, s, partials, L, n_splits, mc, out);
   else if (n_splits > 16)
-    hipLaunchKernelGGL((attn_merge_kernel<T, 32>), dim3((unsigned)((n_rh + 3) / 4)), dim3(256), 0, s, partials, L, n_splits,
+    hipLaunchKernelGGL((attn_merge_kernel<T, 32>), dim3((unsigned)((n_rh + 3) / 4)), dim3(256), 0, s, partials, L, n_splits, mc,
                        n_rh, out);
   else
-    hipLaunchKernelGGL((attn_merge_kernel<T, 8>), dim3((unsigned)((n_rh + 3) / 4)), dim3(256), 0, s, partials, L, n_splits,
+    hipLaunchKernelGGL((attn_merge_kernel<T, 8>), dim3((unsigned)((n_rh + 3) / 4)), dim3(256), 0, s, partials, L, n_splits, mc,
                        n_rh, out);
 }
-template void launch_attn_merge<float>(const float *, const LayerDims &, int, int, float *, hipStream_t);
-template void launch_attn_merge<bf16>(const float *, const LayerDims &, int, int, bf16 *, hipStream_t);
+template void launch_attn_merge<float>(const float *, const LayerDims &, int, int, MergeCounts, float *, hipStream_t);
+template void launch_attn_merge<bf16>(const float *, const LayerDims &, int, int, MergeCounts, bf16 *, hipStream_t);
 
 // ---------------------------------------------------------------------------------------
 template <typename T>

@@ -111,25 +111,34 @@ void launch_attn_prefill_mfma(const AttnArgs &a, int n_work, int G, int waves, b
 float attn_prefill_mfma_q_scale(const LayerDims &L, bool fold);
 
 // Decode attention (Eq.4): one query row per sequence over its whole cache.
-// One workgroup of the decode kernel: the query heads of up to 16 / G rows, for up to eight kv heads (one wave
-// each), against one range of keys.  shared = 0: the row's own cached positions [prefix_len, pos];
-// shared = 1: the prefix [0, prefix_len) that all the item's rows name (one physical copy), so
-// its keys and values are read once for all of them.
+// One workgroup of the decode kernel: the query heads of one row, or of up to 32 / G rows on one shared prefix, for up to eight kv
+// heads, against one range of keys.  shared = 0: the row's own cached positions from prefix_len on; shared = 1: the prefix that
+// all the item's rows name (one physical copy), so its keys and values are read once for all of them.
 struct DecItem {
-  int32_t n_rows;           // rows whose heads fill the MFMA columns (column = row index * G + head)
-  int32_t g;                // first kv head of the workgroup (its waves take g, g + 1, ...)
-  int32_t split, n_splits;  // this item's share of its key range
-  int32_t part;             // which of the n_parts partial records of (row, head) it writes
-  int32_t shared;
-  int32_t pad_[2];
-  int32_t rows[16];
+  int64_t key_row0;         // pool row of key 0 of this item
+  int32_t row;              // own: the row; shared: where the item's rows begin in DecodeArgs::rows
+  int32_t kbeg, kend;       // key range, counted from key_row0
+  int16_t n_rows;           // rows whose heads fill the MFMA columns (column = row index * G + head); 0: nothing to do
+  int16_t g;                // first kv head of the workgroup
+  int16_t part;             // which of the n_parts partial records of (row, head) it writes
+  int8_t shared;
+  int8_t grows;             // the range ends at the row's newest key: one more in every step of a multi-step decode
 };
+// How the keys of one row (or prefix) are cut: `parts` ranges of `len` keys (whole steps of 32), the last one shorter.
+struct DecCut { int parts, len; };
+__host__ __device__ inline DecCut dec_cut(int n_keys, int range) {
+  int parts = (n_keys + range - 1) / range;
+  if (parts < 1) parts = 1;
+  const int len = ((n_keys + parts - 1) / parts + 31) & ~31;
+  parts = (n_keys + len - 1) / (len > 0 ? len : 1);
+  return DecCut{parts < 1 ? 1 : parts, len};
+}
 struct DecodeArgs {
   const _Float16 *Q;        // [rows, n_q] rotated queries as fp16
   const bf16 *K, *V;        // pool [tokens, n_kv]
-  const SeqMeta *seqs;
-  RowMeta rm;               // seq and pos of every row
   const DecItem *items;     // one per workgroup
+  const int32_t *rows;      // rows of the shared items
+  int pos_shift;            // step of a multi-step decode
   int n_q, n_kv, n_q_heads, n_kv_heads;
   int n_parts;              // partial records per (row, head)
   int heads_per_wg;         // kv heads a workgroup covers (one wave each) and ...
@@ -140,7 +149,7 @@ struct DecodeArgs {
 };
 bool attn_decode_mfma_supported(const LayerDims &L);
 void launch_attn_decode_mfma(const DecodeArgs &a, int n_items, hipStream_t s);
-void decode_mfma_shape(int n_kv_heads, int *heads_per_wg, int *ranges_per_wg);
+void decode_mfma_shape(int n_kv_heads, bool short_work, int *heads_per_wg, int *ranges_per_wg);
 
 bool gemm_mfma_supported(int M, int N, int K);
 int gemm_mfma_pick_splits(int M, int N, int K, int n_cu);
