@@ -433,7 +433,7 @@ Workspace layout_workspace(char *base, const LayerDims &L, int T, size_t esz, in
   w.rm.adapter = b.take<int32_t>(T);
   w.rm.slot = b.take<int64_t>(T);
   w.rm.present16 = b.take<unsigned long long>((T + 15) / 16);
-  w.xh = b.take<char>((size_t)((T + 31) & ~31) * L.d * esz);      // (operand order comes in blocks of 32 rows)
+  w.xh = b.take<char>((size_t)(T <= QKV_STREAM_ROWS ? (T + 31) & ~31 : T) * L.d * esz);      // (operand order: blocks of 32 rows)
   w.tlow = b.take<float>((size_t)T * 3 * std::max(L.rank, 1));
   w.y_floats = (size_t)T * L.n_qkv * (std::max(k_splits, 1) + 1);
   if (stack) {      // split-K partials of W_o / W_down and of the down-projections of their adapters
@@ -479,7 +479,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
   // the weights past all rows, beyond that the one whose tiles are large in both directions; both add in one order.
   const bool fuse = mfma && q_half && ctx->opt_rope_fuse && ctx->opt_gemm_splits <= 1 && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
   const bool stream = fuse && prep_mfma && ctx->opt_gemm_tile == 0 && pl.T <= QKV_STREAM_ROWS &&
-                      qkv_stream_supported(pl.T, L.n_qkv, L.d, L.n_q, L.n_kv, L.head_dim);
+                      qkv_stream_supported(ly->W_qkv, pl.T, L.n_qkv, L.d, L.n_q, L.n_kv, L.head_dim);
   auto stage_of = [&](bool first) {
     StagedCall st{};
     if (w.stage_n16 > 0) {
@@ -809,7 +809,8 @@ struct DecodePlan {
   int n_device_items = 0;          // size of the device-built list: rows x head groups x n_own
   int hw = 1, kr = 1, groups = 1, cols_max = 1;
 };
-DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, int B, int n_steps, bool on_device) {
+// `cap`: most records of either kind a row may have (every row's place in memory is that large).
+DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, int cap, bool on_device) {
   DecodePlan dp;
   const int G = L.n_q_heads / L.n_kv_heads;
   const int pack = std::max(1, 32 / G);
@@ -818,13 +819,13 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
   std::vector<Chunk> chunks;
   dp.cols_max = G;
   if (pl.any_prefix) {
-    std::vector<int> order(B);
-    for (int b = 0; b < B; ++b) order[b] = b;
+    std::vector<int> order(pl.B);
+    for (int b = 0; b < pl.B; ++b) order[b] = b;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
       if (pl.seqs[x].prefix_off != pl.seqs[y].prefix_off) return pl.seqs[x].prefix_off < pl.seqs[y].prefix_off;
       return pl.seqs[x].prefix_len < pl.seqs[y].prefix_len;
     });
-    for (int i = 0; i < B; ++i) {
+    for (int i = 0; i < pl.B; ++i) {
       const SeqMeta &m = pl.seqs[order[i]];
       if (m.n_new <= 0 || m.prefix_len <= 0) continue;
       if (chunks.empty() || chunks.back().n >= pack || chunks.back().off != m.prefix_off || chunks.back().len != m.prefix_len)
@@ -843,7 +844,7 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
   // two kv heads x four sub-ranges and the ranges are as long as one round of workgroups allows, but no shorter than the four
   // sub-ranges' steps.  Otherwise eight kv heads side by side, two rounds of workgroups (every range of a head costs a
   // partial record), at least 512 keys each.
-  const bool short_work = keys * L.n_kv_heads < 384 * 8 * (int64_t)ctx->n_cu && ctx->opt_splits == 0;
+  const bool short_work = keys * L.n_kv_heads < 384 * 8 * (int64_t)ctx->n_cu && ctx->opt_splits == 0 && cap > 1;
   decode_mfma_shape(L.n_kv_heads, short_work, &dp.hw, &dp.kr);
   dp.groups = (L.n_kv_heads + dp.hw - 1) / dp.hw;
   auto workgroups = [&](int range) {
@@ -858,7 +859,6 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
   range = std::max<int64_t>(range, keys * dp.groups / most);
   if (ctx->opt_splits == 0)
     for (int i = 0; i < 12 && workgroups(range) > most && range < longest; ++i) range += std::max(32, range / 16);
-  const int cap = pl.T <= 16 ? 256 : 64;      // most records of either kind a row may have (every row's place is that large)
   range = std::max(range, (longest + cap - 1) / cap);
   auto cut_of = [&](int n) {
     if (ctx->opt_splits > 0) return dec_cut(n, std::max(1, (n + ctx->opt_splits - 1) / ctx->opt_splits));
@@ -1098,20 +1098,6 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   int n_splits = pick_splits(ctx, pl.T, L.n_kv_heads, pl.max_len);
   const bool decode_mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && decode &&
                            attn_decode_mfma_supported(L);
-  // work lists of the MFMA attention kernels (the number of partial records per (row, head) comes out of them)
-  DecodePlan dp;
-  PrefillPlan pp;
-  if (decode_mfma) {
-    dp = plan_decode_items(ctx, pl, L, B, n_steps, use_static);
-    n_splits = dp.n_own + dp.n_shared;
-  }
-  if (attn_mfma) {
-    pp = plan_prefill_ranges(ctx, pl, L, B, attn_waves);
-    n_splits = pp.n_own + pp.n_sh;
-  }
-  const std::vector<DecItem> &ditems = dp.items;
-  const int n_static_items = dp.n_device_items;
-  const int dec_hw = dp.hw, dec_kr = dp.kr, dec_groups = dp.groups, dec_cols_max = dp.cols_max;
   // kernel family: MFMA for bf16 shapes it covers, plain otherwise
   const bool mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && L.d % 64 == 0 &&
                     (L.n_adapters == 0 || (L.rank % 8 == 0 && L.n_adapters <= 64)) && L.n_q % 32 == 0 &&
@@ -1121,6 +1107,32 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   int k_segments = 1;
   if (mfma && ctx->opt_gemm_splits > 0) k_segments = L.d % (64 * ctx->opt_gemm_splits) == 0 ? ctx->opt_gemm_splits : 1;
   const int k_splits = (k_segments > 1 && gemm_mfma_split_segments(pl.T, L.n_qkv, ctx->n_cu)) ? k_segments : 1;
+  // What the static entry point needs with `n` partial records per (row, head) and `groups` work items per row and record
+  auto static_bytes = [&](int n, int groups) {
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    return up(layout_workspace(nullptr, L, pl.T, esz, n, k_splits, 0, false).bytes) + up((size_t)B * sizeof(SeqMeta)) +
+           up((size_t)pl.T * groups * n * sizeof(DecItem)) + up((size_t)2 * pl.T * sizeof(int32_t)) +
+           (size_t)pl.T * (L.head_dim / 2) * sizeof(float2);
+  };
+  // work lists of the MFMA attention kernels (the number of partial records per (row, head) comes out of them)
+  DecodePlan dp;
+  PrefillPlan pp;
+  if (decode_mfma) {
+    // One long sequence among many short ones asks for many records in every row's place: bounded to about 130 MB at 32 heads,
+    // and to what the static scratch array holds where one record per row fits there (both entry points cut the keys alike).
+    int cap = pl.T <= 16 ? 256 : std::max(1, std::min(64, 8192 / pl.T));
+    if (!pl.any_prefix && static_bytes(1, (L.n_kv_heads + 7) / 8) <= SCRATCH_BYTES)
+      while (cap > 1 && static_bytes(cap, (L.n_kv_heads + 1) / 2) > SCRATCH_BYTES) --cap;
+    dp = plan_decode_items(ctx, pl, L, cap, use_static);
+    n_splits = dp.n_own + dp.n_shared;
+  }
+  if (attn_mfma) {
+    pp = plan_prefill_ranges(ctx, pl, L, B, attn_waves);
+    n_splits = pp.n_own + pp.n_sh;
+  }
+  const std::vector<DecItem> &ditems = dp.items;
+  const int n_static_items = dp.n_device_items;
+  const int dec_hw = dp.hw, dec_kr = dp.kr, dec_groups = dp.groups, dec_cols_max = dp.cols_max;
   const bool f32_tail = stack && !mfma && layers[0].dtype == ALORA_BF16;
   Workspace probe = layout_workspace(nullptr, L, pl.T, esz, n_splits, k_splits, layers[0].intermediate, stack, f32_tail);
   if (use_static) {

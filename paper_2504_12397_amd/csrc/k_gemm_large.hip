@@ -508,6 +508,7 @@ static void launch_cfg(const GemmArgs &g, hipStream_t s) {
 // (32-bit byte offsets into both operands; at least four k-tiles per split, in pairs)
 bool gemm_large_supported(const GemmArgs &g, int epi) {
   const uint64_t b_rows = epi == GEMM_EPI_SWIGLU ? g.N / 2 : g.N;
+  if (!lds_aligned(g.A) || !lds_aligned(g.B) || (epi == GEMM_EPI_SWIGLU && !lds_aligned(g.B2)) || g.lda % 8 != 0 || g.ldb % 8 != 0) return false;
   return g.K % (128 * g.k_splits) == 0 && g.K >= 256 * g.k_splits && g.N % 32 == 0 && b_rows * g.ldb * 2 < (1ull << 31) && !(epi == GEMM_EPI_PARTIAL && g.lora_split) && (uint64_t)g.M * g.lda * 2 < (epi == GEMM_EPI_PARTIAL ? 1ull << 31 : ~0ull);
 }
 

@@ -342,7 +342,7 @@ static void launch_prep_ch(const PrepArgs &a, hipStream_t s) {
   const int row_tiles = (a.T + PREP_ROWS - 1) / PREP_ROWS;
   if (a.rank == 0 || a.A == nullptr || a.n_used == 0) {
     launch_norm<CH>(a, s);
-  } else if (a.few == 2 || (a.few == 1 && row_tiles * ((3 * a.rank + 15) / 16) * a.n_used <= PREP_FEW)) {
+  } else if (a.few == 2 || !lds_aligned(a.A) || (a.few == 1 && row_tiles * ((3 * a.rank + 15) / 16) * a.n_used <= PREP_FEW)) {
     hipLaunchKernelGGL(prep_few_kernel<CH>, dim3(row_tiles, (3 * a.rank + 15) / 16, a.n_used), dim3(512), 0, s, a);
   } else {
     launch_norm<CH>(a, s);

@@ -220,8 +220,8 @@ __global__ __launch_bounds__(64 * (CW + 4)) void qkv_stream_kernel(GemmArgs g, i
   }
 }
 
-bool qkv_stream_supported(int M, int N, int K, int n_q, int n_kv, int head_dim) {
-  return M > 0 && head_dim == 128 && K % QS_K == 0 && n_q % 128 == 0 && n_kv % 128 == 0 && (uint64_t)N * K * 2 < (1ull << 31);
+bool qkv_stream_supported(const void *W, int M, int N, int K, int n_q, int n_kv, int head_dim) {
+  return M > 0 && lds_aligned(W) && head_dim == 128 && K % QS_K == 0 && n_q % 128 == 0 && n_kv % 128 == 0 && (uint64_t)N * K * 2 < (1ull << 31);
 }
 
 template <int CW, int PW>

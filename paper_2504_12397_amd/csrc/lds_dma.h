@@ -28,6 +28,9 @@ __device__ __forceinline__ i32x4 make_rsrc(const void *p, uint64_t bytes) {
   return r;
 }
 
+// Requests to LDS want 16-byte addresses (ordinary loads do not care): weights that lie otherwise take the kernels without them.
+inline bool lds_aligned(const void *p) { return ((uintptr_t)p & 15) == 0; }
+
 // One rotation pair (u, w) = columns c and c + h/2 of a head (Eq.3's K_t before it is appended), the sums and products in one
 // fixed form: the rows that different kernels append are compared bit for bit.
 __device__ __forceinline__ float rope_lo(float u, float w, float cs, float sn) { return __builtin_fmaf(u, cs, -(w * sn)); }

@@ -158,7 +158,7 @@ bool gemm_mfma_split_segments(int M, int N, int n_cu);     // one workgroup per 
 void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s);
 // many rows: 256 x 256 or 128 x 256 tiles (rows = 256 / 128), one running sum over K; BF16, SWIGLU and ROPE epilogues
 // few rows: the whole QKV projection with rotation and append, A packed (PrepArgs::packed)
-bool qkv_stream_supported(int M, int N, int K, int n_q, int n_kv, int head_dim);
+bool qkv_stream_supported(const void *W, int M, int N, int K, int n_q, int n_kv, int head_dim);
 void launch_qkv_stream(const GemmArgs &g, int n_cu, hipStream_t s);
 struct GemmLargePlan { int rows, splits; };      // tile rows (128 / 256); workgroups per output tile (> 1: PARTIAL)
 GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits);      // hint 2 / 3: 128 / 256 rows

@@ -1,0 +1,150 @@
+"""Parity at the edges of the tiles and rules that choose a kernel: row counts around a tile's height, widths that leave
+a partial last tile or one that straddles q | k | v, ranks that are no multiple of 16, short reductions, records
+bounded by memory.  Everything against the oracle at the stated tolerances, cache bytes outside the new rows exact."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import alora_oracle as orc
+from paper_2504_12397_amd import workloads as wl
+from tests import helpers as H
+from tests.test_gpu_parity import SMALL_BF16, SMALL_F32, check_case
+from tests.test_zz_no_alloc import _both
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ab():
+    from paper_2504_12397_amd import binding
+    return binding
+
+
+@pytest.fixture()
+def ctx(ab):
+    c = ab.Context(0)
+    yield c
+    c.close()
+
+
+def _split(T, n):
+    """T rows as n sequences of uneven lengths"""
+    cuts = [T * i * i // (n * n) for i in range(n + 1)]
+    return [max(0, b - a) for a, b in zip(cuts, cuts[1:])]
+
+
+# heads / kv heads give 6, 20, 32 columns of 256: tiles of 8, 12 and 16 rotation pairs, the 12-pair ones crossing heads and kinds
+@pytest.mark.parametrize("hq,hkv,rank,T", [(8, 2, 8, 1), (8, 2, 24, 33), (32, 4, 64, 32), (32, 4, 8, 65), (32, 16, 16, 129),
+                                           (32, 16, 40, 256), (32, 4, 16, 255)])
+def test_few_rows_through_the_streaming_projection(ab, ctx, hq, hkv, rank, T):
+    shape = wl.LayerShape(d=512, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rank=rank, n_adapters=4)
+    n = min(T, 5)
+    S = _split(T, n)
+    P = [40, 0, 17, 90, 3][:n]
+    case = H.make_case(shape, P, S, [P[b] + (S[b] // 2 if b % 2 else 0) for b in range(n)], [3, 1, -1, 2, 0][:n], seed=1000 + T,
+                       prefix="random")
+    check_case(ab, ctx, case)
+
+
+@pytest.mark.parametrize("rank,T,few", [(8, 15, 2), (24, 31, 0), (40, 257, 0), (40, 257, 2), (64, 33, 0), (64, 2049, 1)])
+def test_down_projection_in_one_kernel_or_two(ab, ctx, rank, T, few):
+    """t = s A x_hat for every row from the kernel of few rows and from that of many; 3 * rank columns that end inside a tile."""
+    ctx.set_option("prep_split", few)
+    shape = wl.LayerShape(d=1024, n_q_heads=2, n_kv_heads=1, head_dim=128, rank=rank, n_adapters=3)
+    S = _split(T, 4)
+    case = H.make_case(shape, [5] * 4, S, [5, 5 + S[1] // 2, 5, 0], [0, 2, -1, 2], seed=1100 + rank + T, prefix="random")
+    check_case(ab, ctx, case)
+
+
+def _one_stack_layer(ab, ctx, shape, T, seed, ads=(1, -1, 2)):
+    """A call of T rows in three sequences from empty caches through one whole layer, against the oracle"""
+    rng = wl.Rng(seed)
+    tensors = wl.make_layer(shape, rng, "L0")
+    layer = H.oracle_layer(tensors, shape)
+    S = _split(T, 3)
+    ks = [S[0] // 2, 0, 0]
+    xs = [H.f64(wl.make_hidden(rng, f"x{b}", S[b], shape)) for b in range(3)]
+    cu = [0, S[0], S[0] + S[1], T]
+    cache = [ab.KVCache([s + 1 for s in S], shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda")]
+    xg = torch.from_numpy(np.concatenate(xs)).to(shape.torch_dtype).cuda().contiguous()
+    out = ab.alora_stack_prefill(ctx, [H.gpu_layer(tensors, shape)], cache, xg, cu, ks, list(ads))
+    torch.cuda.synchronize()
+    for b in range(3):
+        ref, _ = orc.ref_stack_full([layer], xs[b], ks[b], ads[b], shape.dtype)
+        e = H.rel_err(H.f64(out[cu[b]:cu[b + 1]]), ref)
+        H.report(check="one layer, large tiles", rows=T, sequence=b, err=e)
+        assert e <= H.TOL[shape.dtype], f"sequence {b}: {e:.3e}"
+
+
+# 1216 = 19 * 64: no large tiles for W_down (the reduction is no multiple of 128), 9.5 column tiles of gate | up;
+# 1280: W_down split over two workgroups per tile
+@pytest.mark.parametrize("T,inter,tile,rest,rank", [(257, 1280, 0, False, 16), (300, 1216, 2, True, 24), (511, 1280, 3, True, 8),
+                                                    (513, 1216, 3, False, 8), (700, 1280, 0, True, 40), (700, 1280, 2, False, 16)])
+def test_many_rows_through_the_large_tiles(ab, ctx, T, inter, tile, rest, rank):
+    ctx.set_option("gemm_tile", tile)
+    shape = dataclasses.replace(SMALL_BF16, intermediate=inter, rank=rank, adapt_rest=rest)
+    _one_stack_layer(ab, ctx, shape, T, 1200 + T + inter)
+
+
+@pytest.mark.parametrize("T", [20, 300])
+def test_weights_that_are_not_16_byte_aligned(ab, ctx, T):
+    """Parameters that are views into one flat buffer, eight bytes off: the kernels whose weights go to LDS by request
+    are passed by."""
+    shape = dataclasses.replace(SMALL_BF16, intermediate=1280)
+    case = H.make_case(shape, [30, 7], [T - 8, 8], [30, 7], [1, 2], seed=1300 + T, prefix="random")
+    tensors = {}
+    for name, t in case.tensors.items():
+        if isinstance(t, torch.Tensor):
+            flat = torch.empty(t.numel() + 4, dtype=t.dtype, device="cuda")
+            flat[4:] = t.reshape(-1).cuda()
+            t = flat[4:].view(t.shape)
+            assert t.data_ptr() % 16 == 8
+        tensors[name] = t
+    layer = ab.Layer(tensors, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.rms_eps, shape.rope_theta, shape.intermediate)
+    x = case.x_packed.cuda().contiguous()
+    for call in (ab.alora_prefill, ab.alora_stack_prefill):
+        stack = call is ab.alora_stack_prefill
+        cache, same = H.gpu_cache(case), H.gpu_cache(case)
+        aligned = H.gpu_layer(case, shape)
+        args = (x, case.cu, case.k, case.adapter)
+        out = call(ctx, [layer], [cache], *args) if stack else call(ctx, layer, cache, *args)
+        want = call(ctx, [aligned], [same], *args) if stack else call(ctx, aligned, same, *args)
+        torch.cuda.synchronize()
+        if not stack:
+            ref, _ = H.oracle_prefill(case)
+            assert H.rel_err(H.f64(out), ref) <= H.TOL["bf16"]
+        # two correct results at half the tolerance each
+        assert H.rel_err(H.f64(out), H.f64(want)) <= H.TOL["bf16"]
+
+
+@pytest.mark.parametrize("T", [1, 3, 16, 17, 63, 65])
+@pytest.mark.parametrize("d,hq,hkv,h", [(256, 4, 2, 64), (200, 6, 3, 36), (520, 16, 1, 48)])
+def test_small_calls_on_the_plain_kernels(ab, ctx, T, d, hq, hkv, h):
+    """One kernel for projection, rotation and append; hidden sizes that end inside its 256 values of k, pair counts that end
+    inside a tile, head sizes with and without 16-byte loads, more query heads per kv head than one workgroup takes."""
+    shape = dataclasses.replace(SMALL_F32, d=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=h, rank=5)
+    S = _split(T, min(T, 3))
+    n = len(S)
+    case = H.make_case(shape, [64, 0, 129][:n], S, [64, S[1] // 2 if n > 1 else 0, 130][:n], [0, 1, -1][:n], seed=1400 + T + d,
+                       prefix="random")
+    check_case(ab, ctx, case)
+
+
+@pytest.mark.parametrize("P", [[4000] + [60] * 20, [31, 32, 33, 1, 0, 127, 128, 129, 511, 513], [9000], [700] * 33])
+def test_decode_key_ranges(ab, ctx, P):
+    """Lists of uneven lengths: one long sequence among short ones, lengths around a step of 32 keys, one sequence alone."""
+    shape = wl.LayerShape(d=512, n_q_heads=8, n_kv_heads=4, head_dim=128, rank=16, n_adapters=3)
+    n = len(P)
+    case = H.make_case(shape, P, [1] * n, [max(0, p - 10) for p in P], [b % 4 - 1 for b in range(n)], seed=1500 + n, prefix="random")
+    check_case(ab, ctx, case, decode=True)
+
+
+def test_static_decode_of_one_long_sequence_among_short_ones(ab, ctx):
+    """64 sequences, one of them long: as many partial records per row as the long one alone would like do not fit the
+    static scratch array; the call is taken with fewer, bit-identical to alora_decode."""
+    shape = wl.LayerShape(d=512, n_q_heads=32, n_kv_heads=8, head_dim=128, rank=16, n_adapters=2)
+    P = [16448] + [100 + b for b in range(63)]
+    case = H.make_case(shape, P, [1] * 64, P, [b % 3 - 1 for b in range(64)], seed=1600, prefix="random")
+    _both(ab, ctx, case)
