@@ -539,7 +539,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
         launch_qkv_stream(g, ctx->n_cu, s);
         rope_fused = true;
       } else if (fuse && !w.rope_by_row && pl.T > 256 && gemm_mfma_rope_supported(g, L.head_dim)) {
-        launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, GEMM_EPI_ROPE, ctx->n_cu, 1).rows, s);
+        launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, GEMM_EPI_ROPE, ctx->n_cu, 1).tile, s);
         rope_fused = true;
       } else {
         launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
@@ -651,7 +651,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     const int epi = pn.splits > 1 ? GEMM_EPI_PARTIAL : GEMM_EPI_BF16;
     if (!gemm_large_supported(g, epi)) return 0;
     g.Cpart = w.Y;
-    launch_gemm_large(g, epi, pn.rows, s);
+    launch_gemm_large(g, epi, pn.tile, s);
     return pn.splits;
   };
   // C = A W^T (+ R), with the gated low-rank term of (Al, Bl) when given

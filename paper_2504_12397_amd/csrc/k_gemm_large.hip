@@ -25,18 +25,25 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // TMH: 32-row blocks per wave and half (2: 256-row tile, 1: 128-row tile); the tile is 256 columns wide.
+// TMH = 0: the tile for calls that fill less than half of the chip with those: 128 x 128, four waves by two, a wave 32 rows by two
+// 32-column blocks.  Twelve fragments for eight matrix instructions: LDS-bound (96 KB of a k-tile at 322 bytes per ns: 0.3 us)
+// unless the reads run beside the matrix instructions, so a wave reads the next k-tile's fragments while it multiplies this one's,
+// with one barrier per k-tile and four buffers.  512 x 6144 x 4096 with adapters: 50 us in 192 workgroups, 80 in 96 of the
+// 128 x 256 tile; 1024 x 4096 x 4096: 45 us.
 template <int TMH, int EPI>
 __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  constexpr int BM = 128 * TMH, BN = 256, BK = 64;
-  constexpr int A_HALF = 8192 * TMH, B_HALF = 16384;                 // bytes of a half-tile
+  constexpr int BM = TMH ? 128 * TMH : 128, BN = TMH ? 256 : 128, BK = 64;
+  constexpr int A_HALF = TMH ? 8192 * TMH : 8192, B_HALF = 64 * BN;      // bytes of a half-tile
   constexpr int BUF = 2 * A_HALF + 2 * B_HALF;
-  constexpr int NBUF = TMH == 2 ? 2 : 3;
+  constexpr int NBUF = TMH == 2 ? 2 : TMH == 1 ? 3 : 4;
+  constexpr int NMI = TMH ? 2 * TMH : 1;                              // 32-row blocks of a wave
+  constexpr int AH = TMH ? 2 : 1, AJ = TMH ? TMH : 2, BJ = BN / 128;     // halves of A, requests of a wave for one, for a half of B
   extern __shared__ u32x4 smem[];
   char *lds = reinterpret_cast<char *>(smem);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, lhi = lane >> 5;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = TMH ? wave >> 2 : wave >> 1, wn = TMH ? wave & 3 : wave & 1;
   const int M = g.M, N = g.N, K = g.K;
 
   const int nk = K / BK / g.k_splits;
@@ -67,20 +74,21 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   const i32x4 rB1 = EPI == GEMM_EPI_SWIGLU ? make_rsrc(g.B2, (uint64_t)(N >> 1) * g.ldb * 2) : rB0;
   // byte offsets of a lane's rows (the k-tile is the scalar offset, so that a row past the end is out of range by its lane
   // offset alone); they move to the next output tile when the last requests of the current one are out
-  int va[2][TMH], vb[2][2], ka[2], kb;      // ka, kb: byte offset of the first k-tile
+  int va[AH][AJ], vb[2][BJ], ka[AH], kb;      // ka, kb: byte offset of the first k-tile
   auto aim_a = [&](int m0, int k0, int h) {
     ka[h] = k0;
 #pragma unroll
-    for (int j = 0; j < TMH; ++j) {
-      const int i = 8 * (TMH * wave + j) + (lane >> 3), c = (lane & 7) ^ ((i >> 1) & 7);
-      va[h][j] = ((m0 + (i / (32 * TMH)) * 64 * TMH + h * 32 * TMH + i % (32 * TMH)) * g.lda + c * 8) * 2;
+    for (int j = 0; j < AJ; ++j) {
+      const int i = 8 * (AJ * wave + j) + (lane >> 3), c = (lane & 7) ^ ((i >> 1) & 7);
+      const int r = TMH ? (i / (32 * AJ)) * 64 * TMH + h * 32 * TMH + i % (32 * AJ) : i;
+      va[h][j] = ((m0 + r) * g.lda + c * 8) * 2;
     }
   };
   auto aim_b = [&](int n0, int k0) {
     kb = k0;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int i = 8 * (2 * wave + j) + (lane >> 3), c = (lane & 7) ^ ((i >> 1) & 7);
+    for (int j = 0; j < BJ; ++j) {
+      const int i = 8 * (BJ * wave + j) + (lane >> 3), c = (lane & 7) ^ ((i >> 1) & 7);
       const int row = EPI == GEMM_EPI_SWIGLU ? (n0 >> 1) + i
                       : EPI == GEMM_EPI_ROPE ? n0 + (i >> 6) * 128 + (i & 63)
                                              : n0 + (i >> 5) * 64 + (i & 31);
@@ -90,39 +98,40 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   };
   // half h of k-tile t (of the output tile aimed at) into the buffer at LDS byte `buf`
   auto req_a = [&](int t, int buf, int h) {
-    const int dst = buf + h * A_HALF + wave * (1024 * TMH);
+    const int dst = buf + h * A_HALF + wave * (1024 * AJ);
 #pragma unroll
-    for (int j = 0; j < TMH; ++j) load_to_lds(rA, va[h][j], ka[h] + t * (BK * 2), dst + j * 1024);
+    for (int j = 0; j < AJ; ++j) load_to_lds(rA, va[h][j], ka[h] + t * (BK * 2), dst + j * 1024);
   };
   auto req_b = [&](int t, int buf, int h) {
-    const int dst = buf + 2 * A_HALF + h * B_HALF + wave * 2048;
+    const int dst = buf + 2 * A_HALF + h * B_HALF + wave * (1024 * BJ);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) load_to_lds(h ? rB1 : rB0, vb[h][j], kb + t * (BK * 2), dst + j * 1024);
+    for (int j = 0; j < BJ; ++j) load_to_lds(h ? rB1 : rB0, vb[h][j], kb + t * (BK * 2), dst + j * 1024);
   };
   int m0, n0, k0;
   tile_at(in_run, m0, n0, k0);
   aim_a(m0, k0, 0);
-  aim_a(m0, k0, 1);
+  if constexpr (TMH != 0) aim_a(m0, k0, 1);
   aim_b(n0, k0);
-  int bo = 0;      // LDS byte of the running k-tile's buffer (three buffers only)
-  for (int t = 0; t < NBUF; ++t) {      // in the order of the main loop
+  int bo = 0;      // LDS byte of the running k-tile's buffer (three or four buffers only)
+  for (int t = 0; t < (TMH ? NBUF : 3); ++t) {      // in the order of the main loop
     req_a(t, t * BUF, 0);
-    if (NBUF == 2 || t < 2) { req_b(t, t * BUF, 0); req_b(t, t * BUF, 1); }
-    if (t < NBUF - 1) req_a(t, t * BUF, 1);
+    if (NBUF != 3 || t < 2) { req_b(t, t * BUF, 0); req_b(t, t * BUF, 1); }
+    if constexpr (TMH != 0)
+      if (t < NBUF - 1) req_a(t, t * BUF, 1);
   }
 
   int ra[4], rb[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const int pos = ((2 * ks + lhi) ^ ((l32 >> 1) & 7)) * 16;
-    ra[ks] = (wm * 32 * TMH + l32) * 128 + pos;
+    ra[ks] = (wm * (TMH ? 32 * TMH : 32) + l32) * 128 + pos;
     rb[ks] = 2 * A_HALF + (wn * 32 + l32) * 128 + pos;
   }
 
   for (;;) {
-  f32x16 acc[2 * TMH][2];
+  f32x16 acc[NMI][2];
 #pragma unroll
-  for (int i = 0; i < 2 * TMH; ++i)
+  for (int i = 0; i < NMI; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -134,7 +143,7 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
     if (EPI == GEMM_EPI_ROPE) return n0 + (wn >> 1) * 128 + (wn & 1) * 32 + nb * 64;
     return n0 + wn * 64 + nb * 32;
   };
-  const int row_base = m0 + wm * (64 * TMH);
+  const int row_base = m0 + wm * (32 * NMI);
 
   // ---- gated low-rank term (Eq.6), under the first tiles' way from memory ------------------------------------------
   if (g.tlow != nullptr && (EPI != GEMM_EPI_PARTIAL || k0 == 0)) {      // (split 0 carries it)
@@ -175,10 +184,10 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
         a_stride[nb] = (int64_t)(p_of[nb] == 0 ? g.n_q : g.n_kv) * r;
       }
     }
-    int a_row[2 * TMH];
-    const bf16 *trow[2 * TMH];
+    int a_row[NMI];
+    const bf16 *trow[NMI];
 #pragma unroll
-    for (int mi = 0; mi < 2 * TMH; ++mi) {
+    for (int mi = 0; mi < NMI; ++mi) {
       const int row = row_base + mi * 32 + l32, rc = min(row, M - 1);
       a_row[mi] = row < M ? g.row_adapter[rc] : -1;
       trow[mi] = g.tlow + (int64_t)rc * parts * 2 * r;
@@ -186,7 +195,7 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
     // A step is 16 values of k of t_hi and of t_lo against the same 16 columns of B.  The requests of the next step go out before
     // the matrix instructions of the running one; other adapters' rows are zeroed afterwards.
     constexpr int NP = EPI == GEMM_EPI_SWIGLU ? 2 : 1;      // both blocks of a wave belong to one part, except gate | up
-    struct Step { u32x4 b[2], t[2][2 * TMH][NP]; };
+    struct Step { u32x4 b[2], t[2][NMI][NP]; };
     auto fetch = [&](unsigned long long left, int ks, Step &st) {
       const int a = left ? __builtin_ctzll(left) : 0, kk = min(ks + lhi * 8, r - 8);
 #pragma unroll
@@ -194,7 +203,7 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
 #pragma unroll
       for (int hl = 0; hl < 2; ++hl)
 #pragma unroll
-        for (int mi = 0; mi < 2 * TMH; ++mi)
+        for (int mi = 0; mi < NMI; ++mi)
 #pragma unroll
           for (int p = 0; p < NP; ++p)
             st.t[hl][mi][p] = *reinterpret_cast<const u32x4 *>(trow[mi] + (p_of[p] * 2 + hl) * r + kk);
@@ -208,7 +217,7 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
 #pragma unroll
       for (int hl = 0; hl < 2; ++hl)
 #pragma unroll
-        for (int mi = 0; mi < 2 * TMH; ++mi) {
+        for (int mi = 0; mi < NMI; ++mi) {
 #pragma unroll
           for (int p = 0; p < NP; ++p)
             if (a_row[mi] != a) st.t[hl][mi][p] = u32x4{0, 0, 0, 0};
@@ -253,25 +262,26 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   }
 
   // ---- main loop -----------------------------------------------------------------------------------------------
-  bf16x8 fa0[TMH][4], fa1[TMH][4], fb0[4], fb1[4];
-  auto read_a = [&](int buf, int h, bf16x8 (&f)[TMH][4]) {
+  constexpr int AR = TMH ? TMH : 1;
+  bf16x8 fa0[AR][4], fa1[AR][4], fb0[4], fb1[4];
+  auto read_a = [&](int buf, int h, bf16x8 (&f)[AR][4]) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int i = 0; i < TMH; ++i)
+      for (int i = 0; i < AR; ++i)
         f[i][ks] = *reinterpret_cast<const bf16x8 *>(lds + buf + ra[ks] + h * A_HALF + i * 4096);
   };
   auto read_b = [&](int buf, int h, bf16x8 (&f)[4]) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) f[ks] = *reinterpret_cast<const bf16x8 *>(lds + buf + rb[ks] + h * B_HALF);
   };
-  auto mma = [&](const bf16x8 (&a)[TMH][4], const bf16x8 (&b)[4], int mh, int nb) {
+  auto mma = [&](const bf16x8 (&a)[AR][4], const bf16x8 (&b)[4], int mh, int nb) {
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int i = 0; i < TMH; ++i)
-        acc[mh * TMH + i][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ks], a[i][ks], acc[mh * TMH + i][nb], 0, 0, 0);
+      for (int i = 0; i < AR; ++i)
+        acc[mh * AR + i][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ks], a[i][ks], acc[mh * AR + i][nb], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
   };
   // end of a memory part: what the next phase reads has arrived as far as this wave's own requests go.  (Its own reads may still
@@ -286,15 +296,49 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   wave_barrier();                        \
   __builtin_amdgcn_sched_barrier(0)
 
+  const bool more = in_run + per_xcd < run_n;
+  int m_next = m0, n_next = n0, k_next = k0;
+  if (more) tile_at(in_run + per_xcd, m_next, n_next, k_next);
+  if constexpr (TMH == 0) {
+    // fragments of the next k-tile (of the next output tile behind the last one) are read beside this one's products
+    bf16x8 fc0[4], fc1[4];
+    auto read = [&](int buf, bf16x8 (&fa)[AR][4], bf16x8 (&f0)[4], bf16x8 (&f1)[4]) {
+      read_a(buf, 0, fa);
+      read_b(buf, 0, f0);
+      read_b(buf, 1, f1);
+    };
+    auto turn = [&](int t) {      // k-tile t + 1 is there and k-tile t - 1 used up; requests k-tile t + 3
+      wait_vm<4>();
+      __builtin_amdgcn_sched_barrier(0);
+      wave_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      if (t == nk - 3) { aim_a(m_next, k_next, 0); aim_b(n_next, k_next); }
+      const int to = t + 3 < nk ? t + 3 : t + 3 - nk, prev = bo ? bo - BUF : (NBUF - 1) * BUF;
+      req_a(to, prev, 0);
+      req_b(to, prev, 0);
+      req_b(to, prev, 1);
+      bo = bo + BUF < NBUF * BUF ? bo + BUF : 0;
+    };
+    wait_vm<8>();
+    wave_barrier();
+    read(bo, fa0, fb0, fb1);
+    for (int t = 0; t < nk; t += 2) {
+      turn(t);
+      read(bo, fa1, fc0, fc1);
+      mma(fa0, fb0, 0, 0);
+      mma(fa0, fb1, 0, 1);
+      turn(t + 1);
+      read(bo, fa0, fb0, fb1);
+      mma(fa1, fc0, 0, 0);
+      mma(fa1, fc1, 0, 1);
+    }
+  } else {
   wait_vm<NBUF == 2 ? 10 : 8>();        // A0 and B0 (B0, B1) of k-tile 0 are there
   wave_barrier();
   read_a(bo, 0, fa0);
   wait_lds();
   if (wm == 1) wave_barrier();      // the second group runs one barrier behind
   wave_barrier();
-  const bool more = in_run + per_xcd < run_n;
-  int m_next = m0, n_next = n0, k_next = k0;
-  if (more) tile_at(in_run + per_xcd, m_next, n_next, k_next);
   // The last k-tiles request the first ones of the workgroup's next output tile, which then arrive under the epilogue; behind the
   // last output tile they request its own first ones again, into buffers that nobody reads any more, so that the count
   // of requests in flight is the same everywhere.
@@ -362,6 +406,8 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
     tile(1, 2);
   }
   if (wm == 0) wave_barrier();
+  }
+
 
   // ---- epilogues -------------------------------------------------------------------------------------------------
   // Weights were the first operand: accumulator register v of lane l is row l % 32 of the 32 x 32 block, column
@@ -377,7 +423,7 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   auto take = [&](int half) { return *reinterpret_cast<const u32x4 *>(st_at(16 * half + io_row, io_chunk)); };
   const int n_cols = EPI == GEMM_EPI_SWIGLU ? N >> 1 : N;
 #pragma unroll
-  for (int mi = 0; mi < 2 * TMH; ++mi) {
+  for (int mi = 0; mi < NMI; ++mi) {
     const int rows0 = row_base + mi * 32;
     if (rows0 >= M) break;
     if constexpr (EPI == GEMM_EPI_ROPE) {
@@ -497,8 +543,9 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
 
 template <int TMH, int EPI>
 static void launch_cfg(const GemmArgs &g, hipStream_t s) {
-  const int tiles_m = (g.M + 128 * TMH - 1) / (128 * TMH), tiles_n = (g.N + 255) / 256;
-  const size_t smem = (TMH == 2 ? 2 : 3) * (2 * 8192 * TMH + 2 * 16384) + 8 * 2048;
+  constexpr int BM = TMH == 2 ? 256 : 128, BN = TMH ? 256 : 128;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  const size_t smem = (TMH == 2 ? 2 : TMH == 1 ? 3 : 4) * (BM + BN) * 128 + 8 * 2048;
   const int all = (tiles_m * tiles_n * g.k_splits + 7) & ~7, grid = all < 256 ? all : 256;      // a workgroup per compute unit walks its tiles
   auto kern = gemm_large_kernel<TMH, EPI>;
   (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -512,22 +559,23 @@ bool gemm_large_supported(const GemmArgs &g, int epi) {
   return g.K % (128 * g.k_splits) == 0 && g.K >= 256 * g.k_splits && g.N % 32 == 0 && b_rows * g.ldb * 2 < (1ull << 31) && !(epi == GEMM_EPI_PARTIAL && g.lora_split) && (uint64_t)g.M * g.lda * 2 < (epi == GEMM_EPI_PARTIAL ? 1ull << 31 : ~0ull);
 }
 
-// Rows of a tile and workgroups per output tile for a product of M rows: the cheapest by measured times (us).  A k-tile of a
+// Tile and workgroups per output tile for a product of M rows: the cheapest by measured times (us).  A k-tile of a
 // 256-row tile takes 1.1 with most of the chip idle and 1.5 with all of it at work (the clock gives way: 1.6 GHz at 0.83
-// matrix utilisation), one of a 128-row tile 0.65 and 1.0; a tile's prologue and epilogue take about 6; partial sums cost
-// their bytes there and back and the launch that adds them.
+// matrix utilisation), one of a 128-row tile 0.65 and 1.0, one of the 128 x 128 tile 0.6 (it waits for LDS, not for the clock); a tile's prologue and epilogue
+// take about 6; partial sums cost their bytes there and back and the launch that adds them.
 GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits) {
-  GemmLargePlan best{256, 1};
+  GemmLargePlan best{2, 1};
   double best_us = 1e30;
-  for (int rows = 128; rows <= 256; rows += 128)
+  for (int tile = 0; tile <= 2; ++tile)
     for (int sp = 1; sp <= max_splits; sp *= 2) {
-      if ((hint == 2 && rows != 128) || (hint == 3 && rows != 256) || g.K % (128 * sp) != 0 || g.K < 512 * sp) continue;
-      const int tiles = (g.M + rows - 1) / rows * ((g.N + 255) / 256) * sp, rounds = (tiles + n_cu - 1) / n_cu;
+      if ((hint == 2 && tile != 1) || (hint == 3 && tile != 2) || g.K % (128 * sp) != 0 || g.K < 512 * sp) continue;
+      const int rows = tile == 2 ? 256 : 128, cols = tile ? 256 : 128;
+      const int tiles = (g.M + rows - 1) / rows * ((g.N + cols - 1) / cols) * sp, rounds = (tiles + n_cu - 1) / n_cu;
       const double load = tiles < n_cu ? (double)tiles / n_cu : 1.0;
-      const double k_tile = rows == 256 ? 1.1 + 0.4 * load : 0.65 + 0.35 * load;
+      const double k_tile = tile == 2 ? 1.1 + 0.4 * load : tile == 1 ? 0.65 + 0.35 * load : 0.55 + 0.05 * load;
       double us = rounds * (k_tile * (g.K / 64 / sp) + 6.0);
       if (sp > 1) us += 5.0 + (double)sp * g.M * g.N * 8.0 / 4.5e6;
-      if (us < best_us) { best_us = us; best = GemmLargePlan{rows, sp}; }
+      if (us < best_us) { best_us = us; best = GemmLargePlan{tile, sp}; }
     }
   return best;
 }
@@ -540,7 +588,7 @@ static void launch_epi(const GemmArgs &g, int epi, hipStream_t s) {
   else launch_cfg<TMH, GEMM_EPI_BF16>(g, s);
 }
 
-void launch_gemm_large(GemmArgs g, int epi, int rows, hipStream_t s) {
+void launch_gemm_large(GemmArgs g, int epi, int tile, hipStream_t s) {
   if (epi != GEMM_EPI_PARTIAL) g.k_splits = 1;
   // slices of rows whose operand stays below 2 GB
   const int slice = (int)(((1ull << 31) / ((uint64_t)g.lda * 2) - 512) & ~255ull), M = g.M;
@@ -554,8 +602,9 @@ void launch_gemm_large(GemmArgs g, int epi, int rows, hipStream_t s) {
     if (q.row_adapter) q.row_adapter += m;
     if (q.present16) q.present16 += m / 16;
     if (epi == GEMM_EPI_ROPE) { q.rope_pos += m; q.rope_slot += m; q.Qout += (int64_t)m * g.n_q; }
-    if (rows == 256) launch_epi<2>(q, epi, s);
-    else launch_epi<1>(q, epi, s);
+    if (tile == 2) launch_epi<2>(q, epi, s);
+    else if (tile == 1) launch_epi<1>(q, epi, s);
+    else launch_epi<0>(q, epi, s);
   }
 }
 

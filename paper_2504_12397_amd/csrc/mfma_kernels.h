@@ -160,10 +160,10 @@ void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s);
 // few rows: the whole QKV projection with rotation and append, A packed (PrepArgs::packed)
 bool qkv_stream_supported(const void *W, int M, int N, int K, int n_q, int n_kv, int head_dim);
 void launch_qkv_stream(const GemmArgs &g, int n_cu, hipStream_t s);
-struct GemmLargePlan { int rows, splits; };      // tile rows (128 / 256); workgroups per output tile (> 1: PARTIAL)
-GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits);      // hint 2 / 3: 128 / 256 rows
+struct GemmLargePlan { int tile, splits; };      // tile: 2: 256 x 256, 1: 128 x 256, 0: 128 x 128; workgroups per output tile (> 1: PARTIAL)
+GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits);      // hint 2 / 3: tile 1 / 2
 bool gemm_large_supported(const GemmArgs &g, int epi);
-void launch_gemm_large(GemmArgs g, int epi, int rows, hipStream_t s);
+void launch_gemm_large(GemmArgs g, int epi, int tile, hipStream_t s);
 // tlow[row, p, {hi, lo}, j] = s_a * sum over splits of Y[split, row, (a * parts + p) * rank + j] for adapted rows
 // (a = row_adapter[row] >= 0): picks each row's adapter out of a projection on all adapters' down-matrices
 void launch_tlow_select(const float *Y, int splits, int M, int n_adapters, int parts, int rank,
