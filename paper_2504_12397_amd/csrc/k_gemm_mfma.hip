@@ -501,29 +501,31 @@ void launch_splitk_reduce(const float *part, int splits, int64_t mn, const bf16 
 }
 
 // The same sum for whole rows, followed by the RMSNorm of the row (h = sum + residual is normalised from its
-// fp32 value): C = bf16(h), Cn = bf16(h * gain / rms(h)).  One workgroup per row, N <= 16384, N % 4 == 0.
-__global__ __launch_bounds__(256) void splitk_reduce_norm_kernel(const float *__restrict__ part, int splits, int M,
-                                                                 int N, const bf16 *__restrict__ R,
-                                                                 const bf16 *__restrict__ gain, float eps,
-                                                                 bf16 *__restrict__ C, bf16 *__restrict__ Cn) {
-  __shared__ float s_red[4];
+// fp32 value): C = bf16(h), Cn = bf16(h * gain / rms(h)).  One workgroup per row, N <= 16384, N % 4 == 0.  With few rows
+// it is one round trip and a barrier on otherwise idle units: 16 waves, so that a row of up to 4096 values is one
+// request per lane and kind, the gain asked for together with the partials (one row of 4096, eight partials: 9.4 us with four waves
+// and the gain last, 4.8 now).
+constexpr int RN_THREADS = 1024;
+__global__ __launch_bounds__(RN_THREADS) void splitk_reduce_norm_kernel(const float *__restrict__ part, int splits, int M,
+                                                                        int N, const bf16 *__restrict__ R,
+                                                                        const bf16 *__restrict__ gain, float eps,
+                                                                        bf16 *__restrict__ C, bf16 *__restrict__ Cn) {
+  constexpr int U = 16384 / (4 * RN_THREADS);
+  __shared__ float s_red[RN_THREADS / 64];
   const int row = blockIdx.x, tid = threadIdx.x;
   const int64_t mn = (int64_t)M * N, ro = (int64_t)row * N;
-  float4 h[16], res[16];
+  float4 h[U], gn[U];
   float ssq = 0.f;
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int c = (u * 256 + tid) * 4;
-    res[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (c < N && R != nullptr) res[u] = load_bf16x4(R + ro + c);
-  }
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int c = (u * 256 + tid) * 4;
-    h[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int u = 0; u < U; ++u) {
+    const int c = (u * RN_THREADS + tid) * 4;
+    h[u] = gn[u] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (c < N) {
+      gn[u] = load_bf16x4(gain + c);
+      float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (R != nullptr) res = load_bf16x4(R + ro + c);
       float4 acc = sum_partials(part + ro + c, splits, mn);
-      acc.x += res[u].x; acc.y += res[u].y; acc.z += res[u].z; acc.w += res[u].w;
+      acc.x += res.x; acc.y += res.y; acc.z += res.z; acc.w += res.w;
       h[u] = acc;
       ssq += acc.x * acc.x + acc.y * acc.y + acc.z * acc.z + acc.w * acc.w;
     }
@@ -531,14 +533,16 @@ __global__ __launch_bounds__(256) void splitk_reduce_norm_kernel(const float *__
   ssq = wave_sum(ssq);
   if ((tid & 63) == 0) s_red[tid >> 6] = ssq;
   __syncthreads();
-  const float rinv = 1.0f / sqrtf((s_red[0] + s_red[1] + s_red[2] + s_red[3]) / (float)N + eps);
+  float total = 0.f;
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int c = (u * 256 + tid) * 4;
+  for (int w = 0; w < RN_THREADS / 64; ++w) total += s_red[w];
+  const float rinv = 1.0f / sqrtf(total / (float)N + eps);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int c = (u * RN_THREADS + tid) * 4;
     if (c < N) {
-      const float4 gn = load_bf16x4(gain + c);
       store_bf16x4(C + ro + c, h[u].x, h[u].y, h[u].z, h[u].w);
-      store_bf16x4(Cn + ro + c, h[u].x * gn.x * rinv, h[u].y * gn.y * rinv, h[u].z * gn.z * rinv, h[u].w * gn.w * rinv);
+      store_bf16x4(Cn + ro + c, h[u].x * gn[u].x * rinv, h[u].y * gn[u].y * rinv, h[u].z * gn[u].z * rinv, h[u].w * gn[u].w * rinv);
     }
   }
 }
@@ -575,7 +579,7 @@ bool splitk_reduce_norm_supported(int N) { return N % 4 == 0 && N <= 16384; }
 void launch_splitk_reduce_norm(const float *part, int splits, int M, int N, const bf16 *R, const bf16 *gain, float eps,
                                bf16 *C, bf16 *Cn, hipStream_t s) {
   if (M == 0) return;
-  hipLaunchKernelGGL(splitk_reduce_norm_kernel, dim3(M), dim3(256), 0, s, part, splits, M, N, R, gain, eps, C, Cn);
+  hipLaunchKernelGGL(splitk_reduce_norm_kernel, dim3(M), dim3(RN_THREADS), 0, s, part, splits, M, N, R, gain, eps, C, Cn);
 }
 
 bool gemm_mfma_supported(int M, int N, int K) { return M > 0 && N > 0 && K >= 64 && K % 64 == 0; }
