@@ -115,7 +115,7 @@ typedef struct {
  * same rows to another sequence of the same call as rows to be written.
  * The shared rows are also WALKED once: sequences of a call that name the same (prefix_offset,
  * prefix_len) put their new rows into common workgroups for the prefix keys -- in a decode step any
- * such sequences, up to 16 query-head rows per workgroup; in a prefill sequences that are neighbours
+ * such sequences, up to 32 query-head rows per workgroup; in a prefill sequences that are neighbours
  * in the batch, up to 256 query-head rows -- so a caller keeps the sequences of one context next to
  * each other.  Results do not depend on it beyond the summation order of the attention (see
  * "Summation order" at alora_set_option). */
@@ -149,22 +149,23 @@ const char *alora_status_string(alora_status s);
  *                     otherwise.  1: force the plain kernels (any dtype, any shape).
  *   "kv_splits"       0 (default): automatic.  n in 1..256: split the key axis of attention into n chunks
  *                     (partial results are merged by log-sum-exp weights).
- *   "gemm_splits"     0 (default): the reduction axis of every linear is cut into a number of equal segments
- *                     fixed by the shape of its weight matrix.  n in 1..64: into n segments (where the
- *                     reduction length allows; 1 = a single running sum).  See "Summation order" below.
+ *   "gemm_splits"     0 (default): the QKV projection is a single running sum; the reduction axis of a stack's
+ *                     other linears is cut by the shape of the weight matrix (up to 256 rows) or by what fills
+ *                     the chip (more rows).  n in 1..64: every linear in n equal segments (where the reduction
+ *                     length allows; 1 = a single running sum).  See "Summation order" below.
  *   "gemm_tile"       0 (default): automatic block shape.  1: 128x128, 2: 256x128, 3: 256x256, 4: 128x64
  *                     (four waves); 5 / 6: 128x128 on eight waves of 32x64 / 64x32.  1 and 4..6 also apply to
  *                     the other linears of a stack.  A tuning experiment: with a value other than 0 the
  *                     summation-order guarantee below does not hold.
- *   "prep_split"      1 (default): calls without any adapter, with 512 rows or more at hidden size 4096 (a
- *                     base-model prefill), normalise their rows in a row-per-wave kernel; shorter calls and
- *                     calls with adapters use the kernel that prepares 16 rows per workgroup.  0: never, 2: at any
- *                     number of rows.  The normalised rows are bit-identical either way.
+ *   "prep_split"      1 (default): calls with adapters normalise their rows and compute the down projection in one
+ *                     kernel while they are short (up to 512 workgroups of it), in two kernels beyond that.
+ *                     0: always in two (except with down matrices that are not 16-byte aligned), 2: always in one.
+ *                     Calls without adapters only normalise.  The normalised rows are bit-identical either way.
  *   "lora_split"      0 (default): automatic.  1: always, 2: never give the low-rank term of the QKV
  *                     projection workgroups (and a partial sum) of its own.
- *   "rope_fuse"       1 (default): where the shape allows (more than 256 rows, head size 128) the QKV
- *                     projection rotates q and k and appends k and v in its own epilogue.  0: a separate
- *                     kernel does, from the fp32 projection.  Same bits either way.
+ *   "rope_fuse"       1 (default): where the shape allows (head size 128) the QKV projection rotates q and k and
+ *                     appends k and v in its own epilogue.  0: a separate kernel does, from the fp32 projection.
+ *                     Same bits either way.
  *   "attn_waves"      0 (default) / 8: eight waves per workgroup in the prefill attention kernel.  4: four.
  *   "attn_lazy"       0..16 (default 3): the running row maximum of the prefill attention kernels moves only
  *                     when a block of scores exceeds it by more than this many powers of two (0 = exact
@@ -184,9 +185,8 @@ const char *alora_status_string(alora_status s);
  * Summation order (Proposition 1 in its strong form: rows before the invocation index are the base model's
  * rows).  With "gemm_tile" = 0 the key and value rows a call appends are a function of the row's own input and
  * position alone: bit-identical whether the row came in a long prefill, a short one, a decode step, alone or
- * in a mixed batch, with or without an adapter active on OTHER rows -- every linear adds the products of a row
- * in one fixed order (segments fixed by the weight shape, each summed from zero, the sums added in ascending
- * order).  Rows before k_b of an adapter call are therefore bitwise the rows a base-only call writes.  What
+ * in a mixed batch, with or without an adapter active on OTHER rows -- the QKV projection adds the products of a
+ * row in one fixed order (a running sum in ascending order, whichever kernel computes it).  Rows before k_b of an adapter call are therefore bitwise the rows a base-only call writes.  What
  * is NOT bit-stable across differently shaped calls: attention outputs (the key axis is split by a heuristic
  * that looks at the whole batch, and prefill and decode attention are different kernels), and with them the
  * hidden states and cache rows of layers after the first in alora_stack_prefill; those agree to rounding. */
