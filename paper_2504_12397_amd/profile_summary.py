@@ -40,7 +40,7 @@ TITLES = {
 BENCH_WORKLOAD = {"r3pp": "r3p"}         # summary key -> bench.py --workload, where they differ
 # kernel symbol -> the kernel family bench.py reports (only where one symbol is one family in that workload)
 FAMILY = [("attn_prefill_mfma_kernel", "attn_prefill"), ("attn_decode_mfma_kernel", "attn_decode"),
-          ("prep_rows_mfma_kernel", "prep_rows"), ("rope_append_kernel", "rope_append"), ("attn_merge", "attn_merge")]
+          ("prep_few_kernel", "prep_rows"), ("qkv_stream_kernel", "qkv_gemm"), ("rope_append_kernel", "rope_append"), ("attn_merge", "attn_merge")]
 
 
 def short(name: str) -> str:
@@ -57,13 +57,12 @@ def family_of(workload: str, kernel: str):
     for pat, fam in FAMILY:
         if pat in kernel:
             return fam
+    large = re.search(r"gemm_large_kernel<\d+, (\d)>", kernel)
+    if large:
+        return {"2": "gate_up", "3": "qkv_gemm"}.get(large.group(1))
     if "gemm_mfma_kernel" in kernel:
         epi = re.search(r"gemm_mfma_kernel<\d+, \d+, \d+, \d+, (\d),", kernel)
         epi = epi.group(1) if epi else ""
-        if workload == "c3":
-            return "qkv_gemm"
-        if workload in ("c2", "c4") and epi == "0":       # (c2 also runs a 4096-row base prefill at set-up: epilogue 3)
-            return "qkv_gemm"
         if workload == "c5" and epi == "2":
             return "gate_up"
     return None

@@ -148,3 +148,13 @@ def test_static_decode_of_one_long_sequence_among_short_ones(ab, ctx):
     P = [16448] + [100 + b for b in range(63)]
     case = H.make_case(shape, P, [1] * 64, P, [b % 3 - 1 for b in range(64)], seed=1600, prefix="random")
     _both(ab, ctx, case)
+
+
+# a range is 128 keys here: 16 records (the fewest that a workgroup merges), 64 with and without the next one, places that shorter
+# rows leave without a record
+@pytest.mark.parametrize("P", [[2047], [8191], [8192], [8063, 127, 0, 129], [9000, 8300, 5]])
+def test_merge_of_many_records(ab, ctx, P):
+    shape = wl.LayerShape(d=512, n_q_heads=4, n_kv_heads=2, head_dim=128, rank=16, n_adapters=3)
+    n = len(P)
+    case = H.make_case(shape, P, [1] * n, [max(0, p - 10) for p in P], [b % 4 - 1 for b in range(n)], seed=1700 + P[0], prefix="random")
+    check_case(ab, ctx, case, decode=True)
