@@ -18,6 +18,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int PREP_ROWS = 16;
 constexpr int PREP_WAVES = 8;
 constexpr int PREP_FEW = 512;      // workgroups
+constexpr int PREP_NARROW = 128;      // up to so many of 16 columns (half of the compute units) they take 8 columns instead
 
 // Sum of squares of a row, in ONE order for every kernel that normalises rows (a row's x_hat must not depend on
 // which of them ran -- the base rows of a long prefill and of a decode step are compared bit for bit): the
@@ -62,13 +63,17 @@ __device__ __forceinline__ void fill_row_meta(const PrepArgs &a, const SeqMeta &
   if (adapter >= 0) atomicOr(s_present, 1ull << adapter);
 }
 
-// Few rows with adapters (up to PREP_FEW workgroups): workgroup (x, y, z) takes row tile x (16 rows), columns 16 y .. of the 3 * rank columns of t and
-// adapter used[z]; the first of a tile also writes x_hat and the row metadata.  Eight waves split the hidden dimension; a lane
+// Few rows with adapters (up to PREP_FEW workgroups): workgroup (x, y, z) takes row tile x (16 rows), columns NC y .. of the 3 * rank
+// columns of t and adapter used[z]; the first of a tile also writes x_hat and the row metadata.  Eight waves split the hidden dimension; a lane
 // owns 8 consecutive elements of one row at a time, which is both the 16-byte global access and the operand layout of
 // v_mfma_f32_16x16x32_bf16 (lane l: row l % 16, k = 8 * (l / 16) ..).  CH = d / 256: chunks of its row a lane holds.
 // The kernel is memory round trips and little else, so everything is requested at once: x, the gain, the sequences' records (in the kernel arguments when they are few)
 // and this adapter's down matrix, before anybody knows whether a row of the tile uses it.
-template <int CH>
+// NC = 8: half the columns of the matrix operand, for calls whose 16-column workgroups would leave half of the chip idle: a compute
+// unit takes operands in this order at 28 bytes per ns, so it is
+// done sooner with half the 128 KB of 16 columns.  A one-row token step of 16 layers at rank 64 2615 -> 2589 us (1.6 a layer), five rows of
+// rank-8 adapters 50.7 -> 49.4, 128 rows through 16 layers 4083 -> 4063.  With more workgroups than units the rows would be read twice.
+template <int CH, int NC>
 __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   __shared__ float s_ssq[PREP_WAVES][PREP_ROWS];
   __shared__ int s_adapter[PREP_ROWS];
@@ -81,7 +86,7 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   const int r16 = lane & 15, kg = lane >> 4;
   const int row0 = blockIdx.x * PREP_ROWS;
   constexpr int d = CH * 256;
-  const int rank = a.rank, col0 = blockIdx.y * 16, ad = a.used[blockIdx.z];
+  const int rank = a.rank, col0 = blockIdx.y * NC, ad = a.used[blockIdx.z];
   const bool lead = blockIdx.y == 0 && blockIdx.z == 0;
   const int row = min(row0 + r16, a.T - 1);
   const bool row_ok = row0 + r16 < a.T;
@@ -99,7 +104,7 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   const int my_col = min(col0 + r16, 3 * rank - 1);      // (3 * rank need not be a multiple of 16)
   const bf16 *Ab = a.A + ((int64_t)ad * 3 * rank + my_col) * d + k_lo;
 #pragma unroll
-  for (int u = 0; u < CH; ++u) br[u] = *reinterpret_cast<const u32x4 *>(Ab + 32 * u);
+  for (int u = 0; u < CH; ++u) br[u] = NC == 16 || r16 < NC ? *reinterpret_cast<const u32x4 *>(Ab + 32 * u) : u32x4{0, 0, 0, 0};
 
   if (tid == 0) s_present = 0ull;
   if (tid < PREP_ROWS) { s_adapter[tid] = -1; s_scale[tid] = 0.f; }
@@ -161,7 +166,7 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   __syncthreads();
   if (tid < PREP_ROWS * 16) {
     const int lr = tid >> 4, col = tid & 15, orow = row0 + lr;
-    if (orow < a.T && s_adapter[lr] == ad && col0 + col < 3 * rank) {
+    if (orow < a.T && s_adapter[lr] == ad && col < NC && col0 + col < 3 * rank) {
       float t = 0.f;
 #pragma unroll
       for (int w = 0; w < PREP_WAVES; ++w) t += s_part[w][lr][col];
@@ -339,11 +344,14 @@ static void launch_norm(const PrepArgs &a, hipStream_t s) {
 
 template <int CH>
 static void launch_prep_ch(const PrepArgs &a, hipStream_t s) {
-  const int row_tiles = (a.T + PREP_ROWS - 1) / PREP_ROWS;
+  const int row_tiles = (a.T + PREP_ROWS - 1) / PREP_ROWS, cols16 = (3 * a.rank + 15) / 16;
   if (a.rank == 0 || a.A == nullptr || a.n_used == 0) {
     launch_norm<CH>(a, s);
-  } else if (a.few == 2 || !lds_aligned(a.A) || (a.few == 1 && row_tiles * ((3 * a.rank + 15) / 16) * a.n_used <= PREP_FEW)) {
-    hipLaunchKernelGGL(prep_few_kernel<CH>, dim3(row_tiles, (3 * a.rank + 15) / 16, a.n_used), dim3(512), 0, s, a);
+  } else if (a.few == 2 || !lds_aligned(a.A) || (a.few == 1 && row_tiles * cols16 * a.n_used <= PREP_FEW)) {
+    if (row_tiles * cols16 * a.n_used <= PREP_NARROW)
+      hipLaunchKernelGGL((prep_few_kernel<CH, 8>), dim3(row_tiles, (3 * a.rank + 7) / 8, a.n_used), dim3(512), 0, s, a);
+    else
+      hipLaunchKernelGGL((prep_few_kernel<CH, 16>), dim3(row_tiles, cols16, a.n_used), dim3(512), 0, s, a);
   } else {
     launch_norm<CH>(a, s);
     (void)hipFuncSetAttribute((const void *)t_rows_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * T_STEP);
