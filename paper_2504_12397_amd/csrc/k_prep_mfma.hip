@@ -265,12 +265,12 @@ __global__ __launch_bounds__(512) void t_rows_kernel(PrepArgs a) {
   const int g0 = row0 / 16, g1 = min(g0 + 1, (a.T - 1) / 16);
   if (!(((a.rm.present16[g0] | a.rm.present16[g1]) >> ad) & 1)) return;
 
-  const i32x4 rx = make_rsrc(a.xh, (uint64_t)((a.T + 31) & ~31) * d * 2);
+  const i32x4 rx = make_rsrc(a.xh + (int64_t)row0 * d, (uint64_t)32 * d * 2);      // (this tile's rows: offsets are 32 bits wide)
   const i32x4 rw = make_rsrc(a.A + ((int64_t)ad * cols + col0) * d, (uint64_t)(cols - col0) * d * 2);      // rows past the end: zeros
   const int r4 = lane >> 4, pos = lane & 15;
   int vx, vw[3];
-  if (a.packed) vx = (row0 >> 5) * (d >> 4) * 1024 + wave * 1024 + lane * 16;
-  else vx = min(row0 + 4 * wave + r4, a.T - 1) * d * 2 + (pos ^ ((4 * wave + r4) & 15)) * 16;
+  if (a.packed) vx = wave * 1024 + lane * 16;
+  else vx = min(4 * wave + r4, a.T - 1 - row0) * d * 2 + (pos ^ ((4 * wave + r4) & 15)) * 16;
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
     const int i = 4 * (3 * wave + j) + r4;

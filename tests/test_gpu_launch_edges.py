@@ -158,3 +158,25 @@ def test_merge_of_many_records(ab, ctx, P):
     n = len(P)
     case = H.make_case(shape, P, [1] * n, [max(0, p - 10) for p in P], [b % 4 - 1 for b in range(n)], seed=1700 + P[0], prefix="random")
     check_case(ab, ctx, case, decode=True)
+
+
+def test_down_projection_of_more_rows_than_32_bit_offsets_reach(ab, ctx):
+    """524544 rows of 4096: byte offsets of x_hat pass 2^31 at row 262144 and 2^32 at row 524288.  W_v = 0 and no RMSNorm, so the
+    appended value rows are s B (A x) and nothing else."""
+    n, each, d, r = 2049, 256, 4096, 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1800)
+    T = n * each
+    x = torch.empty((T, d), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    t = {"W_qkv": torch.zeros((384, d), dtype=torch.bfloat16, device="cuda"),
+         "A": torch.empty((1, 3, r, d), dtype=torch.bfloat16, device="cuda").normal_(0, d ** -0.5, generator=g), "scale": [2.0], "rms_gain": None}
+    for p in ("B_q", "B_k", "B_v"):
+        t[p] = torch.empty((1, 128, r), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    cache = ab.KVCache([each] * n, 1, 128, torch.bfloat16, "cuda")
+    ab.alora_prefill(ctx, ab.Layer(t, 1, 1, 128), cache, x, [each * i for i in range(n + 1)], [0] * n, [0] * n)
+    torch.cuda.synchronize()
+    for b in (0, 1023, 1024, 2047, 2048):
+        xb = x[b * each:(b + 1) * each].cpu().double()
+        ref = 2.0 * (xb @ t["A"][0, 2].cpu().double().T) @ t["B_v"][0].cpu().double().T
+        e = H.rel_err(H.f64(cache.rows(b, 0, each)[1][:, 0]), ref.numpy())
+        assert e <= H.TOL["bf16"], f"rows {b * each} ..: {e:.3e}"
