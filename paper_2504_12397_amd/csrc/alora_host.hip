@@ -645,7 +645,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
   auto large = [&](GemmArgs &g) -> int {
     if (T_rows <= 256 || ctx->opt_gemm_splits != 0 || g.tile_hint == 1 || g.tile_hint >= 4) return 0;
     int most = 4;
-    while (most > 1 && ((size_t)most * T_rows * g.N > w.y_floats || (uint64_t)T_rows * g.lda * 2 >= (1ull << 31))) most /= 2;
+    while (most > 1 && ((size_t)most * T_rows * g.N > w.y_floats || T_rows > gemm_large_slice_rows(g.lda))) most /= 2;
     const GemmLargePlan pn = gemm_large_plan(g.tile_hint, g, GEMM_EPI_BF16, ctx->n_cu, most);
     g.k_splits = pn.splits;
     const int epi = pn.splits > 1 ? GEMM_EPI_PARTIAL : GEMM_EPI_BF16;

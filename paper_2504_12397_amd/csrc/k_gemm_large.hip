@@ -552,11 +552,17 @@ static void launch_cfg(const GemmArgs &g, hipStream_t s) {
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, g, tiles_m, tiles_n);
 }
 
-// (32-bit byte offsets into both operands; at least four k-tiles per split, in pairs)
+// Rows of A that one launch takes: their byte offsets are 32 bits wide, tiles past the end included.
+int gemm_large_slice_rows(int lda) { return (int)(((int64_t)((1ull << 31) / ((uint64_t)lda * 2)) - 512) & ~(int64_t)255); }
+
+// (32-bit byte offsets into both operands; at least four k-tiles per split, in pairs; partial sums of one launch only: a second one
+// would put its rows where the first one's are)
 bool gemm_large_supported(const GemmArgs &g, int epi) {
   const uint64_t b_rows = epi == GEMM_EPI_SWIGLU ? g.N / 2 : g.N;
+  const int slice = gemm_large_slice_rows(g.lda);
   if (!lds_aligned(g.A) || !lds_aligned(g.B) || (epi == GEMM_EPI_SWIGLU && !lds_aligned(g.B2)) || g.lda % 8 != 0 || g.ldb % 8 != 0) return false;
-  return g.K % (128 * g.k_splits) == 0 && g.K >= 256 * g.k_splits && g.N % 32 == 0 && b_rows * g.ldb * 2 < (1ull << 31) && !(epi == GEMM_EPI_PARTIAL && g.lora_split) && (uint64_t)g.M * g.lda * 2 < (epi == GEMM_EPI_PARTIAL ? 1ull << 31 : ~0ull);
+  if (slice < 256 || (epi == GEMM_EPI_PARTIAL && (g.lora_split || g.M > slice))) return false;
+  return g.K % (128 * g.k_splits) == 0 && g.K >= 256 * g.k_splits && g.N % 32 == 0 && b_rows * g.ldb * 2 < (1ull << 31);
 }
 
 // Tile and workgroups per output tile for a product of M rows: the cheapest by measured times (us).  A k-tile of a
@@ -590,8 +596,7 @@ static void launch_epi(const GemmArgs &g, int epi, hipStream_t s) {
 
 void launch_gemm_large(GemmArgs g, int epi, int tile, hipStream_t s) {
   if (epi != GEMM_EPI_PARTIAL) g.k_splits = 1;
-  // slices of rows whose operand stays below 2 GB
-  const int slice = (int)(((1ull << 31) / ((uint64_t)g.lda * 2) - 512) & ~255ull), M = g.M;
+  const int slice = gemm_large_slice_rows(g.lda), M = g.M;
   for (int m = 0; m < M; m += slice) {
     GemmArgs q = g;
     q.M = M - m < slice ? M - m : slice;

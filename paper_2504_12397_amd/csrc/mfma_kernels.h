@@ -163,6 +163,7 @@ void launch_qkv_stream(const GemmArgs &g, int n_cu, hipStream_t s);
 struct GemmLargePlan { int tile, splits; };      // tile: 2: 256 x 256, 1: 128 x 256, 0: 128 x 128; workgroups per output tile (> 1: PARTIAL)
 GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits);      // hint 2 / 3: tile 1 / 2
 bool gemm_large_supported(const GemmArgs &g, int epi);
+int gemm_large_slice_rows(int lda);      // more rows than this take several launches (and no PARTIAL)
 void launch_gemm_large(GemmArgs g, int epi, int tile, hipStream_t s);
 // tlow[row, p, {hi, lo}, j] = s_a * sum over splits of Y[split, row, (a * parts + p) * rank + j] for adapted rows
 // (a = row_adapter[row] >= 0): picks each row's adapter out of a projection on all adapters' down-matrices

@@ -180,3 +180,34 @@ def test_down_projection_of_more_rows_than_32_bit_offsets_reach(ab, ctx):
         ref = 2.0 * (xb @ t["A"][0, 2].cpu().double().T) @ t["B_v"][0].cpu().double().T
         e = H.rel_err(H.f64(cache.rows(b, 0, each)[1][:, 0]), ref.numpy())
         assert e <= H.TOL["bf16"], f"rows {b * each} ..: {e:.3e}"
+
+
+def test_large_tiles_of_an_operand_just_short_of_2_gb(ab, ctx):
+    """74241 rows of 14336 through W_down: the operand is below 2 GB but one row more than the kernel takes at once, and a narrow
+    output asks for several workgroups per tile.  W_o = 0, so the layer is x + MLP(x)."""
+    n, each, d, inter = 291, 256, 512, 14336
+    S = [each] * (n - 1) + [1]
+    T = sum(S)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1900)
+
+    def normal(*shape, std=1.0):
+        return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=g)
+
+    t = {"W_qkv": normal(384, d, std=d ** -0.5), "W_o": torch.zeros((d, 128), dtype=torch.bfloat16, device="cuda"), "rms_gain": None,
+         "rms2_gain": torch.ones(d, dtype=torch.bfloat16, device="cuda"), "W_gate": normal(inter, d, std=d ** -0.5),
+         "W_up": normal(inter, d, std=d ** -0.5), "W_down": normal(d, inter, std=4 * inter ** -0.5)}
+    x = normal(T, d)
+    cu = [0]
+    for s in S:
+        cu.append(cu[-1] + s)
+    cache = [ab.KVCache(S, 1, 128, torch.bfloat16, "cuda")]
+    out = ab.alora_stack_prefill(ctx, [ab.Layer(t, 1, 1, 128, 1e-5, 10000.0, inter)], cache, x, cu, [0] * n, [-1] * n)
+    torch.cuda.synchronize()
+    w = {k: v.cpu().double() for k, v in t.items() if v is not None}
+    for lo, hi in ((0, 64), (30000, 30064), (T - 65, T)):
+        h = x[lo:hi].cpu().double()
+        hn = (h * torch.rsqrt((h * h).mean(1, keepdim=True) + 1e-5)).to(torch.bfloat16).double()
+        act = (torch.nn.functional.silu(hn @ w["W_gate"].T) * (hn @ w["W_up"].T)).to(torch.bfloat16).double()
+        e = H.rel_err(H.f64(out[lo:hi]), (h + act @ w["W_down"].T).numpy())
+        assert e <= H.TOL["bf16"], f"rows {lo} ..: {e:.3e}"
