@@ -183,10 +183,13 @@ const char *alora_status_string(alora_status s);
  *   "profile"         0 (default) / 1: see alora_profile_read.
  *
  * Summation order (Proposition 1 in its strong form: rows before the invocation index are the base model's
- * rows).  With "gemm_tile" = 0 the key and value rows a call appends are a function of the row's own input and
- * position alone: bit-identical whether the row came in a long prefill, a short one, a decode step, alone or
- * in a mixed batch, with or without an adapter active on OTHER rows -- the QKV projection adds the products of a
- * row in one fixed order (a running sum in ascending order, whichever kernel computes it).  Rows before k_b of an adapter call are therefore bitwise the rows a base-only call writes.  What
+ * rows).  With "gemm_tile" = 0 the key and value rows a call appends for positions before k_b (and every row of
+ * a base-only sequence) are a function of the row's own input and position alone: bit-identical whether the row came in
+ * a long prefill, a short one, a decode step, alone or in a mixed batch, with or without an adapter active on OTHER
+ * rows -- the QKV projection adds the products of a row in one fixed order, whichever kernel computes it.  Rows before
+ * k_b of an adapter call are therefore bitwise the rows a base-only call writes.  Adapted rows are that only with calls
+ * that compute the down projection t = s A x in the same kernel (see "prep_split"): the two kernels add its products in
+ * different orders, and the rows agree to rounding.  What
  * is NOT bit-stable across differently shaped calls: attention outputs (the key axis is split by a heuristic
  * that looks at the whole batch, and prefill and decode attention are different kernels), and with them the
  * hidden states and cache rows of layers after the first in alora_stack_prefill; those agree to rounding. */

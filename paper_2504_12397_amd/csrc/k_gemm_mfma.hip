@@ -309,18 +309,18 @@ __attribute__((amdgpu_waves_per_eu((WEAVE && SEG) ? 2 : 1))) void gemm_mfma_kern
       const int a = __builtin_ctzll(present);
       present &= present - 1;
       constexpr int PB = TM * TN > 4 ? 1 : 2;         // k-steps whose loads are issued together
-      for (int kb2 = 0; kb2 < 2 * r; kb2 += 16 * PB) {     // k runs over [t_hi | t_lo] against [B | B]
+      // per 16 values of k first t_hi, then t_lo against the same values of B, as in the other projection kernels
+      for (int step = 0; step < 2 * ((r + 15) / 16); step += PB) {
         u32x4 bu[PB][TN], au[PB][TM][TN];
 #pragma unroll
         for (int h2 = 0; h2 < PB; ++h2) {
-          const int ks2 = kb2 + 16 * h2;
-          const bool live = ks2 < 2 * r;
-          const int kk = ks2 + lhi * 8, kb = kk < r ? kk : kk - r;
+          const int kk = 16 * ((step + h2) >> 1) + lhi * 8, hl = (step + h2) & 1;
+          const bool live = kk < r;      // (ranks that are not a multiple of 16)
 #pragma unroll
           for (int ni = 0; ni < TN; ++ni) {
             bu[h2][ni] = u32x4{0, 0, 0, 0};
             if (live && col_ok[ni])
-              bu[h2][ni] = *reinterpret_cast<const u32x4 *>(brow[ni] + (int64_t)a * a_stride[ni] + kb);
+              bu[h2][ni] = *reinterpret_cast<const u32x4 *>(brow[ni] + (int64_t)a * a_stride[ni] + kk);
           }
 #pragma unroll
           for (int mi = 0; mi < TM; ++mi) {
@@ -332,7 +332,7 @@ __attribute__((amdgpu_waves_per_eu((WEAVE && SEG) ? 2 : 1))) void gemm_mfma_kern
               au[h2][mi][ni] = u32x4{0, 0, 0, 0};
               if (live)
                 au[h2][mi][ni] =
-                    *reinterpret_cast<const u32x4 *>(g.tlow + ((int64_t)row * parts + p_of[ni]) * 2 * r + kk);
+                    *reinterpret_cast<const u32x4 *>(g.tlow + (((int64_t)row * parts + p_of[ni]) * 2 + hl) * r + kk);
             }
           }
         }

@@ -1,6 +1,7 @@
 // QKV projection of a call with few rows (up to 32 CW per row tile): y = W x_hat + gated low-rank term (Eq.6), rotated and
 // appended (Eq.3) in the epilogue, ONE running sum over K per output -- the same sums in the same order as the projection of
-// many rows (k_gemm_large.hip), so a row's keys and values are the same bits whatever call it came in.
+// many rows (k_gemm_large.hip), so a base row's keys and values are the same bits whatever call it came in, and an adapted
+// row's where t is (the two kernels that compute t add its products over different slices of d).
 //
 // What bounds it: streaming the weights (50 MB at the 8B-class shape), and from about 64 rows on the rows, which every workgroup
 // reads whole.  The reduction is not split, so the chip is filled over the columns alone: a tile is PP <= 16 rotation pairs
@@ -108,35 +109,37 @@ __global__ __launch_bounds__(64 * (CW + 4)) void qkv_stream_kernel(GemmArgs g, i
                                   : (kind == 1 ? g.Bk + (int64_t)(col - g.n_q) * r : g.Bv + (int64_t)(col - g.n_q - g.n_kv) * r));
     const int64_t a_stride = (int64_t)(kind == 0 ? g.n_q : g.n_kv) * r;
     // The columns of one tile may belong to two parts (q | k or k | v): t of every part is multiplied with the columns of that
-    // part.  k runs over [t_hi | t_lo] against [B | B], LS steps of 16 at a time, the next adapter's B one ahead: a round trip per
-    // adapter would be most of this kernel's time when a decode step runs eight of them.
+    // part.  Per 16 values of k first t_hi, then t_lo, as in the other projection kernels; LS such slices at a time, the next adapter's B
+    // one ahead: a round trip per adapter would be most of this kernel's time when a decode step runs eight of them.
     const int c_lo = col_of(pair0), c_hi = col_of(min(pair0 + PP, n_pairs) - 1);
     const int k_lo = c_lo < g.n_q ? 0 : (c_lo < g.n_q + g.n_kv ? 1 : 2), k_hi = c_hi < g.n_q ? 0 : (c_hi < g.n_q + g.n_kv ? 1 : 2);
     // t of a row is the same whatever adapter is multiplied (the others' rows are zeroed): it stays in registers.
-    constexpr int LS = 4;
+    constexpr int LS = 2;
     auto fetch_b = [&](unsigned long long left, int ks0, u32x4 (&b)[LS]) {
       if (!left) return;
       const bf16 *bp = brow + __builtin_ctzll(left) * a_stride;
 #pragma unroll
-      for (int i = 0; i < LS; ++i) {
-        const int kk = min(ks0 + 16 * i + lhi * 8, 2 * r - 8);
-        b[i] = *reinterpret_cast<const u32x4 *>(bp + (kk < r ? kk : kk - r));
-      }
+      for (int i = 0; i < LS; ++i) b[i] = *reinterpret_cast<const u32x4 *>(bp + min(ks0 + 16 * i + lhi * 8, r - 8));
     };
     for (int part = k_lo; part <= k_hi; ++part)
-      for (int ks0 = 0; ks0 < 2 * r; ks0 += 16 * LS) {
+      for (int ks0 = 0; ks0 < r; ks0 += 16 * LS) {
         const bf16 *tp = g.tlow + ((int64_t)rc * 3 + part) * 2 * r;
-        u32x4 t[LS], b0[LS], b1[LS];
+        u32x4 t[LS][2], b0[LS], b1[LS];
 #pragma unroll
-        for (int i = 0; i < LS; ++i) t[i] = *reinterpret_cast<const u32x4 *>(tp + min(ks0 + 16 * i + lhi * 8, 2 * r - 8));
+        for (int i = 0; i < LS; ++i)
+#pragma unroll
+          for (int hl = 0; hl < 2; ++hl) t[i][hl] = *reinterpret_cast<const u32x4 *>(tp + hl * r + min(ks0 + 16 * i + lhi * 8, r - 8));
         auto apply = [&](unsigned long long left, u32x4 (&b)[LS]) {
           const bool mine = a_row == (int)__builtin_ctzll(left);
 #pragma unroll
           for (int i = 0; i < LS; ++i) {
-            if (ks0 + 16 * i >= 2 * r) continue;
-            if (kind != part) b[i] = u32x4{0, 0, 0, 0};
-            const u32x4 tm = mine ? t[i] : u32x4{0, 0, 0, 0};
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b[i]), __builtin_bit_cast(bf16x8, tm), acc, 0, 0, 0);
+            if (ks0 + 16 * i >= r) continue;
+            if (kind != part || ks0 + 16 * i + lhi * 8 >= r) b[i] = u32x4{0, 0, 0, 0};      // (ranks that are not a multiple of 16)
+#pragma unroll
+            for (int hl = 0; hl < 2; ++hl) {
+              const u32x4 tm = mine ? t[i][hl] : u32x4{0, 0, 0, 0};
+              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b[i]), __builtin_bit_cast(bf16x8, tm), acc, 0, 0, 0);
+            }
           }
         };
         unsigned long long left = present;

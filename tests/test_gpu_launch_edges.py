@@ -211,3 +211,37 @@ def test_large_tiles_of_an_operand_just_short_of_2_gb(ab, ctx):
         act = (torch.nn.functional.silu(hn @ w["W_gate"].T) * (hn @ w["W_up"].T)).to(torch.bfloat16).double()
         e = H.rel_err(H.f64(out[lo:hi]), (h + act @ w["W_down"].T).numpy())
         assert e <= H.TOL["bf16"], f"rows {lo} ..: {e:.3e}"
+
+
+@pytest.mark.parametrize("rank", [8, 24, 32, 64])
+def test_rotation_fused_or_not_gives_the_same_bits_at_every_rank(ab, rank):
+    """The low-rank term joins the sums in one order in every projection kernel: the large tiles, the one that leaves the rotation
+    to another kernel and, given the same t (prep_split = 0), the one that streams the weights past few rows."""
+    shape = dataclasses.replace(SMALL_BF16, rank=rank)
+    case = H.make_case(shape, [30, 0, 64], [230, 190, 77], [40, 0, 100], [1, 2, -1], seed=2000 + rank, prefix="random")
+    got = []
+    for fuse in (1, 0):
+        c = ab.Context(0)
+        try:
+            c.set_option("rope_fuse", fuse)
+            out, cache = check_case(ab, c, case)
+            got.append((out.clone(), cache.k.clone(), cache.v.clone()))
+        finally:
+            c.close()
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    layer = H.gpu_layer(case, shape)
+    x = wl.make_hidden(wl.Rng(2010 + rank), "x", 300, shape).cuda()
+    rows = []
+    for n in (40, 300):
+        c = ab.Context(0)
+        try:
+            c.set_option("prep_split", 0)
+            cache = ab.KVCache([n], shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda")
+            ab.alora_prefill(c, layer, cache, x[:n].contiguous(), [0, n], [7], [2])
+            torch.cuda.synchronize()
+            rows.append(cache.rows(0, 0, 40))
+        finally:
+            c.close()
+    for a, b in zip(*rows):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
