@@ -151,8 +151,9 @@ const char *alora_status_string(alora_status s);
  *                     (partial results are merged by log-sum-exp weights).
  *   "gemm_splits"     0 (default): the QKV projection is a single running sum; the reduction axis of a stack's
  *                     other linears is cut by the shape of the weight matrix (up to 256 rows) or by what fills
- *                     the chip (more rows).  n in 1..64: every linear in n equal segments (where the reduction
- *                     length allows; 1 = a single running sum).  See "Summation order" below.
+ *                     the chip (more rows).  n in 1..64: QKV, W_o and W_down in n equal segments (where the
+ *                     reduction length allows; 1 = a single running sum); gate and up are a single
+ *                     running sum always.  See "Summation order" below.
  *   "gemm_tile"       0 (default): automatic block shape.  1: 128x128, 2: 256x128, 3: 256x256, 4: 128x64
  *                     (four waves); 5 / 6: 128x128 on eight waves of 32x64 / 64x32.  1 and 4..6 also apply to
  *                     the other linears of a stack.  A tuning experiment: with a value other than 0 the

@@ -630,7 +630,8 @@ void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s) {
   // tile shapes behind tile_hint are tuning experiments and do not carry that code.)
   const bool seg = g.k_splits == 1 && g.k_segments > 1 && g.tile_hint == 0 && (g.K / 64) % g.k_segments == 0;
   if (!seg && g.k_splits == 1) g.k_segments = 1;
-  if (epi != GEMM_EPI_PARTIAL && g.M > (epi == GEMM_EPI_SWIGLU ? 128 : 256) && g.tile_hint != 1 && g.tile_hint < 4) {
+  // (the large tiles keep one running sum)
+  if (epi != GEMM_EPI_PARTIAL && !seg && g.M > (epi == GEMM_EPI_SWIGLU ? 128 : 256) && g.tile_hint != 1 && g.tile_hint < 4) {
     GemmArgs q = g;
     q.k_splits = 1;
     if (gemm_large_supported(q, epi)) {

@@ -245,3 +245,33 @@ def test_rotation_fused_or_not_gives_the_same_bits_at_every_rank(ab, rank):
             c.close()
     for a, b in zip(*rows):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("linear", ["W_o", "W_down"])
+def test_gemm_splits_cuts_the_same_segments_at_every_number_of_rows(ab, linear):
+    """gemm_splits = 4: a row's sums are the same bits from a call of 256 rows (a workgroup per segment) and one of 300 (a workgroup
+    adds the segments itself), and other ones than with a single running sum.  Sequences of one row, so attention hands on v; for
+    W_down W_v = 0 and x is +-1, so both calls normalise exactly the same rows."""
+    shape = dataclasses.replace(SMALL_BF16, intermediate=1280)
+    rng = wl.Rng(2100)
+    t = wl.make_layer(shape, rng)
+    if linear == "W_o":
+        t["W_down"].zero_()
+        x = wl.make_hidden(rng, "x", 300, shape)
+    else:
+        t["W_qkv"][-shape.n_kv:].zero_()
+        x = wl.make_hidden(rng, "x", 300, shape).sign()
+    layer, x = H.gpu_layer(t, shape), x.cuda()
+    got = {}
+    for splits, n in ((4, 256), (4, 300), (1, 300)):
+        c = ab.Context(0)
+        try:
+            c.set_option("gemm_splits", splits)
+            cache = ab.KVCache([1] * n, shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda")
+            out = ab.alora_stack_prefill(c, [layer], [cache], x[:n].contiguous(), list(range(n + 1)), [0] * n, [-1] * n)
+            torch.cuda.synchronize()
+            got[splits, n] = out[:256].clone().view(torch.int16)
+        finally:
+            c.close()
+    assert torch.equal(got[4, 256], got[4, 300])
+    assert not torch.equal(got[4, 300], got[1, 300])
