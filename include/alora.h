@@ -149,7 +149,9 @@ const char *alora_status_string(alora_status s);
  *                     otherwise.  1: force the plain kernels (any dtype, any shape).
  *   "kv_splits"       0 (default): automatic.  n in 1..256: split the key axis of attention into n chunks
  *                     (partial results are merged by log-sum-exp weights).
- *   "gemm_splits"     0 (default): the QKV projection is a single running sum; the reduction axis of a stack's
+ *   "gemm_splits"     0 (default): the QKV projection is a single running sum (weights that are not 16-byte
+ *                     aligned, or a hidden size that is no multiple of 128: segments fixed by the
+ *                     weight shape, as with a value); the reduction axis of a stack's
  *                     other linears is cut by the shape of the weight matrix (up to 256 rows) or by what fills
  *                     the chip (more rows).  n in 1..64: QKV, W_o and W_down in n equal segments (where the
  *                     reduction length allows; 1 = a single running sum); gate and up are a single
@@ -164,8 +166,8 @@ const char *alora_status_string(alora_status s);
  *                     Calls without adapters only normalise.  The normalised rows are bit-identical either way.
  *   "lora_split"      0 (default): automatic.  1: always, 2: never give the low-rank term of the QKV
  *                     projection workgroups (and a partial sum) of its own.
- *   "rope_fuse"       1 (default): where the shape allows (head size 128) the QKV projection rotates q and k and
- *                     appends k and v in its own epilogue.  0: a separate kernel does, from the fp32 projection.
+ *   "rope_fuse"       1 (default): where the shape allows (few rows: head sizes that are multiples of 8; many: head
+ *                     size 128) the QKV projection rotates q and k and appends k and v in its own epilogue.  0: a separate kernel does, from the fp32 projection.
  *                     Same bits either way.
  *   "attn_waves"      0 (default) / 8: eight waves per workgroup in the prefill attention kernel.  4: four.
  *   "attn_lazy"       0..16 (default 3): the running row maximum of the prefill attention kernels moves only
@@ -187,7 +189,7 @@ const char *alora_status_string(alora_status s);
  * rows).  With "gemm_tile" = 0 the key and value rows a call appends for positions before k_b (and every row of
  * a base-only sequence) are a function of the row's own input and position alone: bit-identical whether the row came in
  * a long prefill, a short one, a decode step, alone or in a mixed batch, with or without an adapter active on OTHER
- * rows -- the QKV projection adds the products of a row in one fixed order, whichever kernel computes it.  Rows before
+ * rows -- the QKV projection adds the products of a row in one order, fixed by the weights, whichever kernel computes it.  Rows before
  * k_b of an adapter call are therefore bitwise the rows a base-only call writes.  Adapted rows are that only with calls
  * that compute the down projection t = s A x in the same kernel (see "prep_split"): the two kernels add its products in
  * different orders, and the rows agree to rounding.  What

@@ -26,7 +26,6 @@ static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 namespace {
 
 constexpr int N_SLOTS = 8;
-constexpr int QKV_STREAM_ROWS = 256;
 
 // per-sequence records travel to the device as kernel arguments (no staging buffer, no copy from host memory)
 constexpr int STAGE_SEQS = 32;
@@ -475,11 +474,11 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
   const bool q_half = (w.attn_mfma || w.decode_mfma) && std::is_same<T, bf16>::value;
   const int q_mode = q_half ? 1 : 2;
   const float q_scale = (w.attn_mfma && q_half) ? attn_prefill_mfma_q_scale(L, ctx->opt_attn_fold != 0) : 1.0f;
-  // The projection rotates and appends by itself where a head is 128 columns.  Up to QKV_STREAM_ROWS rows the kernel that streams
-  // the weights past all rows, beyond that the one whose tiles are large in both directions; both add in one order.
-  const bool fuse = mfma && q_half && ctx->opt_rope_fuse && ctx->opt_gemm_splits <= 1 && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
-  const bool stream = fuse && prep_mfma && ctx->opt_gemm_tile == 0 && pl.T <= QKV_STREAM_ROWS &&
-                      qkv_stream_supported(ly->W_qkv, pl.T, L.n_qkv, L.d, L.n_q, L.n_kv, L.head_dim);
+  // The projection rotates and appends by itself: up to stream_rows rows in the kernel that streams the weights past all rows,
+  // beyond that, where a head is 128 columns, in the one whose tiles are large in both directions; both add in one order.
+  const bool fuse = mfma && ctx->opt_rope_fuse && w.k_segments == 1 && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
+  const int stream_rows = qkv_stream_rows(L.n_qkv, ctx->n_cu);
+  const bool stream = fuse && ctx->opt_gemm_tile == 0 && pl.T <= stream_rows && qkv_stream_supported(ly->W_qkv, L.n_qkv, L.d, L.head_dim);
   auto stage_of = [&](bool first) {
     StagedCall st{};
     if (w.stage_n16 > 0) {
@@ -508,7 +507,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       launch_prep_rows_mfma(pa, s);
     } else {
       launch_prep_rows<T>(x, (const T *)ly->rms_gain, ly->rms_eps, pl.T, L.d, seqs_dev, pl.B, pos_shift,
-                          (const T *)ly->A, rank_used, write_meta, (T *)w.xh, w.tlow, mfma ? (bf16 *)w.tlow : nullptr, w.rm, stage_of(write_meta && pos_shift == 0), s);
+                          (const T *)ly->A, rank_used, write_meta, (T *)w.xh, w.tlow, mfma ? (bf16 *)w.tlow : nullptr, w.rm, stage_of(write_meta && pos_shift == 0), stream, s);
     }
   }
   if (w.rope_by_row) launch_rope_rows(w.rope_rows, w.rm.pos, pl.T, L.head_dim / 2, ly->rope_theta, s);
@@ -534,11 +533,12 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       g.present16 = prep_mfma ? w.rm.present16 : nullptr;
       g.rope_pos = w.rm.pos; g.rope_slot = w.rm.slot; g.rope_table = w.rope; g.q_scale = q_scale;
       g.rope_by_row = w.rope_by_row ? 1 : 0;
+      g.head_dim = L.head_dim; g.q_f32 = q_half ? 0 : 1;
       g.Qout = (bf16 *)w.Q; g.cacheK = (bf16 *)cache->k; g.cacheV = (bf16 *)cache->v;
       if (stream) {
         launch_qkv_stream(g, ctx->n_cu, s);
         rope_fused = true;
-      } else if (fuse && !w.rope_by_row && pl.T > 256 && gemm_mfma_rope_supported(g, L.head_dim)) {
+      } else if (fuse && q_half && !w.rope_by_row && pl.T > stream_rows && gemm_mfma_rope_supported(g, L.head_dim)) {
         launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, GEMM_EPI_ROPE, ctx->n_cu, 1).tile, s);
         rope_fused = true;
       } else {
@@ -746,7 +746,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
       launch_prep_rows_mfma(pa, s);
     } else {
       launch_prep_rows<T>((const T *)w.h1, (const T *)ly->rms2_gain, ly->rms_eps, T_rows, L.d, nullptr, 0, 0,
-                          (const T *)nullptr, 0, false, (T *)w.hn, nullptr, nullptr, none, StagedCall{}, s);
+                          (const T *)nullptr, 0, false, (T *)w.hn, nullptr, nullptr, none, StagedCall{}, false, s);
     }
   }
   if (mfma) {   // act = silu(hn W_gate^T) * (hn W_up^T) in one pass
@@ -1102,11 +1102,20 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   const bool mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && L.d % 64 == 0 &&
                     (L.n_adapters == 0 || (L.rank % 8 == 0 && L.n_adapters <= 64)) && L.n_q % 32 == 0 &&
                     L.n_kv % 32 == 0 && (!stack || (layers[0].intermediate % 64 == 0 && L.n_q % 64 == 0));
-  // The reduction axis of the QKV projection is one running sum (or gemm_splits segments, added in order: whether they run in
-  // workgroups of their own or one after the other inside one does not change a bit of the result).
+  // The reduction axis of the QKV projection is one running sum where the kernel that streams the weights can take few rows, and
+  // segments fixed by the weight shape where it cannot (unaligned weights, reductions that are no multiple of 128): 16 rows of the
+  // 8B-class shape with unaligned weights are 43 us as one sum, 21 in segments.  Weights decide, never the number of rows, so that a
+  // row's sums don't depend on it.  (Whether segments run in workgroups of their own or one after the other inside one does not
+  // change a bit of the result.)
   int k_segments = 1;
-  if (mfma && ctx->opt_gemm_splits > 0) k_segments = L.d % (64 * ctx->opt_gemm_splits) == 0 ? ctx->opt_gemm_splits : 1;
-  const int k_splits = (k_segments > 1 && gemm_mfma_split_segments(pl.T, L.n_qkv, ctx->n_cu)) ? k_segments : 1;
+  if (mfma && ctx->opt_gemm_splits > 0) {
+    k_segments = L.d % (64 * ctx->opt_gemm_splits) == 0 ? ctx->opt_gemm_splits : 1;
+  } else if (mfma) {
+    bool streamed = true;
+    for (int l = 0; l < n_layers; ++l) streamed = streamed && qkv_stream_supported(layers[l].W_qkv, L.n_qkv, L.d, L.head_dim);
+    if (!streamed) k_segments = gemm_mfma_fixed_segments(L.n_qkv, L.d, ctx->n_cu);
+  }
+  int k_splits = (k_segments > 1 && gemm_mfma_split_segments(pl.T, L.n_qkv, ctx->n_cu)) ? k_segments : 1;
   // What the static entry point needs with `n` partial records per (row, head) and `groups` work items per row and record
   auto static_bytes = [&](int n, int groups) {
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
@@ -1114,6 +1123,9 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
            up((size_t)pl.T * groups * n * sizeof(DecItem)) + up((size_t)2 * pl.T * sizeof(int32_t)) +
            (size_t)pl.T * (L.head_dim / 2) * sizeof(float2);
   };
+  // A decode step whose segment sums alone keep it out of the static scratch array adds them inside the workgroups (both entry points
+  // alike: they give the same bits).
+  if (decode && k_splits > 1 && static_bytes(1, (L.n_kv_heads + 7) / 8) > SCRATCH_BYTES) k_splits = 1;
   // work lists of the MFMA attention kernels (the number of partial records per (row, head) comes out of them)
   DecodePlan dp;
   PrefillPlan pp;
@@ -1487,10 +1499,10 @@ alora_status alora_lm_head(alora_ctx *ctx, alora_dtype dtype, int32_t d, int32_t
       launch_prep_rows_mfma(pa, s);
     } else if (bf) {
       launch_prep_rows<bf16>((const bf16 *)x_last, (const bf16 *)final_gain, rms_eps, B, d, nullptr, 0, 0, nullptr, 0,
-                             false, (bf16 *)xh, nullptr, nullptr, none, StagedCall{}, s);
+                             false, (bf16 *)xh, nullptr, nullptr, none, StagedCall{}, false, s);
     } else {
       launch_prep_rows<float>((const float *)x_last, (const float *)final_gain, rms_eps, B, d, nullptr, 0, 0, nullptr,
-                              0, false, (float *)xh, nullptr, nullptr, none, StagedCall{}, s);
+                              0, false, (float *)xh, nullptr, nullptr, none, StagedCall{}, false, s);
     }
     rows = xh;
   }

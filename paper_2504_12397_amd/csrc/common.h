@@ -82,7 +82,7 @@ void launch_rope_rows(float2 *table, const int32_t *pos, int n_rows, int half_di
 template <typename T>
 void launch_prep_rows(const T *x, const T *gain, float eps, int T_rows, int d, const SeqMeta *seqs,
                       int n_seqs, int pos_shift, const T *A, int rank, bool write_meta, T *xh, float *tlow,
-                      bf16 *tlow16, RowMeta rm, const StagedCall &st, hipStream_t s);
+                      bf16 *tlow16, RowMeta rm, const StagedCall &st, bool packed, hipStream_t s);      // (packed: PrepArgs::packed)
 
 // Y[T, n_qkv] (fp32) = xh W^T + gated low-rank term (Eq.6)
 template <typename T>

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const T *__restrict__ x,
                                                         int n_seqs, int pos_shift, const T *__restrict__ A, int rank,
                                                         int write_meta, T *__restrict__ xh,
                                                         float *__restrict__ tlow, bf16 *__restrict__ tlow16,
-                                                        RowMeta rm, StagedCall st) {
+                                                        RowMeta rm, StagedCall st, int packed) {
   extern __shared__ float xs[];
   __shared__ float red[4];
   __shared__ int s_adapter;
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const T *__restrict__ x,
     float v = xs[c];
     if (gain != nullptr) v = v * to_f32<T>(gain[c]) * rinv;
     T stored = from_f32<T>(v);
-    xh[(int64_t)row * d + c] = stored;
+    xh[packed ? xh_chunk(row, c >> 3, d, 1) * 8 + (c & 7) : (int64_t)row * d + c] = stored;
     xs[c] = to_f32<T>(stored);      // the projections consume the stored (rounded) value
   }
   if (carry) st.dst[tid] = staged;
@@ -143,15 +143,15 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const T *__restrict__ x,
 template <typename T>
 void launch_prep_rows(const T *x, const T *gain, float eps, int T_rows, int d, const SeqMeta *seqs,
                       int n_seqs, int pos_shift, const T *A, int rank, bool write_meta, T *xh, float *tlow,
-                      bf16 *tlow16, RowMeta rm, const StagedCall &st, hipStream_t s) {
+                      bf16 *tlow16, RowMeta rm, const StagedCall &st, bool packed, hipStream_t s) {
   if (T_rows == 0) return;
   hipLaunchKernelGGL((prep_rows_kernel<T>), dim3(T_rows), dim3(256), (size_t)d * sizeof(float), s, x, gain,
-                     eps, d, seqs, n_seqs, pos_shift, A, rank, write_meta ? 1 : 0, xh, tlow, tlow16, rm, st);
+                     eps, d, seqs, n_seqs, pos_shift, A, rank, write_meta ? 1 : 0, xh, tlow, tlow16, rm, st, packed ? 1 : 0);
 }
 template void launch_prep_rows<float>(const float *, const float *, float, int, int, const SeqMeta *, int, int,
-                                      const float *, int, bool, float *, float *, bf16 *, RowMeta, const StagedCall &, hipStream_t);
+                                      const float *, int, bool, float *, float *, bf16 *, RowMeta, const StagedCall &, bool, hipStream_t);
 template void launch_prep_rows<bf16>(const bf16 *, const bf16 *, float, int, int, const SeqMeta *, int, int,
-                                     const bf16 *, int, bool, bf16 *, float *, bf16 *, RowMeta, const StagedCall &, hipStream_t);
+                                     const bf16 *, int, bool, bf16 *, float *, bf16 *, RowMeta, const StagedCall &, bool, hipStream_t);
 
 // ---------------------------------------------------------------------------------------
 // plain tiled GEMM  C[M,N] = A[M,K] B[N,K]^T, 64x64 tile, 16-deep, 4x4 outputs per thread

@@ -40,10 +40,6 @@ __device__ __forceinline__ u32x4 norm_chunk(u32x4 x, u32x4 g, float rinv) {
   for (int e = 0; e < 8; ++e) xh[e] = (bf16)((float)xv[e] * (float)gv[e] * rinv);
   return __builtin_bit_cast(u32x4, xh);
 }
-// 16-byte chunk c of a row in x_hat: row-major, or in the order of the matrix operand (PrepArgs::packed)
-__device__ __forceinline__ int64_t xh_chunk(int row, int c, int d, int packed) {
-  return packed ? ((int64_t)(row >> 5) * (d >> 4) + (c >> 1)) * 64 + (row & 31) + 32 * (c & 1) : (int64_t)row * (d >> 3) + c;
-}
 // Metadata of the rows [row0, tile_end) of one tile: a thread takes a sequence, fetches its record once and fills
 // in the rows of the tile that belong to it -- one memory round trip, where a search over the sequence table
 // per row costs log2(n_seqs) dependent ones.  s_adapter / s_scale may be nullptr.

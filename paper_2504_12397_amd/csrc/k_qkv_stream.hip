@@ -3,9 +3,11 @@
 // many rows (k_gemm_large.hip), so a base row's keys and values are the same bits whatever call it came in, and an adapted
 // row's where t is (the two kernels that compute t add its products over different slices of d).
 //
+// Any head size that is a multiple of 8, any reduction length that is a multiple of 128.
+//
 // What bounds it: streaming the weights (50 MB at the 8B-class shape), and from about 64 rows on the rows, which every workgroup
 // reads whole.  The reduction is not split, so the chip is filled over the columns alone: a tile is PP <= 16 rotation pairs
-// (c, c + 64), chosen so that there is about one tile per compute unit (N = 6144: 12 pairs, 256 tiles), and a workgroup keeps
+// (c, c + h / 2), chosen so that there is about one tile per compute unit (N = 6144: 12 pairs, 256 tiles), and a workgroup keeps
 // up to 112 KB of its weight rows on the way.  Four waves do nothing but move weights into an LDS ring (stages of 512
 // bytes of every row); CW waves multiply, 32 rows each, and take their rows from memory (L2) in the order of the matrix operand --
 // row preparation writes x_hat that way (PrepArgs::packed), 1 KB per operand.  The two kinds of waves are apart because a wave's
@@ -38,9 +40,10 @@ __global__ __launch_bounds__(64 * (CW + 4)) void qkv_stream_kernel(GemmArgs g, i
   // the row tiles of one column tile follow each other at a distance of 8: same XCD, one copy of the weights in its L2
   const int x = blockIdx.x & 7, q0 = blockIdx.x >> 3, tm = q0 % tiles_m, pair0 = ((q0 / tiles_m) * 8 + x) * PP;
   if (pair0 >= n_pairs) return;
-  const int n_stages = K / QS_K;
-  // pair p: columns (p / 64) * 128 + p % 64 and 64 more
-  auto col_of = [&](int p) { return (p >> 6) * 128 + (p & 63); };
+  const int n_stages = (K + QS_K - 1) / QS_K, n_full = K / QS_K;      // (the last stage may be half a one: what it holds beyond K is not used)
+  // pair p of a head of 2 h2: columns (p / h2) * 2 h2 + p % h2 and h2 more
+  const int h2 = g.head_dim >> 1;
+  auto col_of = [&](int p) { const int hd = p / h2; return p + hd * h2; };
 
   if (wave >= CW) {
     // ---- loading waves: PW KB of every stage each ---------------------------------------------------------------------
@@ -50,7 +53,7 @@ __global__ __launch_bounds__(64 * (CW + 4)) void qkv_stream_kernel(GemmArgs g, i
     for (int j = 0; j < PW; ++j) {
       const int row = ((wave - CW) * PW + j) * 2 + lhi;      // row of the stage: first columns, then their partners
       const int p = min(pair0 + row % PP, n_pairs - 1);
-      vo[j] = (col_of(p) + (row / PP) * 64) * g.ldb * 2 + ((lane & 31) ^ (row & 15)) * 16;
+      vo[j] = (col_of(p) + (row / PP) * h2) * g.ldb * 2 + ((lane & 31) ^ (row & 15)) * 16;
     }
     auto req = [&](int s) {
       const int so = min(s, n_stages - 1) * (QS_K * 2), dst = (s % QS_DEPTH) * STAGE + (wave - CW) * (PW * 1024);
@@ -103,7 +106,7 @@ __global__ __launch_bounds__(64 * (CW + 4)) void qkv_stream_kernel(GemmArgs g, i
         present |= ((unsigned long long)__shfl_xor((int)(present >> 32), o, 64) << 32) | (uint32_t)__shfl_xor((int)present, o, 64);
     }
     const int r = g.rank, a_row = row < M ? g.row_adapter[rc] : -1;
-    const int col = col_of(my_pair) + (l32 >> 4) * 64;
+    const int col = col_of(my_pair) + (l32 >> 4) * h2;
     const int kind = col < g.n_q ? 0 : (col < g.n_q + g.n_kv ? 1 : 2);      // q, k or v
     const bf16 *brow = (kind == 0 ? g.Bq + (int64_t)col * r
                                   : (kind == 1 ? g.Bk + (int64_t)(col - g.n_q) * r : g.Bv + (int64_t)(col - g.n_q - g.n_kv) * r));
@@ -158,11 +161,11 @@ __global__ __launch_bounds__(64 * (CW + 4)) void qkv_stream_kernel(GemmArgs g, i
 
   float2 rot[2][4];
   {
-    const float2 *table = g.rope_table + (int64_t)(g.rope_by_row ? rc : pos) * 64;
+    const float2 *table = g.rope_table + (int64_t)(g.rope_by_row ? rc : pos) * h2;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) rot[q][i] = table[(min(pair0 + 8 * q + 4 * lhi, n_pairs - 4) & 63) + i];
+      for (int i = 0; i < 4; ++i) rot[q][i] = table[min(pair0 + 8 * q + 4 * lhi, n_pairs - 4) % h2 + i];
   }
   auto multiply = [&](int s, const u32x4 (&x0)[8], const u32x4 (&x1)[8], auto between) {      // stage s
     const char *w = lds + (s % QS_DEPTH) * STAGE + lds_row * (QS_K * 2);
@@ -176,16 +179,25 @@ __global__ __launch_bounds__(64 * (CW + 4)) void qkv_stream_kernel(GemmArgs g, i
     for (int i = 0; i < 8; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[8 + i], __builtin_bit_cast(bf16x8, x1[i]), acc, 0, 0, 0);
   };
   // (XB / 2 stages to a round, so that the buffers' numbers are constants)
-  for (int s0 = 0; s0 < n_stages; s0 += XB / 2) {
+  for (int s0 = 0; s0 < n_full; s0 += XB / 2) {
 #pragma unroll
     for (int j = 0; j < XB / 2; ++j) {
       const int s = s0 + j;
-      if (j > 0 && s >= n_stages) break;
+      if (j > 0 && s >= n_full) break;
       fetch(2 * s + XB - 1, xr[(2 * j + XB - 1) % XB]);
       wave_barrier();
       multiply(s, xr[2 * j], xr[2 * j + 1], [&] { fetch(2 * s + XB, xr[2 * j]); });
       wait_lds();      // the reads are done before the next barrier hands the stage back to the loading waves
     }
+  }
+  if (n_full < n_stages) {
+    fetch(2 * n_full, xr[0]);
+    wave_barrier();
+    const char *w = lds + (n_full % QS_DEPTH) * STAGE + lds_row * (QS_K * 2);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(w + ((i * 2 + lhi) ^ (lds_row & 15)) * 16),
+                                                    __builtin_bit_cast(bf16x8, xr[0][i]), acc, 0, 0, 0);
   }
 
   // ---- rotation and append: lane l32 is a row, register 4 q + i the slot 8 q + 4 lhi + i -------------------------------
@@ -205,27 +217,36 @@ __global__ __launch_bounds__(64 * (CW + 4)) void qkv_stream_kernel(GemmArgs g, i
       lo[i] = kind == 2 ? u : rope_lo(u, w, cs.x, cs.y) * qs;
       hi[i] = kind == 2 ? w : rope_hi(u, w, cs.x, cs.y) * qs;
     }
-    if (kind == 0) {      // queries as fp16 for the MFMA attention kernels
+    if (kind == 0 && g.q_f32) {      // queries for the plain attention kernel
+      float *dst = reinterpret_cast<float *>(g.Qout) + (int64_t)row * g.n_q + hcol;
+      *reinterpret_cast<float4 *>(dst) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+      *reinterpret_cast<float4 *>(dst + h2) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+    } else if (kind == 0) {      // queries as fp16 for the MFMA attention kernels
       half4 a, b;
 #pragma unroll
       for (int i = 0; i < 4; ++i) { a[i] = (_Float16)lo[i]; b[i] = (_Float16)hi[i]; }
       _Float16 *dst = reinterpret_cast<_Float16 *>(g.Qout) + (int64_t)row * g.n_q + hcol;
       *reinterpret_cast<half4 *>(dst) = a;
-      *reinterpret_cast<half4 *>(dst + 64) = b;
+      *reinterpret_cast<half4 *>(dst + h2) = b;
     } else {
       bf16x4 a, b;
 #pragma unroll
       for (int i = 0; i < 4; ++i) { a[i] = (bf16)lo[i]; b[i] = (bf16)hi[i]; }
       bf16 *dst = (kind == 1 ? g.cacheK : g.cacheV) + slot * g.n_kv + hcol;
       *reinterpret_cast<bf16x4 *>(dst) = a;
-      *reinterpret_cast<bf16x4 *>(dst + 64) = b;
+      *reinterpret_cast<bf16x4 *>(dst + h2) = b;
     }
   }
 }
 
-bool qkv_stream_supported(const void *W, int M, int N, int K, int n_q, int n_kv, int head_dim) {
-  return M > 0 && lds_aligned(W) && head_dim == 128 && K % QS_K == 0 && n_q % 128 == 0 && n_kv % 128 == 0 && (uint64_t)N * K * 2 < (1ull << 31);
+// A matter of the weights alone, never of the number of rows.  (Pairs are stored in fours, which must not straddle two heads.)
+bool qkv_stream_supported(const void *W, int N, int K, int head_dim) {
+  return lds_aligned(W) && head_dim % 8 == 0 && K % 128 == 0 && K >= QS_K && (uint64_t)N * K * 2 < (1ull << 31);
 }
+
+// Weights of more than one round of the widest tiles (8192 x 10240: 427 tiles of 12 pairs, every one with all of the rows): from 129 rows
+// on the 128 x 128 tiles, or the kernel without rotation, are quicker (256 rows: 111 us here, 79 and 93 there; 128 rows: 71 here, 90 there).
+int qkv_stream_rows(int N, int n_cu) { return N / 2 > 16 * n_cu ? QKV_STREAM_ROWS / 2 : QKV_STREAM_ROWS; }
 
 template <int CW, int PW>
 static void launch_cfg(const GemmArgs &g, hipStream_t s) {
@@ -237,10 +258,15 @@ static void launch_cfg(const GemmArgs &g, hipStream_t s) {
 }
 template <int CW>
 static void launch_cw(const GemmArgs &g, int n_cu, hipStream_t s) {
-  // pairs per tile: the fewest of 8, 12, 16 that leave one tile per compute unit
+  // pairs per tile: the one of 8, 12, 16 whose rounds of a tile per compute unit move the fewest weights one after the other
   const int pairs = g.N / 2;
-  if (pairs <= 8 * n_cu) launch_cfg<CW, 2>(g, s);
-  else if (pairs <= 12 * n_cu) launch_cfg<CW, 3>(g, s);
+  int pw = 4, least = 0;
+  for (int p = 4; p >= 2; --p) {
+    const int t = ((pairs + 4 * p - 1) / (4 * p) + n_cu - 1) / n_cu * p;
+    if (p == 4 || t < least) { least = t; pw = p; }
+  }
+  if (pw == 2) launch_cfg<CW, 2>(g, s);
+  else if (pw == 3) launch_cfg<CW, 3>(g, s);
   else launch_cfg<CW, 4>(g, s);
 }
 

@@ -39,10 +39,11 @@ struct GemmArgs {
   // put it -- Q [M, n_q], the cache rows rope_slot[row] of K and V -- without the fp32 round trip through memory
   const int32_t *rope_pos;     // [M] absolute positions
   const int64_t *rope_slot;    // [M] pool rows
-  const float2 *rope_table;    // [positions, 64] (cos, sin)
+  const float2 *rope_table;    // [positions, head_dim / 2] (cos, sin)
   float q_scale;               // multiplies the rotated queries
   int rope_by_row;             // 1: rope_table has a line per row instead of one per position (few-row kernel only)
-  int q_half;                  // 1: Qout receives fp16 (the MFMA prefill attention kernel's operand type) instead of bf16
+  int head_dim;                // few-row kernel only (the others: 128)
+  int q_f32;                   // few-row kernel only, 1: Qout receives fp32 (plain attention) instead of fp16
   bf16 *Qout, *cacheK, *cacheV;
 };
 bool gemm_mfma_rope_supported(const GemmArgs &g, int head_dim);
@@ -69,6 +70,10 @@ struct PrepArgs {
   bf16 *tlow16;             // [T, 3, 2, rank]
   RowMeta rm;
 };
+// 16-byte chunk c of a row in x_hat: row-major, or in the order of the matrix operand (PrepArgs::packed)
+__device__ __forceinline__ int64_t xh_chunk(int row, int c, int d, int packed) {
+  return packed ? ((int64_t)(row >> 5) * (d >> 4) + (c >> 1)) * 64 + (row & 31) + 32 * (c & 1) : (int64_t)row * (d >> 3) + c;
+}
 bool prep_rows_mfma_supported(int d, int rank);
 void launch_prep_rows_mfma(const PrepArgs &a, hipStream_t s);
 // One workgroup of the prefill attention kernel: up to 256/G consecutive packed rows (tokens) against the key
@@ -158,7 +163,9 @@ bool gemm_mfma_split_segments(int M, int N, int n_cu);     // one workgroup per 
 void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s);
 // many rows: 256 x 256 or 128 x 256 tiles (rows = 256 / 128), one running sum over K; BF16, SWIGLU and ROPE epilogues
 // few rows: the whole QKV projection with rotation and append, A packed (PrepArgs::packed)
-bool qkv_stream_supported(const void *W, int M, int N, int K, int n_q, int n_kv, int head_dim);
+constexpr int QKV_STREAM_ROWS = 256;      // most rows that the kernel takes, and those of a call with N columns
+int qkv_stream_rows(int N, int n_cu);
+bool qkv_stream_supported(const void *W, int N, int K, int head_dim);
 void launch_qkv_stream(const GemmArgs &g, int n_cu, hipStream_t s);
 struct GemmLargePlan { int tile, splits; };      // tile: 2: 256 x 256, 1: 128 x 256, 0: 128 x 128; workgroups per output tile (> 1: PARTIAL)
 GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits);      // hint 2 / 3: tile 1 / 2

@@ -275,3 +275,90 @@ def test_gemm_splits_cuts_the_same_segments_at_every_number_of_rows(ab, linear):
             c.close()
     assert torch.equal(got[4, 256], got[4, 300])
     assert not torch.equal(got[4, 300], got[1, 300])
+
+
+def _appended(ab, layer, shape, x, opts=(), profile=False, decode=False):
+    """The rows that a base-only call on the hidden states x appends: one sequence, or (decode) a sequence per row"""
+    c = ab.Context(0)
+    try:
+        for k, v in opts:
+            c.set_option(k, v)
+        if profile:
+            c.set_option("profile", 1)
+        n = x.shape[0]
+        cache = ab.KVCache([1] * n if decode else [n], shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda")
+        if decode:
+            ab.alora_decode(c, layer, cache, x, [0] * n, [-1] * n)
+        else:
+            ab.alora_prefill(c, layer, cache, x, [0, n], [0], [-1])
+        torch.cuda.synchronize()
+        return torch.cat([cache.k, cache.v], dim=2).view(torch.int16), c.profile_read() if profile else None
+    finally:
+        c.close()
+
+
+# hidden sizes of the plain row preparation, reductions that end in half a stage (384, 640, 896), heads of 48, 64 and 256 columns, query
+# groups that the matrix attention kernels do not take (5, and any other head size: queries as fp32); 320 is not streamed
+OTHER_SHAPES = [(640, 8, 2, 128), (384, 4, 2, 64), (1280, 10, 2, 128), (768, 4, 1, 256), (896, 16, 2, 48), (320, 8, 2, 128)]
+
+
+@pytest.mark.parametrize("d,hq,hkv,h", OTHER_SHAPES)
+@pytest.mark.parametrize("T", [1, 70, 200])
+def test_few_rows_of_other_shapes(ab, ctx, d, hq, hkv, h, T):
+    shape = wl.LayerShape(d=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=h, rank=24, n_adapters=4)
+    n = min(T, 4)
+    S = _split(T, n)
+    P = [40, 0, 17, 90][:n]
+    case = H.make_case(shape, P, S, [P[b] + (S[b] // 2 if b % 2 else 0) for b in range(n)], [3, 1, -1, 2][:n], seed=2200 + T + d,
+                       prefix="random")
+    check_case(ab, ctx, case)
+    if T > 1:
+        case = H.make_case(shape, [40] * T, [1] * T, [20] * T, [b % 5 - 1 for b in range(T)], seed=2210 + T + d, prefix="random")
+        check_case(ab, ctx, case, decode=True)
+
+
+@pytest.mark.parametrize("d,hq,hkv,h", OTHER_SHAPES)
+def test_rows_of_other_shapes_do_not_depend_on_the_call(ab, d, hq, hkv, h):
+    """One row, 40, 200 and 300, a decode step: the same bits; few rows are rotated in the projection except where it cannot."""
+    shape = wl.LayerShape(d=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=h, rank=8, n_adapters=1)
+    rng = wl.Rng(2300 + d)
+    layer, x = H.gpu_layer(wl.make_layer(shape, rng), shape), wl.make_hidden(rng, "x", 300, shape).cuda()
+    want, _ = _appended(ab, layer, shape, x)
+    for n in (1, 40, 200):
+        got, prof = _appended(ab, layer, shape, x[:n].contiguous(), profile=True)
+        assert torch.equal(got, want[:n])
+        assert ("rope_append" in prof) == (d == 320)
+    step, _ = _appended(ab, layer, shape, x[:1].contiguous(), decode=True)
+    assert torch.equal(step, want[:1])
+
+
+def test_unaligned_weights_keep_the_segments_of_their_shape(ab):
+    """2048 x 1536 a few bytes off: four segments, from one row to 300 (default = gemm_splits 4, bit for bit)."""
+    shape = wl.LayerShape(d=2048, n_q_heads=8, n_kv_heads=2, head_dim=128, rank=8, n_adapters=1)
+    rng = wl.Rng(2400)
+    t = wl.make_layer(shape, rng)
+    x = wl.make_hidden(rng, "x", 300, shape).cuda()
+    flat = torch.empty(t["W_qkv"].numel() + 4, dtype=torch.bfloat16, device="cuda")
+    flat[4:] = t["W_qkv"].reshape(-1).cuda()
+    t["W_qkv"] = flat[4:].view(t["W_qkv"].shape)
+    layer = H.gpu_layer(t, shape)
+    assert layer.t["W_qkv"].data_ptr() % 16 == 8
+    want, _ = _appended(ab, layer, shape, x, [("gemm_splits", 4)])
+    for n in (1, 40, 200, 300):
+        got, _ = _appended(ab, layer, shape, x[:n].contiguous())
+        assert torch.equal(got, want[:n])
+    one, _ = _appended(ab, layer, shape, x, [("gemm_splits", 1)])
+    assert not torch.equal(one, want)
+
+
+@pytest.mark.parametrize("T", [128, 129, 256])
+def test_rows_of_wide_weights_do_not_depend_on_the_call(ab, ctx, T):
+    """More than 4096 rotation pairs: the streaming kernel up to 128 rows, the tiles beyond, the same bits."""
+    shape = wl.LayerShape(d=512, n_q_heads=64, n_kv_heads=8, head_dim=128, rank=8, n_adapters=2)
+    S = _split(T, 3)
+    case = H.make_case(shape, [30, 0, 64], S, [30, S[1] // 2, 64], [1, 0, -1], seed=2500 + T, prefix="random")
+    check_case(ab, ctx, case)
+    layer, x = H.gpu_layer(case, shape), wl.make_hidden(wl.Rng(2510), "x", 300, shape).cuda()
+    want, _ = _appended(ab, layer, shape, x)
+    got, _ = _appended(ab, layer, shape, x[:T].contiguous())
+    assert torch.equal(got, want[:T])
