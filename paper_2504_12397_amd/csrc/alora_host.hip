@@ -475,10 +475,11 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
   const int q_mode = q_half ? 1 : 2;
   const float q_scale = (w.attn_mfma && q_half) ? attn_prefill_mfma_q_scale(L, ctx->opt_attn_fold != 0) : 1.0f;
   // The projection rotates and appends by itself: up to stream_rows rows in the kernel that streams the weights past all rows,
-  // beyond that, where a head is 128 columns, in the one whose tiles are large in both directions; both add in one order.
-  const bool fuse = mfma && ctx->opt_rope_fuse && w.k_segments == 1 && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
+  // beyond that, where a head is 128 columns, in the one whose tiles are large in both directions (both add in one order), or in the
+  // 128 x 128 block of four waves, which also adds segments.
+  const bool fuse = mfma && ctx->opt_rope_fuse && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
   const int stream_rows = qkv_stream_rows(L.n_qkv, ctx->n_cu);
-  const bool stream = fuse && ctx->opt_gemm_tile == 0 && pl.T <= stream_rows && qkv_stream_supported(ly->W_qkv, L.n_qkv, L.d, L.head_dim);
+  const bool stream = fuse && w.k_segments == 1 && ctx->opt_gemm_tile == 0 && pl.T <= stream_rows && qkv_stream_supported(ly->W_qkv, L.n_qkv, L.d, L.head_dim);
   auto stage_of = [&](bool first) {
     StagedCall st{};
     if (w.stage_n16 > 0) {
@@ -538,8 +539,12 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       if (stream) {
         launch_qkv_stream(g, ctx->n_cu, s);
         rope_fused = true;
-      } else if (fuse && q_half && !w.rope_by_row && pl.T > stream_rows && gemm_mfma_rope_supported(g, L.head_dim)) {
+      } else if (fuse && q_half && !w.rope_by_row && w.k_segments == 1 && pl.T > stream_rows && gemm_mfma_rope_supported(g, L.head_dim) &&
+                 gemm_large_supported(g, GEMM_EPI_ROPE)) {
         launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, GEMM_EPI_ROPE, ctx->n_cu, 1).tile, s);
+        rope_fused = true;
+      } else if (fuse && q_half && !w.rope_by_row && ctx->opt_gemm_tile == 0 && pl.T > 256 && gemm_mfma_rope_supported(g, L.head_dim)) {
+        launch_gemm_mfma(g, GEMM_EPI_ROPE, s);
         rope_fused = true;
       } else {
         launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);

@@ -16,10 +16,11 @@
 //   adapted by a), B-operand = B_{a,p} (twice).  Rows that are not adapted accumulate exact zeros into zero
 //   accumulators, so their results are bitwise what a base-only call gives.
 // * Epilogues: fp32 partial sums (split-K capable, summed later in a fixed order), bf16 store
-//   (+ residual), SwiGLU (gate and up columns interleaved in 32-column blocks inside the tile).
+//   (+ residual), SwiGLU (gate and up columns interleaved in 32-column blocks inside the tile), rotation and
+//   append of one head per tile.
 #include <type_traits>
 
-#include "mfma_kernels.h"
+#include "lds_dma.h"
 
 namespace alora {
 
@@ -407,6 +408,62 @@ __attribute__((amdgpu_waves_per_eu((WEAVE && SEG) ? 2 : 1))) void gemm_mfma_kern
   }
 
   // ---- epilogue ---------------------------------------------------------------------------
+  if constexpr (EPI == GEMM_EPI_ROPE) {
+    // The 128-column tile is one head.  The accumulators go through LDS as fp32 (the k-tiles are done with it); then each wave takes
+    // 32 rows, two at a time: a lane the columns 2 j, 2 j + 1 and their partners, the table lines of eight rows asked for together.
+    // For weights that the large tiles do not take (unaligned, or reduced in segments); without it the fp32 projection goes through
+    // memory and another launch (4096 x 6144 unaligned, 600 rows: 69 us, 1500 rows: 145; with it 62 and 132).
+    static_assert(BM == 128 && BN == 128 && NT == 256, "one head per tile, four waves");
+    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+    typedef _Float16 half2 __attribute__((ext_vector_type(2)));
+    float *ys = reinterpret_cast<float *>(smem);       // [128][128]
+    __syncthreads();
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < TN; ++ni)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          ys[(wm0 + mi * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3)) * 128 + wn0 + ni * 32 + l32] = acc[mi][ni][v];
+    __syncthreads();
+    const int kind = n0 < g.n_q ? 0 : (n0 < g.n_q + g.n_kv ? 1 : 2);          // q, k or v head
+    const int hcol = kind == 0 ? n0 : (kind == 1 ? n0 - g.n_q : n0 - g.n_q - g.n_kv);
+    const int j2 = 2 * l32;
+    for (int r0 = 0; r0 < 32; r0 += 8) {
+      const int wrow = m0 + wave * 32 + r0;
+      if (wrow >= M) break;
+      float4 cs[4];
+      int64_t slot[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int rc = min(wrow + 2 * i + lhi, M - 1);
+        slot[i] = kind == 0 ? rc : g.rope_slot[rc];
+        cs[i] = kind == 2 ? make_float4(1.f, 0.f, 1.f, 0.f) : *reinterpret_cast<const float4 *>(g.rope_table + (int64_t)g.rope_pos[rc] * 64 + j2);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int rr = wave * 32 + r0 + 2 * i + lhi;
+        if (m0 + rr >= M) continue;
+        const float2 u = *reinterpret_cast<const float2 *>(ys + rr * 128 + j2), w = *reinterpret_cast<const float2 *>(ys + rr * 128 + 64 + j2);
+        if (kind == 0) {      // queries as fp16 for the MFMA prefill attention kernel
+          half2 lo, hi;
+          lo[0] = (_Float16)(rope_lo(u.x, w.x, cs[i].x, cs[i].y) * g.q_scale); lo[1] = (_Float16)(rope_lo(u.y, w.y, cs[i].z, cs[i].w) * g.q_scale);
+          hi[0] = (_Float16)(rope_hi(u.x, w.x, cs[i].x, cs[i].y) * g.q_scale); hi[1] = (_Float16)(rope_hi(u.y, w.y, cs[i].z, cs[i].w) * g.q_scale);
+          _Float16 *dst = reinterpret_cast<_Float16 *>(g.Qout) + slot[i] * g.n_q + hcol + j2;
+          *reinterpret_cast<half2 *>(dst) = lo;
+          *reinterpret_cast<half2 *>(dst + 64) = hi;
+        } else {
+          bf16x2 lo, hi;
+          lo[0] = (bf16)(kind == 2 ? u.x : rope_lo(u.x, w.x, cs[i].x, cs[i].y)); lo[1] = (bf16)(kind == 2 ? u.y : rope_lo(u.y, w.y, cs[i].z, cs[i].w));
+          hi[0] = (bf16)(kind == 2 ? w.x : rope_hi(u.x, w.x, cs[i].x, cs[i].y)); hi[1] = (bf16)(kind == 2 ? w.y : rope_hi(u.y, w.y, cs[i].z, cs[i].w));
+          bf16 *dst = (kind == 1 ? g.cacheK : g.cacheV) + slot[i] * g.n_kv + hcol + j2;
+          *reinterpret_cast<bf16x2 *>(dst) = lo;
+          *reinterpret_cast<bf16x2 *>(dst + 64) = hi;
+        }
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int mi = 0; mi < TM; ++mi) {
 #pragma unroll
@@ -614,8 +671,7 @@ bool gemm_mfma_split_segments(int M, int N, int n_cu) {
 }
 
 bool gemm_mfma_rope_supported(const GemmArgs &g, int head_dim) {
-  return head_dim == 128 && g.k_splits == 1 && g.lora_split == 0 && g.n_q % 128 == 0 && g.n_kv % 128 == 0 &&
-         g.N == g.n_q + 2 * g.n_kv && gemm_large_supported(g, GEMM_EPI_ROPE);
+  return head_dim == 128 && g.k_splits == 1 && g.lora_split == 0 && g.n_q % 128 == 0 && g.n_kv % 128 == 0 && g.N == g.n_q + 2 * g.n_kv;
 }
 
 void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s) {
@@ -630,6 +686,11 @@ void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s) {
   // tile shapes behind tile_hint are tuning experiments and do not carry that code.)
   const bool seg = g.k_splits == 1 && g.k_segments > 1 && g.tile_hint == 0 && (g.K / 64) % g.k_segments == 0;
   if (!seg && g.k_splits == 1) g.k_segments = 1;
+  if (epi == GEMM_EPI_ROPE) {
+    if (seg) launch_cfg<128, 128, 64, 64, GEMM_EPI_ROPE, 2, true, true>(g, s);
+    else launch_cfg<128, 128, 64, 64, GEMM_EPI_ROPE, 2, true>(g, s);
+    return;
+  }
   // (the large tiles keep one running sum)
   if (epi != GEMM_EPI_PARTIAL && !seg && g.M > (epi == GEMM_EPI_SWIGLU ? 128 : 256) && g.tile_hint != 1 && g.tile_hint < 4) {
     GemmArgs q = g;

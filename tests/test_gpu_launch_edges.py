@@ -345,8 +345,11 @@ def test_unaligned_weights_keep_the_segments_of_their_shape(ab):
     assert layer.t["W_qkv"].data_ptr() % 16 == 8
     want, _ = _appended(ab, layer, shape, x, [("gemm_splits", 4)])
     for n in (1, 40, 200, 300):
-        got, _ = _appended(ab, layer, shape, x[:n].contiguous())
+        got, prof = _appended(ab, layer, shape, x[:n].contiguous(), profile=True)
         assert torch.equal(got, want[:n])
+        assert ("rope_append" in prof) == (n <= 256)
+    got, _ = _appended(ab, layer, shape, x, [("rope_fuse", 0)])
+    assert torch.equal(got, want)
     one, _ = _appended(ab, layer, shape, x, [("gemm_splits", 1)])
     assert not torch.equal(one, want)
 
