@@ -814,6 +814,43 @@ struct DecodePlan {
   int n_device_items = 0;          // size of the device-built list: rows x head groups x n_own
   int hw = 1, kr = 1, groups = 1, cols_max = 1;
 };
+
+// What one way of cutting the keys would take, in us: `cuts` are (32-key steps of a wave, workgroups of that length), `records` partial
+// records of `most` at most per (row, head) are merged.  Longest first on n_cu units, one workgroup each: either the longest chain of
+// steps counts (3.76 us a step) or memory, which delivers 24 bytes per ns and unit once 5/8 of the units ask, and waits with the tail
+// where fewer do.  4.8 us a round, 0.5 to join sub-ranges in LDS, 3 % for rows of which a workgroup reads but two heads.  Fitted to
+// 5600 measured plans (1 to 500 rows of 64 to 40000 keys, 1 to 16 kv heads, shared prefixes; 6 % mean error).  Picked by it, attention
+// with its merge takes 1.8 % longer than with the best of those plans on average; the rule it replaces (at least 512 keys each in two
+// rounds, or sub-ranges in one) 5.7 %, and up to 1.8 x: 256 rows of 64 keys 40 -> 28 us, 64 rows of 4000 214 -> 188, 33 of 4000 150 -> 105.
+double decode_cut_us(std::vector<std::pair<int, int>> &cuts, int n_cu, double bytes, bool join, bool two_heads, double records, int most) {
+  std::sort(cuts.begin(), cuts.end(), [](const std::pair<int, int> &x, const std::pair<int, int> &y) { return x.first > y.first; });
+  int64_t steps = 0, n = 0;
+  for (const auto &c : cuts) { steps += (int64_t)c.first * c.second; n += c.second; }
+  const int ks = n_cu * 5 / 8;                       // units that keep memory busy
+  const int rounds = (int)((n + n_cu - 1) / n_cu);
+  double longest = cuts[0].first, busy = 0;          // steps of the unit that ends last, and of the ks that do
+  if (n <= n_cu) {
+    int left = ks;
+    for (const auto &c : cuts) { const int k = std::min(left, c.second); busy += (double)k * c.first; left -= k; }
+  } else if (n <= 2 * n_cu) {
+    std::vector<int> d;
+    d.reserve((size_t)n);
+    for (const auto &c : cuts) d.insert(d.end(), (size_t)c.second, c.first);
+    for (int64_t i = n_cu; i < n; ++i) d[2 * n_cu - 1 - i] += d[i];
+    d.resize(n_cu);
+    std::nth_element(d.begin(), d.begin() + ks, d.end(), [](int x, int y) { return x > y; });
+    for (int i = 0; i < ks; ++i) { busy += d[i]; longest = std::max(longest, (double)d[i]); }
+  } else {
+    const double mean = (double)steps / n_cu;
+    longest = std::max(longest, mean + 0.5 * cuts.back().first);
+    busy = ks * mean;
+  }
+  // (a round that fills the chip to the last unit: a hundredth more, 64 rows of 4000 keys 181 us in 192 workgroups and 196 in 256)
+  const double full = !two_heads && n > n_cu * 15 / 16 && n <= n_cu ? 1.01 : 1.0;
+  const double memory = bytes / (24e3 * n_cu) * (1.0 + (ks * longest - busy) / (double)steps) * full / (two_heads ? 0.97 : 1.0);
+  return std::max(3.76 * longest, memory) + 4.8 * rounds + (join ? 0.5 : 0.0) + 200e-6 * records + (most > 1 ? 0.7 : 0.0) + 0.017 * most;
+}
+
 // `cap`: most records of either kind a row may have (every row's place in memory is that large).
 DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, int cap, bool on_device) {
   DecodePlan dp;
@@ -842,29 +879,77 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
   auto own_keys = [&](const SeqMeta &m) { return m.P + 1 - m.prefix_len; };      // of the first step, the new key included
   int64_t keys = 0;
   int longest = 1;
+  std::vector<int> lens;           // of the rows' own keys, then of the prefixes
+  lens.reserve((size_t)pl.B + chunks.size());
   for (const SeqMeta &m : pl.seqs)
-    if (m.n_new > 0) { keys += own_keys(m); longest = std::max(longest, own_keys(m)); }
-  for (const Chunk &c : chunks) { keys += c.len; longest = std::max(longest, c.len); }
-  // Short work: spread over one wave per SIMD slot (2048 of them) a wave has fewer than 384 keys of one kv head.  Then a workgroup is
-  // two kv heads x four sub-ranges and the ranges are as long as one round of workgroups allows, but no shorter than the four
-  // sub-ranges' steps.  Otherwise eight kv heads side by side, two rounds of workgroups (every range of a head costs a
-  // partial record), at least 512 keys each.
-  const bool short_work = keys * L.n_kv_heads < 384 * 8 * (int64_t)ctx->n_cu && ctx->opt_splits == 0 && cap > 1;
-  decode_mfma_shape(L.n_kv_heads, short_work, &dp.hw, &dp.kr);
+    if (m.n_new > 0) lens.push_back(own_keys(m));
+  const size_t n_rows = lens.size();
+  for (const Chunk &c : chunks) lens.push_back(c.len);
+  for (int n : lens) { keys += n; longest = std::max(longest, n); }
+  // A workgroup is eight kv heads side by side, each over the whole range, or (a long row among few, heads that are no multiple of
+  // eight) two kv heads x four sub-ranges that join in LDS; the ranges are as long as gives nearly one round of workgroups, one,
+  // two, or one workgroup per row and group of heads.  Whichever takes the least time (decode_cut_us).
+  decode_mfma_shape(L.n_kv_heads, false, &dp.hw, &dp.kr);
   dp.groups = (L.n_kv_heads + dp.hw - 1) / dp.hw;
-  auto workgroups = [&](int range) {
-    int64_t n = 0;
-    for (const SeqMeta &m : pl.seqs)
-      if (m.n_new > 0) n += dec_cut(own_keys(m), range).parts;
-    for (const Chunk &c : chunks) n += dec_cut(c.len, range).parts;
-    return n * dp.groups;
-  };
-  const int64_t most = short_work ? ctx->n_cu : 2 * ctx->n_cu;
-  int range = short_work ? 32 * dp.kr : 512;
-  range = std::max<int64_t>(range, keys * dp.groups / most);
-  if (ctx->opt_splits == 0)
-    for (int i = 0; i < 12 && workgroups(range) > most && range < longest; ++i) range += std::max(32, range / 16);
-  range = std::max(range, (longest + cap - 1) / cap);
+  const int least = (longest + cap - 1) / cap;
+  int range = longest;
+  if (ctx->opt_splits == 0) {
+    const int n_cu = ctx->n_cu;
+    double best = 1e30;
+    std::vector<std::pair<int, int>> cuts;
+    auto consider = [&](int hw, int kr, int r) {
+      const int groups = (L.n_kv_heads + hw - 1) / hw;
+      cuts.clear();
+      auto put = [&](int len, int n) {
+        const int st = (((len + kr - 1) / kr) + 31) >> 5;
+        if (!cuts.empty() && cuts.back().first == st) cuts.back().second += n;
+        else cuts.emplace_back(st, n);
+      };
+      double records = 0;
+      int own = 0, shared = 0;
+      DecCut c{1, 0};
+      for (size_t i = 0; i < lens.size(); ++i) {
+        if (i == 0 || i == n_rows || lens[i] != lens[i - 1]) c = dec_cut(lens[i], r);
+        if (c.parts > 1) put(c.len, (c.parts - 1) * groups);
+        put(lens[i] - (c.parts - 1) * c.len, groups);
+        (i < n_rows ? own : shared) = std::max(i < n_rows ? own : shared, c.parts);
+        records += (double)c.parts * (i < n_rows ? 1 : chunks[i - n_rows].n);
+      }
+      const double us = decode_cut_us(cuts, n_cu, 512.0 * keys * L.n_kv_heads, kr > 1, hw < dp.hw, records * L.n_q_heads, own + shared);
+      if (us < best) { best = us; dp.hw = hw; dp.kr = kr; range = r; }
+    };
+    const int wide = dp.hw;
+    for (int form = cap > 1 && wide > 2 ? 0 : 1; form < 2; ++form) {
+      int hw, kr, last = 0;
+      decode_mfma_shape(L.n_kv_heads, form == 0, &hw, &kr);
+      const int64_t groups = (L.n_kv_heads + hw - 1) / hw;
+      const int64_t n1 = groups * (int64_t)lens.size();      // workgroups, one range each
+      // (the last one: where rows alone are more than that, a long row among them still wants to be cut)
+      for (int64_t most : {(int64_t)(form == 0 ? 0 : n_cu * 15 / 16), (int64_t)n_cu, (int64_t)2 * n_cu, n1 > n_cu ? n1 + n1 / 8 : 0}) {
+        if (most < n1 || (form == 0 && n1 > (L.n_kv_heads % 8 ? 4 : 2) * n_cu)) continue;
+        // the shortest ranges that `most` workgroups take, to within a tenth
+        int r = (int)std::max<int64_t>({(int64_t)32 * kr, keys * groups / most & ~31, (int64_t)least});
+        for (int i = 0; i < 24 && r < longest; ++i) {
+          int64_t n = 0;
+          if (n1 > 64) {      // (a number of workgroups that is a little too large now and then)
+            const float inv = 1.0f / (float)r;
+            int k = 0;
+            for (int len : lens) k += (int)((float)(len - 1) * inv) + 1;
+            n = k * groups;
+          } else {
+            for (int len : lens) n += dec_cut(len, r).parts;
+            n *= groups;
+          }
+          if (n <= most) break;
+          r += std::max(32, (int)(r * (n - most) / (2 * most)) & ~31);
+        }
+        if (r != last) consider(hw, kr, r);
+        last = r;
+      }
+      if (form == 1 && n1 > n_cu * 15 / 16) consider(hw, kr, longest);
+    }
+    dp.groups = (L.n_kv_heads + dp.hw - 1) / dp.hw;
+  }
   auto cut_of = [&](int n) {
     if (ctx->opt_splits > 0) return dec_cut(n, std::max(1, (n + ctx->opt_splits - 1) / ctx->opt_splits));
     return dec_cut(n, range);

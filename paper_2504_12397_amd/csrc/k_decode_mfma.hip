@@ -3,11 +3,10 @@
 //
 // Work item: one workgroup of eight waves = (rows, range of keys), listed by the host with the pool rows it reads, so that a
 // wave requests keys as soon as it has its item.  Wave w takes kv head g0 + w % HW and sub-range w / HW of the item's keys.
-// Long work (c4: 64 sequences of 16448 keys): HW = 8 kv heads side by side, whole 2 KB token rows of the token-major
-// cache at a time -- HBM delivers 6.2 TB/s to that pattern and 5.6 TB/s when the heads of a row are fetched by unrelated
-// workgroups -- and the waves never meet.  Short work (a handful of sequences, or short ones): HW = 2, four sub-ranges that join
-// in LDS, so that every wave's chain of 32-key steps (2.5 us each when memory is idle) is a quarter as long and a head still has
-// few partial records.  Normally an item is one row (one sequence's new token) over that sequence's own cache rows.  Sequences
+// HW = 8 kv heads side by side read whole 2 KB token rows of the token-major cache, and the waves never meet.  HW = 2 with four
+// sub-ranges that join in LDS: every wave's chain of 32-key steps is a quarter as long and a head still has few partial records
+// (one row of 16448 keys: 24 us, 27 with eight heads and 172 records).  The host cuts the keys and takes the form that is
+// quicker for the call.  Normally an item is one row (one sequence's new token) over that sequence's own cache rows.  Sequences
 // that name the same shared prefix (Section 2, "Cache reuse patterns": several adapters on one context) are packed 32 / G to an
 // item for the prefix part: their heads fill the MFMA columns a single sequence leaves empty (NC blocks of 16), and the prefix
 // is read from memory once for all of them.  A wave consumes 32 keys per step:
@@ -281,8 +280,8 @@ bool attn_decode_mfma_supported(const LayerDims &L) {
   return L.head_dim == 128 && G <= 16;
 }
 
-void decode_mfma_shape(int n_kv_heads, bool short_work, int *heads_per_wg, int *ranges_per_wg) {
-  const int most = short_work ? 2 : 8, hw = n_kv_heads < most ? n_kv_heads : most;
+void decode_mfma_shape(int n_kv_heads, bool two_heads, int *heads_per_wg, int *ranges_per_wg) {
+  const int most = two_heads ? 2 : 8, hw = n_kv_heads < most ? n_kv_heads : most;
   *heads_per_wg = hw;
   *ranges_per_wg = 8 / hw;
 }

@@ -154,7 +154,7 @@ struct DecodeArgs {
 };
 bool attn_decode_mfma_supported(const LayerDims &L);
 void launch_attn_decode_mfma(const DecodeArgs &a, int n_items, hipStream_t s);
-void decode_mfma_shape(int n_kv_heads, bool short_work, int *heads_per_wg, int *ranges_per_wg);
+void decode_mfma_shape(int n_kv_heads, bool two_heads, int *heads_per_wg, int *ranges_per_wg);
 
 bool gemm_mfma_supported(int M, int N, int K);
 int gemm_mfma_pick_splits(int M, int N, int K, int n_cu);

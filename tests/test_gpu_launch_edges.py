@@ -365,3 +365,16 @@ def test_rows_of_wide_weights_do_not_depend_on_the_call(ab, ctx, T):
     want, _ = _appended(ab, layer, shape, x)
     got, _ = _appended(ab, layer, shape, x[:T].contiguous())
     assert torch.equal(got, want[:T])
+
+
+# one range per row and eight heads side by side; heads that are no multiple of eight; a long row among more rows than two rounds of
+# workgroups; four heads, ranges of one round; one row with as many records as it may have
+@pytest.mark.parametrize("hq,hkv,P", [(16, 16, [64] * 130), (20, 10, [300] * 70 + [31, 0]), (8, 8, [5000] + [20] * 600), (8, 4, [900] * 33),
+                                      (16, 16, [63, 1, 200] * 50), (8, 8, [20000])])
+def test_decode_cuts_of_many_and_few_rows(ab, ctx, hq, hkv, P):
+    shape = wl.LayerShape(d=512, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rank=16, n_adapters=3)
+    n = len(P)
+    case = H.make_case(shape, P, [1] * n, [max(0, p - 10) for p in P], [b % 4 - 1 for b in range(n)], seed=2600 + n + hkv, prefix="random")
+    check_case(ab, ctx, case, decode=True)
+    if n < 200:
+        _both(ab, ctx, case)
