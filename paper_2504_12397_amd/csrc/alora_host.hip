@@ -52,7 +52,7 @@ __global__ void make_decode_items_kernel(const SeqMeta *seqs, int n_seqs, DecIte
   it.n_rows = part < c.parts ? 1 : 0;
   it.g = (int16_t)(((i / n_own) % n_groups) * heads_per_wg);
   it.part = (int16_t)part;
-  it.grows = part == c.parts - 1;
+  it.n_keys = n_keys;
   items[i] = it;
   if (i % (n_own * n_groups) == 0) { counts[2 * row] = c.parts; counts[2 * row + 1] = 0; }
 }
@@ -852,7 +852,7 @@ double decode_cut_us(std::vector<std::pair<int, int>> &cuts, int n_cu, double by
 }
 
 // `cap`: most records of either kind a row may have (every row's place in memory is that large).
-DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, int cap, bool on_device) {
+DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, int cap, int n_steps, bool on_device) {
   DecodePlan dp;
   const int G = L.n_q_heads / L.n_kv_heads;
   const int pack = std::max(1, 32 / G);
@@ -876,7 +876,7 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
       dp.cols_max = std::max(dp.cols_max, ++chunks.back().n * G);
     }
   }
-  auto own_keys = [&](const SeqMeta &m) { return m.P + 1 - m.prefix_len; };      // of the first step, the new key included
+  auto own_keys = [&](const SeqMeta &m) { return m.P + n_steps - m.prefix_len; };      // of the last step, the new key included
   int64_t keys = 0;
   int longest = 1;
   std::vector<int> lens;           // of the rows' own keys, then of the prefixes
@@ -980,7 +980,7 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
       for (int sp = 0; sp < cut.parts; ++sp) {
         DecItem it{};
         it.key_row0 = m.pool_off + m.prefix_len; it.row = m.row_start; it.kbeg = sp * cut.len; it.kend = std::min(own_keys(m), it.kbeg + cut.len);
-        it.n_rows = 1; it.g = (int16_t)(gb * dp.hw); it.part = (int16_t)sp; it.grows = sp == cut.parts - 1;
+        it.n_rows = 1; it.g = (int16_t)(gb * dp.hw); it.part = (int16_t)sp; it.n_keys = m.P + 1 - m.prefix_len;
         dp.items.push_back(it);
       }
   }
@@ -1225,7 +1225,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
     int cap = pl.T <= 16 ? 256 : std::max(1, std::min(64, 8192 / pl.T));
     if (!pl.any_prefix && static_bytes(1, (L.n_kv_heads + 7) / 8) <= SCRATCH_BYTES)
       while (cap > 1 && static_bytes(cap, (L.n_kv_heads + 1) / 2) > SCRATCH_BYTES) --cap;
-    dp = plan_decode_items(ctx, pl, L, cap, use_static);
+    dp = plan_decode_items(ctx, pl, L, cap, n_steps, use_static);
     n_splits = dp.n_own + dp.n_shared;
   }
   if (attn_mfma) {

@@ -67,7 +67,7 @@ __global__ __launch_bounds__(512, 2) void attn_decode_mfma_kernel(DecodeArgs a) 
   const int g = min(it.g + hw, a.n_kv_heads - 1);
   const int G = a.n_q_heads / a.n_kv_heads;
   const int n_cols = it.n_rows * G;                 // MFMA columns in use: column = row index * G + head
-  const int item_end = it.kend + (it.grows ? a.pos_shift : 0);
+  const int item_end = it.shared ? it.kend : min(it.kend, it.n_keys + a.pos_shift);
   // keys of this sub-range: contiguous, multiple of 32
   int per = (item_end - it.kbeg + KR - 1) / KR;
   per = (per + 31) & ~31;

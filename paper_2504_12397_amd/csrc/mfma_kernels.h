@@ -126,8 +126,9 @@ struct DecItem {
   int16_t n_rows;           // rows whose heads fill the MFMA columns (column = row index * G + head); 0: nothing to do
   int16_t g;                // first kv head of the workgroup
   int16_t part;             // which of the n_parts partial records of (row, head) it writes
-  int8_t shared;
-  int8_t grows;             // the range ends at the row's newest key: one more in every step of a multi-step decode
+  int16_t shared;
+  int32_t n_keys;           // own: the row's keys in the first step of a multi-step decode, one more in every other; ranges that lie
+                            // beyond them (the cut is that of the last step) are empty
 };
 // How the keys of one row (or prefix) are cut: `parts` ranges of `len` keys (whole steps of 32), the last one shorter.
 struct DecCut { int parts, len; };

@@ -378,3 +378,20 @@ def test_decode_cuts_of_many_and_few_rows(ab, ctx, hq, hkv, P):
     check_case(ab, ctx, case, decode=True)
     if n < 200:
         _both(ab, ctx, case)
+
+
+@pytest.mark.parametrize("P", [[5, 200], [0], [31, 700, 64, 1, 90]])
+def test_long_run_of_decode_steps(ab, ctx, P):
+    """300 steps: the keys are cut as the last step has them, so the first steps meet ranges that hold nothing yet."""
+    shape = wl.LayerShape(d=512, n_q_heads=8, n_kv_heads=4, head_dim=128, rank=16, n_adapters=3)
+    n, steps = len(P), 300
+    case = H.make_case(shape, P, [steps] * n, [p + 40 * b for b, p in enumerate(P)], [b % 4 - 1 for b in range(n)], seed=2700 + n, prefix="random")
+    x = torch.stack([torch.stack([case.x_new[b][t] for b in range(n)]) for t in range(steps)]).cuda().contiguous()
+    cache = H.gpu_cache(case)
+    before_k, before_v = cache.k.cpu(), cache.v.cpu()
+    out = ab.alora_decode_steps(ctx, H.gpu_layer(case, shape), cache, x, case.k, case.adapter)
+    torch.cuda.synchronize()
+    ref, rows = H.oracle_prefill(case)
+    H.check_cache_after(case, cache, before_k, before_v, rows, H.TOL["bf16"])
+    got = H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1)
+    assert H.rel_err(got, ref) <= H.TOL["bf16"]
