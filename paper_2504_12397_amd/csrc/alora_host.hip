@@ -1165,21 +1165,10 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   if (pl.T == 0) return ALORA_OK;
   if (use_static && pl.any_prefix)
     return fail(ctx, ALORA_EINVAL, "alora_decode_static does not take shared prefixes (prefix_len must be NULL or all zero)");
-  const size_t esz0 = layers[0].dtype == ALORA_BF16 ? 2 : 4;
-  if (ctx->device < 0) {
-    // a validation-only context still answers the size question of the static entry point
-    if (use_static) {
-      const int ns = std::max(1, std::min(128, pl.max_len / 256));      // upper bound on the key splits
-      const size_t need = layout_workspace(nullptr, L, pl.T, esz0, ns, 8, 0, false).bytes + (size_t)B * sizeof(SeqMeta) +
-                          (size_t)pl.T * L.n_kv_heads * ns * sizeof(DecItem) + (size_t)pl.T * (L.head_dim / 2) * sizeof(float2) + 1024;
-      if (need > SCRATCH_BYTES)
-        return fail(ctx, ALORA_ECAPACITY, "alora_decode_static: this call needs up to %zu bytes of scratch, the static buffer holds %zu",
-                    need, SCRATCH_BYTES);
-    }
-    return fail(ctx, ALORA_EHIP, "arguments are valid, but this is a validation-only context (device -1)");
-  }
-
-  HIP_TRY(ctx, hipSetDevice(ctx->device));
+  // (the size question of the static entry point is answered on a validation-only context too, by the same plan)
+  const auto validation_only = [&] { return fail(ctx, ALORA_EHIP, "arguments are valid, but this is a validation-only context (device -1)"); };
+  if (ctx->device < 0 && !use_static) return validation_only();
+  if (ctx->device >= 0) HIP_TRY(ctx, hipSetDevice(ctx->device));
   hipStream_t s = (hipStream_t)stream;
   const size_t esz = layers[0].dtype == ALORA_BF16 ? 2 : 4;
   const bool attn_mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && !decode &&
@@ -1252,6 +1241,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
     if (need > SCRATCH_BYTES)
       return fail(ctx, ALORA_ECAPACITY, "alora_decode_static: this call needs %zu bytes of scratch, the static buffer holds %zu",
                   need, SCRATCH_BYTES);
+    if (ctx->device < 0) return validation_only();
     if (!ctx->scratch_dev) return fail(ctx, ALORA_EHIP, "the static scratch array has no device address on this context");
     char *base = (char *)ctx->scratch_dev;
     SeqMeta *seqs_dev = (SeqMeta *)(base + ws_bytes);

@@ -265,3 +265,24 @@ def test_static_decode_rejects_what_its_scratch_cannot_hold(ab, vctx):
     assert go(5000)[0] == "ALORA_ECAPACITY"               # more than 4096 sequences
     assert go(0)[0] == "ALORA_EINVAL"
     assert go(2, dtype=9)[0] == "ALORA_EDTYPE"
+
+
+def test_static_decode_is_sized_by_the_plan_a_device_would_use(ab, vctx):
+    """A validation-only context and a real one give the same answer: one long sequence among 63 short ones fits, because the records of
+    a row are bounded by what the scratch holds (an estimate from the longest sequence alone refused it); so do long batches."""
+    p = C.POINTER(C.c_int32)
+
+    def go(P):
+        B, off = len(P), [0]
+        for n in P:
+            off.append(off[-1] + n + 1)
+        desc, cache, cu, k, a, _, keep, ln = make_args(ab, B=B, seq_offset=off[:-1], seq_capacity=[n + 1 for n in P], seq_len=list(P), pool_tokens=off[-1],
+                                                       k=[0] * B, a=[0] * B, d=4096, n_q_heads=32, n_kv_heads=8, head_dim=128)
+        st = ab._lib.alora_decode_static(vctx, C.byref(desc), C.byref(cache), FakeBuf.PTR, k.ctypes.data_as(p), a.ctypes.data_as(p), B,
+                                         FakeBuf.PTR, None)
+        return ab._lib.alora_status_string(st).decode()
+
+    assert go([16448] + [100 + b for b in range(63)]) == "ALORA_EHIP"
+    assert go([16448] * 64) == "ALORA_EHIP"
+    assert go([8191]) == "ALORA_EHIP"
+    assert go([3] * 600) == "ALORA_ECAPACITY"
