@@ -164,8 +164,9 @@ const char *alora_status_string(alora_status s);
  *                     kernel while they are short (up to 512 workgroups of it), in two kernels beyond that.
  *                     0: always in two (except with down matrices that are not 16-byte aligned), 2: always in one.
  *                     Calls without adapters only normalise.  The normalised rows are bit-identical either way.
- *   "lora_split"      0 (default): automatic.  1: always, 2: never give the low-rank term of the QKV
- *                     projection workgroups (and a partial sum) of its own.
+ *   "lora_split"      0 (default): automatic, where the reduction of the QKV projection is split over workgroups.
+ *                     1: always (the projection then leaves rotation and append to another kernel), 2: never
+ *                     give its low-rank term workgroups (and a partial sum) of its own.
  *   "rope_fuse"       1 (default): where the shape allows (few rows: head sizes that are multiples of 8; many: head
  *                     size 128) the QKV projection rotates q and k and appends k and v in its own epilogue.  0: a separate kernel does, from the fp32 projection.
  *                     Same bits either way.

@@ -479,7 +479,8 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
   // 128 x 128 block of four waves, which also adds segments.
   const bool fuse = mfma && ctx->opt_rope_fuse && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
   const int stream_rows = qkv_stream_rows(L.n_qkv, ctx->n_cu);
-  const bool stream = fuse && w.k_segments == 1 && ctx->opt_gemm_tile == 0 && pl.T <= stream_rows && qkv_stream_supported(ly->W_qkv, L.n_qkv, L.d, L.head_dim);
+  const bool lora_split = pl.any_adapter && w.lora_split;      // (in a kernel that takes partial sums)
+  const bool stream = fuse && !lora_split && w.k_segments == 1 && ctx->opt_gemm_tile == 0 && pl.T <= stream_rows && qkv_stream_supported(ly->W_qkv, L.n_qkv, L.d, L.head_dim);
   auto stage_of = [&](bool first) {
     StagedCall st{};
     if (w.stage_n16 > 0) {
@@ -522,7 +523,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       g.M = pl.T; g.N = L.n_qkv; g.K = L.d;
       g.k_splits = w.k_splits;
       g.k_segments = w.k_segments;
-      g.lora_split = (pl.any_adapter && w.lora_split) ? 1 : 0;
+      g.lora_split = lora_split ? 1 : 0;
       g.tile_hint = ctx->opt_gemm_tile;
       g.Cpart = w.Y;
       g.tlow = pl.any_adapter ? (const bf16 *)w.tlow : nullptr;
@@ -560,7 +561,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
   }
   if (!rope_fused) {
     ProfScope p(ctx, K_ROPE, s);
-    launch_rope_append<T>(w.Y, mfma ? w.k_splits + ((pl.any_adapter && w.lora_split) ? 1 : 0) : 1, L, w.rm, pl.T, w.rope, w.rope_by_row, q_scale, q_mode, w.Q,
+    launch_rope_append<T>(w.Y, mfma ? w.k_splits + (lora_split ? 1 : 0) : 1, L, w.rm, pl.T, w.rope, w.rope_by_row, q_scale, q_mode, w.Q,
                           (T *)cache->k, (T *)cache->v, s);
   }
   const bool mfma_attn = std::is_same<T, bf16>::value && (w.attn_mfma || w.decode_mfma);

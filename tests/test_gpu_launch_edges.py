@@ -395,3 +395,24 @@ def test_long_run_of_decode_steps(ab, ctx, P):
     H.check_cache_after(case, cache, before_k, before_v, rows, H.TOL["bf16"])
     got = H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1)
     assert H.rel_err(got, ref) <= H.TOL["bf16"]
+
+
+@pytest.mark.parametrize("T", [40, 300])
+def test_lora_split_gives_the_low_rank_term_a_partial_sum(ab, T):
+    """Always (1): few rows and many leave the fused kernels, which have no partial sums; rows without an adapter keep their bits."""
+    S = _split(T, 3)
+    case = H.make_case(SMALL_BF16, [30, 0, 64], S, [30, S[1], 64], [1, 0, -1], seed=2800 + T, prefix="random")
+    got = {}
+    for split in (0, 1, 2):
+        c = ab.Context(0)
+        try:
+            c.set_option("lora_split", split)
+            c.set_option("profile", 1)
+            _, cache = check_case(ab, c, case)
+            assert ("rope_append" in c.profile_read()) == (split == 1)
+            got[split] = [torch.cat([t[int(o) + p:int(o) + p + s] for o, p, s in zip(cache.seq_offset[1:], case.P[1:], S[1:])]).clone().view(torch.int16)
+                          for t in (cache.k, cache.v)]
+        finally:
+            c.close()
+    for split in (1, 2):
+        assert all(torch.equal(a, b) for a, b in zip(got[0], got[split]))
