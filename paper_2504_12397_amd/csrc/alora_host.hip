@@ -545,10 +545,10 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
         launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, GEMM_EPI_ROPE, ctx->n_cu, 1).tile, s);
         rope_fused = true;
       } else if (fuse && q_half && !w.rope_by_row && ctx->opt_gemm_tile == 0 && pl.T > 256 && gemm_mfma_rope_supported(g, L.head_dim)) {
-        launch_gemm_mfma(g, GEMM_EPI_ROPE, s);
+        launch_gemm_mfma(g, GEMM_EPI_ROPE, ctx->n_cu, s);
         rope_fused = true;
       } else {
-        launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
+        launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
       }
     } else if (qkv_small_plain_wanted(pl.T, L.n_qkv, ctx->n_cu)) {
       launch_qkv_small_plain<T>((const T *)w.xh, (const T *)ly->W_qkv, w.tlow, (const T *)ly->B_q, (const T *)ly->B_k, (const T *)ly->B_v,
@@ -630,7 +630,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     g.k_splits = splits;
     g.k_segments = splits;
     g.Cpart = w.Y;
-    launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
+    launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
     launch_tlow_select(w.Y, splits, T_rows, n_ad, parts, r, w.rm.adapter, w.scale_dev, (bf16 *)w.tlow, s);
   };
   auto set_lowrank = [&](GemmArgs &g, const void *B0, const void *B1, int parts, int width) {
@@ -685,11 +685,11 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
           ((int64_t)T_rows * N) % 4 == 0) {
         g.k_splits = segs;
         g.Cpart = w.Y;
-        launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
+        launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
         launch_splitk_reduce(w.Y, segs, (int64_t)T_rows * N, (const bf16 *)R, (bf16 *)C, s);
       } else {
         g.k_splits = 1;
-        launch_gemm_mfma(g, GEMM_EPI_BF16, s);
+        launch_gemm_mfma(g, GEMM_EPI_BF16, ctx->n_cu, s);
       }
     } else if (w.f0 != nullptr) {
       // bf16 on the plain kernels: base product, low-rank term and residual are added in fp32 and rounded once
@@ -728,7 +728,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
         g.k_splits = parts = splits;
         g.k_segments = splits;
         g.Cpart = w.Y;
-        launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
+        launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
       }
       if (parts > 1) {
         launch_splitk_reduce_norm(w.Y, parts, T_rows, L.d, (const bf16 *)x, (const bf16 *)ly->rms2_gain, ly->rms_eps,
@@ -737,7 +737,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
       } else if (parts == 0) {
         g.k_splits = 1;
         g.k_segments = splits;
-        launch_gemm_mfma(g, GEMM_EPI_BF16, s);
+        launch_gemm_mfma(g, GEMM_EPI_BF16, ctx->n_cu, s);
       }
     } else {
       dense(w.attn, ly->W_o, x, w.h1, L.d, L.n_q, ly->A_o, ly->B_o);
@@ -767,7 +767,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
       set_lowrank(g, ly->B_gate, ly->B_up, 2, ly->intermediate);
     }
     g.C = (bf16 *)w.gate; g.ldc = ly->intermediate;
-    launch_gemm_mfma(g, GEMM_EPI_SWIGLU, s);
+    launch_gemm_mfma(g, GEMM_EPI_SWIGLU, ctx->n_cu, s);
   } else if (w.f0 != nullptr) {
     // bf16 on the plain kernels: gate and up stay in fp32 until silu(gate) * up is rounded, once
     const bool lr = ly->A_gu != nullptr && w.any_adapter;
@@ -1597,7 +1597,7 @@ alora_status alora_lm_head(alora_ctx *ctx, alora_dtype dtype, int32_t d, int32_t
       g.k_splits = 1;
       g.k_segments = 1;
       g.Cpart = lg;
-      launch_gemm_mfma(g, GEMM_EPI_PARTIAL, s);
+      launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
     } else if (bf) {
       launch_lm_logits_plain<bf16>((const bf16 *)rows, (const bf16 *)W_vocab, B, vocab, d, lg, s);
     } else {

@@ -674,7 +674,7 @@ bool gemm_mfma_rope_supported(const GemmArgs &g, int head_dim) {
   return head_dim == 128 && g.k_splits == 1 && g.lora_split == 0 && g.n_q % 128 == 0 && g.n_kv % 128 == 0 && g.N == g.n_q + 2 * g.n_kv;
 }
 
-void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s) {
+void launch_gemm_mfma(GemmArgs g, int epi, int n_cu, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return;
   if (g.k_segments < 1) g.k_segments = 1;
   if (epi == GEMM_EPI_SWIGLU) {
@@ -696,7 +696,7 @@ void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s) {
     GemmArgs q = g;
     q.k_splits = 1;
     if (gemm_large_supported(q, epi)) {
-      launch_gemm_large(q, epi, gemm_large_plan(g.tile_hint, q, epi, 256, 1).tile, s);
+      launch_gemm_large(q, epi, gemm_large_plan(g.tile_hint, q, epi, n_cu, 1).tile, s);
       return;
     }
   }

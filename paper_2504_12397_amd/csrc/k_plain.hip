@@ -302,7 +302,10 @@ __global__ __launch_bounds__(256) void qkv_small_plain_kernel(const T *__restric
   else reinterpret_cast<float *>(Q)[(int64_t)row * L.n_q + hcol] = y;
 }
 
-// where the 64 x 64 tiles of the projection would leave most of the chip idle
+// Where the 64 x 64 tiles of the projection would leave half of the chip idle or more.  Projection and rotation in fp32, us, here / tiled:
+// 12 tiles (16 x 768 x 256) 8 / 49, 64 (64 x 4096 x 1024) 30 / 144, at the line 120 (640 x 768 x 256) 21 / 57 and 128 (64 x 8192 x 4096) 170 / 518.
+// Beyond it the distance shrinks with the reuse that 16 x 16 outputs lack: 192 tiles (192 x 4096 x 1024) 68 / 145, 384 (192 x 8192 x 4096)
+// 465 / 681, 480 (640 x 3072 x 4096) 571 / 690.
 bool qkv_small_plain_wanted(int T_rows, int n_qkv, int n_cu) { return ((T_rows + 63) / 64) * ((n_qkv + 63) / 64) * 2 <= n_cu; }
 
 template <typename T>

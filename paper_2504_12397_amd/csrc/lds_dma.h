@@ -11,7 +11,8 @@ template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_wai
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // 64 lanes x 16 bytes from rsrc[voff + soff] to LDS bytes lds .. lds + 1023, lane after lane; lanes whose offset is out of the
-// resource's range write zeros.  Inline assembly: the compiler would make every later LDS read wait for all of these.
+// resource's range write zeros.  Inline assembly: the compiler would make every later LDS read wait for all of these.  (m0 is a
+// reserved register, in which the compiler keeps no value from one instruction to another: it takes it for no clobber.)
 __device__ __forceinline__ void load_to_lds(i32x4 rsrc, int voff, int soff, int lds) {
   lds = __builtin_amdgcn_readfirstlane(lds);      // (no instruction where the compiler has it in a scalar register already)
   soff = __builtin_amdgcn_readfirstlane(soff);

@@ -161,13 +161,13 @@ bool gemm_mfma_supported(int M, int N, int K);
 int gemm_mfma_pick_splits(int M, int N, int K, int n_cu);
 int gemm_mfma_fixed_segments(int N, int K, int n_cu);      // reduction segments of a linear: from the weight shape alone
 bool gemm_mfma_split_segments(int M, int N, int n_cu);     // one workgroup per segment (few row tiles) or one for all
-void launch_gemm_mfma(GemmArgs g, int epi, hipStream_t s);
-// many rows: 256 x 256 or 128 x 256 tiles (rows = 256 / 128), one running sum over K; BF16, SWIGLU and ROPE epilogues
+void launch_gemm_mfma(GemmArgs g, int epi, int n_cu, hipStream_t s);
 // few rows: the whole QKV projection with rotation and append, A packed (PrepArgs::packed)
 constexpr int QKV_STREAM_ROWS = 256;      // most rows that the kernel takes, and those of a call with N columns
 int qkv_stream_rows(int N, int n_cu);
 bool qkv_stream_supported(const void *W, int N, int K, int head_dim);
 void launch_qkv_stream(const GemmArgs &g, int n_cu, hipStream_t s);
+// many rows: 256 x 256, 128 x 256 or 128 x 128 tiles, one running sum over K
 struct GemmLargePlan { int tile, splits; };      // tile: 2: 256 x 256, 1: 128 x 256, 0: 128 x 128; workgroups per output tile (> 1: PARTIAL)
 GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits);      // hint 2 / 3: tile 1 / 2
 bool gemm_large_supported(const GemmArgs &g, int epi);

@@ -290,8 +290,7 @@ def test_base_rows_do_not_depend_on_the_number_of_rows_at_the_8b_width(ab):
     """Proposition 1, strong form, with DEFAULT options at d = 4096 (N = 6144): the key and value rows of
     positions before the invocation point are bit-identical whether a 700-row straddling adapter call, a
     650-row or a 256-row base call, a 64-row prefill or a 64-sequence decode step computed them -- the
-    reduction axis of the projection is cut into the same segments, summed in the same order, in all of them
-    (one workgroup per segment for few rows, one workgroup walking through the segments for many)."""
+    projection is one running sum in ascending order in all of them (weights streamed past few rows, large tiles for many)."""
     shape = wl.SHAPE_8B_4AD
     c = ab.Context(0)
     try:
