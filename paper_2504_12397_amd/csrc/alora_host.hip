@@ -816,40 +816,42 @@ struct DecodePlan {
   int hw = 1, kr = 1, groups = 1, cols_max = 1;
 };
 
-// What one way of cutting the keys would take, in us: `cuts` are (32-key steps of a wave, workgroups of that length), `records` partial
-// records of `most` at most per (row, head) are merged.  Longest first on n_cu units, one workgroup each: either the longest chain of
+// What one way of cutting the keys would take, in us: `n_of` [s] workgroups run s steps of 32 keys per wave, `records` partial records, at
+// most `most` per (row, head), are merged.  Longest first on n_cu units, one workgroup each: either the longest chain of
 // steps counts (3.76 us a step) or memory, which delivers 24 bytes per ns and unit once 5/8 of the units ask, and waits with the tail
-// where fewer do.  4.8 us a round, 0.5 to join sub-ranges in LDS, 3 % for rows of which a workgroup reads but two heads.  Fitted to
+// where fewer do.  4.8 us a round, 0.5 to join sub-ranges in LDS, 3 % for rows of which a workgroup reads but two heads; 2.8 where
+// more than 16 records of more than 512 (row, head) pairs are merged by a wave each.  Fitted to
 // 5600 measured plans (1 to 500 rows of 64 to 40000 keys, 1 to 16 kv heads, shared prefixes; 6 % mean error).  Picked by it, attention
 // with its merge takes 1.8 % longer than with the best of those plans on average; the rule it replaces (at least 512 keys each in two
 // rounds, or sub-ranges in one) 5.7 %, and up to 1.8 x: 256 rows of 64 keys 40 -> 28 us, 64 rows of 4000 214 -> 188, 33 of 4000 150 -> 105.
-double decode_cut_us(std::vector<std::pair<int, int>> &cuts, int n_cu, double bytes, bool join, bool two_heads, double records, int most) {
-  std::sort(cuts.begin(), cuts.end(), [](const std::pair<int, int> &x, const std::pair<int, int> &y) { return x.first > y.first; });
+double decode_cut_us(const std::vector<int> &n_of, int n_cu, double bytes, bool join, bool two_heads, double records, int64_t pairs, int most) {
   int64_t steps = 0, n = 0;
-  for (const auto &c : cuts) { steps += (int64_t)c.first * c.second; n += c.second; }
+  int first = 0, last = 0;                           // most and fewest steps
+  for (int s = (int)n_of.size() - 1; s > 0; --s)
+    if (n_of[s]) { steps += (int64_t)s * n_of[s]; n += n_of[s]; first = std::max(first, s); last = s; }
   const int ks = n_cu * 5 / 8;                       // units that keep memory busy
   const int rounds = (int)((n + n_cu - 1) / n_cu);
-  double longest = cuts[0].first, busy = 0;          // steps of the unit that ends last, and of the ks that do
+  double longest = first, busy = 0;                  // steps of the unit that ends last, and of the ks that do
   if (n <= n_cu) {
-    int left = ks;
-    for (const auto &c : cuts) { const int k = std::min(left, c.second); busy += (double)k * c.first; left -= k; }
+    for (int s = first, left = ks; s > 0 && left > 0; --s) { const int k = std::min(left, n_of[s]); busy += (double)k * s; left -= k; }
   } else if (n <= 2 * n_cu) {
     std::vector<int> d;
     d.reserve((size_t)n);
-    for (const auto &c : cuts) d.insert(d.end(), (size_t)c.second, c.first);
+    for (int s = first; s > 0; --s) d.insert(d.end(), (size_t)n_of[s], s);
     for (int64_t i = n_cu; i < n; ++i) d[2 * n_cu - 1 - i] += d[i];
     d.resize(n_cu);
     std::nth_element(d.begin(), d.begin() + ks, d.end(), [](int x, int y) { return x > y; });
     for (int i = 0; i < ks; ++i) { busy += d[i]; longest = std::max(longest, (double)d[i]); }
   } else {
     const double mean = (double)steps / n_cu;
-    longest = std::max(longest, mean + 0.5 * cuts.back().first);
+    longest = std::max(longest, mean + 0.5 * last);
     busy = ks * mean;
   }
   // (a round that fills the chip to the last unit: a hundredth more, 64 rows of 4000 keys 181 us in 192 workgroups and 196 in 256)
   const double full = !two_heads && n > n_cu * 15 / 16 && n <= n_cu ? 1.01 : 1.0;
   const double memory = bytes / (24e3 * n_cu) * (1.0 + (ks * longest - busy) / (double)steps) * full / (two_heads ? 0.97 : 1.0);
-  return std::max(3.76 * longest, memory) + 4.8 * rounds + (join ? 0.5 : 0.0) + 200e-6 * records + (most > 1 ? 0.7 : 0.0) + 0.017 * most;
+  return std::max(3.76 * longest, memory) + 4.8 * rounds + (join ? 0.5 : 0.0) + 200e-6 * records + (most > 1 ? 0.7 : 0.0) +
+         (most > 16 && pairs > 512 ? 2.8 : 0.0) + 0.017 * most;
 }
 
 // `cap`: most records of either kind a row may have (every row's place in memory is that large).
@@ -880,13 +882,21 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
   auto own_keys = [&](const SeqMeta &m) { return m.P + n_steps - m.prefix_len; };      // of the last step, the new key included
   int64_t keys = 0;
   int longest = 1;
-  std::vector<int> lens;           // of the rows' own keys, then of the prefixes
-  lens.reserve((size_t)pl.B + chunks.size());
+  // the rows' own keys, then the prefixes; equal neighbours are one entry
+  struct Run { int len, n, rows; bool own; };      // (rows: that get a record of every range)
+  std::vector<Run> runs;
+  runs.reserve((size_t)pl.B + chunks.size());
+  int n_lens = 0;
+  auto put_len = [&](int len, int rows, bool own) {
+    if (!runs.empty() && runs.back().len == len && runs.back().own == own) { ++runs.back().n; runs.back().rows += rows; }
+    else runs.push_back(Run{len, 1, rows, own});
+    ++n_lens;
+    keys += len;
+    longest = std::max(longest, len);
+  };
   for (const SeqMeta &m : pl.seqs)
-    if (m.n_new > 0) lens.push_back(own_keys(m));
-  const size_t n_rows = lens.size();
-  for (const Chunk &c : chunks) lens.push_back(c.len);
-  for (int n : lens) { keys += n; longest = std::max(longest, n); }
+    if (m.n_new > 0) put_len(own_keys(m), 1, true);
+  for (const Chunk &c : chunks) put_len(c.len, c.n, false);
   // A workgroup is eight kv heads side by side, each over the whole range, or (a long row among few, heads that are no multiple of
   // eight) two kv heads x four sub-ranges that join in LDS; the ranges are as long as gives nearly one round of workgroups, one,
   // two, or one workgroup per row and group of heads.  Whichever takes the least time (decode_cut_us).
@@ -897,34 +907,29 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
   if (ctx->opt_splits == 0) {
     const int n_cu = ctx->n_cu;
     double best = 1e30;
-    std::vector<std::pair<int, int>> cuts;
+    const int wide = dp.hw;
+    std::vector<int> n_of;
     auto consider = [&](int hw, int kr, int r) {
       const int groups = (L.n_kv_heads + hw - 1) / hw;
-      cuts.clear();
-      auto put = [&](int len, int n) {
-        const int st = (((len + kr - 1) / kr) + 31) >> 5;
-        if (!cuts.empty() && cuts.back().first == st) cuts.back().second += n;
-        else cuts.emplace_back(st, n);
-      };
+      auto steps_of = [&](int len) { return (((len + kr - 1) / kr) + 31) >> 5; };
+      n_of.assign((size_t)steps_of(((r + 31) & ~31)) + 1, 0);      // (dec_cut's ranges are whole steps of r or less)
       double records = 0;
       int own = 0, shared = 0;
-      DecCut c{1, 0};
-      for (size_t i = 0; i < lens.size(); ++i) {
-        if (i == 0 || i == n_rows || lens[i] != lens[i - 1]) c = dec_cut(lens[i], r);
-        if (c.parts > 1) put(c.len, (c.parts - 1) * groups);
-        put(lens[i] - (c.parts - 1) * c.len, groups);
-        (i < n_rows ? own : shared) = std::max(i < n_rows ? own : shared, c.parts);
-        records += (double)c.parts * (i < n_rows ? 1 : chunks[i - n_rows].n);
+      for (const Run &q : runs) {
+        const DecCut c = dec_cut(q.len, r);
+        n_of[steps_of(c.len)] += (c.parts - 1) * groups * q.n;
+        n_of[steps_of(q.len - (c.parts - 1) * c.len)] += groups * q.n;
+        (q.own ? own : shared) = std::max(q.own ? own : shared, c.parts);
+        records += (double)c.parts * q.rows;
       }
-      const double us = decode_cut_us(cuts, n_cu, 512.0 * keys * L.n_kv_heads, kr > 1, hw < dp.hw, records * L.n_q_heads, own + shared);
+      const double us = decode_cut_us(n_of, n_cu, 512.0 * keys * L.n_kv_heads, kr > 1, hw < wide, records * L.n_q_heads, (int64_t)pl.T * L.n_q_heads, own + shared);
       if (us < best) { best = us; dp.hw = hw; dp.kr = kr; range = r; }
     };
-    const int wide = dp.hw;
     for (int form = cap > 1 && wide > 2 ? 0 : 1; form < 2; ++form) {
       int hw, kr, last = 0;
       decode_mfma_shape(L.n_kv_heads, form == 0, &hw, &kr);
       const int64_t groups = (L.n_kv_heads + hw - 1) / hw;
-      const int64_t n1 = groups * (int64_t)lens.size();      // workgroups, one range each
+      const int64_t n1 = groups * (int64_t)n_lens;      // workgroups, one range each
       // (the last one: where rows alone are more than that, a long row among them still wants to be cut)
       for (int64_t most : {(int64_t)(form == 0 ? 0 : n_cu * 15 / 16), (int64_t)n_cu, (int64_t)2 * n_cu, n1 > n_cu ? n1 + n1 / 8 : 0}) {
         if (most < n1 || (form == 0 && n1 > (L.n_kv_heads % 8 ? 4 : 2) * n_cu)) continue;
@@ -932,17 +937,17 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
         int r = (int)std::max<int64_t>({(int64_t)32 * kr, keys * groups / most & ~31, (int64_t)least});
         for (int i = 0; i < 24 && r < longest; ++i) {
           int64_t n = 0;
-          if (n1 > 64) {      // (a number of workgroups that is a little too large now and then)
+          if (runs.size() > 16) {      // (a number of workgroups that is a little too large now and then)
             const float inv = 1.0f / (float)r;
             int k = 0;
-            for (int len : lens) k += (int)((float)(len - 1) * inv) + 1;
+            for (const Run &q : runs) k += ((int)((float)(q.len - 1) * inv) + 1) * q.n;
             n = k * groups;
           } else {
-            for (int len : lens) n += dec_cut(len, r).parts;
+            for (const Run &q : runs) n += dec_cut(q.len, r).parts * q.n;
             n *= groups;
           }
           if (n <= most) break;
-          r += std::max(32, (int)(r * (n - most) / (2 * most)) & ~31);
+          r += std::max(32, (int)(r * (n - most) / most) & ~31);
         }
         if (r != last) consider(hw, kr, r);
         last = r;
@@ -986,7 +991,8 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
       }
   }
   // longest first, so that the short ones even out the end
-  std::stable_sort(dp.items.begin(), dp.items.end(), [](const DecItem &x, const DecItem &y) { return x.kend - x.kbeg > y.kend - y.kbeg; });
+  auto longer = [](const DecItem &x, const DecItem &y) { return x.kend - x.kbeg > y.kend - y.kbeg; };
+  if (!std::is_sorted(dp.items.begin(), dp.items.end(), longer)) std::stable_sort(dp.items.begin(), dp.items.end(), longer);
   return dp;
 }
 
