@@ -315,6 +315,7 @@ def test_few_rows_of_other_shapes(ab, ctx, d, hq, hkv, h, T):
     if T > 1:
         case = H.make_case(shape, [40] * T, [1] * T, [20] * T, [b % 5 - 1 for b in range(T)], seed=2210 + T + d, prefix="random")
         check_case(ab, ctx, case, decode=True)
+        _both(ab, ctx, case)
 
 
 @pytest.mark.parametrize("d,hq,hkv,h", OTHER_SHAPES)
@@ -352,6 +353,34 @@ def test_unaligned_weights_keep_the_segments_of_their_shape(ab):
     assert torch.equal(got, want)
     one, _ = _appended(ab, layer, shape, x, [("gemm_splits", 1)])
     assert not torch.equal(one, want)
+
+
+def test_static_decode_with_segments_that_do_not_fit_the_scratch(ab, ctx):
+    """200 rows of unaligned 4096 x 6144 weights: four partial sums of the projection alone are 20 MB of the 32; both entry points add the
+    segments inside the workgroups, with the bits that one row gets from partial sums."""
+    shape = wl.SHAPE_8B_4AD
+    rng = wl.Rng(2450, "cuda")
+    t = wl.make_layer(shape, rng)
+    flat = torch.empty(t["W_qkv"].numel() + 4, dtype=torch.bfloat16, device="cuda")
+    flat[4:] = t["W_qkv"].reshape(-1)
+    t["W_qkv"] = flat[4:].view(t["W_qkv"].shape)
+    layer = ab.Layer(t, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.rms_eps, shape.rope_theta)
+    n = 200
+    x = wl.make_hidden(rng, "x", n, shape)
+    got = []
+    for call in (ab.alora_decode, ab.alora_decode_static):
+        cache = ab.KVCache([6] * n, shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda", fill=0.5)
+        cache.seq_len[:] = 5
+        out = torch.empty((n, shape.n_q), dtype=shape.torch_dtype, device="cuda")
+        call(ctx, layer, cache, x, [0] * n, [b % 5 - 1 for b in range(n)], out)
+        torch.cuda.synchronize()
+        got.append([v.view(torch.int16) for v in (out, cache.k, cache.v)])
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    cache = ab.KVCache([6], shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda", fill=0.5)
+    cache.seq_len[:] = 5
+    ab.alora_decode(ctx, layer, cache, x[:1].contiguous(), [0], [-1])
+    torch.cuda.synchronize()
+    assert torch.equal(cache.k[5].view(torch.int16), got[0][1][5]) and torch.equal(cache.v[5].view(torch.int16), got[0][2][5])
 
 
 @pytest.mark.parametrize("T", [128, 129, 256])
