@@ -235,8 +235,8 @@ alora_status alora_decode(alora_ctx *ctx, const alora_layer_desc *layer, alora_k
  * alora_decode, but the call allocates nothing, frees nothing, synchronises nothing and copies nothing from host
  * memory: its workspace, the per-sequence records (passed to the device as kernel arguments), the decode work
  * list and the rotary lines of the new rows live in one static device array of 32 MiB (33554432 bytes) that every
- * GPU the library runs on holds until the process ends.  A call that needs more (roughly: 5 fp32 copies of the
- * [B, N_q + 2 N_kv] projection plus B * n_q_heads * key-splits partial attention records; 64 sequences of the
+ * GPU the library runs on holds until the process ends.  A call that needs more (roughly: 2 fp32 copies of the
+ * [B, N_q + 2 N_kv] projection, 5 where its reduction is cut and that still fits, plus B * n_q_heads * key-splits partial attention records; 64 sequences of the
  * 8B-class shape over 16k-token caches take 14 MiB) is rejected with ALORA_ECAPACITY before anything is launched,
  * as is B > 4096.  Shared prefixes are not taken (ALORA_EINVAL); the "profile" option is ignored.  All calls on
  * one GPU -- from any context, stream or thread -- share that GPU's array and it keeps the last call's contents:

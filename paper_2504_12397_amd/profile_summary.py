@@ -2,8 +2,8 @@
 
     python -m paper_2504_12397_amd.profile_summary --in <directory with the rocprofv3 output> --out profiles
 
-Expects under --in, per workload w in {c2, c3, c4, c5, r3p, r3pp} (any subset; r3p and r3pp are bench.py's r3p workload with
---variant shared and --variant private):
+Expects under --in, per workload w in {c2, c3, c4, c5, c5f, r3p, r3pp} (any subset; r3p and r3pp are bench.py's r3p workload with
+--variant shared and --variant private, c5f its c5 with the recompute of the whole context, two layers):
     kt_<w>/<w>_kernel_stats.csv, kt_<w>.json          rocprofv3 --kernel-trace --stats, and bench.py's JSON line
     pmc_FETCH_<w>/, pmc_WRITE_<w>/                    --pmc FETCH_SIZE / WRITE_SIZE  (<w>_counter_collection.csv)
     pmc_A_<w>/, pmc_B_<w>/                            the two sets of SQ counters listed in COUNTER_SETS
@@ -32,12 +32,14 @@ TITLES = {
     "c4": ("c4_decode_step", "c4: decode step, 64 sequences x 16448 cached tokens, one new token each", ""),
     "c5": ("c5_stack_first_token", "c5: 32-layer 8B-class stack, 32768 cached base tokens + 128 adapted suffix tokens, rank 64",
            " --only --no-full-lora"),
+    "c5f": ("c5_full_recompute", "c5 with the context recomputed (32896 rows from an empty cache, k = 0: the large tiles) after the 128-row steps, two layers",
+            " --only --layers 2"),
     "r3p": ("r3p_shared_context_prefill", "r3p: prefill of 32 invocation sequences of 16 tokens, 4 contexts of 16384 cached base "
             "tokens x 8 adapter calls, each context's rows stored once and walked once per run of sequences", " --variant shared"),
     "r3pp": ("r3p_private_copies_prefill", "r3p with private copies: the same 32 invocation sequences, every sequence holding "
              "(and walking) its own copy of the 16384 context rows", " --variant private"),
 }
-BENCH_WORKLOAD = {"r3pp": "r3p"}         # summary key -> bench.py --workload, where they differ
+BENCH_WORKLOAD = {"r3pp": "r3p", "c5f": "c5"}         # summary key -> bench.py --workload, where they differ
 # kernel symbol -> the kernel family bench.py reports (only where one symbol is one family in that workload)
 FAMILY = [("attn_prefill_mfma_kernel", "attn_prefill"), ("attn_decode_mfma_kernel", "attn_decode"),
           ("prep_few_kernel", "prep_rows"), ("qkv_stream_kernel", "qkv_gemm"), ("rope_append_kernel", "rope_append"), ("attn_merge", "attn_merge")]
@@ -54,6 +56,8 @@ def short(name: str) -> str:
 
 
 def family_of(workload: str, kernel: str):
+    if workload == "c5f":      # bench.py's events are those of the 128-row steps
+        return None
     for pat, fam in FAMILY:
         if pat in kernel:
             return fam
@@ -175,6 +179,9 @@ def main():
                 "SQ_LDS_IDX_ACTIVE / (cycles x 256 CUs); bank conflict = SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE; waiting = SQ_WAIT_INST_ANY / SQ_WAVE_CYCLES."]
         if w == "c5":
             out += ["The counter runs use 4 layers (`--layers 4`); per-launch figures do not depend on the layer count."]
+        if w == "c5f":
+            out += ["The attention kernel's average is over the 128-row steps and the recompute, its counters over the later half of its "
+                    "dispatches: its clock column means nothing here."]
         open(os.path.join(args.out, fname + ".md"), "w").write("\n".join(out) + "\n")
         print("wrote", fname)
     if traffic:
