@@ -1210,8 +1210,8 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
            (size_t)pl.T * (L.head_dim / 2) * sizeof(float2);
   };
   // A decode step whose segment sums alone keep it out of the static scratch array adds them inside the workgroups (both entry points
-  // alike: they give the same bits).
-  if (decode && k_splits > 1 && static_bytes(1, (L.n_kv_heads + 7) / 8) > SCRATCH_BYTES) k_splits = 1;
+  // alike: they give the same bits).  Not where the option asked for the segments: such a call is refused.
+  if (decode && ctx->opt_gemm_splits == 0 && k_splits > 1 && static_bytes(1, (L.n_kv_heads + 7) / 8) > SCRATCH_BYTES) k_splits = 1;
   // work lists of the MFMA attention kernels (the number of partial records per (row, head) comes out of them)
   DecodePlan dp;
   PrefillPlan pp;

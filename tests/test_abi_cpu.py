@@ -272,12 +272,13 @@ def test_static_decode_is_sized_by_the_plan_a_device_would_use(ab, vctx):
     a row are bounded by what the scratch holds (an estimate from the longest sequence alone refused it); so do long batches."""
     p = C.POINTER(C.c_int32)
 
-    def go(P):
+    def go(P, off_by=0):
         B, off = len(P), [0]
         for n in P:
             off.append(off[-1] + n + 1)
         desc, cache, cu, k, a, _, keep, ln = make_args(ab, B=B, seq_offset=off[:-1], seq_capacity=[n + 1 for n in P], seq_len=list(P), pool_tokens=off[-1],
-                                                       k=[0] * B, a=[0] * B, d=4096, n_q_heads=32, n_kv_heads=8, head_dim=128)
+                                                       k=[0] * B, a=[0] * B, d=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, rank=8)
+        desc.W_qkv = FakeBuf.PTR + off_by
         st = ab._lib.alora_decode_static(vctx, C.byref(desc), C.byref(cache), FakeBuf.PTR, k.ctypes.data_as(p), a.ctypes.data_as(p), B,
                                          FakeBuf.PTR, None)
         return ab._lib.alora_status_string(st).decode()
@@ -286,3 +287,10 @@ def test_static_decode_is_sized_by_the_plan_a_device_would_use(ab, vctx):
     assert go([16448] * 64) == "ALORA_EHIP"
     assert go([8191]) == "ALORA_EHIP"
     assert go([3] * 600) == "ALORA_ECAPACITY"
+    # unaligned weights are reduced in segments, but not at the price of the call; segments that the option asked for are
+    assert FakeBuf.PTR % 16 == 0 and go([3] * 240, 8) == "ALORA_EHIP"
+    assert ab._lib.alora_set_option(vctx, b"gemm_splits", 4) == 0
+    try:
+        assert go([3] * 240) == "ALORA_ECAPACITY" and go([3] * 20) == "ALORA_EHIP"
+    finally:
+        ab._lib.alora_set_option(vctx, b"gemm_splits", 0)

@@ -356,7 +356,7 @@ def test_unaligned_weights_keep_the_segments_of_their_shape(ab):
 
 
 def test_static_decode_with_segments_that_do_not_fit_the_scratch(ab, ctx):
-    """200 rows of unaligned 4096 x 6144 weights: four partial sums of the projection alone are 20 MB of the 32; both entry points add the
+    """240 rows of unaligned 4096 x 6144 weights: four partial sums of the projection alone are 24 MB of the 32; both entry points add the
     segments inside the workgroups, with the bits that one row gets from partial sums."""
     shape = wl.SHAPE_8B_4AD
     rng = wl.Rng(2450, "cuda")
@@ -365,7 +365,7 @@ def test_static_decode_with_segments_that_do_not_fit_the_scratch(ab, ctx):
     flat[4:] = t["W_qkv"].reshape(-1)
     t["W_qkv"] = flat[4:].view(t["W_qkv"].shape)
     layer = ab.Layer(t, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.rms_eps, shape.rope_theta)
-    n = 200
+    n = 240
     x = wl.make_hidden(rng, "x", n, shape)
     got = []
     for call in (ab.alora_decode, ab.alora_decode_static):
