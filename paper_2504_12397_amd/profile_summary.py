@@ -40,6 +40,7 @@ TITLES = {
              "(and walking) its own copy of the 16384 context rows", " --variant private"),
 }
 BENCH_WORKLOAD = {"r3pp": "r3p", "c5f": "c5"}         # summary key -> bench.py --workload, where they differ
+KT_EXTRA = {"c5f": " --steps 3 --warmup 1"}      # of the kernel trace alone
 # kernel symbol -> the kernel family bench.py reports (only where one symbol is one family in that workload)
 FAMILY = [("attn_prefill_mfma_kernel", "attn_prefill"), ("attn_decode_mfma_kernel", "attn_decode"),
           ("prep_few_kernel", "prep_rows"), ("qkv_stream_kernel", "qkv_gemm"), ("rope_append_kernel", "rope_append"), ("attn_merge", "attn_merge")]
@@ -122,7 +123,7 @@ def main():
         bw = BENCH_WORKLOAD.get(w, w)
         out = [f"# rocprofv3 summary, workload {title}", "",
                "Commands (from /tmp with TMPDIR=/tmp on one MI355X; paths relative to the repository root; every --pmc pass is a run of its own):", "",
-               f"    rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/prof/kt_{w} -o {w} -- python3 bench.py --workload {bw} --no-cpu-baseline{extra}",
+               f"    rocprofv3 --kernel-trace --stats --output-format csv -d gpurun_out/prof/kt_{w} -o {w} -- python3 bench.py --workload {bw} --no-cpu-baseline{extra}{KT_EXTRA.get(w, '')}",
                f"    rocprofv3 --pmc FETCH_SIZE --output-format csv -d gpurun_out/prof/pmc_FETCH_{w} -o {w} -- python3 bench.py --workload {bw} --no-cpu-baseline --steps 3 --warmup 1{pmc_extra}",
                "    (the same with WRITE_SIZE, and with the two SQ counter sets below)",
                f"    set A: {COUNTER_SETS['A']}",
