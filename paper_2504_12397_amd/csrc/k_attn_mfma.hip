@@ -12,10 +12,9 @@
 // Work item: one workgroup = (q-tile of 256/G tokens of one sequence, kv head, key split).
 // The G query heads of the kv group are packed next to the tokens into 256 "packed rows"
 // (packed row = token * G + head), 32 per wave and eight waves per workgroup, so every K/V tile
-// fetched from HBM serves all heads of the group.  Two waves share a SIMD, so the softmax of one
-// (exponentials and rescaling on the vector ALU) can in principle run under the matrix work of the
-// other; measured, the tile time is close to the sum of its parts (MFMAs 1.59 us, softmax 0.35,
-// tile loads 0.27, LDS reads 0.17, LDS stores 0.14 of 2.37 us per 256 x 64 tile).
+// fetched from HBM serves all heads of the group.  Two kernels: attn_prefill_pipe_kernel (folded softmax, eight waves: what calls
+// take by default) weaves the steps of consecutive key blocks together; attn_prefill_mfma_kernel does them one after the other and
+// serves the options attn_fold = 0 and attn_waves = 4.
 //
 // Per 64-key tile, each wave computes S^T = K Q^T (keys are MFMA rows, packed query rows are
 // MFMA columns).  In that orientation a lane owns one query row (column l%32) in every
@@ -86,6 +85,13 @@ __device__ __forceinline__ float sum_f16x2(uint32_t pair, float acc) {
   return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, pair), __builtin_bit_cast(half2_t, 0x3c003c00u), acc, false);
 }
 
+// the same on one half of the pair at a time.  v_dot2 shares the matrix pipe: one of them between matrix instructions keeps that pipe for 16
+// cycles more (32 -> 49 per v_mfma_f32_32x32x16 with one dot2, 33 with six of these); v_fma_mix_f32 runs beside them.
+template <int HI> __device__ __forceinline__ void add_f16(uint32_t pair, float &acc) {
+  if (HI) asm volatile("v_fma_mix_f32 %0, %1, 1.0, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(acc) : "v"(pair));
+  else asm volatile("v_fma_mix_f32 %0, %1, 1.0, %0 op_sel_hi:[1,0,0]" : "+v"(acc) : "v"(pair));
+}
+
 // Waits for every outstanding global load (s_waitcnt vmcnt(0); the other counters left alone).
 // Used once before the key loops: the query fragments are loaded before a conditional prologue,
 // and unless their loads are known to be complete on every path into the loop the compiler guards
@@ -96,6 +102,76 @@ __device__ __forceinline__ void wait_all_global_loads() { __builtin_amdgcn_s_wai
 constexpr int ATT_BN = 64;        // keys per tile
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
+
+// ---- write the partial (or final) result of a row: the lane's half of its columns -------------------------------------
+__device__ __forceinline__ void write_result(const AttnArgs &a, int part, int row0, int ntok, int tok, int head, int kh, float m_ref,
+                                             float l_run, const f32x16 (&o)[4]) {
+  constexpr int H = 128;
+  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);      // the two halves of the wave hold disjoint keys
+  if (tok >= ntok) return;
+  const int64_t row = row0 + tok;
+  if (a.out != nullptr) {
+    const float inv = 1.0f / l_tot;
+    bf16 *op = a.out + row * a.n_q + head * H;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const int col = cb * 32 + 8 * v4 + 4 * kh;
+        uint2 w;
+        w.x = pack_bf16x2(o[cb][4 * v4] * inv, o[cb][4 * v4 + 1] * inv);
+        w.y = pack_bf16x2(o[cb][4 * v4 + 2] * inv, o[cb][4 * v4 + 3] * inv);
+        *reinterpret_cast<uint2 *>(op + col) = w;
+      }
+  } else if (a.compact) {
+    // compact partial record (ATTN_REC16 bytes): the unnormalised accumulators of the row divided by their
+    // largest magnitude, as 128 fp16 values (relative precision 2^-11, finer than the bf16 the merged result
+    // is rounded to; no overflow whatever the values), then that magnitude, the reference and the row sum.
+    // Half the bytes of the fp32 record -- and these records are most of what a short call writes and reads.
+    float amax = 0.f;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) amax = fmaxf(amax, fabsf(o[cb][v]));
+    amax = max_with_other_half(amax);
+    const float rs = amax > 0.f ? 1.0f / amax : 0.f;
+    char *rec = reinterpret_cast<char *>(a.partials) +
+                ((row * a.n_q_heads + head) * a.n_parts + part) * (int64_t)ATTN_REC16;
+    typedef __attribute__((__vector_size__(4 * sizeof(_Float16)))) _Float16 half4_t;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const int col = cb * 32 + 8 * v4 + 4 * kh;
+        half4_t hv;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) hv[i] = (_Float16)(o[cb][4 * v4 + i] * rs);
+        *reinterpret_cast<half4_t *>(rec + col * 2) = hv;
+      }
+    if (kh == 0) {
+      float *tail = reinterpret_cast<float *>(rec + 2 * H);
+      tail[0] = (l_tot == 0.f || m_ref == -INFINITY) ? -INFINITY : m_ref * LN2;
+      tail[1] = l_tot;
+      tail[2] = amax;
+    }
+  } else {
+    float *pp = a.partials + ((row * a.n_q_heads + head) * a.n_parts + part) * (H + 2);
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const int col = cb * 32 + 8 * v4 + 4 * kh;
+        // (H + 2) floats per record keeps 8-byte, not 16-byte, alignment
+        *reinterpret_cast<float2 *>(pp + col) = make_float2(o[cb][4 * v4], o[cb][4 * v4 + 1]);
+        *reinterpret_cast<float2 *>(pp + col + 2) = make_float2(o[cb][4 * v4 + 2], o[cb][4 * v4 + 3]);
+      }
+    if (kh == 0) {
+      // natural-log domain; a row that saw no key keeps -inf so that the merge gives it no weight
+      pp[H] = (l_tot == 0.f || m_ref == -INFINITY) ? -INFINITY : m_ref * LN2;
+      pp[H + 1] = l_tot;
+    }
+  }
+}
 
 // PFX: tile loads with full 64-bit address arithmetic (items whose keys lie beyond 2 GB from their first row)
 // instead of buffer loads with 32-bit offsets
@@ -114,7 +190,6 @@ template <int G, int NW, bool PFX, bool FOLD>      // NW waves per workgroup (8 
 __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) {
   constexpr int H = 128;
   constexpr int NT = 64 * NW;
-  constexpr int NB = 1;             // 32-row query blocks per wave
   __shared__ u32x4 Ks[2][ATT_BN * 16];
   __shared__ u32x4 Vs[2][H * 8];
 
@@ -137,27 +212,20 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) 
   const int first_pos = wk.pos0;                     // smallest query position in the tile
 
   // ---- this wave's queries as B operands: 2 column blocks x 8 k-steps ---------------------
-  u32x4 qf[NB][8];
-  int pos[NB], tok[NB], head[NB];
+  u32x4 qf[8];
+  const int pr = wave * 32 + l32, tok = pr / G, head = g * G + pr % G;
+  const int pos = tok < ntok ? first_pos + tok : -1;       // -1: padding row, sees nothing
+  {
+    const _Float16 *qp = a.Q + (int64_t)(row0 + min(tok, ntok - 1)) * a.n_q + head * H + kh * 8;
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const int pr = wave * (32 * NB) + nb * 32 + l32;
-    tok[nb] = pr / G;
-    head[nb] = g * G + pr % G;
-    const int tc = min(tok[nb], ntok - 1);
-    pos[nb] = tok[nb] < ntok ? first_pos + tok[nb] : -1;       // -1: padding row, sees nothing
-    const _Float16 *qp = a.Q + (int64_t)(row0 + tc) * a.n_q + head[nb] * H + kh * 8;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[nb][ks] = *reinterpret_cast<const u32x4 *>(qp + ks * 16);
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const u32x4 *>(qp + ks * 16);
   }
 
-  f32x16 o[4][NB];
+  f32x16 o[4];
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) o[cb][nb][v] = 0.f;
+    for (int v = 0; v < 16; ++v) o[cb][v] = 0.f;
   const float c_scale = a.sm_scale * LOG2E;
   // softmax state of the lane's query row: the reference exponent m_ref (exp2 domain), the sum l_run of the
   // probabilities of the keys this half of the wave holds (for FOLD the score accumulators start at -m_ref)
@@ -275,7 +343,7 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) 
       for (int v = 0; v < 16; ++v) sv[v] = 0.f;
     }
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) sv = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[ks], u4_as_f16x8(qf[0][ks]), sv, 0, 0, 0);
+    for (int ks = 0; ks < 8; ++ks) sv = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[ks], u4_as_f16x8(qf[ks]), sv, 0, 0, 0);
   };
   // ---- causal mask and online softmax (log2 domain), one query row per lane -----------------------
   auto softmax = [&](int t, int kb) {
@@ -285,7 +353,7 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) 
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int key = k0 + kb * 32 + 8 * (v >> 2) + 4 * kh + (v & 3);
-        if (key > pos[0] || key >= kend) sv[v] = -INFINITY;
+        if (key > pos || key >= kend) sv[v] = -INFINITY;
       }
     }
     float mx = sv[0];
@@ -318,7 +386,7 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) 
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) o[cb][0][v] *= alpha;
+          for (int v = 0; v < 16; ++v) o[cb][v] *= alpha;
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) sv[v] = __builtin_amdgcn_exp2f(sv[v]);
@@ -334,7 +402,7 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) 
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) o[cb][0][v] *= alpha;
+          for (int v = 0; v < 16; ++v) o[cb][v] *= alpha;
       }
       m_ref = m_new;
 #pragma unroll
@@ -366,7 +434,7 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) 
     for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb)
-        o[cb][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[hf][cb], u4_as_f16x8(pf[hf]), o[cb][0], 0, 0, 0);
+        o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[hf][cb], u4_as_f16x8(pf[hf]), o[cb], 0, 0, 0);
   };
 
   {
@@ -402,77 +470,266 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) 
     }
   }
 
-  // ---- write the partial (or final) result ----------------------------------------------------
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);      // the two halves of the wave hold disjoint keys
-    if (tok[nb] >= ntok) continue;
-    const int64_t row = row0 + tok[nb];
-    if (a.out != nullptr) {
-      const float inv = 1.0f / l_tot;
-      bf16 *op = a.out + row * a.n_q + head[nb] * H;
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-          const int col = cb * 32 + 8 * v4 + 4 * kh;
-          uint2 w;
-          w.x = pack_bf16x2(o[cb][nb][4 * v4] * inv, o[cb][nb][4 * v4 + 1] * inv);
-          w.y = pack_bf16x2(o[cb][nb][4 * v4 + 2] * inv, o[cb][nb][4 * v4 + 3] * inv);
-          *reinterpret_cast<uint2 *>(op + col) = w;
-        }
-    } else if (a.compact) {
-      // compact partial record (ATTN_REC16 bytes): the unnormalised accumulators of the row divided by their
-      // largest magnitude, as 128 fp16 values (relative precision 2^-11, finer than the bf16 the merged result
-      // is rounded to; no overflow whatever the values), then that magnitude, the reference and the row sum.
-      // Half the bytes of the fp32 record -- and these records are most of what a short call writes and reads.
-      float amax = 0.f;
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) amax = fmaxf(amax, fabsf(o[cb][nb][v]));
-      amax = max_with_other_half(amax);
-      const float rs = amax > 0.f ? 1.0f / amax : 0.f;
-      char *rec = reinterpret_cast<char *>(a.partials) +
-                  ((row * a.n_q_heads + head[nb]) * a.n_parts + split) * (int64_t)ATTN_REC16;
-      typedef __attribute__((__vector_size__(4 * sizeof(_Float16)))) _Float16 half4_t;
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-          const int col = cb * 32 + 8 * v4 + 4 * kh;
-          half4_t hv;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) hv[i] = (_Float16)(o[cb][nb][4 * v4 + i] * rs);
-          *reinterpret_cast<half4_t *>(rec + col * 2) = hv;
-        }
-      if (kh == 0) {
-        float *tail = reinterpret_cast<float *>(rec + 2 * H);
-        tail[0] = (l_tot == 0.f || m_ref == -INFINITY) ? -INFINITY : m_ref * LN2;
-        tail[1] = l_tot;
-        tail[2] = amax;
-      }
-    } else {
-      float *pp = a.partials + ((row * a.n_q_heads + head[nb]) * a.n_parts + split) * (H + 2);
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-          const int col = cb * 32 + 8 * v4 + 4 * kh;
-          // (H + 2) floats per record keeps 8-byte, not 16-byte, alignment
-          *reinterpret_cast<float2 *>(pp + col) = make_float2(o[cb][nb][4 * v4], o[cb][nb][4 * v4 + 1]);
-          *reinterpret_cast<float2 *>(pp + col + 2) = make_float2(o[cb][nb][4 * v4 + 2], o[cb][nb][4 * v4 + 3]);
-        }
-      if (kh == 0) {
-        // natural-log domain; a row that saw no key keeps -inf so that the merge gives it no weight
-        pp[H] = (l_tot == 0.f || m_ref == -INFINITY) ? -INFINITY : m_ref * LN2;
-        pp[H + 1] = l_tot;
-      }
-    }
-  }
+  write_result(a, split, row0, ntok, tok, head, kh, m_ref, l_run, o);
 }
 
+// ---- folded softmax, eight waves: the steps of consecutive 32-key blocks woven together -----------------------------------
+//
+// While a block's probabilities are made and multiplied with V, the scores of the next block come out of the matrix unit: every one of a
+// block's 16 matrix instructions (32 cycles each) carries one operand read from LDS and at most six vector instructions of another
+// step beside it -- eight for K Q^T of the next block with the exponentials of this one, eight for P V with the row sums, the maximum
+// of the next block's scores, and the conversion of the tile after next, a word at a time.  The order is fixed in the source
+// (sched_barrier after every matrix instruction); in the compiler's own order LDS waits and softmax stand between the products.
+// What it rests on (measured beside v_mfma_f32_32x32x16): six v_fma / v_cvt / v_max3 or two v_exp cost nothing; one v_dot2_f32_f16 costs 16 cycles
+// of the matrix pipe, which is why the row sums are v_fma_mix; a branch on the mask between the two halves of a block costs 70
+// register moves, so blocks that may need the mask run in a loop of their own, whose scores start from -inf where a row does not see
+// a key.
+//
+// 1024 rows x 32 heads over 32768 keys: 555 -> 497 us (0.99 -> 1.11 PFLOP/s), 4300 -> 3150 cycles per 256 x 64 tile, matrix pipes busy 0.48 ->
+// 0.65 of the time; the power limit takes part of it back (1.97 -> 1.62 GHz).  Bound now: that limit -- the matrix work alone, without
+// tiles, LDS reads and exponentials, takes 388 us at 0.84 busy and 1.6 GHz; without the tile traffic 430; without operand reads 470.
+// No gain (within 1 %): operands requested 2 to 6 instructions ahead, two tiles in registers instead of one, other wave priorities.
+template <int N> using ic = std::integral_constant<int, N>;
+// one K tile (rows 16 bytes apart from a multiple of 256, so that 16 of them lie in different banks) and one V^T tile in LDS; four of each
+constexpr int PIPE_AHEAD = 4;      // operand reads run this many matrix instructions ahead
+constexpr int PIPE_KROW = 272, PIPE_K = ATT_BN * PIPE_KROW, PIPE_VT = ATT_BN * 256;
+constexpr int PIPE_V = 4 * PIPE_K, PIPE_LDS = PIPE_V + 4 * PIPE_VT;
+// a value that the compiler takes as computed here (and whose parts it does not look into)
+__device__ __forceinline__ void pin(int &x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(uint32_t &x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void pin(float &x) { asm volatile("" : "+v"(x)); }
+// LDS by its byte address
+template <typename V> __device__ __forceinline__ V lds_read(int at) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) V *>((uint32_t)at);
+}
+template <typename V> __device__ __forceinline__ void lds_write(int at, V v) {
+  *reinterpret_cast<__attribute__((address_space(3))) V *>((uint32_t)at) = v;
+}
 
+__global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int g_log2) {
+  constexpr int H = 128;
+  extern __shared__ u32x4 pipe_lds[];
+  const int lds = (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) u32x4 *)pipe_lds;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, kh = lane >> 5;
+  const AttnItem wk = a.work[blockIdx.x];
+  if (wk.ntok <= 0) return;
+  const int ntok = wk.ntok, row0 = wk.row0, n_visible = wk.n_addr, kbeg = wk.kbeg, kend = wk.kend, first_pos = wk.pos0;
+  const int ntiles = kend > kbeg ? (kend - kbeg + ATT_BN - 1) / ATT_BN : 0;
+  const bf16 *Kp = a.K + wk.key_row0 * a.n_kv + wk.g * H;
+  const bf16 *Vp = a.V + wk.key_row0 * a.n_kv + wk.g * H;
+
+  const int pr = wave * 32 + l32, tok = pr >> g_log2, head = (wk.g << g_log2) + (pr & ((1 << g_log2) - 1));
+  const int pos = tok < ntok ? first_pos + tok : -1;       // -1: padding row
+  u32x4 qf[8];
+  {
+    const _Float16 *qp = a.Q + (int64_t)(row0 + min(tok, ntok - 1)) * a.n_q + head * H + kh * 8;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const u32x4 *>(qp + ks * 16);
+  }
+  f32x16 o[4], negm;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    negm[v] = 0.f;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) o[cb][v] = 0.f;
+  }
+  float l_run = 0.f, thr = -INFINITY;      // thr: what a block's maximum (relative to m_ref) has to exceed to move m_ref
+
+  // ---- tiles: memory -> registers (a tile's time before the store) -> LDS (two tiles ahead of the products) ----------------
+  const int v_qd = tid >> 5, v_cg = tid & 31;
+  const uint32_t row_bytes = (uint32_t)a.n_kv * 2u;
+  const int k_off0 = (int)((uint32_t)(tid >> 4) * row_bytes + (tid & 15) * 16u), k_step = (int)(32u * row_bytes);
+  const int v_off0 = (int)((uint32_t)(v_qd * 4) * row_bytes + v_cg * 8u);
+  const int n_load = min(n_visible, kbeg + ntiles * ATT_BN);
+  auto rsrc_of = [&](const bf16 *base, int t) {      // the rows of tile t that exist; the others read as zero
+    const int k0 = kbeg + t * ATT_BN, n = min(n_load - k0, ATT_BN);
+    const int bytes = max((n - 1) * (int)row_bytes + H * 2, 0);
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(base + (int64_t)k0 * a.n_kv), 0, bytes, 0x00020000);
+  };
+  u32x4 rk[2];
+  u32x2 rv[4];
+  auto load_k = [&](int t, int i, u32x4 (&r)[2]) {
+    r[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_of(Kp, t), k_off0, i * k_step, 0));
+  };
+  auto load_v = [&](int t, int i, u32x2 (&r)[4]) {
+    r[i] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc_of(Vp, t), v_off0, i * (int)row_bytes, 0));
+  };
+  auto load_tile = [&](int t, u32x4 (&k)[2], u32x2 (&v)[4]) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) load_k(t, i, k);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_v(t, i, v);
+  };
+  int k_st = lds + 2 * PIPE_K + (tid >> 4) * PIPE_KROW + (tid & 15) * 16;
+  uint32_t cv[4];      // what goes to LDS next, converted a word at a time
+  auto cv_k = [&](int par, int n, const u32x4 (&r)[2]) {      // n = 0 .. 7: word n % 4 of chunk n / 4
+    cv[n & 3] = bf16x2_to_f16x2(r[n >> 2][n & 3]);
+    pin(cv[n & 3]);
+    if ((n & 3) == 3) lds_write(k_st + par * PIPE_K + (n >> 2) * (32 * PIPE_KROW), u32x4{cv[0], cv[1], cv[2], cv[3]});
+  };
+  // column c = 4 v_cg + j of key quad v_qd: chunk ((v_qd / 4) * 2 + (v_qd & 1)) ^ v_swz(c), half (v_qd >> 1) & 1 of it; columns 2 j and 2 j + 1 share
+  // their swizzle
+  const int v_chunk = (v_qd >> 2) * 2 + (v_qd & 1), v_half = (v_qd >> 1) & 1;
+  int v_st[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) v_st[j] = lds + PIPE_V + 2 * PIPE_VT + (v_cg * 4 + 2 * j) * 128 + (v_chunk ^ v_swz(v_cg * 4 + 2 * j)) * 16 + v_half * 8;
+  auto cv_v = [&](int par, int n, const u32x2 (&r)[4]) {      // n = 0 .. 7: column n / 2, keys 2 (n % 2) and the next of the quad
+    const int j = n >> 2, odd = (n >> 1) & 1, p = (n & 1) * 2;
+    cv[n & 1] = odd ? pack_f16x2(bf16_hi(r[p][j]), bf16_hi(r[p + 1][j])) : pack_f16x2(bf16_lo(r[p][j]), bf16_lo(r[p + 1][j]));
+    pin(cv[n & 1]);
+    if (n & 1) lds_write(v_st[j] + par * PIPE_VT + odd * 128, u32x2{cv[0], cv[1]});
+  };
+
+  // ---- operands from LDS ---------------------------------------------------------------------------------------------------
+  int ka = lds + l32 * PIPE_KROW + kh * 16, va[4];
+  pin(ka);
+#pragma unroll
+  for (int x = 0; x < 4; ++x) { va[x] = lds + PIPE_V + l32 * 128 + (((2 * x + kh) ^ (((l32 >> 1) ^ (l32 >> 4)) & 7)) * 16); pin(va[x]); }
+  pin(k_st); pin(v_st[0]); pin(v_st[1]);
+  // operands on their way: PIPE_AHEAD matrix instructions before they are needed
+  u32x4 fr[8];
+  auto read_k = [&](int par, int kb, int ks) { fr[ks] = lds_read<u32x4>(ka + par * PIPE_K + kb * (32 * PIPE_KROW) + ks * 32); };
+  auto read_v = [&](int par, int kb, int n) {      // n = 4 * (half of the block's keys) + column block
+    const int s4 = kb * 2 + (n >> 2), cb = n & 3;
+    fr[n] = lds_read<u32x4>(va[s4 ^ cb] + par * PIPE_VT + cb * 4096);
+  };
+
+  // what the scores of key block k0 .. k0 + 31 start from: -m_ref, or -inf where the row does not see the key
+  const int vis = min(pos, kend - 1) - 4 * kh;
+  auto start_masked = [&](f32x16 &s, int k0) {
+    int lim = vis - k0;
+    pin(lim);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s[v] = 8 * (v >> 2) + (v & 3) > lim ? -INFINITY : negm[v];
+  };
+  auto move_ref = [&](f32x16 &s, float mx) {
+    mx = max_with_other_half(mx);
+    const bool fresh = thr == -INFINITY;
+    const float delta = mx > thr ? mx : 0.f;
+    const float alpha = fresh ? 1.0f : __builtin_amdgcn_exp2f(-delta);
+    if (mx > -INFINITY) thr = a.lazy;
+    l_run *= alpha;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { s[v] -= delta; negm[v] -= delta; }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[cb][v] *= alpha;
+  };
+
+  // ---- one 32-key block: its probabilities and P V, woven with K Q^T and the maximum of the next ------------------------
+  uint32_t pw[8];
+  auto pf_of = [&](int hf) { return u4_as_f16x8(u32x4{pw[4 * hf], pw[4 * hf + 1], pw[4 * hf + 2], pw[4 * hf + 3]}); };
+  int dk = 2 * PIPE_K, dv = 2 * PIPE_VT;      // to the other pair of buffers
+  auto block = [&](auto par_c, auto kb_c, auto mask_c, f32x16 &sc, f32x16 &sn, int t) {
+    constexpr int PAR = par_c, KB = kb_c, MASK = mask_c;
+    if constexpr (MASK) start_masked(sn, kbeg + t * ATT_BN + (KB + 1) * 32);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      sn = __builtin_amdgcn_mfma_f32_32x32x16_f16(u4_as_f16x8(fr[n]), u4_as_f16x8(qf[n]), n == 0 && !MASK ? negm : sn, 0, 0, 0);
+      if (n < 8 - PIPE_AHEAD) read_k(MASK ? 0 : PAR ^ KB, KB ^ 1, n + PIPE_AHEAD);
+      else read_v(PAR, KB, n + PIPE_AHEAD - 8);
+      // requests of the tile that takes the place of what the last block stored, a few at a time (all eight waves ask together)
+      if (KB == 1 && (n & 3) == 1) load_k(t + 3, n >> 2, rk);
+      if (KB == 0 && (n & 1) == 1) load_v(t + 2, n >> 1, rv);
+      sc[2 * n] = __builtin_amdgcn_exp2f(sc[2 * n]);
+      sc[2 * n + 1] = __builtin_amdgcn_exp2f(sc[2 * n + 1]);
+      if (n >= 1) { pw[n - 1] = pack_f16x2(sc[2 * n - 2], sc[2 * n - 1]); pin(pw[n - 1]); }
+      if (KB == 0 && n == 7) {
+        // the stores of the tile before are done (the eight youngest LDS operations are this block's reads), in every wave
+        asm volatile("s_waitcnt lgkmcnt(8)\n\ts_barrier" ::: "memory");
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (MASK && KB == 0) ka += (t & 3) == 3 ? -3 * PIPE_K : PIPE_K;
+    if (!MASK && PAR == 1 && KB == 0) ka += dk;      // (the other pair of buffers)
+    __builtin_amdgcn_s_setprio(1);
+    float m0 = 0.f;
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      o[n & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(u4_as_f16x8(fr[n]), pf_of(n >> 2), o[n & 3], 0, 0, 0);
+      if (n < 8 - PIPE_AHEAD) read_v(PAR, KB, n + PIPE_AHEAD);
+      else read_k(MASK ? 0 : PAR ^ 1, KB, n + PIPE_AHEAD - 8);
+      if (n == 0) { pw[7] = pack_f16x2(sc[14], sc[15]); pin(pw[7]); }
+      add_f16<0>(pw[n], l_run);
+      add_f16<1>(pw[n], l_run);
+      // (the scores are there two matrix instructions after the last that made them)
+      if (n == 2) m0 = fmaxf(fmaxf(sn[0], sn[1]), sn[2]);
+      if (n >= 3) m0 = fmaxf(fmaxf(m0, sn[2 * n - 3]), sn[2 * n - 2]);
+      if (n == 6) m0 = fmaxf(fmaxf(m0, sn[13]), sn[14]);
+      if (n == 7) m0 = __builtin_amdgcn_fmed3f(m0, sn[15], INFINITY);
+      if (n >= 2) pin(m0);
+      if constexpr (KB == 0) {
+        cv_k(PAR, n, rk);
+      } else {
+        cv_v(PAR, n, rv);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    if (__any(m0 > thr)) move_ref(sn, m0);
+  };
+  // the other pair of buffers: reads of K; reads of V^T, and the stores
+  auto other_v = [&] {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) va[x] += dv;
+    k_st -= dk; v_st[0] -= dv; v_st[1] -= dv;
+    dk = -dk; dv = -dv;
+  };
+
+  if (ntiles > 0) {
+    u32x4 rk1[2];
+    u32x2 rv1[4];
+    load_tile(0, rk, rv);
+    load_tile(1, rk1, rv1);
+    wait_all_global_loads();
+    k_st -= dk; v_st[0] -= dv; v_st[1] -= dv;
+#pragma unroll
+    for (int n = 0; n < 8; ++n) cv_k(0, n, rk);
+    load_k(2, 0, rk); load_k(2, 1, rk);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) cv_v(0, n, rv);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) cv_k(1, n, rk1);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) cv_v(1, n, rv1);
+    k_st += dk; v_st[0] += dv; v_st[1] += dv;
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    f32x16 s0, s1;
+#pragma unroll
+    for (int n = 0; n < 8; ++n) read_k(0, 0, n);
+    start_masked(s0, kbeg);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) s0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(u4_as_f16x8(fr[n]), u4_as_f16x8(qf[n]), s0, 0, 0, 0);
+#pragma unroll
+    for (int n = 0; n < PIPE_AHEAD; ++n) read_k(0, 1, n);
+    float m0 = s0[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) m0 = fmaxf(m0, s0[v]);
+    if (__any(m0 > thr)) move_ref(s0, m0);
+    // tiles that every row of the item sees whole; a pair of tiles goes without the mask if they and the next are
+    const int n_full = (min(first_pos + 1, kend) - kbeg) / ATT_BN;
+    int t = 0;
+    for (; t + 2 < n_full; t += 2) {
+      block(ic<0>{}, ic<0>{}, ic<0>{}, s0, s1, t);
+      block(ic<0>{}, ic<1>{}, ic<0>{}, s1, s0, t);
+      block(ic<1>{}, ic<0>{}, ic<0>{}, s0, s1, t + 1);
+      block(ic<1>{}, ic<1>{}, ic<0>{}, s1, s0, t + 1);
+      other_v();
+    }
+    for (; t < ntiles; ++t) {      // (a tile at a time, round the four buffers)
+      block(ic<0>{}, ic<0>{}, ic<1>{}, s0, s1, t);
+      block(ic<0>{}, ic<1>{}, ic<1>{}, s1, s0, t);
+      const int av = (t & 3) == 3 ? -3 * PIPE_VT : PIPE_VT, as = (t & 3) == 1 ? -3 : 1;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) va[x] += av;
+      k_st += as * PIPE_K; v_st[0] += as * PIPE_VT; v_st[1] += as * PIPE_VT;
+    }
+  }
+  const float m_ref = -negm[0];
+  write_result(a, wk.part, row0, ntok, tok, head, kh, m_ref, l_run, o);
+}
 
 bool attn_prefill_mfma_supported(const LayerDims &L) {
   const int G = L.n_q_heads / L.n_kv_heads;
@@ -495,15 +752,10 @@ static void launch_attn_nw(const AttnArgs &a, int n_work, int G, hipStream_t s) 
   }
 }
 
-template <int NW>
+template <int NW, bool FOLD>
 static void launch_attn_nw_any(const AttnArgs &a, int n_work, int G, bool prefix, hipStream_t s) {
-  if (a.q_prescaled) {
-    if (prefix) launch_attn_nw<NW, true, true>(a, n_work, G, s);
-    else launch_attn_nw<NW, false, true>(a, n_work, G, s);
-  } else {
-    if (prefix) launch_attn_nw<NW, true, false>(a, n_work, G, s);
-    else launch_attn_nw<NW, false, false>(a, n_work, G, s);
-  }
+  if (prefix) launch_attn_nw<NW, true, FOLD>(a, n_work, G, s);
+  else launch_attn_nw<NW, false, FOLD>(a, n_work, G, s);
 }
 
 // Log-sum-exp merge of the compact partial records (Eq.1 over the union of the key splits): one wave per
@@ -558,8 +810,17 @@ void launch_attn_merge16(const float *partials, const LayerDims &L, int T_rows, 
 
 void launch_attn_prefill_mfma(const AttnArgs &a, int n_work, int G, int waves, bool prefix, hipStream_t s) {
   if (n_work == 0) return;
-  if (waves == 4) launch_attn_nw_any<4>(a, n_work, G, prefix, s);
-  else launch_attn_nw_any<8>(a, n_work, G, prefix, s);
+  if (waves == 8 && a.q_prescaled) {
+    auto kern = attn_prefill_pipe_kernel;
+    (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, PIPE_LDS);
+    hipLaunchKernelGGL(kern, dim3(n_work), dim3(512), PIPE_LDS, s, a, G == 1 ? 0 : G == 2 ? 1 : G == 4 ? 2 : 3);
+  } else if (waves == 8) {
+    launch_attn_nw_any<8, false>(a, n_work, G, prefix, s);
+  } else if (a.q_prescaled) {
+    launch_attn_nw_any<4, true>(a, n_work, G, prefix, s);
+  } else {
+    launch_attn_nw_any<4, false>(a, n_work, G, prefix, s);
+  }
 }
 
 // What the rotation kernel multiplies the queries by: the folded softmax wants them in the exp2 domain,

@@ -445,3 +445,16 @@ def test_lora_split_gives_the_low_rank_term_a_partial_sum(ab, T):
             c.close()
     for split in (1, 2):
         assert all(torch.equal(a, b) for a, b in zip(got[0], got[split]))
+
+
+# one to five tiles of 64 keys, whole, one short and one over; padding rows; a causal edge in every place of a tile
+@pytest.mark.parametrize("splits", [0, 1, 3])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_prefill_attention_around_tiles_of_keys(ab, ctx, G, splits):
+    ctx.set_option("kv_splits", splits)
+    shape = wl.LayerShape(d=256, n_q_heads=8, n_kv_heads=8 // G, head_dim=128, rank=8, n_adapters=2)
+    P = [0, 0, 0, 31, 32, 62, 63, 64, 127, 128, 190, 191, 192, 193, 255, 256, 257, 320]
+    S = [1, 33, 64, 1, 1, 1, 2, 65, 1, 1, 2, 1, 130, 1, 1, 1, 63, 257]
+    n = len(P)
+    case = H.make_case(shape, P, S, [P[b] + b % 2 for b in range(n)], [b % 3 - 1 for b in range(n)], seed=1500 + G, prefix="random")
+    check_case(ab, ctx, case)
