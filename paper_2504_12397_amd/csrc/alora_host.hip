@@ -445,8 +445,9 @@ Workspace layout_workspace(char *base, const LayerDims &L, int T, size_t esz, in
   if (stack) {
     w.attn = b.take<char>((size_t)T * L.n_q * esz);
     w.h1 = b.take<char>((size_t)T * L.d * esz);
-    w.hn = b.take<char>((size_t)T * L.d * esz);
-    w.gate = b.take<char>((size_t)T * intermediate * esz);
+    const size_t rows = T <= STREAM_ROWS ? (T + 31) & ~31 : T;      // (operand order: blocks of 32 rows)
+    w.hn = b.take<char>(rows * L.d * esz);
+    w.gate = b.take<char>(rows * intermediate * esz);
     w.up = b.take<char>((size_t)T * intermediate * esz);
     w.xa = b.take<char>((size_t)T * L.d * esz);
     w.xb = b.take<char>((size_t)T * L.d * esz);
@@ -616,21 +617,37 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
   RowMeta none{};
   const bool mfma = w.mfma && std::is_same<T, bf16>::value;
   const int r = L.rank, n_ad = L.n_adapters;
+  // Few rows with default options: gate/up, W_down and the adapters' down-projections in the kernel that streams weights past all rows
+  auto streamed = [&](const GemmArgs &g, int epi) {
+    return mfma && ctx->opt_gemm_splits == 0 && ctx->opt_gemm_tile == 0 && gemm_stream_supported(g, epi);
+  };
+  auto linear = [&](const void *W, const void *W2, int N, int K) {
+    GemmArgs g{};
+    g.B = (const bf16 *)W; g.B2 = (const bf16 *)W2; g.ldb = K;
+    g.M = T_rows; g.N = W2 ? 2 * N : N; g.K = K; g.rank = r;
+    return g;
+  };
   // Adapters of these linears (Eq.6 applied to them): on the MFMA path t = s_a A_a z is computed for all
   // adapters at once as a skinny GEMM against the stacked down-matrices [n_ad * parts * r, K] (exactly how
   // they are stored), each adapted row then picks its adapter's slice as a bf16 (hi, lo) pair, and the
   // up-projection runs as extra k-steps of the base GEMM; on the plain path the term is added afterwards.
-  auto lowrank_t = [&](const void *z, int K, const void *A_all, int parts) {
+  auto lowrank_t = [&](const void *z, bool packed, int K, const void *A_all, int parts) {
     GemmArgs g{};
-    g.A = (const bf16 *)z; g.lda = K;
+    g.A = (const bf16 *)z; g.lda = K; g.packed = packed ? 1 : 0;
     g.B = (const bf16 *)A_all; g.ldb = K;
     g.M = T_rows; g.N = n_ad * parts * r; g.K = K;
-    int splits = gemm_mfma_pick_splits(T_rows, g.N, K, ctx->n_cu);
-    while (splits > 1 && (size_t)splits * T_rows * g.N > w.y_floats) splits /= 2;
-    g.k_splits = splits;
-    g.k_segments = splits;
     g.Cpart = w.Y;
-    launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
+    int splits;
+    if (streamed(g, GEMM_EPI_PARTIAL)) {
+      splits = g.k_splits = gemm_stream_segments(g, ctx->n_cu, (int)std::min<size_t>(32, w.y_floats / ((size_t)T_rows * g.N)));
+      launch_gemm_stream(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
+    } else {
+      splits = gemm_mfma_pick_splits(T_rows, g.N, K, ctx->n_cu);
+      while (splits > 1 && (size_t)splits * T_rows * g.N > w.y_floats) splits /= 2;
+      g.k_splits = splits;
+      g.k_segments = splits;
+      launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
+    }
     launch_tlow_select(w.Y, splits, T_rows, n_ad, parts, r, w.rm.adapter, w.scale_dev, (bf16 *)w.tlow, s);
   };
   auto set_lowrank = [&](GemmArgs &g, const void *B0, const void *B1, int parts, int width) {
@@ -662,10 +679,10 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
   };
   // C = A W^T (+ R), with the gated low-rank term of (Al, Bl) when given
   auto dense = [&](const void *A, const void *W, const void *R, void *C, int N, int K, const void *Al, const void *Bl,
-                   int parts = 1, int part = 0) {
+                   int parts = 1, int part = 0, bool packed = false) {
     const bool lr = Al != nullptr && w.any_adapter;
     if (mfma) {
-      if (lr) lowrank_t(A, K, Al, 1);
+      if (lr) lowrank_t(A, packed, K, Al, 1);
       GemmArgs g{};
       g.A = (const bf16 *)A; g.lda = K;
       g.B = (const bf16 *)W; g.ldb = K;
@@ -673,6 +690,11 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
       g.tile_hint = ctx->opt_gemm_tile;
       if (lr) set_lowrank(g, Bl, nullptr, 1, N);
       g.C = (bf16 *)C; g.ldc = N; g.R = (const bf16 *)R;
+      g.packed = packed ? 1 : 0;
+      if (streamed(g, GEMM_EPI_BF16)) {
+        launch_gemm_stream(g, GEMM_EPI_BF16, ctx->n_cu, s);
+        return;
+      }
       if (const int n = large(g)) {
         if (n > 1) launch_splitk_reduce(w.Y, n, (int64_t)T_rows * N, (const bf16 *)R, (bf16 *)C, s);
         return;
@@ -707,6 +729,12 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
   };
   // h1 = x + attn W_o^T, hn = RMSNorm(h1).  When the projection is split over the reduction axis anyway, the
   // kernel that adds the partial sums also normalises the row (from its fp32 value) -- one launch less.
+  // Between streamed products rows travel in the order of the matrix operand (a request of 64 lanes is 1 KB in a row, not 32 bytes of
+  // 32 rows): 128 rows of gate/up 66 -> 48 us.  (The adapters' down-projections read them too.)
+  const bool gu_stream = streamed(linear(ly->W_gate, ly->W_up, ly->intermediate, L.d), GEMM_EPI_SWIGLU);
+  const bool hn_packed = gu_stream && (!(ly->A_gu && w.any_adapter) || streamed(linear(ly->A_gu, nullptr, n_ad * 2 * r, L.d), GEMM_EPI_PARTIAL));
+  const bool act_packed = gu_stream && streamed(linear(ly->W_down, nullptr, L.d, ly->intermediate), GEMM_EPI_BF16) &&
+                          (!(ly->A_down && w.any_adapter) || streamed(linear(ly->A_down, nullptr, n_ad * r, ly->intermediate), GEMM_EPI_PARTIAL));
   bool normed = false;
   {
     ProfScope p(ctx, K_OPROJ, s);
@@ -719,7 +747,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
       g.M = T_rows; g.N = L.d; g.K = L.n_q;
       g.tile_hint = ctx->opt_gemm_tile;
       if (ly->A_o && w.any_adapter) {
-        lowrank_t(w.attn, L.n_q, ly->A_o, 1);
+        lowrank_t(w.attn, false, L.n_q, ly->A_o, 1);
         set_lowrank(g, ly->B_o, nullptr, 1, L.d);
       }
       g.C = (bf16 *)w.h1; g.ldc = L.d; g.R = (const bf16 *)x;
@@ -732,7 +760,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
       }
       if (parts > 1) {
         launch_splitk_reduce_norm(w.Y, parts, T_rows, L.d, (const bf16 *)x, (const bf16 *)ly->rms2_gain, ly->rms_eps,
-                                  (bf16 *)w.h1, (bf16 *)w.hn, s);
+                                  (bf16 *)w.h1, (bf16 *)w.hn, hn_packed, s);
         normed = true;
       } else if (parts == 0) {
         g.k_splits = 1;
@@ -748,11 +776,11 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     if (mfma && prep_rows_mfma_supported(L.d, 0)) {
       PrepArgs pa{};
       pa.x = (const bf16 *)w.h1; pa.gain = (const bf16 *)ly->rms2_gain; pa.eps = ly->rms_eps;
-      pa.T = T_rows; pa.d = L.d; pa.xh = (bf16 *)w.hn; pa.rm = none;
+      pa.T = T_rows; pa.d = L.d; pa.xh = (bf16 *)w.hn; pa.packed = hn_packed ? 1 : 0; pa.rm = none;
       launch_prep_rows_mfma(pa, s);
     } else {
       launch_prep_rows<T>((const T *)w.h1, (const T *)ly->rms2_gain, ly->rms_eps, T_rows, L.d, nullptr, 0, 0,
-                          (const T *)nullptr, 0, false, (T *)w.hn, nullptr, nullptr, none, StagedCall{}, false, s);
+                          (const T *)nullptr, 0, false, (T *)w.hn, nullptr, nullptr, none, StagedCall{}, hn_packed, s);
     }
   }
   if (mfma) {   // act = silu(hn W_gate^T) * (hn W_up^T) in one pass
@@ -763,11 +791,13 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     g.M = T_rows; g.N = 2 * ly->intermediate; g.K = L.d; g.k_splits = 1; g.k_segments = 1;
     g.tile_hint = ctx->opt_gemm_tile;
     if (ly->A_gu && w.any_adapter) {
-      lowrank_t(w.hn, L.d, ly->A_gu, 2);
+      lowrank_t(w.hn, hn_packed, L.d, ly->A_gu, 2);
       set_lowrank(g, ly->B_gate, ly->B_up, 2, ly->intermediate);
     }
     g.C = (bf16 *)w.gate; g.ldc = ly->intermediate;
-    launch_gemm_mfma(g, GEMM_EPI_SWIGLU, ctx->n_cu, s);
+    g.packed = (hn_packed ? 1 : 0) | (act_packed ? 2 : 0);
+    if (streamed(g, GEMM_EPI_SWIGLU)) launch_gemm_stream(g, GEMM_EPI_SWIGLU, ctx->n_cu, s);
+    else launch_gemm_mfma(g, GEMM_EPI_SWIGLU, ctx->n_cu, s);
   } else if (w.f0 != nullptr) {
     // bf16 on the plain kernels: gate and up stay in fp32 until silu(gate) * up is rounded, once
     const bool lr = ly->A_gu != nullptr && w.any_adapter;
@@ -799,7 +829,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
   }
   {
     ProfScope p(ctx, K_DOWN, s);
-    dense(w.gate, ly->W_down, w.h1, out, L.d, ly->intermediate, ly->A_down, ly->B_down);
+    dense(w.gate, ly->W_down, w.h1, out, L.d, ly->intermediate, ly->A_down, ly->B_down, 1, 0, act_packed);
   }
 }
 
@@ -1603,7 +1633,10 @@ alora_status alora_lm_head(alora_ctx *ctx, alora_dtype dtype, int32_t d, int32_t
       g.k_splits = 1;
       g.k_segments = 1;
       g.Cpart = lg;
-      launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
+      if (ctx->opt_gemm_splits == 0 && ctx->opt_gemm_tile == 0 && gemm_stream_supported(g, GEMM_EPI_PARTIAL))
+        launch_gemm_stream(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
+      else
+        launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
     } else if (bf) {
       launch_lm_logits_plain<bf16>((const bf16 *)rows, (const bf16 *)W_vocab, B, vocab, d, lg, s);
     } else {

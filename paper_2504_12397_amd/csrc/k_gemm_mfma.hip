@@ -566,7 +566,7 @@ constexpr int RN_THREADS = 1024;
 __global__ __launch_bounds__(RN_THREADS) void splitk_reduce_norm_kernel(const float *__restrict__ part, int splits, int M,
                                                                         int N, const bf16 *__restrict__ R,
                                                                         const bf16 *__restrict__ gain, float eps,
-                                                                        bf16 *__restrict__ C, bf16 *__restrict__ Cn) {
+                                                                        bf16 *__restrict__ C, bf16 *__restrict__ Cn, int packed) {
   constexpr int U = 16384 / (4 * RN_THREADS);
   __shared__ float s_red[RN_THREADS / 64];
   const int row = blockIdx.x, tid = threadIdx.x;
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(RN_THREADS) void splitk_reduce_norm_kernel(const fl
     const int c = (u * RN_THREADS + tid) * 4;
     if (c < N) {
       store_bf16x4(C + ro + c, h[u].x, h[u].y, h[u].z, h[u].w);
-      store_bf16x4(Cn + ro + c, h[u].x * gn[u].x * rinv, h[u].y * gn[u].y * rinv, h[u].z * gn[u].z * rinv, h[u].w * gn[u].w * rinv);
+      store_bf16x4(Cn + (packed ? xh_chunk(row, c >> 3, N, 1) * 8 + (c & 7) : ro + c), h[u].x * gn[u].x * rinv, h[u].y * gn[u].y * rinv, h[u].z * gn[u].z * rinv, h[u].w * gn[u].w * rinv);
     }
   }
 }
@@ -634,9 +634,9 @@ void launch_tlow_select(const float *Y, int splits, int M, int n_adapters, int p
 bool splitk_reduce_norm_supported(int N) { return N % 4 == 0 && N <= 16384; }
 
 void launch_splitk_reduce_norm(const float *part, int splits, int M, int N, const bf16 *R, const bf16 *gain, float eps,
-                               bf16 *C, bf16 *Cn, hipStream_t s) {
+                               bf16 *C, bf16 *Cn, bool packed, hipStream_t s) {
   if (M == 0) return;
-  hipLaunchKernelGGL(splitk_reduce_norm_kernel, dim3(M), dim3(RN_THREADS), 0, s, part, splits, M, N, R, gain, eps, C, Cn);
+  hipLaunchKernelGGL(splitk_reduce_norm_kernel, dim3(M), dim3(RN_THREADS), 0, s, part, splits, M, N, R, gain, eps, C, Cn, packed ? 1 : 0);
 }
 
 bool gemm_mfma_supported(int M, int N, int K) { return M > 0 && N > 0 && K >= 64 && K % 64 == 0; }

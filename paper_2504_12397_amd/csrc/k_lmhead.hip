@@ -34,7 +34,7 @@ __device__ __forceinline__ void take_better(float &bv, int &bi, float v, int i) 
   if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
 }
 
-constexpr int ARGMAX_SLAB = 8192;
+constexpr int ARGMAX_SLAB = 1024;
 
 __global__ __launch_bounds__(256) void argmax_partial_kernel(const float *__restrict__ logits, int V, int n_slabs,
                                                              float *__restrict__ pv, int *__restrict__ pi) {

@@ -45,6 +45,7 @@ struct GemmArgs {
   int head_dim;                // few-row kernel only (the others: 128)
   int q_f32;                   // few-row kernel only, 1: Qout receives fp32 (plain attention) instead of fp16
   bf16 *Qout, *cacheK, *cacheV;
+  int packed;                  // launch_gemm_stream only, 1: A in operand order (as PrepArgs::packed, rows padded to 32); 2: the SwiGLU output too
 };
 bool gemm_mfma_rope_supported(const GemmArgs &g, int head_dim);
 
@@ -167,6 +168,11 @@ constexpr int QKV_STREAM_ROWS = 256;      // most rows that the kernel takes, an
 int qkv_stream_rows(int N, int n_cu);
 bool qkv_stream_supported(const void *W, int N, int K, int head_dim);
 void launch_qkv_stream(const GemmArgs &g, int n_cu, hipStream_t s);
+// few rows: SWIGLU, BF16 (unsplit) or PARTIAL, weights streamed past all rows
+constexpr int STREAM_ROWS = 256;
+bool gemm_stream_supported(const GemmArgs &g, int epi);
+int gemm_stream_segments(const GemmArgs &g, int n_cu, int most);      // PARTIAL: how many
+void launch_gemm_stream(const GemmArgs &g, int epi, int n_cu, hipStream_t s);
 // many rows: 256 x 256, 128 x 256 or 128 x 128 tiles, one running sum over K
 struct GemmLargePlan { int tile, splits; };      // tile: 2: 256 x 256, 1: 128 x 256, 0: 128 x 128; workgroups per output tile (> 1: PARTIAL)
 GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits);      // hint 2 / 3: tile 1 / 2
@@ -182,6 +188,6 @@ void launch_splitk_reduce(const float *part, int splits, int64_t mn, const bf16 
 // the same for whole rows plus the RMSNorm of the summed row: C = bf16(h), Cn = bf16(RMSNorm(h; gain))
 bool splitk_reduce_norm_supported(int N);
 void launch_splitk_reduce_norm(const float *part, int splits, int M, int N, const bf16 *R, const bf16 *gain, float eps,
-                               bf16 *C, bf16 *Cn, hipStream_t s);
+                               bf16 *C, bf16 *Cn, bool packed, hipStream_t s);      // packed: Cn in operand order (PrepArgs::packed)
 
 }  // namespace alora

@@ -458,3 +458,29 @@ def test_prefill_attention_around_tiles_of_keys(ab, ctx, G, splits):
     n = len(P)
     case = H.make_case(shape, P, S, [P[b] + b % 2 for b in range(n)], [b % 3 - 1 for b in range(n)], seed=1500 + G, prefix="random")
     check_case(ab, ctx, case)
+
+
+# gate/up tiles of 16, 32, 48, 56 and 64 pairs, one round or several, a partial last one; W_down streamed (whole kilobytes, up to 32 rows) or not;
+# rows around the row blocks; adapters on every linear with ranks that are no multiple of 16
+@pytest.mark.parametrize("T,inter,d,rest,rank", [(1, 1280, 512, False, 16), (32, 8192, 512, True, 8), (33, 12224, 256, False, 16), (31, 14336, 512, True, 24),
+                                                 (64, 14336, 256, False, 8), (65, 16320, 256, True, 40), (128, 14336, 256, False, 16), (129, 8192, 256, True, 8),
+                                                 (200, 14336, 256, True, 16), (256, 20032, 256, False, 16), (7, 20032, 640, True, 16), (3, 7168, 1152, True, 16)])
+def test_few_rows_through_the_streaming_linears(ab, ctx, T, inter, d, rest, rank):
+    shape = wl.LayerShape(d=d, n_q_heads=4, n_kv_heads=1, head_dim=128, rank=rank, n_adapters=3, intermediate=inter, adapt_rest=rest)
+    _one_stack_layer(ab, ctx, shape, T, 1700 + T + inter)
+
+
+@pytest.mark.parametrize("B,V,d", [(1, 1000, 512), (32, 40004, 256), (33, 1024, 1024), (200, 2052, 256)])
+def test_output_head_of_few_rows(ab, ctx, B, V, d):
+    g = torch.Generator(device="cuda").manual_seed(V + B)
+    x = torch.randn(B, d, device="cuda", generator=g).to(torch.bfloat16)
+    gain = (1 + 0.1 * torch.randn(d, device="cuda", generator=g)).to(torch.bfloat16)
+    W = (torch.randn(V, d, device="cuda", generator=g) * d ** -0.5).to(torch.bfloat16)
+    token, logits = ab.alora_lm_head(ctx, x, gain, 1e-5, W, want_logits=True)
+    torch.cuda.synchronize()
+    x64 = x.double().cpu()
+    xh = (x64 * gain.double().cpu() / torch.sqrt((x64 * x64).mean(1, keepdim=True) + 1e-5)).to(torch.bfloat16).double()
+    ref = xh @ W.double().cpu().T
+    # a row's d products of bf16 values summed in fp32, and elements of x_hat that round the other way (2^-9 of one of d terms)
+    assert H.rel_err(H.f64(logits), ref.numpy()) <= 1e-2
+    assert torch.equal(token.cpu().long(), logits.float().cpu().argmax(1))
