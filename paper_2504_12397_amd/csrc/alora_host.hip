@@ -238,6 +238,7 @@ struct Plan {
   int n_used = 0;            // adapters that a row of the call may use (at most 64 listed), and their scales
   uint8_t used[64] = {};
   float used_scale[64] = {};
+  int n_adapted = 0;         // rows (of the last step) that an adapter applies to
 };
 
 alora_status check_layer(alora_ctx *ctx, const alora_layer_desc *ly, bool need_tail, LayerDims *L) {
@@ -294,6 +295,7 @@ alora_status check_batch(alora_ctx *ctx, const alora_layer_desc *ly, const alora
   pl->any_adapter = false;
   pl->any_prefix = false;
   pl->n_used = 0;
+  pl->n_adapted = 0;
   uint64_t listed = 0;
   for (int b = 0; b < B; ++b) {
     const int S = cu[b + 1] - cu[b];
@@ -331,6 +333,7 @@ alora_status check_batch(alora_ctx *ctx, const alora_layer_desc *ly, const alora
     if (plen > 0) pl->any_prefix = true;
     if (aps[b] >= 0 && S > 0 && grown > kps[b]) {
       pl->any_adapter = true;
+      pl->n_adapted += (int)std::min<int64_t>(S, grown - kps[b]);
       if (aps[b] < 64 && !((listed >> aps[b]) & 1)) {
         listed |= 1ull << aps[b];
         pl->used[pl->n_used] = (uint8_t)aps[b];
@@ -501,6 +504,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       pa.A = rank_used ? (const bf16 *)ly->A : nullptr; pa.rank = rank_used;
       if (rank_used) {
         pa.n_used = pl.n_used;
+        pa.n_adapted = pl.n_adapted;
         memcpy(pa.used, pl.used, sizeof pa.used);
         memcpy(pa.used_scale, pl.used_scale, sizeof pa.used_scale);
       }

@@ -18,6 +18,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int PREP_ROWS = 16;
 constexpr int PREP_WAVES = 8;
 constexpr int PREP_FEW = 512;      // workgroups
+constexpr int T_NARROW = 256;      // workgroups with something to do, up to which t_rows takes 32 columns each instead of 96
 constexpr int PREP_NARROW = 128;      // up to so many of 16 columns (half of the compute units) they take 8 columns instead
 
 // Sum of squares of a row, in ONE order for every kernel that normalises rows (a row's x_hat must not depend on
@@ -176,16 +177,17 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   }
 }
 
-// Metadata and RMSNorm, 16 rows per workgroup of 16 / RW waves, RW rows per wave.  A wave takes its rows whole -- every load and
+// Metadata and RMSNorm, four waves per workgroup, RW rows per wave.  A wave takes its rows whole -- every load and
 // store instruction covers 1 KB of one row -- and the only wait besides the rows themselves is the sequences' records.  One row
-// per wave while that still fills the chip, four rows (32 KB in flight) for long calls.  Memory-bound: 21 us at 4096 rows of 4096.
+// per wave (four per workgroup, so that a few hundred rows reach every compute unit: 512 rows 12 -> 8.4 us against 16 rows per workgroup), four
+// rows (32 KB in flight) for long calls.  Memory-bound: 21 us at 4096 rows of 4096.  The first workgroup of 16 rows sees to their metadata.
 // Lane l holds the chunks c = l + 64 j: in the terms of chunk_ssq's order, a lane group of 4 CH lanes is one w.
 template <int CH, int RW>
-__global__ __launch_bounds__(64 * (PREP_ROWS / RW)) void norm_rows_kernel(PrepArgs a) {
+__global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
   __shared__ unsigned long long s_present;
-  constexpr int NT = 64 * (PREP_ROWS / RW);
+  constexpr int NT = 256;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row0 = blockIdx.x * PREP_ROWS;
+  const int row0 = blockIdx.x * (4 * RW);
   constexpr int D = CH * 256, NJ = D / 512;
   const int wrow0 = row0 + wave * RW;
   uint4 staged{};
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(64 * (PREP_ROWS / RW)) void norm_rows_kernel(PrepAr
 #pragma unroll
     for (int j = 0; j < NJ; ++j) gr[j] = *reinterpret_cast<const u32x4 *>(a.gain + lane * 8 + 512 * j);
   }
-  if (a.seqs != nullptr && a.write_meta) {
+  if (a.seqs != nullptr && a.write_meta && row0 % PREP_ROWS == 0) {
     if (tid == 0) s_present = 0ull;
     __syncthreads();
     const int tile_end = min(row0 + PREP_ROWS, a.T);
@@ -213,7 +215,7 @@ __global__ __launch_bounds__(64 * (PREP_ROWS / RW)) void norm_rows_kernel(PrepAr
       for (int mrow = lo; mrow < hi; ++mrow) fill_row_meta(a, sm, sq, mrow, row0, true, nullptr, nullptr, &s_present);
     }
     __syncthreads();
-    if (tid == 0 && a.rm.present16 != nullptr) a.rm.present16[blockIdx.x] = s_present;
+    if (tid == 0 && a.rm.present16 != nullptr) a.rm.present16[row0 / PREP_ROWS] = s_present;
   }
   constexpr int GL = 4 * CH, GW = 64 / GL;      // lanes of one w, and how many w a chunk row j of the wave covers
 #pragma unroll
@@ -243,20 +245,24 @@ __global__ __launch_bounds__(64 * (PREP_ROWS / RW)) void norm_rows_kernel(PrepAr
   if (carry) a.st.dst[tid] = staged;
 }
 
-// t of many rows from x_hat: workgroup (x, y, z) takes 32 rows, columns 96 y .. of the 3 * rank and adapter used[z]; it leaves at
-// once when no row of its tile uses that adapter.  What bounds it: 1 MB (down matrix and rows) through one compute unit, which
-// loads to registers in operand order brought in at 28 bytes per ns (36 us); requests to LDS arrive at 130.  128 values of k per
-// step, four steps in the ring; wave w multiplies the 16 values 16 w .. of a step, the eight sums are added in wave order.
+// t of many rows from x_hat: workgroup (x, y, z) takes 32 rows, columns 32 NB y .. of the 3 * rank and adapter used[z]; it leaves at
+// once when no row of its tile uses that adapter.  What bounds it: down matrix and rows through one compute unit, which
+// loads to registers in operand order brought in at 28 bytes per ns; requests to LDS arrive at 50 to 130.  So 96 columns per workgroup
+// (1 MB) only where the adapted rows would make more workgroups of 32 columns (0.5 MB) than there are compute units: 512 rows of four
+// adapters 20.5 -> 11.3 us, 1024 rows at rank 64 23 -> 17, 8131 rows of which 127 are adapted 20.5 -> 11.6; 4458 rows 24.6 with 96, 31.7 with 32.  128 values of k per
+// step, RING steps on their way; wave w multiplies the 16 values 16 w .. of a step, the eight sums are added in wave order.
 // LDS rows are 256 bytes, chunk c of row i at c ^ (i & 15); x_hat in operand order needs no rows (1 KB per 16 values of k).
-constexpr int T_STEP = 32 * 1024;
+template <int NB> struct TRows { static constexpr int STEP = (1 + NB) * 8192, RING = NB == 1 ? 8 : 4, LDS = RING * STEP > 8 * 32 * 100 * 4 ? RING * STEP : 8 * 32 * 100 * 4; };
+template <int NB>
 __global__ __launch_bounds__(512) void t_rows_kernel(PrepArgs a) {
+  constexpr int T_STEP = TRows<NB>::STEP, RING = TRows<NB>::RING;
   extern __shared__ u32x4 smem[];
   char *lds = reinterpret_cast<char *>(smem);
   typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, lhi = lane >> 5;
   const int row0 = blockIdx.x * 32, ad = a.used[blockIdx.z], cols = 3 * a.rank, d = a.d;
-  const int col0 = blockIdx.y * 96, nb = min(3, (cols - col0 + 31) / 32);
+  const int col0 = blockIdx.y * (32 * NB), nb = min(NB, (cols - col0 + 31) / 32);
   const int my_row = row0 + (tid >> 4), mine = a.rm.adapter[min(my_row, a.T - 1)];      // (of the row this thread finishes)
   const int g0 = row0 / 16, g1 = min(g0 + 1, (a.T - 1) / 16);
   if (!(((a.rm.present16[g0] | a.rm.present16[g1]) >> ad) & 1)) return;
@@ -264,46 +270,46 @@ __global__ __launch_bounds__(512) void t_rows_kernel(PrepArgs a) {
   const i32x4 rx = make_rsrc(a.xh + (int64_t)row0 * d, (uint64_t)32 * d * 2);      // (this tile's rows: offsets are 32 bits wide)
   const i32x4 rw = make_rsrc(a.A + ((int64_t)ad * cols + col0) * d, (uint64_t)(cols - col0) * d * 2);      // rows past the end: zeros
   const int r4 = lane >> 4, pos = lane & 15;
-  int vx, vw[3];
+  int vx, vw[NB];
   if (a.packed) vx = wave * 1024 + lane * 16;
   else vx = min(4 * wave + r4, a.T - 1 - row0) * d * 2 + (pos ^ ((4 * wave + r4) & 15)) * 16;
 #pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const int i = 4 * (3 * wave + j) + r4;
+  for (int j = 0; j < NB; ++j) {
+    const int i = 4 * (NB * wave + j) + r4;
     vw[j] = i * d * 2 + (pos ^ (i & 15)) * 16;
   }
   const int steps = d / 128, x_step = a.packed ? 8 * 1024 : 256;
   auto req = [&](int s) {
-    const int t = min(s, steps - 1), dst = (s & 3) * T_STEP;      // (past the end: the last step again, which nobody reads)
+    const int t = min(s, steps - 1), dst = (s & (RING - 1)) * T_STEP;      // (past the end: the last step again, which nobody reads)
     load_to_lds(rx, vx, t * x_step, dst + wave * 1024);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) load_to_lds(rw, vw[j], t * 256, dst + 8192 + (3 * wave + j) * 1024);
+    for (int j = 0; j < NB; ++j) load_to_lds(rw, vw[j], t * 256, dst + 8192 + (NB * wave + j) * 1024);
   };
-  f32x16 acc[3];
+  f32x16 acc[NB];
 #pragma unroll
-  for (int j = 0; j < 3; ++j)
+  for (int j = 0; j < NB; ++j)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
   const int at = ((2 * wave + lhi) ^ (l32 & 15)) * 16, xa = a.packed ? wave * 1024 + lane * 16 : l32 * 256 + at;
-  for (int s = 0; s < 3; ++s) req(s);
+  for (int s = 0; s < RING - 1; ++s) req(s);
   for (int s = 0; s < steps; ++s) {
-    wait_vm<8>();
+    wait_vm<(RING - 2) * (1 + NB)>();
     wave_barrier();      // step s is there, step s - 1 used up
-    const char *b = lds + (s & 3) * T_STEP;
+    const char *b = lds + (s & (RING - 1)) * T_STEP;
     const bf16x8 x = *reinterpret_cast<const bf16x8 *>(b + xa);
-    bf16x8 w[3];
+    bf16x8 w[NB];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) w[j] = *reinterpret_cast<const bf16x8 *>(b + 8192 + (32 * j + l32) * 256 + at);
-    req(s + 3);
+    for (int j = 0; j < NB; ++j) w[j] = *reinterpret_cast<const bf16x8 *>(b + 8192 + (32 * j + l32) * 256 + at);
+    req(s + RING - 1);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[j], x, acc[j], 0, 0, 0);
+    for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[j], x, acc[j], 0, 0, 0);
   }
   wait_vm<0>();
   wave_barrier();      // the ring becomes the place of the eight sums: [wave][row][100]
   // weights first: register v of lane l is column 8 (v / 4) + 4 (l / 32) + v % 4 of row l % 32
   float *part = reinterpret_cast<float *>(lds);
 #pragma unroll
-  for (int j = 0; j < 3; ++j)
+  for (int j = 0; j < NB; ++j)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       *reinterpret_cast<float4 *>(part + (wave * 32 + l32) * 100 + 32 * j + 8 * q + 4 * lhi) =
@@ -333,9 +339,15 @@ bool prep_rows_mfma_supported(int d, int rank) {
 
 template <int CH>
 static void launch_norm(const PrepArgs &a, hipStream_t s) {
-  const dim3 grid((a.T + PREP_ROWS - 1) / PREP_ROWS);
-  if (a.T <= 2048) hipLaunchKernelGGL((norm_rows_kernel<CH, 1>), grid, dim3(1024), 0, s, a);
-  else hipLaunchKernelGGL((norm_rows_kernel<CH, 4>), grid, dim3(256), 0, s, a);
+  if (a.T <= 2048) hipLaunchKernelGGL((norm_rows_kernel<CH, 1>), dim3((a.T + 3) / 4), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((norm_rows_kernel<CH, 4>), dim3((a.T + 15) / 16), dim3(256), 0, s, a);
+}
+
+template <int NB>
+static void launch_t_rows(const PrepArgs &a, hipStream_t s) {
+  auto kern = t_rows_kernel<NB>;
+  (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, TRows<NB>::LDS);
+  hipLaunchKernelGGL(kern, dim3((a.T + 31) / 32, (3 * a.rank + 32 * NB - 1) / (32 * NB), a.n_used), dim3(512), TRows<NB>::LDS, s, a);
 }
 
 template <int CH>
@@ -350,8 +362,8 @@ static void launch_prep_ch(const PrepArgs &a, hipStream_t s) {
       hipLaunchKernelGGL((prep_few_kernel<CH, 16>), dim3(row_tiles, cols16, a.n_used), dim3(512), 0, s, a);
   } else {
     launch_norm<CH>(a, s);
-    (void)hipFuncSetAttribute((const void *)t_rows_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * T_STEP);
-    hipLaunchKernelGGL(t_rows_kernel, dim3((a.T + 31) / 32, (3 * a.rank + 95) / 96, a.n_used), dim3(512), 4 * T_STEP, s, a);
+    if ((a.n_adapted + 31) / 32 * ((3 * a.rank + 31) / 32) <= T_NARROW) launch_t_rows<1>(a, s);
+    else launch_t_rows<3>(a, s);
   }
 }
 

@@ -484,3 +484,13 @@ def test_output_head_of_few_rows(ab, ctx, B, V, d):
     # a row's d products of bf16 values summed in fp32, and elements of x_hat that round the other way (2^-9 of one of d terms)
     assert H.rel_err(H.f64(logits), ref.numpy()) <= 1e-2
     assert torch.equal(token.cpu().long(), logits.float().cpu().argmax(1))
+
+
+# 96 columns per workgroup (many adapted rows) or 32; 3 * rank columns that end inside a tile of either
+@pytest.mark.parametrize("rank,T", [(64, 3000), (40, 5200), (24, 700), (64, 2800)])
+def test_down_projection_of_many_adapted_rows(ab, ctx, rank, T):
+    ctx.set_option("prep_split", 0)
+    shape = wl.LayerShape(d=512, n_q_heads=2, n_kv_heads=1, head_dim=128, rank=rank, n_adapters=3)
+    S = _split(T, 3)
+    case = H.make_case(shape, [5] * 3, S, [5, 5 + S[1] // 2, 5], [0, 2, 1], seed=1900 + rank + T, prefix="random")
+    check_case(ab, ctx, case)
