@@ -1041,6 +1041,45 @@ struct PrefillPlan {
   std::vector<PrefixRun> runs;
   int n_own = 1, n_sh = 0;
 };
+// What cutting the keys in n_own / n_sh ranges would take, in 64-key tiles of one workgroup: an eighth of the items on an XCD, one at a
+// time on a compute unit, longest first, each PREFILL_ITEM_TILES long besides its keys (first tiles, queries, result), and the records
+// that the merge then reads.  (Lengths in 64 classes: a few microseconds of host time for all the cuts of a call.)
+constexpr int PREFILL_ITEM_TILES = 5;
+double prefill_cut_tiles(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, int tq, const PrefillPlan &pp, int longest, int n_own, int n_sh) {
+  int len[64] = {}, count[64] = {};
+  int64_t work = 0, rows = 0;
+  auto add = [&](int l, int n) {
+    if (n <= 0) return;
+    const int c = (int)((int64_t)l * 63 / longest);
+    len[c] = std::max(len[c], l);
+    count[c] += n;
+    work += (int64_t)n * (l + PREFILL_ITEM_TILES);
+  };
+  auto cut = [&](int keys, int parts, int q_tiles) {      // q_tiles row tiles against the ranges of so many keys
+    const int chunk = std::max(1, ((keys + parts - 1) / parts + 63) / 64), t = (keys + 63) / 64, whole = t / chunk;
+    add(chunk, whole * q_tiles);
+    if (t > whole * chunk) add(t - whole * chunk, q_tiles);
+    add(0, (parts - whole - (t > whole * chunk ? 1 : 0)) * q_tiles);
+  };
+  for (const SeqMeta &m : pl.seqs) {
+    if (m.n_new <= 0) continue;
+    rows += m.n_new;
+    cut(m.P + m.n_new - m.prefix_len, m.prefix_len > 0 ? n_own : n_own + n_sh, (m.n_new + tq - 1) / tq);
+  }
+  for (const PrefixRun &r : pp.runs) cut(r.prefix_len, n_sh, (r.n_rows + tq - 1) / tq);
+  // no schedule ends before its rounds of the longest items do, or before the work is done
+  const double cus = ctx->n_cu / 8.0, per = L.n_kv_heads / 8.0;
+  double worst = (double)work * per / cus, n = 0;
+  for (int c = 63; c >= 0; --c) {
+    if (count[c] == 0) continue;
+    n += count[c] * per;
+    worst = std::max(worst, std::ceil(n / cus) * (len[c] + PREFILL_ITEM_TILES));
+  }
+  // (a tile is about 1.7 us; a record of 272 bytes is written and read at about 4 TB/s, and the merge is a launch)
+  if (n_own + n_sh > 1) worst += 2.0 + (double)rows * (n_own + n_sh) * L.n_q_heads * (2 * 272) / 4e6 / 1.7;
+  return worst;
+}
+
 PrefillPlan plan_prefill_ranges(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, int B, int attn_waves) {
   PrefillPlan pp;
   const int tq = attn_prefill_mfma_tokens_per_tile(L, attn_waves);
@@ -1059,30 +1098,28 @@ PrefillPlan plan_prefill_ranges(const alora_ctx *ctx, const Plan &pl, const Laye
     else
       pp.runs.push_back(PrefixRun{m.prefix_off, m.prefix_len, m.row_start, m.n_new});
   }
-  if (pp.runs.empty()) {
-    // aim at one full wave of workgroups over the chip, with at least 256 keys per range
-    tiles *= L.n_kv_heads;
-    const int want = (int)std::min<int64_t>(16, std::max<int64_t>(1, ctx->n_cu / std::max<int64_t>(tiles, 1)));
-    pp.n_own = ctx->opt_splits > 0 ? ctx->opt_splits : std::max(1, std::min(want, pl.max_len / 256));
+  if (ctx->opt_splits > 0) {
+    pp.n_own = ctx->opt_splits;
+    pp.n_sh = pp.runs.empty() ? 0 : ctx->opt_splits;
     return pp;
   }
-  // The work is uneven (long contexts walked by few packed tiles, short own parts walked by many): size the
-  // ranges by work.  One unit = one 64-key tile of one workgroup; aim at two workgroups per compute unit of
-  // equal length, at least four tiles each.
-  int64_t units = 0;
-  for (int b = 0; b < B; ++b) {
-    const SeqMeta &m = pl.seqs[b];
-    for (int q0 = 0; q0 < m.n_new; q0 += tq) units += (m.P + std::min(m.n_new, q0 + tq) - m.prefix_len + 63) / 64;
+  // Ranges of at least four tiles, at most 16, the cut that takes the least.  Before, ranges were as long as two items per compute unit (shared
+  // prefixes) or one (no prefix) would have them: 32 x 16 rows on four contexts of 16384 keys 249 -> 224 us with one range per unit instead
+  // of two, eight sequences of 128 rows on 32768 keys 4285 -> 4228 (four layers).
+  // (and at most 2^20 records of a kind: half a gigabyte)
+  const int longest = std::max(max_own, max_pfx), most = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(16, longest / 256), (1 << 20) / ((int64_t)pl.T * L.n_q_heads)));
+  if (pp.runs.empty() && tiles * L.n_kv_heads >= 4 * (int64_t)ctx->n_cu) return pp;      // more items than could be evened out by cutting them
+  double least = 0;
+  int was_own = 0, was_sh = 0;
+  for (int n = 1; n <= most; ++n) {
+    const int len = std::max(4, ((longest + 63) / 64 + n - 1) / n);      // tiles of a range
+    auto ranges = [&](int keys) { return std::max(1, std::min(16, ((keys + 63) / 64 + len - 1) / len)); };
+    const int own = ranges(max_own), sh = pp.runs.empty() ? 0 : ranges(max_pfx);
+    if (own == was_own && sh == was_sh) continue;
+    was_own = own; was_sh = sh;
+    const double t = prefill_cut_tiles(ctx, pl, L, tq, pp, (longest + 63) / 64, own, sh);
+    if (n == 1 || t < least) { least = t; pp.n_own = own; pp.n_sh = sh; }
   }
-  for (const PrefixRun &r : pp.runs) units += (int64_t)((r.n_rows + tq - 1) / tq) * ((r.prefix_len + 63) / 64);
-  units *= L.n_kv_heads;
-  const int64_t target = std::max<int64_t>(4, units / (2 * (int64_t)ctx->n_cu));
-  auto ranges = [&](int longest) {
-    if (ctx->opt_splits > 0) return ctx->opt_splits;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(16, ((longest + 63) / 64 + target - 1) / target));
-  };
-  pp.n_own = ranges(max_own);
-  pp.n_sh = ranges(max_pfx);
   return pp;
 }
 
