@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
   if (carry) a.st.dst[tid] = staged;
 }
 
-// t of many rows from x_hat: workgroup (x, y, z) takes 32 rows, columns 32 NB y .. of the 3 * rank and adapter used[z]; it leaves at
+// t of many rows from x_hat (or from the input of another linear with `parts` down-matrices): workgroup (x, y, z) takes 32 rows, columns 32 NB y .. of the parts * rank and adapter used[z]; it leaves at
 // once when no row of its tile uses that adapter.  What bounds it: down matrix and rows through one compute unit, which
 // loads to registers in operand order brought in at 28 bytes per ns; requests to LDS arrive at 50 to 130.  So 96 columns per workgroup
 // (1 MB) only where the adapted rows would make more workgroups of 32 columns (0.5 MB) than there are compute units: 512 rows of four
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(512) void t_rows_kernel(PrepArgs a) {
   typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, lhi = lane >> 5;
-  const int row0 = blockIdx.x * 32, ad = a.used[blockIdx.z], cols = 3 * a.rank, d = a.d;
+  const int row0 = blockIdx.x * 32, ad = a.used[blockIdx.z], cols = a.parts * a.rank, d = a.d;
   const int col0 = blockIdx.y * (32 * NB), nb = min(NB, (cols - col0 + 31) / 32);
   const int my_row = row0 + (tid >> 4), mine = a.rm.adapter[min(my_row, a.T - 1)];      // (of the row this thread finishes)
   const int g0 = row0 / 16, g1 = min(g0 + 1, (a.T - 1) / 16);
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(512) void t_rows_kernel(PrepArgs a) {
     if (my_row < a.T && col < cols && mine == ad) {
       const int p = col / rank, jj = col % rank;
       const bf16 hi = (bf16)t;
-      bf16 *dst = a.tlow16 + (((int64_t)my_row * 3 + p) * 2) * rank + jj;
+      bf16 *dst = a.tlow16 + (((int64_t)my_row * a.parts + p) * 2) * rank + jj;
       dst[0] = hi;
       dst[rank] = (bf16)(t - (float)hi);
     }
@@ -347,7 +347,14 @@ template <int NB>
 static void launch_t_rows(const PrepArgs &a, hipStream_t s) {
   auto kern = t_rows_kernel<NB>;
   (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, TRows<NB>::LDS);
-  hipLaunchKernelGGL(kern, dim3((a.T + 31) / 32, (3 * a.rank + 32 * NB - 1) / (32 * NB), a.n_used), dim3(512), TRows<NB>::LDS, s, a);
+  hipLaunchKernelGGL(kern, dim3((a.T + 31) / 32, (a.parts * a.rank + 32 * NB - 1) / (32 * NB), a.n_used), dim3(512), TRows<NB>::LDS, s, a);
+}
+
+bool t_rows_mfma_supported(const PrepArgs &a) { return a.d % 128 == 0 && lds_aligned(a.A) && lds_aligned(a.xh); }
+
+void launch_t_rows_mfma(const PrepArgs &a, hipStream_t s) {
+  if ((a.n_adapted + 31) / 32 * ((a.parts * a.rank + 31) / 32) <= T_NARROW) launch_t_rows<1>(a, s);
+  else launch_t_rows<3>(a, s);
 }
 
 template <int CH>
@@ -362,8 +369,7 @@ static void launch_prep_ch(const PrepArgs &a, hipStream_t s) {
       hipLaunchKernelGGL((prep_few_kernel<CH, 16>), dim3(row_tiles, cols16, a.n_used), dim3(512), 0, s, a);
   } else {
     launch_norm<CH>(a, s);
-    if ((a.n_adapted + 31) / 32 * ((3 * a.rank + 31) / 32) <= T_NARROW) launch_t_rows<1>(a, s);
-    else launch_t_rows<3>(a, s);
+    launch_t_rows_mfma(a, s);
   }
 }
 

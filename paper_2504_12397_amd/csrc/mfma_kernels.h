@@ -61,6 +61,7 @@ struct PrepArgs {
   int pos_shift;            // added to every position (step index of a multi-step decode)
   const bf16 *A;            // [n_adapters, 3, rank, d] or nullptr
   int rank;
+  int parts;                // down-matrices per adapter (3: q | k | v)
   int n_used;               // the adapters that rows of this call may use ...
   uint8_t used[64];         // ... their ids and their scales s_a
   float used_scale[64];
@@ -78,6 +79,9 @@ __device__ __forceinline__ int64_t xh_chunk(int row, int c, int d, int packed) {
 }
 bool prep_rows_mfma_supported(int d, int rank);
 void launch_prep_rows_mfma(const PrepArgs &a, hipStream_t s);
+// t alone, from rows (xh, packed) whose adapters a call of the above has written (rm): any d that is a multiple of 128
+bool t_rows_mfma_supported(const PrepArgs &a);
+void launch_t_rows_mfma(const PrepArgs &a, hipStream_t s);
 // One workgroup of the prefill attention kernel: up to 256/G consecutive packed rows (tokens) against the key
 // positions [kbeg, kend) of one kv head, counted from pool row key_row0.  Own rows of one sequence: key_row0 is
 // its first own row, pos0 the position of the first token counted from there, and the causal mask applies.
