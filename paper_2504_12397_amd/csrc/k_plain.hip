@@ -118,12 +118,26 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const T *__restrict__ x,
   const int a = s_adapter;
   if (a < 0 || rank == 0) return;
   const float scale = s_scale;
-  for (int j = wave; j < 3 * rank; j += 4) {
-    const T *ar = A + ((int64_t)a * 3 * rank + j) * d;
-    float acc = 0.f;
-    for (int c = lane; c < d; c += 64) acc += to_f32<T>(ar[c]) * xs[c];
-    acc = wave_sum(acc);
-    if (lane == 0) {
+  // eight columns of t at a time, their loads together: one after the other, the round trips were most of a small call's first kernel
+  // (16 rows of rank 8, d = 256: 9.6 -> 6.1 us)
+  constexpr int U = 8;
+  for (int j0 = wave; j0 < 3 * rank; j0 += 4 * U) {
+    const T *ar = A + (int64_t)a * 3 * rank * d;
+    int64_t at[U];
+    float sum[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) { at[u] = (int64_t)min(j0 + 4 * u, 3 * rank - 1) * d; sum[u] = 0.f; }
+#pragma unroll 4
+    for (int c = lane; c < d; c += 64)
+#pragma unroll
+      for (int u = 0; u < U; ++u) sum[u] += to_f32<T>(ar[at[u] + c]) * xs[c];
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum[u] = wave_sum(sum[u]);
+    if (lane < U && j0 + 4 * lane < 3 * rank) {
+      const int j = j0 + 4 * lane;
+      float acc = sum[0];
+#pragma unroll
+      for (int u = 1; u < U; ++u) acc = lane == u ? sum[u] : acc;
       const float t = scale * acc;
       if (tlow16) {
         // bf16 pair (hi, lo) with hi + lo = t to ~2^-17: the MFMA path feeds both as extra k-steps,
@@ -266,6 +280,24 @@ __global__ __launch_bounds__(256) void qkv_small_plain_kernel(const T *__restric
   };
   float acc = 0.f;
   fetch(0);
+  // the low-rank term's operands, eight ranks ahead of their use, the first ones before the product
+  constexpr int RA = 8;
+  const int rk = a >= 0 ? epi.rank : 0;
+  const T *bp = (const T *)epi.Bq;
+  const float *tp = epi.tlow;
+  if (rk > 0) {
+    bp = kind == 0 ? (const T *)epi.Bq + ((int64_t)a * L.n_q + col) * rk
+                   : (kind == 1 ? (const T *)epi.Bk + ((int64_t)a * L.n_kv + col - L.n_q) * rk
+                                : (const T *)epi.Bv + ((int64_t)a * L.n_kv + col - L.n_q - L.n_kv) * rk);
+    tp = epi.tlow + (int64_t)rc * 3 * rk + kind * rk;
+  }
+  float tv[RA];
+  T bv[RA];
+  auto fetch_low = [&](int j0) {
+#pragma unroll
+    for (int i = 0; i < RA; ++i) { tv[i] = tp[min(j0 + i, rk - 1)]; bv[i] = bp[min(j0 + i, rk - 1)]; }
+  };
+  if (rk > 0) fetch_low(0);
   for (int k0 = 0; k0 < K; k0 += KC) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) { xs[r][c + 16 * i] = xv[i]; ws[r][c + 16 * i] = wv[i]; }
@@ -281,14 +313,14 @@ __global__ __launch_bounds__(256) void qkv_small_plain_kernel(const T *__restric
     }
     __syncthreads();
   }
-  if (a >= 0) {
-    const int rk = epi.rank;
-    const T *bp = kind == 0 ? (const T *)epi.Bq + ((int64_t)a * L.n_q + col) * rk
-                            : (kind == 1 ? (const T *)epi.Bk + ((int64_t)a * L.n_kv + col - L.n_q) * rk
-                                         : (const T *)epi.Bv + ((int64_t)a * L.n_kv + col - L.n_q - L.n_kv) * rk);
-    const float *t = epi.tlow + (int64_t)rc * 3 * rk + kind * rk;
+  if (rk > 0) {
     float lo = 0.f;
-    for (int jj = 0; jj < rk; ++jj) lo += t[jj] * to_f32<T>(bp[jj]);
+    for (int j0 = 0; j0 < rk; j0 += RA) {
+      if (j0 > 0) fetch_low(j0);
+#pragma unroll
+      for (int i = 0; i < RA; ++i)
+        if (j0 + i < rk) lo += tv[i] * to_f32<T>(bv[i]);
+    }
     acc += lo;
   }
   const float other = __shfl_xor(acc, 8, 64);      // the rotation partner
@@ -464,15 +496,21 @@ template void launch_rope_append<bf16>(const float *, int, const LayerDims &, Ro
 #define ATT_GMAX 8
 #define ATT_DMAX 4     // head_dim <= 256
 
-template <typename T> __device__ __forceinline__ float4 load4(const T *p);
-template <> __device__ __forceinline__ float4 load4<float>(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-template <> __device__ __forceinline__ float4 load4<bf16>(const bf16 *p) {
-  const uint2 w = *reinterpret_cast<const uint2 *>(p);
-  return make_float4(__builtin_bit_cast(float, w.x << 16), __builtin_bit_cast(float, w.x & 0xffff0000u),
-                     __builtin_bit_cast(float, w.y << 16), __builtin_bit_cast(float, w.y & 0xffff0000u));
-}
+// four neighbouring elements and one, as they lie in memory
+template <typename T> struct Raw;
+template <> struct Raw<float> { typedef float4 Four; static __device__ __forceinline__ float4 f4(float4 v) { return v; } };
+template <> struct Raw<bf16> {
+  typedef uint2 Four;
+  static __device__ __forceinline__ float4 f4(uint2 w) {
+    return make_float4(__builtin_bit_cast(float, w.x << 16), __builtin_bit_cast(float, w.x & 0xffff0000u),
+                       __builtin_bit_cast(float, w.y << 16), __builtin_bit_cast(float, w.y & 0xffff0000u));
+  }
+};
 
-template <typename T, bool VEC>      // VEC: head_dim is a multiple of 16
+// GM: most query heads of a workgroup (G = 1: a third of the code).  DD: 64-column pieces of a head that is a multiple of 16, 0: any head size (column by column, nothing asked for ahead).  A tile's keys
+// are asked for while the tile before it is multiplied with its values, its values while its own scores are computed: a small call has
+// one or two tiles, and every round trip was waited for on its own (16 rows, 80 keys of 64: 14.1 -> 7.5 us).
+template <typename T, int DD, int GM>
 __global__ __launch_bounds__(256) void attn_partial_kernel(const float *__restrict__ Q, const T *__restrict__ cacheK,
                                                           const T *__restrict__ cacheV,
                                                           const SeqMeta *__restrict__ seqs, RowMeta rm,
@@ -496,41 +534,64 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float *__restri
   const float sm_scale = 1.0f / sqrtf((float)h);
   for (int i = tid; i < ng * h; i += 256) qs[i] = Q[(int64_t)row * L.n_q + (g * G + g0) * h + i] * sm_scale;
   float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};      // of heads wave and wave + 4
-  float acc[ATT_GMAX][ATT_DMAX];
+  constexpr int D1 = DD > 0 ? DD : 1, DA = DD > 0 ? DD : ATT_DMAX;
+  float acc[GM][DA];
 #pragma unroll
-  for (int gi = 0; gi < ATT_GMAX; ++gi)
+  for (int gi = 0; gi < GM; ++gi)
 #pragma unroll
-    for (int dd = 0; dd < ATT_DMAX; ++dd) acc[gi][dd] = 0.f;
+    for (int dd = 0; dd < DA; ++dd) acc[gi][dd] = 0.f;
+  typename Raw<T>::Four kf[4 * D1];
+  T vf[16][D1];
+  auto ask_k = [&](int t0) {
+    const T *kr = cacheK + seq_pool_row(sm, min(t0 + (tid >> 2), end - 1)) * L.n_kv + g * h + 4 * (tid & 3);
+#pragma unroll
+    for (int i = 0; i < 4 * D1; ++i)
+      if (16 * i < h) kf[i] = *reinterpret_cast<const typename Raw<T>::Four *>(kr + 16 * i);
+  };
+  auto ask_v = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const T *vr = cacheV + seq_pool_row(sm, min(t0 + wave + 4 * i, end - 1)) * L.n_kv + g * h;
+#pragma unroll
+      for (int dd = 0; dd < D1; ++dd)
+        if (lane + 64 * dd < h) vf[i][dd] = vr[lane + 64 * dd];
+    }
+  };
+  if constexpr (DD > 0) {
+    if (begin < end) { ask_k(begin); ask_v(begin); }
+  }
   __syncthreads();
   for (int t0 = begin; t0 < end; t0 += 64) {
     {
       const int key = t0 + (tid >> 2), q4 = tid & 3;
-      const T *kr = cacheK + seq_pool_row(sm, min(key, end - 1)) * L.n_kv + g * h;
-      float sc[ATT_GMAX];
+      float sc[GM];
 #pragma unroll
-      for (int gi = 0; gi < ATT_GMAX; ++gi) sc[gi] = 0.f;
-      if constexpr (VEC) {
-#pragma unroll 4
-        for (int c = 4 * q4; c < h; c += 16) {
-          const float4 kv = load4<T>(kr + c);
+      for (int gi = 0; gi < GM; ++gi) sc[gi] = 0.f;
+      if constexpr (DD > 0) {
 #pragma unroll
-          for (int gi = 0; gi < ATT_GMAX; ++gi)
-            if (gi < ng) {
-              const float4 qv = *reinterpret_cast<const float4 *>(qs + gi * h + c);
+        for (int i = 0; i < 4 * D1; ++i) {
+          if (16 * i >= h) break;
+          const float4 kv = Raw<T>::f4(kf[i]);
+#pragma unroll
+          for (int gi = 0; gi < GM; ++gi)
+            if (GM == 1 || gi < ng) {
+              const float4 qv = *reinterpret_cast<const float4 *>(qs + gi * h + 4 * q4 + 16 * i);
               sc[gi] += qv.x * kv.x + qv.y * kv.y + qv.z * kv.z + qv.w * kv.w;
             }
         }
+        if (t0 + 64 < end) ask_k(t0 + 64);
       } else {
+        const T *kr = cacheK + seq_pool_row(sm, min(key, end - 1)) * L.n_kv + g * h;
         for (int c = q4; c < h; c += 4) {
           const float kv = to_f32<T>(kr[c]);
 #pragma unroll
-          for (int gi = 0; gi < ATT_GMAX; ++gi)
-            if (gi < ng) sc[gi] += qs[gi * h + c] * kv;
+          for (int gi = 0; gi < GM; ++gi)
+            if (GM == 1 || gi < ng) sc[gi] += qs[gi * h + c] * kv;
         }
       }
 #pragma unroll
-      for (int gi = 0; gi < ATT_GMAX; ++gi)
-        if (gi < ng) {
+      for (int gi = 0; gi < GM; ++gi)
+        if (GM == 1 || gi < ng) {
           float v = sc[gi] + __shfl_xor(sc[gi], 1, 64);
           v += __shfl_xor(v, 2, 64);
           if (q4 == 0) ps[gi * 64 + (tid >> 2)] = key < end ? v : -INFINITY;
@@ -540,7 +601,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float *__restri
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int gi = wave + 4 * u;
-      if (gi < ng) {
+      if (GM == 1 || gi < ng) {
         const float s = ps[gi * 64 + lane];
         const float mn = fmaxf(m[u], wave_max(s));
         const float p = __expf(s - mn), corr = __expf(m[u] - mn);      // (every tile holds a valid key: mn is finite)
@@ -552,22 +613,39 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float *__restri
     }
     __syncthreads();
 #pragma unroll
-    for (int gi = 0; gi < ATT_GMAX; ++gi)
-      if (gi < ng)
+    for (int gi = 0; gi < GM; ++gi)
+      if (GM == 1 || gi < ng)
 #pragma unroll
-        for (int dd = 0; dd < ATT_DMAX; ++dd) acc[gi][dd] *= s_corr[gi];
+        for (int dd = 0; dd < DA; ++dd) acc[gi][dd] *= s_corr[gi];
     const int nk = min(64, end - t0);
+    if constexpr (DD > 0) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int j = wave + 4 * i;
+        if (j >= nk) break;
+#pragma unroll
+        for (int dd = 0; dd < D1; ++dd)
+          if (lane + 64 * dd < h) {
+            const float vv = to_f32<T>(vf[i][dd]);
+#pragma unroll
+            for (int gi = 0; gi < GM; ++gi)
+              if (GM == 1 || gi < ng) acc[gi][dd] += ps[gi * 64 + j] * vv;
+          }
+      }
+      if (t0 + 64 < end) ask_v(t0 + 64);
+    } else {
 #pragma unroll 8
-    for (int j = wave; j < nk; j += 4) {
-      const T *vr = cacheV + seq_pool_row(sm, t0 + j) * L.n_kv + g * h;
+      for (int j = wave; j < nk; j += 4) {
+        const T *vr = cacheV + seq_pool_row(sm, t0 + j) * L.n_kv + g * h;
 #pragma unroll
-      for (int dd = 0; dd < ATT_DMAX; ++dd) {
-        const int c = lane + 64 * dd;
-        if (c < h) {
-          const float vv = to_f32<T>(vr[c]);
+        for (int dd = 0; dd < DA; ++dd) {
+          const int c = lane + 64 * dd;
+          if (c < h) {
+            const float vv = to_f32<T>(vr[c]);
 #pragma unroll
-          for (int gi = 0; gi < ATT_GMAX; ++gi)
-            if (gi < ng) acc[gi][dd] += ps[gi * 64 + j] * vv;
+            for (int gi = 0; gi < GM; ++gi)
+              if (GM == 1 || gi < ng) acc[gi][dd] += ps[gi * 64 + j] * vv;
+          }
         }
       }
     }
@@ -577,10 +655,10 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float *__restri
   for (int u = 0; u < 2; ++u)
     if (wave + 4 * u < ng && lane == 0) { s_m[wave + 4 * u] = m[u]; s_l[wave + 4 * u] = l[u]; }
 #pragma unroll
-  for (int gi = 0; gi < ATT_GMAX; ++gi)
-    if (gi < ng)
+  for (int gi = 0; gi < GM; ++gi)
+    if (GM == 1 || gi < ng)
 #pragma unroll
-      for (int dd = 0; dd < ATT_DMAX; ++dd)
+      for (int dd = 0; dd < DA; ++dd)
         if (lane + 64 * dd < h) smem[(wave * ng + gi) * h + lane + 64 * dd] = acc[gi][dd];
   __syncthreads();
   for (int i = tid; i < ng * h; i += 256) {
@@ -714,10 +792,12 @@ void launch_attn_plain(const float *Q, const T *cacheK, const T *cacheV, const S
   dim3 grid(T_rows * L.n_kv_heads, n_splits, (G + ATT_GMAX - 1) / ATT_GMAX);
   const size_t tile = (size_t)(ATT_GMAX * L.head_dim + ATT_GMAX * 64), sums = (size_t)4 * ng * L.head_dim;
   const size_t smem = (tile > sums ? tile : sums) * sizeof(float);
-  if (L.head_dim % 16 == 0)
-    hipLaunchKernelGGL((attn_partial_kernel<T, true>), grid, dim3(256), smem, s, Q, cacheK, cacheV, seqs, rm, L, n_splits, partials, out);
-  else
-    hipLaunchKernelGGL((attn_partial_kernel<T, false>), grid, dim3(256), smem, s, Q, cacheK, cacheV, seqs, rm, L, n_splits, partials, out);
+  auto of_heads = [&](auto one, auto four, auto more) { return ng == 1 ? one : ng <= 4 ? four : more; };
+  auto kern = L.head_dim % 16 != 0 ? attn_partial_kernel<T, 0, 8>
+              : L.head_dim <= 64   ? of_heads(attn_partial_kernel<T, 1, 1>, attn_partial_kernel<T, 1, 4>, attn_partial_kernel<T, 1, 8>)
+              : L.head_dim <= 128  ? of_heads(attn_partial_kernel<T, 2, 1>, attn_partial_kernel<T, 2, 4>, attn_partial_kernel<T, 2, 8>)
+                                   : of_heads(attn_partial_kernel<T, 4, 1>, attn_partial_kernel<T, 4, 4>, attn_partial_kernel<T, 4, 8>);
+  hipLaunchKernelGGL(kern, grid, dim3(256), smem, s, Q, cacheK, cacheV, seqs, rm, L, n_splits, partials, out);
 }
 template void launch_attn_plain<float>(const float *, const float *, const float *, const SeqMeta *, RowMeta,
                                        const LayerDims &, int, int, float *, float *, hipStream_t);
