@@ -427,8 +427,9 @@ int pick_splits(const alora_ctx *ctx, int T, int n_kv_heads, int max_len) {
   return std::max(1, std::min(want, max_by_len));
 }
 
+// (T_attn: rows that attend together, where that is fewer than are projected together)
 Workspace layout_workspace(char *base, const LayerDims &L, int T, size_t esz, int n_splits, int k_splits,
-                           int intermediate, bool stack, bool f32_tail = false) {
+                           int intermediate, bool stack, bool f32_tail = false, int T_attn = 0) {
   Bump b(base);
   Workspace w{};
   w.rm.seq = b.take<int32_t>(T);
@@ -445,7 +446,7 @@ Workspace layout_workspace(char *base, const LayerDims &L, int T, size_t esz, in
   }
   w.Y = b.take<float>(w.y_floats);
   w.Q = b.take<char>((size_t)T * L.n_q * 4);      // fp16 for the MFMA attention kernels, fp32 for the plain one
-  w.partials = b.take<float>(attn_plain_partial_floats(L, T, n_splits));
+  w.partials = b.take<float>(attn_plain_partial_floats(L, T_attn > 0 ? T_attn : T, n_splits));
   if (stack) {
     w.attn = b.take<char>((size_t)T * L.n_q * esz);
     w.h1 = b.take<char>((size_t)T * L.d * esz);
@@ -464,21 +465,29 @@ Workspace layout_workspace(char *base, const LayerDims &L, int T, size_t esz, in
   return w;
 }
 
-// One attention block on already-staged metadata: rows -> projections -> rotation/append ->
-// attention.  write_meta is false for layers after the first of a stack (same rows).
+// How the queries are stored between projection and attention.
+// The MFMA attention kernels (prefill and decode) take them as fp16 (every operand of their matrix products is fp16), prefill
+// in its folded-softmax form premultiplied by sm_scale * log2(e); the plain attention kernel reads them as fp32 (the Q buffer holds
+// four bytes per element).
+struct QueryForm { bool half; float scale; };
+template <typename T> QueryForm query_form(const alora_ctx *ctx, const LayerDims &L, const Workspace &w) {
+  const bool half = (w.attn_mfma || w.decode_mfma) && std::is_same<T, bf16>::value;
+  return QueryForm{half, (w.attn_mfma && half) ? attn_prefill_mfma_q_scale(L, ctx->opt_attn_fold != 0) : 1.0f};
+}
+
+// The first half of an attention block on already-staged metadata: rows -> projections -> rotation/append.
+// write_meta is false for layers after the first of a stack (same rows).
 template <typename T>
-void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, const alora_kv_cache *cache,
-                     const T *x, const Plan &pl, const SeqMeta *seqs_dev, const Workspace &w, bool write_meta,
-                     int n_splits, bool decode, int pos_shift, T *out, hipStream_t s) {
+void project_rows(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, const alora_kv_cache *cache,
+                  const T *x, const Plan &pl, const SeqMeta *seqs_dev, const Workspace &w, bool write_meta,
+                  int pos_shift, hipStream_t s) {
   const bool mfma = w.mfma && std::is_same<T, bf16>::value;
   const int rank_used = pl.any_adapter ? L.rank : 0;
   const bool prep_mfma = mfma && prep_rows_mfma_supported(L.d, rank_used);      // it also leaves the adapter masks
-  // the MFMA attention kernels (prefill and decode) take their queries as fp16 (every operand of its matrix products is fp16),
-  // in its folded-softmax form premultiplied by sm_scale * log2(e)
-  // (the plain attention kernel reads them as fp32: the Q buffer holds four bytes per element)
-  const bool q_half = (w.attn_mfma || w.decode_mfma) && std::is_same<T, bf16>::value;
+  const QueryForm qf = query_form<T>(ctx, L, w);
+  const bool q_half = qf.half;
   const int q_mode = q_half ? 1 : 2;
-  const float q_scale = (w.attn_mfma && q_half) ? attn_prefill_mfma_q_scale(L, ctx->opt_attn_fold != 0) : 1.0f;
+  const float q_scale = qf.scale;
   // The projection rotates and appends by itself: up to stream_rows rows in the kernel that streams the weights past all rows,
   // beyond that, where a head is 128 columns, in the one whose tiles are large in both directions (both add in one order), or in the
   // 128 x 128 block of four waves, which also adds segments.
@@ -571,6 +580,14 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
     launch_rope_append<T>(w.Y, mfma ? w.k_splits + (lora_split ? 1 : 0) : 1, L, w.rm, pl.T, w.rope, w.rope_by_row, q_scale, q_mode, w.Q,
                           (T *)cache->k, (T *)cache->v, s);
   }
+}
+
+// The second half: attention of pl's rows, whose queries and metadata begin at row `row0` of the workspace's.
+template <typename T>
+void attend_rows(alora_ctx *ctx, const LayerDims &L, const alora_kv_cache *cache, const Plan &pl, const SeqMeta *seqs_dev, const Workspace &w,
+                 int n_splits, bool decode, int pos_shift, int row0, T *out, hipStream_t s) {
+  const QueryForm qf = query_form<T>(ctx, L, w);
+  const void *Q = (const char *)w.Q + (size_t)row0 * L.n_q * (qf.half ? 2 : 4);
   const bool mfma_attn = std::is_same<T, bf16>::value && (w.attn_mfma || w.decode_mfma);
   const bool direct = n_splits == 1 && (mfma_attn ? w.attn_mfma : true);
   // split prefill attention on the MFMA path: partial results travel in the compact record
@@ -579,13 +596,13 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
     ProfScope p(ctx, decode ? K_ATTN_DECODE : K_ATTN_PREFILL, s);
     if (w.attn_mfma && std::is_same<T, bf16>::value) {
       AttnArgs a{};
-      a.Q = (const _Float16 *)w.Q; a.K = (const bf16 *)cache->k; a.V = (const bf16 *)cache->v;
+      a.Q = (const _Float16 *)Q; a.K = (const bf16 *)cache->k; a.V = (const bf16 *)cache->v;
       a.work = w.qtiles;
       a.n_q = L.n_q; a.n_kv = L.n_kv; a.n_q_heads = L.n_q_heads; a.n_kv_heads = L.n_kv_heads;
       a.n_parts = n_splits;
       a.sm_scale = 1.0f / sqrtf((float)L.head_dim);
       a.lazy = (float)ctx->opt_attn_lazy;
-      a.q_prescaled = q_scale != 1.0f;
+      a.q_prescaled = qf.scale != 1.0f;
       a.partials = direct ? nullptr : w.partials;
       a.compact = compact16 ? 1 : 0;
       a.out = direct ? (bf16 *)out : nullptr;
@@ -597,7 +614,7 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       launch_attn_prefill_mfma(a, w.n_qtiles, L.n_q_heads / L.n_kv_heads, w.attn_waves, generic_addr, s);
     } else if (w.decode_mfma && std::is_same<T, bf16>::value) {
       DecodeArgs a{};
-      a.Q = (const _Float16 *)w.Q; a.K = (const bf16 *)cache->k; a.V = (const bf16 *)cache->v;
+      a.Q = (const _Float16 *)Q; a.K = (const bf16 *)cache->k; a.V = (const bf16 *)cache->v;
       a.n_q = L.n_q; a.n_kv = L.n_kv; a.n_q_heads = L.n_q_heads; a.n_kv_heads = L.n_kv_heads;
       a.items = w.ditems; a.rows = w.drows; a.pos_shift = pos_shift;
       a.n_parts = n_splits;
@@ -606,7 +623,9 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
       a.partials = w.partials;
       launch_attn_decode_mfma(a, w.n_ditems, s);
     } else {
-      launch_attn_plain<T>((const float *)w.Q, (const T *)cache->k, (const T *)cache->v, seqs_dev, w.rm, L, pl.T,
+      RowMeta rm = w.rm;
+      rm.seq += row0; rm.pos += row0;      // (all it reads of them)
+      launch_attn_plain<T>((const float *)Q, (const T *)cache->k, (const T *)cache->v, seqs_dev, rm, L, pl.T,
                            n_splits, w.partials, direct ? out : nullptr, s);
     }
   }
@@ -615,6 +634,14 @@ void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims
     if (compact16) launch_attn_merge16(w.partials, L, pl.T, n_splits, (bf16 *)out, s);
     else launch_attn_merge<T>(w.partials, L, pl.T, n_splits, w.merge, out, s);
   }
+}
+
+template <typename T>
+void attention_block(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, const alora_kv_cache *cache,
+                     const T *x, const Plan &pl, const SeqMeta *seqs_dev, const Workspace &w, bool write_meta,
+                     int n_splits, bool decode, int pos_shift, T *out, hipStream_t s) {
+  project_rows<T>(ctx, ly, L, cache, x, pl, seqs_dev, w, write_meta, pos_shift, s);
+  attend_rows<T>(ctx, L, cache, pl, seqs_dev, w, n_splits, decode, pos_shift, 0, out, s);
 }
 
 template <typename T>
@@ -1263,6 +1290,8 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   if (ctx->device >= 0) HIP_TRY(ctx, hipSetDevice(ctx->device));
   hipStream_t s = (hipStream_t)stream;
   const size_t esz = layers[0].dtype == ALORA_BF16 ? 2 : 4;
+  constexpr int RUN_ROWS = 1024;
+  int run_steps = 1;
   const bool attn_mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && !decode &&
                          attn_prefill_mfma_supported(L);
   const int attn_waves = ctx->opt_attn_waves == 4 ? 4 : 8;
@@ -1286,7 +1315,33 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
     for (int l = 0; l < n_layers; ++l) streamed = streamed && qkv_stream_supported(layers[l].W_qkv, L.n_qkv, L.d, L.head_dim);
     if (!streamed) k_segments = gemm_mfma_fixed_segments(L.n_qkv, L.d, ctx->n_cu);
   }
-  int k_splits = (k_segments > 1 && gemm_mfma_split_segments(pl.T, L.n_qkv, ctx->n_cu)) ? k_segments : 1;
+  // A run of decode steps has the inputs of all of them: their rows are prepared, projected and appended RUN_ROWS at a time (one
+  // sum over K whatever the number of rows: base rows come out with the same bits as a step at a time), then every step attends to the
+  // rows up to its own.  A record per row and step stands for a sequence of one new row.  Not where an output lies where a later input
+  // does.  16 steps of 64 rows: 16 x 35 -> 115 us.
+  Plan run_pl;
+  if (n_steps > 1) {
+    const size_t xb = (size_t)n_steps * pl.T * L.d * esz, ob = (size_t)n_steps * pl.T * L.n_q * esz;
+    const bool apart = (const char *)x + xb <= (const char *)out || (const char *)out + ob <= (const char *)x;
+    run_steps = apart ? std::max(1, std::min(n_steps, RUN_ROWS / pl.T)) : 1;
+  }
+  if (run_steps > 1) {
+    run_pl = pl;
+    run_pl.T = run_pl.B = run_steps * pl.T;
+    run_pl.seqs.clear();
+    run_pl.seqs.reserve(run_pl.T);
+    run_pl.n_adapted = 0;
+    for (int t = 0; t < run_steps; ++t)
+      for (const SeqMeta &m : pl.seqs) {
+        SeqMeta q = m;
+        q.row_start += t * pl.T;
+        q.P += t;
+        run_pl.seqs.push_back(q);
+        if (m.adapter >= 0) ++run_pl.n_adapted;      // (at most: the last steps')
+      }
+  }
+  const Plan &ppl = run_steps > 1 ? run_pl : pl;      // the rows that are projected together
+  int k_splits = (k_segments > 1 && gemm_mfma_split_segments(ppl.T, L.n_qkv, ctx->n_cu)) ? k_segments : 1;
   // What the static entry point needs with `n` partial records per (row, head) and `groups` work items per row and record
   auto static_bytes = [&](int n, int groups) {
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
@@ -1317,7 +1372,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   const int n_static_items = dp.n_device_items;
   const int dec_hw = dp.hw, dec_kr = dp.kr, dec_groups = dp.groups, dec_cols_max = dp.cols_max;
   const bool f32_tail = stack && !mfma && layers[0].dtype == ALORA_BF16;
-  Workspace probe = layout_workspace(nullptr, L, pl.T, esz, n_splits, k_splits, layers[0].intermediate, stack, f32_tail);
+  Workspace probe = layout_workspace(nullptr, L, ppl.T, esz, n_splits, k_splits, layers[0].intermediate, stack, f32_tail, pl.T);
   if (use_static) {
     // Everything the call needs beyond its inputs and outputs lives in the static scratch array of this GPU:
     //   [ workspace | per-sequence records | decode work list | rotary lines, one per row ]
@@ -1382,7 +1437,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   // staged metadata: per-sequence records, then the work list of the MFMA attention kernel
   std::vector<AttnItem> qtiles;
   if (attn_mfma) qtiles = build_prefill_items(pl, L, B, attn_waves, pp);
-  const size_t seq_bytes = ((size_t)B * sizeof(SeqMeta) + 15) & ~(size_t)15;
+  const size_t seq_bytes = (ppl.seqs.size() * sizeof(SeqMeta) + 15) & ~(size_t)15;
   const size_t list_bytes = (qtiles.size() * sizeof(AttnItem) + ditems.size() * sizeof(DecItem) + 15) & ~(size_t)15;   // one of the two lists
   const size_t row_bytes = ((dp.rows.size() + dp.counts.size()) * sizeof(int32_t) + 15) & ~(size_t)15;                // decode: shared items' rows, records per row
   const size_t work_bytes = list_bytes + row_bytes;
@@ -1391,14 +1446,14 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   MetaSlot *slot = nullptr;
   st = acquire_slot(ctx, meta_bytes, &slot);
   if (st != ALORA_OK) return st;
-  memcpy(slot->host, pl.seqs.data(), (size_t)B * sizeof(SeqMeta));
+  memcpy(slot->host, ppl.seqs.data(), ppl.seqs.size() * sizeof(SeqMeta));
   if (!qtiles.empty()) memcpy(slot->host + seq_bytes, qtiles.data(), qtiles.size() * sizeof(AttnItem));
   if (!ditems.empty()) memcpy(slot->host + seq_bytes, ditems.data(), ditems.size() * sizeof(DecItem));
   if (!dp.counts.empty()) memcpy(slot->host + seq_bytes + list_bytes, dp.counts.data(), dp.counts.size() * sizeof(int32_t));
   if (!dp.rows.empty()) memcpy(slot->host + seq_bytes + list_bytes + dp.counts.size() * sizeof(int32_t), dp.rows.data(), dp.rows.size() * sizeof(int32_t));
   if (scale_bytes) memcpy(slot->host + seq_bytes + work_bytes, layers[0].scale, (size_t)L.n_adapters * sizeof(float));
   const int n16 = (int)((meta_bytes + 15) / 16);
-  const bool carried = B <= FEW_SEQS && n16 <= STAGE_N16 && !ctx->opt_stage_copy;      // by the call's first kernel
+  const bool carried = ppl.B <= FEW_SEQS && n16 <= STAGE_N16 && !ctx->opt_stage_copy;      // by the call's first kernel
   if (carried) {
   } else if (ctx->opt_stage_copy) {
     HIP_TRY(ctx, hipMemcpyAsync(slot->dev, slot->host, meta_bytes, hipMemcpyHostToDevice, s));
@@ -1407,7 +1462,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
                        (uint4 *)slot->dev, n16);
   }
   const SeqMeta *seqs_dev = (const SeqMeta *)slot->dev;
-  Workspace w = layout_workspace(ctx->ws, L, pl.T, esz, n_splits, k_splits, layers[0].intermediate, stack, f32_tail);
+  Workspace w = layout_workspace(ctx->ws, L, ppl.T, esz, n_splits, k_splits, layers[0].intermediate, stack, f32_tail, pl.T);
   w.mfma = mfma;
   w.k_splits = k_splits;
   w.k_segments = k_segments;
@@ -1438,12 +1493,20 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   const bool bf = layers[0].dtype == ALORA_BF16;
   if (!stack) {
     // n_steps > 1: a run of decode steps on the metadata staged once; step t sits t positions further on
-    for (int t = 0; t < n_steps; ++t) {
-      const char *xt = (const char *)x + (size_t)t * pl.T * L.d * esz;
-      char *ot = (char *)out + (size_t)t * pl.T * L.n_q * esz;
-      if (bf) attention_block<bf16>(ctx, &layers[0], L, &caches[0], (const bf16 *)xt, pl, seqs_dev, w, true, n_splits, decode, t, (bf16 *)ot, s);
-      else attention_block<float>(ctx, &layers[0], L, &caches[0], (const float *)xt, pl, seqs_dev, w, true, n_splits, decode, t, (float *)ot, s);
-    }
+    auto steps = [&](auto one) {
+      using T = decltype(one);
+      for (int t0 = 0; t0 < n_steps; t0 += run_steps) {
+        // (the last rows of a run that run_steps does not divide: the steps that are left)
+        const int n = std::min(run_steps, n_steps - t0);
+        Plan rest;
+        if (n < run_steps) { rest = ppl; rest.T = rest.B = n * pl.T; rest.seqs.resize(rest.T); }
+        project_rows<T>(ctx, &layers[0], L, &caches[0], (const T *)x + (size_t)t0 * pl.T * L.d, n < run_steps ? rest : ppl, seqs_dev, w, true, t0, s);
+        for (int t = 0; t < n; ++t)
+          attend_rows<T>(ctx, L, &caches[0], pl, seqs_dev, w, n_splits, decode, t0 + t, t * pl.T, (T *)out + (size_t)(t0 + t) * pl.T * L.n_q, s);
+      }
+    };
+    if (bf) steps(bf16{});
+    else steps(float{});
   } else {
     const void *cur = x;
     for (int l = 0; l < n_layers; ++l) {

@@ -494,3 +494,41 @@ def test_down_projection_of_many_adapted_rows(ab, ctx, rank, T):
     S = _split(T, 3)
     case = H.make_case(shape, [5] * 3, S, [5, 5 + S[1] // 2, 5], [0, 2, 1], seed=1900 + rank + T, prefix="random")
     check_case(ab, ctx, case)
+
+
+@pytest.mark.parametrize("shape", [wl.LayerShape(d=512, n_q_heads=4, n_kv_heads=2, head_dim=128, rank=16, n_adapters=2),
+                                   wl.LayerShape(d=256, n_q_heads=4, n_kv_heads=4, head_dim=64, rank=8, n_adapters=2, dtype="f32", rmsnorm=False)],
+                         ids=["bf16", "fp32"])
+def test_decode_steps_whose_outputs_are_the_next_inputs(ab, ctx, shape):
+    """attn_out one step into x_steps: every step reads what the step before wrote."""
+    n, P = 5, [40, 7, 129]
+    case = H.make_case(shape, P, [n] * 3, [30, 9, 400], [0, 1, -1], seed=2950, prefix="random")
+    layer = H.gpu_layer(case, shape)
+    x = torch.zeros(n + 1, 3, shape.d, dtype=shape.torch_dtype, device="cuda")
+    x[0] = torch.stack([case.x_new[b][0] for b in range(3)]).cuda()
+    chain, cache = H.gpu_cache(case), H.gpu_cache(case)
+    want = [x[0].clone()]
+    for t in range(n):
+        want.append(ab.alora_decode(ctx, layer, chain, want[-1], case.k, case.adapter).clone())
+    ab.alora_decode_steps(ctx, layer, cache, x[:n], case.k, case.adapter, x[1:])
+    torch.cuda.synchronize()
+    assert torch.equal(cache.k, chain.k) and torch.equal(cache.v, chain.v)
+    # (the keys may be cut in other ranges: a run's as its last step has them)
+    assert H.rel_err(H.f64(x[1:].reshape(3 * n, -1)), H.f64(torch.stack(want[1:]).reshape(3 * n, -1))) <= H.TOL[shape.dtype]
+
+
+# 1024 rows at a time: steps that do and do not divide, more rows than that in one step, a plain shape
+@pytest.mark.parametrize("P,steps,dtype", [([3, 90, 31], 350, "bf16"), ([20] * 300, 4, "bf16"), ([5] * 1100, 2, "bf16"), ([10, 2, 30], 400, "f32")])
+def test_decode_steps_projected_together(ab, ctx, P, steps, dtype):
+    shape = (wl.LayerShape(d=512, n_q_heads=4, n_kv_heads=2, head_dim=128, rank=16, n_adapters=3) if dtype == "bf16" else
+             wl.LayerShape(d=128, n_q_heads=2, n_kv_heads=2, head_dim=32, rank=8, n_adapters=3, dtype="f32", rmsnorm=False))
+    n = len(P)
+    case = H.make_case(shape, P, [steps] * n, [p + b % 3 for b, p in enumerate(P)], [b % 4 - 1 for b in range(n)], seed=2970 + n, prefix="random")
+    x = torch.stack([torch.stack([case.x_new[b][t] for b in range(n)]) for t in range(steps)]).cuda().contiguous()
+    cache = H.gpu_cache(case)
+    before_k, before_v = cache.k.cpu(), cache.v.cpu()
+    out = ab.alora_decode_steps(ctx, H.gpu_layer(case, shape), cache, x, case.k, case.adapter)
+    torch.cuda.synchronize()
+    ref, rows = H.oracle_prefill(case)
+    H.check_cache_after(case, cache, before_k, before_v, rows, H.TOL[dtype])
+    assert H.rel_err(H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1), ref) <= H.TOL[dtype]
