@@ -401,6 +401,7 @@ struct Workspace {
   bool attn_mfma = false;
   bool decode_mfma = false;
   int attn_waves = 8;
+  int run_steps = 0, run_seqs = 0;   // a run of decode steps whose attention is prefill attention (AttnArgs::steps)
   const AttnItem *qtiles = nullptr;
   int n_qtiles = 0;
   const DecItem *ditems = nullptr;   // work list of the MFMA decode kernel
@@ -591,7 +592,8 @@ void attend_rows(alora_ctx *ctx, const LayerDims &L, const alora_kv_cache *cache
   const bool mfma_attn = std::is_same<T, bf16>::value && (w.attn_mfma || w.decode_mfma);
   const bool direct = n_splits == 1 && (mfma_attn ? w.attn_mfma : true);
   // split prefill attention on the MFMA path: partial results travel in the compact record
-  const bool compact16 = w.attn_mfma && std::is_same<T, bf16>::value && !direct && ctx->opt_attn_partials16;
+  // (the records of decode steps stay in fp32)
+  const bool compact16 = w.attn_mfma && std::is_same<T, bf16>::value && !direct && ctx->opt_attn_partials16 && w.run_steps == 0;
   {
     ProfScope p(ctx, decode ? K_ATTN_DECODE : K_ATTN_PREFILL, s);
     if (w.attn_mfma && std::is_same<T, bf16>::value) {
@@ -602,6 +604,7 @@ void attend_rows(alora_ctx *ctx, const LayerDims &L, const alora_kv_cache *cache
       a.n_parts = n_splits;
       a.sm_scale = 1.0f / sqrtf((float)L.head_dim);
       a.lazy = (float)ctx->opt_attn_lazy;
+      a.steps = w.run_steps; a.seqs = w.run_seqs;
       a.q_prescaled = qf.scale != 1.0f;
       a.partials = direct ? nullptr : w.partials;
       a.compact = compact16 ? 1 : 0;
@@ -1292,29 +1295,6 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   const size_t esz = layers[0].dtype == ALORA_BF16 ? 2 : 4;
   constexpr int RUN_ROWS = 1024;
   int run_steps = 1;
-  const bool attn_mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && !decode &&
-                         attn_prefill_mfma_supported(L);
-  const int attn_waves = ctx->opt_attn_waves == 4 ? 4 : 8;
-  int n_splits = pick_splits(ctx, pl.T, L.n_kv_heads, pl.max_len);
-  const bool decode_mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && decode &&
-                           attn_decode_mfma_supported(L);
-  // kernel family: MFMA for bf16 shapes it covers, plain otherwise
-  const bool mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && L.d % 64 == 0 &&
-                    (L.n_adapters == 0 || (L.rank % 8 == 0 && L.n_adapters <= 64)) && L.n_q % 32 == 0 &&
-                    L.n_kv % 32 == 0 && (!stack || (layers[0].intermediate % 64 == 0 && L.n_q % 64 == 0));
-  // The reduction axis of the QKV projection is one running sum where the kernel that streams the weights can take few rows, and
-  // segments fixed by the weight shape where it cannot (unaligned weights, reductions that are no multiple of 128): 16 rows of the
-  // 8B-class shape with unaligned weights are 43 us as one sum, 21 in segments.  Weights decide, never the number of rows, so that a
-  // row's sums don't depend on it.  (Whether segments run in workgroups of their own or one after the other inside one does not
-  // change a bit of the result.)
-  int k_segments = 1;
-  if (mfma && ctx->opt_gemm_splits > 0) {
-    k_segments = L.d % (64 * ctx->opt_gemm_splits) == 0 ? ctx->opt_gemm_splits : 1;
-  } else if (mfma) {
-    bool streamed = true;
-    for (int l = 0; l < n_layers; ++l) streamed = streamed && qkv_stream_supported(layers[l].W_qkv, L.n_qkv, L.d, L.head_dim);
-    if (!streamed) k_segments = gemm_mfma_fixed_segments(L.n_qkv, L.d, ctx->n_cu);
-  }
   // A run of decode steps has the inputs of all of them: their rows are prepared, projected and appended RUN_ROWS at a time (one
   // sum over K whatever the number of rows: base rows come out with the same bits as a step at a time), then every step attends to the
   // rows up to its own.  A record per row and step stands for a sequence of one new row.  Not where an output lies where a later input
@@ -1341,6 +1321,42 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
       }
   }
   const Plan &ppl = run_steps > 1 ? run_pl : pl;      // the rows that are projected together
+  const int attn_waves = ctx->opt_attn_waves == 4 ? 4 : 8;
+  // Where the whole run is projected together, it is also a prefill whose new rows lie step after step: a row sees the keys up to its own
+  // position, and the cache is read once instead of once a step: 16 steps of 64 rows on 16 contexts of 16384 keys 3412 -> 420 us.  (A private cache
+  // read once by the prefill kernel takes about as long as 1.4 decode steps, so this holds from two steps on.  Not for the variants of the
+  // prefill kernel that the options choose.)
+  const bool run_prefill = decode && n_steps > 1 && run_steps == n_steps && layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 &&
+                           attn_waves == 8 && ctx->opt_attn_fold && attn_prefill_mfma_supported(L);
+  Plan run_att;
+  if (run_prefill) {
+    run_att = pl;
+    run_att.T = pl.T * n_steps;
+    for (int b = 0; b < B; ++b) { run_att.seqs[b].n_new = n_steps; run_att.seqs[b].row_start = b * n_steps; }
+  }
+  const Plan &att_pl = run_prefill ? run_att : pl;      // the rows that attend together: sequence after sequence (the kernel finds where they lie)
+  const bool attn_mfma = run_prefill || (layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && !decode &&
+                                         attn_prefill_mfma_supported(L));
+  int n_splits = pick_splits(ctx, pl.T, L.n_kv_heads, pl.max_len);
+  const bool decode_mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && decode && !run_prefill &&
+                           attn_decode_mfma_supported(L);
+  // kernel family: MFMA for bf16 shapes it covers, plain otherwise
+  const bool mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && L.d % 64 == 0 &&
+                    (L.n_adapters == 0 || (L.rank % 8 == 0 && L.n_adapters <= 64)) && L.n_q % 32 == 0 &&
+                    L.n_kv % 32 == 0 && (!stack || (layers[0].intermediate % 64 == 0 && L.n_q % 64 == 0));
+  // The reduction axis of the QKV projection is one running sum where the kernel that streams the weights can take few rows, and
+  // segments fixed by the weight shape where it cannot (unaligned weights, reductions that are no multiple of 128): 16 rows of the
+  // 8B-class shape with unaligned weights are 43 us as one sum, 21 in segments.  Weights decide, never the number of rows, so that a
+  // row's sums don't depend on it.  (Whether segments run in workgroups of their own or one after the other inside one does not
+  // change a bit of the result.)
+  int k_segments = 1;
+  if (mfma && ctx->opt_gemm_splits > 0) {
+    k_segments = L.d % (64 * ctx->opt_gemm_splits) == 0 ? ctx->opt_gemm_splits : 1;
+  } else if (mfma) {
+    bool streamed = true;
+    for (int l = 0; l < n_layers; ++l) streamed = streamed && qkv_stream_supported(layers[l].W_qkv, L.n_qkv, L.d, L.head_dim);
+    if (!streamed) k_segments = gemm_mfma_fixed_segments(L.n_qkv, L.d, ctx->n_cu);
+  }
   int k_splits = (k_segments > 1 && gemm_mfma_split_segments(ppl.T, L.n_qkv, ctx->n_cu)) ? k_segments : 1;
   // What the static entry point needs with `n` partial records per (row, head) and `groups` work items per row and record
   auto static_bytes = [&](int n, int groups) {
@@ -1365,14 +1381,14 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
     n_splits = dp.n_own + dp.n_shared;
   }
   if (attn_mfma) {
-    pp = plan_prefill_ranges(ctx, pl, L, B, attn_waves);
+    pp = plan_prefill_ranges(ctx, att_pl, L, B, attn_waves);
     n_splits = pp.n_own + pp.n_sh;
   }
   const std::vector<DecItem> &ditems = dp.items;
   const int n_static_items = dp.n_device_items;
   const int dec_hw = dp.hw, dec_kr = dp.kr, dec_groups = dp.groups, dec_cols_max = dp.cols_max;
   const bool f32_tail = stack && !mfma && layers[0].dtype == ALORA_BF16;
-  Workspace probe = layout_workspace(nullptr, L, ppl.T, esz, n_splits, k_splits, layers[0].intermediate, stack, f32_tail, pl.T);
+  Workspace probe = layout_workspace(nullptr, L, ppl.T, esz, n_splits, k_splits, layers[0].intermediate, stack, f32_tail, att_pl.T);
   if (use_static) {
     // Everything the call needs beyond its inputs and outputs lives in the static scratch array of this GPU:
     //   [ workspace | per-sequence records | decode work list | rotary lines, one per row ]
@@ -1436,7 +1452,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   if (st != ALORA_OK) return st;
   // staged metadata: per-sequence records, then the work list of the MFMA attention kernel
   std::vector<AttnItem> qtiles;
-  if (attn_mfma) qtiles = build_prefill_items(pl, L, B, attn_waves, pp);
+  if (attn_mfma) qtiles = build_prefill_items(att_pl, L, B, attn_waves, pp);
   const size_t seq_bytes = (ppl.seqs.size() * sizeof(SeqMeta) + 15) & ~(size_t)15;
   const size_t list_bytes = (qtiles.size() * sizeof(AttnItem) + ditems.size() * sizeof(DecItem) + 15) & ~(size_t)15;   // one of the two lists
   const size_t row_bytes = ((dp.rows.size() + dp.counts.size()) * sizeof(int32_t) + 15) & ~(size_t)15;                // decode: shared items' rows, records per row
@@ -1462,13 +1478,14 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
                        (uint4 *)slot->dev, n16);
   }
   const SeqMeta *seqs_dev = (const SeqMeta *)slot->dev;
-  Workspace w = layout_workspace(ctx->ws, L, ppl.T, esz, n_splits, k_splits, layers[0].intermediate, stack, f32_tail, pl.T);
+  Workspace w = layout_workspace(ctx->ws, L, ppl.T, esz, n_splits, k_splits, layers[0].intermediate, stack, f32_tail, att_pl.T);
   w.mfma = mfma;
   w.k_splits = k_splits;
   w.k_segments = k_segments;
   // few row tiles and a split reduction: the workgroups are short and the prologue of split 0 would stick out
   w.lora_split = (k_splits > 1 && ctx->opt_lora_split != 2) || ctx->opt_lora_split == 1 ? 1 : 0;
   w.attn_mfma = attn_mfma;
+  if (run_prefill) { w.run_steps = n_steps; w.run_seqs = B; }
   w.decode_mfma = decode_mfma;
   w.attn_waves = attn_waves;
   w.qtiles = (const AttnItem *)(slot->dev + seq_bytes);
@@ -1501,7 +1518,8 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
         Plan rest;
         if (n < run_steps) { rest = ppl; rest.T = rest.B = n * pl.T; rest.seqs.resize(rest.T); }
         project_rows<T>(ctx, &layers[0], L, &caches[0], (const T *)x + (size_t)t0 * pl.T * L.d, n < run_steps ? rest : ppl, seqs_dev, w, true, t0, s);
-        for (int t = 0; t < n; ++t)
+        if (run_prefill) attend_rows<T>(ctx, L, &caches[0], att_pl, seqs_dev, w, n_splits, false, 0, 0, (T *)out, s);
+        else for (int t = 0; t < n; ++t)
           attend_rows<T>(ctx, L, &caches[0], pl, seqs_dev, w, n_splits, decode, t0 + t, t * pl.T, (T *)out + (size_t)(t0 + t) * pl.T * L.n_q, s);
       }
     };

@@ -104,12 +104,11 @@ constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
 // ---- write the partial (or final) result of a row: the lane's half of its columns -------------------------------------
-__device__ __forceinline__ void write_result(const AttnArgs &a, int part, int row0, int ntok, int tok, int head, int kh, float m_ref,
+__device__ __forceinline__ void write_result(const AttnArgs &a, int part, int64_t row, bool valid, int head, int kh, float m_ref,
                                              float l_run, const f32x16 (&o)[4]) {
   constexpr int H = 128;
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);      // the two halves of the wave hold disjoint keys
-  if (tok >= ntok) return;
-  const int64_t row = row0 + tok;
+  if (!valid) return;
   if (a.out != nullptr) {
     const float inv = 1.0f / l_tot;
     bf16 *op = a.out + row * a.n_q + head * H;
@@ -470,7 +469,7 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) 
     }
   }
 
-  write_result(a, split, row0, ntok, tok, head, kh, m_ref, l_run, o);
+  write_result(a, split, row0 + tok, tok < ntok, head, kh, m_ref, l_run, o);
 }
 
 // ---- folded softmax, eight waves: the steps of consecutive 32-key blocks woven together -----------------------------------
@@ -520,10 +519,12 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
   const bf16 *Vp = a.V + wk.key_row0 * a.n_kv + wk.g * H;
 
   const int pr = wave * 32 + l32, tok = pr >> g_log2, head = (wk.g << g_log2) + (pr & ((1 << g_log2) - 1));
+  const int v = row0 + min(tok, ntok - 1);
+  const int64_t row = a.steps > 0 ? v % a.steps * a.seqs + v / a.steps : v;
   const int pos = tok < ntok ? first_pos + tok : -1;       // -1: padding row
   u32x4 qf[8];
   {
-    const _Float16 *qp = a.Q + (int64_t)(row0 + min(tok, ntok - 1)) * a.n_q + head * H + kh * 8;
+    const _Float16 *qp = a.Q + row * a.n_q + head * H + kh * 8;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const u32x4 *>(qp + ks * 16);
   }
@@ -728,7 +729,7 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
     }
   }
   const float m_ref = -negm[0];
-  write_result(a, wk.part, row0, ntok, tok, head, kh, m_ref, l_run, o);
+  write_result(a, wk.part, row, tok < ntok, head, kh, m_ref, l_run, o);
 }
 
 bool attn_prefill_mfma_supported(const LayerDims &L) {

@@ -532,3 +532,23 @@ def test_decode_steps_projected_together(ab, ctx, P, steps, dtype):
     ref, rows = H.oracle_prefill(case)
     H.check_cache_after(case, cache, before_k, before_v, rows, H.TOL[dtype])
     assert H.rel_err(H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1), ref) <= H.TOL[dtype]
+
+
+# one prefill of all steps (rows step after step), or -- options that choose another prefill kernel -- a step at a time
+@pytest.mark.parametrize("G,steps,opts", [(1, 2, {}), (2, 70, {}), (4, 65, {}), (8, 33, {}), (4, 3, {"kv_splits": 3}), (4, 5, {"attn_partials16": 0}),
+                                          (4, 5, {"attn_fold": 0}), (4, 5, {"attn_waves": 4}), (4, 5, {"kernels": 1}), (16, 5, {})])
+def test_runs_of_decode_steps(ab, ctx, G, steps, opts):
+    for k, v in opts.items():
+        ctx.set_option(k, v)
+    shape = wl.LayerShape(d=256, n_q_heads=16, n_kv_heads=16 // G, head_dim=128, rank=8, n_adapters=2)
+    P = [0, 63, 64, 1, 500]
+    n = len(P)
+    case = H.make_case(shape, P, [steps] * n, [p + b for b, p in enumerate(P)], [b % 3 - 1 for b in range(n)], seed=3000 + G + steps, prefix="random")
+    x = torch.stack([torch.stack([case.x_new[b][t] for b in range(n)]) for t in range(steps)]).cuda().contiguous()
+    cache = H.gpu_cache(case)
+    before_k, before_v = cache.k.cpu(), cache.v.cpu()
+    out = ab.alora_decode_steps(ctx, H.gpu_layer(case, shape), cache, x, case.k, case.adapter)
+    torch.cuda.synchronize()
+    ref, rows = H.oracle_prefill(case)
+    H.check_cache_after(case, cache, before_k, before_v, rows, H.TOL["bf16"])
+    assert H.rel_err(H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1), ref) <= H.TOL["bf16"]
