@@ -42,7 +42,7 @@ TITLES = {
 BENCH_WORKLOAD = {"r3pp": "r3p", "c5f": "c5"}         # summary key -> bench.py --workload, where they differ
 KT_EXTRA = {"c5f": " --steps 3 --warmup 1"}      # of the kernel trace alone
 # kernel symbol -> the kernel family bench.py reports (only where one symbol is one family in that workload)
-FAMILY = [("attn_prefill_mfma_kernel", "attn_prefill"), ("attn_decode_mfma_kernel", "attn_decode"),
+FAMILY = [("attn_prefill_", "attn_prefill"), ("attn_decode_mfma_kernel", "attn_decode"),
           ("prep_few_kernel", "prep_rows"), ("qkv_stream_kernel", "qkv_gemm"), ("rope_append_kernel", "rope_append"), ("attn_merge", "attn_merge")]
 
 
@@ -65,11 +65,9 @@ def family_of(workload: str, kernel: str):
     large = re.search(r"gemm_large_kernel<\d+, (\d)>", kernel)
     if large:
         return {"2": "gate_up", "3": "qkv_gemm"}.get(large.group(1))
-    if "gemm_mfma_kernel" in kernel:
-        epi = re.search(r"gemm_mfma_kernel<\d+, \d+, \d+, \d+, (\d),", kernel)
-        epi = epi.group(1) if epi else ""
-        if workload == "c5" and epi == "2":
-            return "gate_up"
+    few = re.search(r"gemm_(?:mfma_kernel<\d+, \d+, \d+, \d+, |stream_kernel<alora::StreamCfg<\d+, \d+, \d+, \d+, \d+, )(\d)", kernel)
+    if few and workload == "c5" and few.group(1) == "2":
+        return "gate_up"
     return None
 
 
