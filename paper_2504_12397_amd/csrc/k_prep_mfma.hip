@@ -66,6 +66,9 @@ __device__ __forceinline__ void fill_row_meta(const PrepArgs &a, const SeqMeta &
 // v_mfma_f32_16x16x32_bf16 (lane l: row l % 16, k = 8 * (l / 16) ..).  CH = d / 256: chunks of its row a lane holds.
 // The kernel is memory round trips and little else, so everything is requested at once: x, the gain, the sequences' records (in the kernel arguments when they are few)
 // and this adapter's down matrix, before anybody knows whether a row of the tile uses it.
+// No load stands behind a branch of its own or is a generic one (the compiler waits for all that was asked for there), and the arguments arrive
+// together: as it was compiled before, records, x with the gain, one chunk of A and the rest of A were a round trip each.  Token steps of
+// 16 layers 2488 -> 2474 us (one row), of 8 layers 1492 -> 1480 (eight rows of eight adapters), five rows of rank-8 adapters 48.8 -> 47.8.
 // NC = 8: half the columns of the matrix operand, for calls whose 16-column workgroups would leave half of the chip idle: a compute
 // unit takes operands in this order at 28 bytes per ns, so it is
 // done sooner with half the 128 KB of 16 columns.  A one-row token step of 16 layers at rank 64 2615 -> 2589 us (1.6 a layer), five rows of
@@ -83,25 +86,37 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   const int r16 = lane & 15, kg = lane >> 4;
   const int row0 = blockIdx.x * PREP_ROWS;
   constexpr int d = CH * 256;
-  const int rank = a.rank, col0 = blockIdx.y * NC, ad = a.used[blockIdx.z];
+  const int rank = a.rank, col0 = blockIdx.y * NC;
+  const int ad = (reinterpret_cast<const uint32_t *>(a.used)[blockIdx.z >> 2] >> (8 * (blockIdx.z & 3))) & 255;      // (a scalar load)
+  // all arguments in one round trip, not where they are used
+  asm volatile("" ::"s"(a.rm.seq), "s"(a.rm.pos), "s"(a.rm.adapter), "s"(a.rm.slot), "s"(a.rm.present16), "s"(a.xh), "s"(a.tlow16), "s"(a.gain),
+               "s"(a.packed), "s"(a.eps), "s"(a.write_meta), "s"(a.pos_shift), "s"(a.n_seqs), "s"(ad),
+               "s"(a.x), "s"(a.A), "s"(a.rank), "s"(a.T), "s"(a.st.src), "s"(a.st.dst), "s"(a.st.n16));
   const bool lead = blockIdx.y == 0 && blockIdx.z == 0;
   const int row = min(row0 + r16, a.T - 1);
   const bool row_ok = row0 + r16 < a.T;
   const int k_lo = wave * (CH * 32) + kg * 8;  // this lane's first element; chunk u is at k_lo + 32 u
 
-  uint4 staged{};
-  const bool carry = blockIdx.x == 0 && lead && a.st.src != nullptr && tid < a.st.n16;
-  if (carry) staged = a.st.src[tid];
-  u32x4 xr[CH], br[CH], gown = u32x4{0, 0, 0, 0};
+  // this thread's sequence (the first half of its record); of a few sequences, from the kernel arguments
+  typedef uint32_t rec16 __attribute__((ext_vector_type(4), aligned(8)));
+  const uint64_t recs = a.st.n_few ? (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(PrepArgs, st.few) : (uint64_t)a.seqs;
+  const auto *rec = reinterpret_cast<const __attribute__((address_space(1))) rec16 *>(recs + (uint64_t)min(tid, a.n_seqs - 1) * sizeof(SeqMeta));
+  const u32x4 rec0 = rec[0], rec1 = rec[1];
+  u32x4 xr[CH], br[CH];
   const bf16 *xrow = a.x + (int64_t)row * d + k_lo;
 #pragma unroll
   for (int u = 0; u < CH; ++u) xr[u] = *reinterpret_cast<const u32x4 *>(xrow + 32 * u);
   // (the gain goes through LDS: one 16-byte chunk per thread instead of CH of them in every lane's registers)
-  if (a.gain != nullptr && tid < d / 8) gown = *reinterpret_cast<const u32x4 *>(a.gain + tid * 8);
+  // (no branch around these loads: behind one the compiler waits for everything that was asked for before)
+  const u32x4 gown = *reinterpret_cast<const u32x4 *>((a.gain != nullptr ? a.gain : a.x) + min(tid, d / 8 - 1) * 8);
   const int my_col = min(col0 + r16, 3 * rank - 1);      // (3 * rank need not be a multiple of 16)
-  const bf16 *Ab = a.A + ((int64_t)ad * 3 * rank + my_col) * d + k_lo;
+  const auto A_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.A + (int64_t)ad * 3 * rank * d), 0, 3 * rank * d * 2, 0x00020000);
+  const int A_off = NC == 16 || r16 < NC ? (my_col * d + k_lo) * 2 : 0x7fff0000;      // (lanes without a column: out of range, they read zeros)
 #pragma unroll
-  for (int u = 0; u < CH; ++u) br[u] = NC == 16 || r16 < NC ? *reinterpret_cast<const u32x4 *>(Ab + 32 * u) : u32x4{0, 0, 0, 0};
+  for (int u = 0; u < CH; ++u) br[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(A_rsrc, A_off, 64 * u, 0));
+  uint4 staged{};
+  const bool carry = blockIdx.x == 0 && lead && a.st.src != nullptr && tid < a.st.n16;
+  if (carry) staged = a.st.src[tid];      // (host memory: behind what everybody waits for)
 
   if (tid == 0) s_present = 0ull;
   if (tid < PREP_ROWS) { s_adapter[tid] = -1; s_scale[tid] = 0.f; }
@@ -110,13 +125,17 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   auto fill_row = [&](const SeqMeta &sm, int sq, int mrow) {
     fill_row_meta(a, sm, sq, mrow, row0, a.write_meta && lead, s_adapter, s_scale, &s_present);
   };
-  {
-    for (int sq = tid; sq < a.n_seqs; sq += 512) {
-      const SeqMeta sm = a.st.n_few ? a.st.few[sq] : a.seqs[sq];
-      const int lo = max(sm.row_start, row0), hi = min(sm.row_start + sm.n_new, tile_end);
-      for (int mrow = lo; mrow < hi; ++mrow) fill_row(sm, sq, mrow);
-    }
+  auto fill = [&](const SeqMeta &sm, int sq) {
+    const int lo = max(sm.row_start, row0), hi = min(sm.row_start + sm.n_new, tile_end);
+    for (int mrow = lo; mrow < hi; ++mrow) fill_row(sm, sq, mrow);
+  };
+  if (tid < a.n_seqs) {
+    SeqMeta sm{};
+    sm.row_start = (int)rec0[0]; sm.n_new = (int)rec0[1]; sm.P = (int)rec0[2]; sm.k = (int)rec0[3];
+    sm.adapter = (int)rec1[0]; sm.scale = __uint_as_float(rec1[1]); sm.pool_off = (int64_t)((uint64_t)rec1[3] << 32 | rec1[2]);
+    fill(sm, tid);
   }
+  for (int sq = tid + 512; sq < a.n_seqs; sq += 512) fill(a.seqs[sq], sq);      // (a few have fewer)
 
   if (a.gain != nullptr) {
     float cs[CH];
