@@ -552,3 +552,14 @@ def test_runs_of_decode_steps(ab, ctx, G, steps, opts):
     ref, rows = H.oracle_prefill(case)
     H.check_cache_after(case, cache, before_k, before_v, rows, H.TOL["bf16"])
     assert H.rel_err(H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1), ref) <= H.TOL["bf16"]
+
+
+# records from the kernel arguments (up to 16 sequences), one per thread, and more than a workgroup has threads; 3 * rank columns in tiles of 8 and of 16
+@pytest.mark.parametrize("n,rank,n_adapters", [(16, 8, 2), (17, 24, 3), (512, 8, 1), (513, 8, 2), (700, 16, 2)])
+def test_row_preparation_of_many_short_sequences(ab, ctx, n, rank, n_adapters):
+    ctx.set_option("prep_split", 2)
+    shape = wl.LayerShape(d=512, n_q_heads=2, n_kv_heads=1, head_dim=128, rank=rank, n_adapters=n_adapters)
+    P, S = [b % 5 for b in range(n)], [1 + (b % 7 == 3) for b in range(n)]
+    case = H.make_case(shape, P, S, [P[b] + (b % 7 == 3) for b in range(n)], [b % (n_adapters + 1) - 1 for b in range(n)], seed=3100 + n,
+                       prefix="random")
+    check_case(ab, ctx, case)
