@@ -481,7 +481,7 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill_mfma_kernel(AttnArgs a) 
 // (sched_barrier after every matrix instruction); in the compiler's own order LDS waits and softmax stand between the products.
 // What it rests on (measured beside v_mfma_f32_32x32x16): six v_fma / v_cvt / v_max3 or two v_exp cost nothing; one v_dot2_f32_f16 costs 16 cycles
 // of the matrix pipe, which is why the row sums are v_fma_mix; a branch on the mask between the two halves of a block costs 70
-// register moves, so blocks that may need the mask run in a loop of their own, whose scores start from -inf where a row does not see
+// register moves, so blocks that may need the mask run in a loop of their own, which puts -inf in the place of scores whose row does not see
 // a key.
 //
 // 1024 rows x 32 heads over 32768 keys: 555 -> 497 us (0.99 -> 1.11 PFLOP/s), 4300 -> 3150 cycles per 256 x 64 tile, matrix pipes busy 0.48 ->
@@ -596,14 +596,10 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
     fr[n] = lds_read<u32x4>(va[s4 ^ cb] + par * PIPE_VT + cb * 4096);
   };
 
-  // what the scores of key block k0 .. k0 + 31 start from: -m_ref, or -inf where the row does not see the key
-  const int vis = min(pos, kend - 1) - 4 * kh;
-  auto start_masked = [&](f32x16 &s, int k0) {
-    int lim = vis - k0;
-    pin(lim);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) s[v] = 8 * (v >> 2) + (v & 3) > lim ? -INFINITY : negm[v];
-  };
+  // Scores of keys that the row does not see become -inf once their product is there, not before: what lies behind the row may be Inf or NaN,
+  // and -inf plus such a product is NaN.
+  const int vis = min(pos, kend - 1) - 4 * kh;      // (of key block k0 .. k0 + 31, register v holds key k0 + 4 kh + 8 (v / 4) + v % 4)
+  auto hide = [&](f32x16 &s, int v, int lim) { if (8 * (v >> 2) + (v & 3) > lim) s[v] = -INFINITY; };
   auto move_ref = [&](f32x16 &s, float mx) {
     mx = max_with_other_half(mx);
     const bool fresh = thr == -INFINITY;
@@ -625,10 +621,9 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
   int dk = 2 * PIPE_K, dv = 2 * PIPE_VT;      // to the other pair of buffers
   auto block = [&](auto par_c, auto kb_c, auto mask_c, f32x16 &sc, f32x16 &sn, int t) {
     constexpr int PAR = par_c, KB = kb_c, MASK = mask_c;
-    if constexpr (MASK) start_masked(sn, kbeg + t * ATT_BN + (KB + 1) * 32);
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
-      sn = __builtin_amdgcn_mfma_f32_32x32x16_f16(u4_as_f16x8(fr[n]), u4_as_f16x8(qf[n]), n == 0 && !MASK ? negm : sn, 0, 0, 0);
+      sn = __builtin_amdgcn_mfma_f32_32x32x16_f16(u4_as_f16x8(fr[n]), u4_as_f16x8(qf[n]), n == 0 ? negm : sn, 0, 0, 0);
       if (n < 8 - PIPE_AHEAD) read_k(MASK ? 0 : PAR ^ KB, KB ^ 1, n + PIPE_AHEAD);
       else read_v(PAR, KB, n + PIPE_AHEAD - 8);
       // requests of the tile that takes the place of what the last block stored, a few at a time (all eight waves ask together)
@@ -647,6 +642,8 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
     if (!MASK && PAR == 1 && KB == 0) ka += dk;      // (the other pair of buffers)
     __builtin_amdgcn_s_setprio(1);
     float m0 = 0.f;
+    int lim = vis - (kbeg + t * ATT_BN + (KB + 1) * 32);
+    if constexpr (MASK) pin(lim);
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
       o[n & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(u4_as_f16x8(fr[n]), pf_of(n >> 2), o[n & 3], 0, 0, 0);
@@ -656,6 +653,12 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
       add_f16<0>(pw[n], l_run);
       add_f16<1>(pw[n], l_run);
       // (the scores are there two matrix instructions after the last that made them)
+      if constexpr (MASK) {
+        if (n == 2) { hide(sn, 0, lim); hide(sn, 1, lim); hide(sn, 2, lim); }
+        if (n >= 3) { hide(sn, 2 * n - 3, lim); hide(sn, 2 * n - 2, lim); }
+        if (n == 6) { hide(sn, 13, lim); hide(sn, 14, lim); }
+        if (n == 7) hide(sn, 15, lim);
+      }
       if (n == 2) m0 = fmaxf(fmaxf(sn[0], sn[1]), sn[2]);
       if (n >= 3) m0 = fmaxf(fmaxf(m0, sn[2 * n - 3]), sn[2 * n - 2]);
       if (n == 6) m0 = fmaxf(fmaxf(m0, sn[13]), sn[14]);
@@ -700,11 +703,12 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
     f32x16 s0, s1;
 #pragma unroll
     for (int n = 0; n < 8; ++n) read_k(0, 0, n);
-    start_masked(s0, kbeg);
 #pragma unroll
-    for (int n = 0; n < 8; ++n) s0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(u4_as_f16x8(fr[n]), u4_as_f16x8(qf[n]), s0, 0, 0, 0);
+    for (int n = 0; n < 8; ++n) s0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(u4_as_f16x8(fr[n]), u4_as_f16x8(qf[n]), n == 0 ? negm : s0, 0, 0, 0);
 #pragma unroll
     for (int n = 0; n < PIPE_AHEAD; ++n) read_k(0, 1, n);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) hide(s0, v, vis - kbeg);
     float m0 = s0[0];
 #pragma unroll
     for (int v = 1; v < 16; ++v) m0 = fmaxf(m0, s0[v]);

@@ -1,0 +1,60 @@
+"""A later row reaches no earlier one, whatever it holds.  Attention at position p reads keys and values 0 .. p (Eq.1): rows behind it
+may be padding of a shorter answer, Inf or NaN, and the rows before them come out as if they were not there."""
+import pytest
+import torch
+
+from paper_2504_12397_amd import workloads as wl
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ab():
+    from paper_2504_12397_amd import binding
+    return binding
+
+
+@pytest.fixture()
+def ctx(ab):
+    c = ab.Context(0)
+    yield c
+    c.close()
+
+
+def _keys_only(case, rows):
+    """Rows (sequence, row) whose keys are Inf and NaN and whose queries and values do not notice: hidden element 0 is huge there, and only
+    W_k's column 0 is not zero."""
+    s = case.shape
+    W = case.tensors["W_qkv"]
+    W[:, 0] = 0
+    W[s.n_q:s.n_q + s.n_kv, 0] = 8.0
+    case.layer = H.oracle_layer(case.tensors, s)
+    for x in case.x_new:
+        x[:, 0] = 0
+    for b, i in rows:
+        case.x_new[b][i, 0] = 3e38
+
+
+# the row within the first tile of keys, at its edges, the last of all; without a prefix and behind one; one range of keys and several
+@pytest.mark.parametrize("opts", [{}, {"kv_splits": 2}, {"attn_fold": 0}, {"attn_waves": 4}, {"kernels": 1}])
+@pytest.mark.parametrize("G,bad", [(1, 69), (4, 1), (4, 31), (4, 64), (4, 139), (8, 32)])
+def test_prefill_rows_before_a_non_finite_key(ab, ctx, G, bad, opts):
+    for k, v in opts.items():
+        ctx.set_option(k, v)
+    shape = wl.LayerShape(d=256, n_q_heads=8, n_kv_heads=8 // G, head_dim=128, rank=8, n_adapters=1, rmsnorm=False)
+    P, S = [0, 50, 200], [140, 140, 140]
+    case = H.make_case(shape, P, S, P, [-1] * 3, seed=3200 + G + bad, prefix="random")
+    _keys_only(case, [(b, bad) for b in range(3)])
+    cache = H.gpu_cache(case)
+    out = H.f64(ab.alora_prefill(ctx, H.gpu_layer(case, shape), cache, case.x_packed.cuda().contiguous(), case.cu, case.k, case.adapter))
+    torch.cuda.synchronize()
+    for b in range(3):
+        assert not torch.isfinite(cache.k[int(cache.seq_offset[b]) + P[b] + bad].float()).all()
+        assert torch.isfinite(cache.v[int(cache.seq_offset[b]) + P[b] + bad].float()).all()
+    for b, x in enumerate(case.x_new):      # (the oracle's rows before the bad one do not see it either)
+        x[bad, 0] = 0
+    ref, _ = H.oracle_prefill(case)
+    for b in range(3):
+        lo = case.cu[b]
+        assert H.rel_err(out[lo:lo + bad], ref[lo:lo + bad]) <= H.TOL["bf16"], f"sequence {b}"
