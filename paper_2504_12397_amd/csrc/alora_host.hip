@@ -239,6 +239,7 @@ struct Plan {
   uint8_t used[64] = {};
   float used_scale[64] = {};
   int n_adapted = 0;         // rows (of the last step) that an adapter applies to
+  bool cached_only = false;  // prefill attention walks the keys that were cached before the call and no others
 };
 
 alora_status check_layer(alora_ctx *ctx, const alora_layer_desc *ly, bool need_tail, LayerDims *L) {
@@ -590,48 +591,53 @@ void attend_rows(alora_ctx *ctx, const LayerDims &L, const alora_kv_cache *cache
   const QueryForm qf = query_form<T>(ctx, L, w);
   const void *Q = (const char *)w.Q + (size_t)row0 * L.n_q * (qf.half ? 2 : 4);
   const bool mfma_attn = std::is_same<T, bf16>::value && (w.attn_mfma || w.decode_mfma);
-  const bool direct = n_splits == 1 && (mfma_attn ? w.attn_mfma : true);
+  const bool direct = n_splits == 1 && (mfma_attn ? w.attn_mfma && w.run_steps == 0 : true);
   // split prefill attention on the MFMA path: partial results travel in the compact record
   // (the records of decode steps stay in fp32)
   const bool compact16 = w.attn_mfma && std::is_same<T, bf16>::value && !direct && ctx->opt_attn_partials16 && w.run_steps == 0;
-  {
+  // `folded`: the queries carry the softmax scale and log2(e) already
+  auto decode_items = [&](bool folded) {
+    ProfScope p(ctx, K_ATTN_DECODE, s);
+    DecodeArgs a{};
+    a.Q = (const _Float16 *)Q; a.K = (const bf16 *)cache->k; a.V = (const bf16 *)cache->v;
+    a.n_q = L.n_q; a.n_kv = L.n_kv; a.n_q_heads = L.n_q_heads; a.n_kv_heads = L.n_kv_heads;
+    a.items = w.ditems; a.rows = w.drows; a.pos_shift = pos_shift;
+    a.n_parts = n_splits;
+    a.heads_per_wg = w.dec_hw; a.ranges_per_wg = w.dec_kr; a.cols_max = w.dec_cols_max;
+    a.sm_scale = folded ? 0.6931471805599453f : 1.0f / sqrtf((float)L.head_dim);
+    a.partials = w.partials;
+    launch_attn_decode_mfma(a, w.n_ditems, s);
+  };
+  if (w.attn_mfma && std::is_same<T, bf16>::value) {
+    ProfScope p(ctx, K_ATTN_PREFILL, s);
+    AttnArgs a{};
+    a.Q = (const _Float16 *)Q; a.K = (const bf16 *)cache->k; a.V = (const bf16 *)cache->v;
+    a.work = w.qtiles;
+    a.n_q = L.n_q; a.n_kv = L.n_kv; a.n_q_heads = L.n_q_heads; a.n_kv_heads = L.n_kv_heads;
+    a.n_parts = n_splits;
+    a.sm_scale = 1.0f / sqrtf((float)L.head_dim);
+    a.lazy = (float)ctx->opt_attn_lazy;
+    a.steps = w.run_steps; a.seqs = w.run_seqs;
+    a.q_prescaled = qf.scale != 1.0f;
+    a.partials = direct ? nullptr : w.partials;
+    a.compact = compact16 ? 1 : 0;
+    a.out = direct ? (bf16 *)out : nullptr;
+    // the kernels' fast tile loads use 32-bit byte offsets from an item's first key row; (absurdly) long
+    // sequences take the variant with full address arithmetic
+    bool generic_addr = false;
+    for (const SeqMeta &q : pl.seqs)
+      if ((uint64_t)(q.P + q.n_new) * (uint64_t)L.n_kv * 2u >= (1ull << 31)) generic_addr = true;
+    launch_attn_prefill_mfma(a, w.n_qtiles, L.n_q_heads / L.n_kv_heads, w.attn_waves, generic_addr, s);
+  } else if (w.decode_mfma && std::is_same<T, bf16>::value) {
+    decode_items(false);
+  } else {
     ProfScope p(ctx, decode ? K_ATTN_DECODE : K_ATTN_PREFILL, s);
-    if (w.attn_mfma && std::is_same<T, bf16>::value) {
-      AttnArgs a{};
-      a.Q = (const _Float16 *)Q; a.K = (const bf16 *)cache->k; a.V = (const bf16 *)cache->v;
-      a.work = w.qtiles;
-      a.n_q = L.n_q; a.n_kv = L.n_kv; a.n_q_heads = L.n_q_heads; a.n_kv_heads = L.n_kv_heads;
-      a.n_parts = n_splits;
-      a.sm_scale = 1.0f / sqrtf((float)L.head_dim);
-      a.lazy = (float)ctx->opt_attn_lazy;
-      a.steps = w.run_steps; a.seqs = w.run_seqs;
-      a.q_prescaled = qf.scale != 1.0f;
-      a.partials = direct ? nullptr : w.partials;
-      a.compact = compact16 ? 1 : 0;
-      a.out = direct ? (bf16 *)out : nullptr;
-      // the kernels' fast tile loads use 32-bit byte offsets from an item's first key row; (absurdly) long
-      // sequences take the variant with full address arithmetic
-      bool generic_addr = false;
-      for (const SeqMeta &q : pl.seqs)
-        if ((uint64_t)(q.P + q.n_new) * (uint64_t)L.n_kv * 2u >= (1ull << 31)) generic_addr = true;
-      launch_attn_prefill_mfma(a, w.n_qtiles, L.n_q_heads / L.n_kv_heads, w.attn_waves, generic_addr, s);
-    } else if (w.decode_mfma && std::is_same<T, bf16>::value) {
-      DecodeArgs a{};
-      a.Q = (const _Float16 *)Q; a.K = (const bf16 *)cache->k; a.V = (const bf16 *)cache->v;
-      a.n_q = L.n_q; a.n_kv = L.n_kv; a.n_q_heads = L.n_q_heads; a.n_kv_heads = L.n_kv_heads;
-      a.items = w.ditems; a.rows = w.drows; a.pos_shift = pos_shift;
-      a.n_parts = n_splits;
-      a.heads_per_wg = w.dec_hw; a.ranges_per_wg = w.dec_kr; a.cols_max = w.dec_cols_max;
-      a.sm_scale = 1.0f / sqrtf((float)L.head_dim);
-      a.partials = w.partials;
-      launch_attn_decode_mfma(a, w.n_ditems, s);
-    } else {
-      RowMeta rm = w.rm;
-      rm.seq += row0; rm.pos += row0;      // (all it reads of them)
-      launch_attn_plain<T>((const float *)Q, (const T *)cache->k, (const T *)cache->v, seqs_dev, rm, L, pl.T,
-                           n_splits, w.partials, direct ? out : nullptr, s);
-    }
+    RowMeta rm = w.rm;
+    rm.seq += row0; rm.pos += row0;      // (all it reads of them)
+    launch_attn_plain<T>((const float *)Q, (const T *)cache->k, (const T *)cache->v, seqs_dev, rm, L, pl.T,
+                         n_splits, w.partials, direct ? out : nullptr, s);
   }
+  if (w.run_steps > 0) decode_items(true);      // (a run of decode steps: its own keys)
   if (!direct) {
     ProfScope p(ctx, K_ATTN_MERGE, s);
     if (compact16) launch_attn_merge16(w.partials, L, pl.T, n_splits, (bf16 *)out, s);
@@ -1085,6 +1091,9 @@ struct PrefillPlan {
   std::vector<PrefixRun> runs;
   int n_own = 1, n_sh = 0;
 };
+// keys of a sequence behind its prefix that prefill attention walks
+int prefill_own_keys(const Plan &pl, const SeqMeta &m) { return m.P - m.prefix_len + (pl.cached_only ? 0 : m.n_new); }
+
 // What cutting the keys in n_own / n_sh ranges would take, in 64-key tiles of one workgroup: an eighth of the items on an XCD, one at a
 // time on a compute unit, longest first, each PREFILL_ITEM_TILES long besides its keys (first tiles, queries, result), and the records
 // that the merge then reads.  (Lengths in 64 classes: a few microseconds of host time for all the cuts of a call.)
@@ -1100,6 +1109,7 @@ double prefill_cut_tiles(const alora_ctx *ctx, const Plan &pl, const LayerDims &
     work += (int64_t)n * (l + PREFILL_ITEM_TILES);
   };
   auto cut = [&](int keys, int parts, int q_tiles) {      // q_tiles row tiles against the ranges of so many keys
+    if (parts == 0) return;
     const int chunk = std::max(1, ((keys + parts - 1) / parts + 63) / 64), t = (keys + 63) / 64, whole = t / chunk;
     add(chunk, whole * q_tiles);
     if (t > whole * chunk) add(t - whole * chunk, q_tiles);
@@ -1108,7 +1118,7 @@ double prefill_cut_tiles(const alora_ctx *ctx, const Plan &pl, const LayerDims &
   for (const SeqMeta &m : pl.seqs) {
     if (m.n_new <= 0) continue;
     rows += m.n_new;
-    cut(m.P + m.n_new - m.prefix_len, m.prefix_len > 0 ? n_own : n_own + n_sh, (m.n_new + tq - 1) / tq);
+    cut(prefill_own_keys(pl, m), m.prefix_len > 0 ? n_own : n_own + n_sh, (m.n_new + tq - 1) / tq);
   }
   for (const PrefixRun &r : pp.runs) cut(r.prefix_len, n_sh, (r.n_rows + tq - 1) / tq);
   // no schedule ends before its rounds of the longest items do, or before the work is done
@@ -1128,12 +1138,12 @@ PrefillPlan plan_prefill_ranges(const alora_ctx *ctx, const Plan &pl, const Laye
   PrefillPlan pp;
   const int tq = attn_prefill_mfma_tokens_per_tile(L, attn_waves);
   int64_t tiles = 0;
-  int max_own = 1, max_pfx = 0;
+  int max_own = 0, max_pfx = 0;      // (0: nothing cached behind the prefixes, and cached_only)
   for (int b = 0; b < B; ++b) {
     const SeqMeta &m = pl.seqs[b];
     if (m.n_new <= 0) continue;
     tiles += (m.n_new + tq - 1) / tq;
-    max_own = std::max(max_own, m.P + m.n_new - m.prefix_len);
+    max_own = std::max(max_own, prefill_own_keys(pl, m));
     max_pfx = std::max(max_pfx, m.prefix_len);
     if (m.prefix_len <= 0) continue;
     if (!pp.runs.empty() && pp.runs.back().prefix_off == m.prefix_off && pp.runs.back().prefix_len == m.prefix_len &&
@@ -1143,10 +1153,12 @@ PrefillPlan plan_prefill_ranges(const alora_ctx *ctx, const Plan &pl, const Laye
       pp.runs.push_back(PrefixRun{m.prefix_off, m.prefix_len, m.row_start, m.n_new});
   }
   if (ctx->opt_splits > 0) {
-    pp.n_own = ctx->opt_splits;
+    pp.n_own = max_own > 0 ? ctx->opt_splits : 0;
     pp.n_sh = pp.runs.empty() ? 0 : ctx->opt_splits;
     return pp;
   }
+  pp.n_own = max_own > 0 ? 1 : 0;
+  if (max_own + max_pfx == 0) return pp;
   // Ranges of at least four tiles, at most 16, the cut that takes the least.  Before, ranges were as long as two items per compute unit (shared
   // prefixes) or one (no prefix) would have them: 32 x 16 rows on four contexts of 16384 keys 249 -> 224 us with one range per unit instead
   // of two, eight sequences of 128 rows on 32768 keys 4285 -> 4228 (four layers).
@@ -1158,7 +1170,7 @@ PrefillPlan plan_prefill_ranges(const alora_ctx *ctx, const Plan &pl, const Laye
   for (int n = 1; n <= most; ++n) {
     const int len = std::max(4, ((longest + 63) / 64 + n - 1) / n);      // tiles of a range
     auto ranges = [&](int keys) { return std::max(1, std::min(16, ((keys + 63) / 64 + len - 1) / len)); };
-    const int own = ranges(max_own), sh = pp.runs.empty() ? 0 : ranges(max_pfx);
+    const int own = max_own > 0 ? ranges(max_own) : 0, sh = pp.runs.empty() ? 0 : ranges(max_pfx);
     if (own == was_own && sh == was_sh) continue;
     was_own = own; was_sh = sh;
     const double t = prefill_cut_tiles(ctx, pl, L, tq, pp, (longest + 63) / 64, own, sh);
@@ -1199,9 +1211,9 @@ std::vector<AttnItem> build_prefill_items(const Plan &pl, const LayerDims &L, in
           it.ntok = std::min(tq, m.n_new - q0);
           it.row0 = m.row_start + q0;
           // key positions count from the sequence's first own row (position prefix_len)
-          it.pos0 = m.P + q0 - m.prefix_len;
+          it.pos0 = pl.cached_only ? 1 << 30 : m.P + q0 - m.prefix_len;
           it.key_row0 = m.pool_off + m.prefix_len;
-          it.n_addr = it.pos0 + it.ntok;                  // keys visible to the item's last token
+          it.n_addr = pl.cached_only ? prefill_own_keys(pl, m) : it.pos0 + it.ntok;      // keys visible to the item's last token
           cut(0, it.n_addr, parts, sp, &it);
           it.g = g;
           it.part = sp;
@@ -1254,6 +1266,21 @@ std::vector<AttnItem> build_prefill_items(const Plan &pl, const LayerDims &L, in
   return qtiles;
 }
 
+// Work list of a run of decode steps whose cached keys prefill attention walks: the run's own new keys, an item per row and group of kv
+// heads that ends at the row's position (row t * B + b: the t-th new token of sequence b), the longest first.
+std::vector<DecItem> build_run_items(const Plan &pl, const LayerDims &L, int n_steps, int hw, int part) {
+  std::vector<DecItem> items;
+  items.reserve((size_t)n_steps * pl.T * ((L.n_kv_heads + hw - 1) / hw));
+  for (int t = n_steps - 1; t >= 0; --t)
+    for (const SeqMeta &m : pl.seqs)
+      for (int g = 0; g < L.n_kv_heads; g += hw) {
+        DecItem it{};
+        it.key_row0 = m.pool_off + m.P; it.row = t * pl.T + m.row_start; it.kend = it.n_keys = t + 1;
+        it.n_rows = 1; it.g = (int16_t)g; it.part = (int16_t)part;
+        items.push_back(it);
+      }
+  return items;
+}
 
 alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, alora_kv_cache *caches,
                  const void *x, const int32_t *cu, const int32_t *kps, const int32_t *aps, int B, void *out,
@@ -1322,16 +1349,18 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   }
   const Plan &ppl = run_steps > 1 ? run_pl : pl;      // the rows that are projected together
   const int attn_waves = ctx->opt_attn_waves == 4 ? 4 : 8;
-  // Where the whole run is projected together, it is also a prefill whose new rows lie step after step: a row sees the keys up to its own
-  // position, and the cache is read once instead of once a step: 16 steps of 64 rows on 16 contexts of 16384 keys 3412 -> 420 us.  (A private cache
-  // read once by the prefill kernel takes about as long as 1.4 decode steps, so this holds from two steps on.  Not for the variants of the
-  // prefill kernel that the options choose.)
+  // Where the whole run is projected together, prefill attention walks the keys that were cached before it for the rows of all its steps: the
+  // cache is read once instead of once a step.  The run's own keys are for items of the decode kernel that end at each row's position: in a
+  // pass that masked them their values would still be multiplied, by probability 0, and a step whose row is Inf or NaN would reach
+  // the steps before it.  16 steps of 64 rows on 16 contexts of 16384 keys 3412 -> 442 us, 22 of them the new keys.  (A private cache read once by the prefill kernel takes about as long as 1.4 decode steps, so this holds from two steps on.  Not
+  // for the variants of the prefill kernel that the options choose.)
   const bool run_prefill = decode && n_steps > 1 && run_steps == n_steps && layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 &&
                            attn_waves == 8 && ctx->opt_attn_fold && attn_prefill_mfma_supported(L);
   Plan run_att;
   if (run_prefill) {
     run_att = pl;
     run_att.T = pl.T * n_steps;
+    run_att.cached_only = true;
     for (int b = 0; b < B; ++b) { run_att.seqs[b].n_new = n_steps; run_att.seqs[b].row_start = b * n_steps; }
   }
   const Plan &att_pl = run_prefill ? run_att : pl;      // the rows that attend together: sequence after sequence (the kernel finds where they lie)
@@ -1383,6 +1412,11 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   if (attn_mfma) {
     pp = plan_prefill_ranges(ctx, att_pl, L, B, attn_waves);
     n_splits = pp.n_own + pp.n_sh;
+  }
+  if (run_prefill) {      // (one more record per row: the run's own keys)
+    decode_mfma_shape(L.n_kv_heads, false, &dp.hw, &dp.kr);
+    dp.cols_max = L.n_q_heads / L.n_kv_heads;
+    dp.items = build_run_items(pl, L, n_steps, dp.hw, n_splits++);
   }
   const std::vector<DecItem> &ditems = dp.items;
   const int n_static_items = dp.n_device_items;
@@ -1454,7 +1488,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   std::vector<AttnItem> qtiles;
   if (attn_mfma) qtiles = build_prefill_items(att_pl, L, B, attn_waves, pp);
   const size_t seq_bytes = (ppl.seqs.size() * sizeof(SeqMeta) + 15) & ~(size_t)15;
-  const size_t list_bytes = (qtiles.size() * sizeof(AttnItem) + ditems.size() * sizeof(DecItem) + 15) & ~(size_t)15;   // one of the two lists
+  const size_t list_bytes = (qtiles.size() * sizeof(AttnItem) + ditems.size() * sizeof(DecItem) + 15) & ~(size_t)15;   // (both: a run of decode steps)
   const size_t row_bytes = ((dp.rows.size() + dp.counts.size()) * sizeof(int32_t) + 15) & ~(size_t)15;                // decode: shared items' rows, records per row
   const size_t work_bytes = list_bytes + row_bytes;
   const size_t scale_bytes = stack ? (((size_t)L.n_adapters * sizeof(float) + 15) & ~(size_t)15) : 0;
@@ -1464,7 +1498,8 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   if (st != ALORA_OK) return st;
   memcpy(slot->host, ppl.seqs.data(), ppl.seqs.size() * sizeof(SeqMeta));
   if (!qtiles.empty()) memcpy(slot->host + seq_bytes, qtiles.data(), qtiles.size() * sizeof(AttnItem));
-  if (!ditems.empty()) memcpy(slot->host + seq_bytes, ditems.data(), ditems.size() * sizeof(DecItem));
+  const size_t dec_at = seq_bytes + qtiles.size() * sizeof(AttnItem);
+  if (!ditems.empty()) memcpy(slot->host + dec_at, ditems.data(), ditems.size() * sizeof(DecItem));
   if (!dp.counts.empty()) memcpy(slot->host + seq_bytes + list_bytes, dp.counts.data(), dp.counts.size() * sizeof(int32_t));
   if (!dp.rows.empty()) memcpy(slot->host + seq_bytes + list_bytes + dp.counts.size() * sizeof(int32_t), dp.rows.data(), dp.rows.size() * sizeof(int32_t));
   if (scale_bytes) memcpy(slot->host + seq_bytes + work_bytes, layers[0].scale, (size_t)L.n_adapters * sizeof(float));
@@ -1490,7 +1525,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   w.attn_waves = attn_waves;
   w.qtiles = (const AttnItem *)(slot->dev + seq_bytes);
   w.n_qtiles = (int)qtiles.size();
-  w.ditems = (const DecItem *)(slot->dev + seq_bytes);
+  w.ditems = (const DecItem *)(slot->dev + dec_at);
   w.n_ditems = (int)ditems.size();
   if (!dp.counts.empty()) {
     w.merge = MergeCounts{(const int32_t *)(slot->dev + seq_bytes + list_bytes), dp.n_own};

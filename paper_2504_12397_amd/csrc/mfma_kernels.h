@@ -112,7 +112,7 @@ struct AttnArgs {
   int compact;              // partial records in the compact form (ATTN_REC16 bytes each) that launch_attn_merge16 reads
   bf16 *out;                // [T, n_q] final output, only with n_parts == 1
   int steps, seqs;          // steps > 0: row v of an item (sequence v / steps, its new token v % steps) is row (v % steps) * seqs + v / steps of Q,
-                            // the records and the output (a run of decode steps: step after step); eight waves and prescaled queries only
+                            // and the records (a run of decode steps: step after step); eight waves and prescaled queries only
 };
 constexpr int ATTN_REC16 = 272;      // 128 fp16 + (reference, row sum, scale) as fp32 + 4 bytes of padding
 bool attn_prefill_mfma_supported(const LayerDims &L);

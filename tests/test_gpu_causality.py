@@ -58,3 +58,48 @@ def test_prefill_rows_before_a_non_finite_key(ab, ctx, G, bad, opts):
     for b in range(3):
         lo = case.cu[b]
         assert H.rel_err(out[lo:lo + bad], ref[lo:lo + bad]) <= H.TOL["bf16"], f"sequence {b}"
+
+
+# ragged answers: one sequence ends in the first step, one in the last but one; what follows is padding that nobody wrote
+@pytest.mark.parametrize("what", [float("nan"), float("inf"), 3e38])
+@pytest.mark.parametrize("G,steps,contexts,cached", [(4, 5, False, True), (4, 5, True, True), (1, 40, False, True), (8, 70, True, True), (2, 2, True, True),
+                                                     (4, 9, True, False), (4, 33, False, False)])
+def test_decode_steps_before_a_non_finite_row(ab, ctx, G, steps, contexts, cached, what):
+    shape = wl.LayerShape(d=256, n_q_heads=8, n_kv_heads=8 // G, head_dim=128, rank=8, n_adapters=2, rmsnorm=False)
+    n, C = 6, [150, 64]
+    group = [b % 2 for b in range(n)] if contexts else [-1] * n
+    own = [0, 3, 64, 100, 63, 30] if cached else [0] * n
+    ends = [1, steps - 1, steps, (steps + 1) // 2, steps, steps - 1]      # good rows of each sequence
+    start = [(C[group[b]] if contexts else 0) + own[b] for b in range(n)]
+    case, ctx_kv = H.contexts_case(shape, C, group, own, [steps] * n, [s + 1 for s in start], [b % 3 - 1 for b in range(n)], seed=3300 + G)
+    x = torch.stack([torch.stack([case.x_new[b][t] for b in range(n)]) for t in range(steps)])
+    for b in range(n):
+        x[ends[b]:, b] = what
+    x = x.cuda().contiguous()
+
+    def cache():
+        c = ab.KVCache([own[b] + steps for b in range(n)] + C, shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda", guard_rows=2)
+
+        def put(o, K, V):
+            for pool, rows in ((c.k, K), (c.v, V)):
+                pool[o:o + len(rows)] = torch.from_numpy(rows).to(shape.torch_dtype).reshape(len(rows), shape.n_kv_heads, shape.head_dim).cuda()
+
+        for i in range(2):
+            put(int(c.seq_offset[n + i]), *ctx_kv[i])
+        for b in range(n):
+            lo = start[b] - own[b]
+            put(int(c.seq_offset[b]), case.cache_K[b][lo:], case.cache_V[b][lo:])
+            c.seq_len[b] = start[b]
+            if contexts:
+                c.share_prefix(b, int(c.seq_offset[n + group[b]]), lo)
+        return c
+
+    layer, run, chain = H.gpu_layer(case, shape), cache(), cache()
+    out = ab.alora_decode_steps(ctx, layer, run, x, case.k, case.adapter)
+    want = torch.stack([ab.alora_decode(ctx, layer, chain, x[t], case.k, case.adapter) for t in range(steps)])
+    torch.cuda.synchronize()
+    ref, _ = H.oracle_prefill(case)      # (of the good rows throughout: the rows before the padding are its rows)
+    for b in range(n):
+        good = H.f64(out[:ends[b], b])
+        assert H.rel_err(good, ref[case.cu[b]:case.cu[b] + ends[b]]) <= H.TOL["bf16"], f"sequence {b}"
+        assert H.rel_err(good, H.f64(want[:ends[b], b])) <= H.TOL["bf16"]
