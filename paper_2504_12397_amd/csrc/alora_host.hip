@@ -402,7 +402,8 @@ struct Workspace {
   bool attn_mfma = false;
   bool decode_mfma = false;
   int attn_waves = 8;
-  int run_steps = 0, run_seqs = 0;   // a run of decode steps whose attention is prefill attention (AttnArgs::steps)
+  int run_steps = 0, run_seqs = 0;   // a run of decode steps whose attention is prefill attention (AttnArgs::steps, order)
+  const int32_t *run_order = nullptr;
   const AttnItem *qtiles = nullptr;
   int n_qtiles = 0;
   const DecItem *ditems = nullptr;   // work list of the MFMA decode kernel
@@ -617,7 +618,7 @@ void attend_rows(alora_ctx *ctx, const LayerDims &L, const alora_kv_cache *cache
     a.n_parts = n_splits;
     a.sm_scale = 1.0f / sqrtf((float)L.head_dim);
     a.lazy = (float)ctx->opt_attn_lazy;
-    a.steps = w.run_steps; a.seqs = w.run_seqs;
+    a.steps = w.run_steps; a.seqs = w.run_seqs; a.order = w.run_order;
     a.q_prescaled = qf.scale != 1.0f;
     a.partials = direct ? nullptr : w.partials;
     a.compact = compact16 ? 1 : 0;
@@ -938,6 +939,18 @@ double decode_cut_us(const std::vector<int> &n_of, int n_cu, double bytes, bool 
          (most > 16 && pairs > 512 ? 2.8 : 0.0) + 0.017 * most;
 }
 
+// the sequences of a call, those that name one prefix next to each other
+std::vector<int32_t> by_prefix(const Plan &pl) {
+  std::vector<int32_t> order(pl.B);
+  for (int b = 0; b < pl.B; ++b) order[b] = b;
+  auto before = [&](int x, int y) {
+    if (pl.seqs[x].prefix_off != pl.seqs[y].prefix_off) return pl.seqs[x].prefix_off < pl.seqs[y].prefix_off;
+    return pl.seqs[x].prefix_len < pl.seqs[y].prefix_len;
+  };
+  if (!std::is_sorted(order.begin(), order.end(), before)) std::stable_sort(order.begin(), order.end(), before);
+  return order;
+}
+
 // `cap`: most records of either kind a row may have (every row's place in memory is that large).
 DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, int cap, int n_steps, bool on_device) {
   DecodePlan dp;
@@ -948,12 +961,7 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
   std::vector<Chunk> chunks;
   dp.cols_max = G;
   if (pl.any_prefix) {
-    std::vector<int> order(pl.B);
-    for (int b = 0; b < pl.B; ++b) order[b] = b;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-      if (pl.seqs[x].prefix_off != pl.seqs[y].prefix_off) return pl.seqs[x].prefix_off < pl.seqs[y].prefix_off;
-      return pl.seqs[x].prefix_len < pl.seqs[y].prefix_len;
-    });
+    const std::vector<int32_t> order = by_prefix(pl);
     for (int i = 0; i < pl.B; ++i) {
       const SeqMeta &m = pl.seqs[order[i]];
       if (m.n_new <= 0 || m.prefix_len <= 0) continue;
@@ -1357,10 +1365,17 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   const bool run_prefill = decode && n_steps > 1 && run_steps == n_steps && layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 &&
                            attn_waves == 8 && ctx->opt_attn_fold && attn_prefill_mfma_supported(L);
   Plan run_att;
+  // sequences by prefix, so that those of one context share its items wherever they stand in the batch: two steps of 64 rows on 16 contexts of 16384
+  // keys, in turn, 977 us in the order of the batch (a step at a time 490), 368 like this
+  std::vector<int32_t> run_order;
   if (run_prefill) {
     run_att = pl;
     run_att.T = pl.T * n_steps;
     run_att.cached_only = true;
+    if (pl.any_prefix) {
+      run_order = by_prefix(pl);
+      for (int b = 0; b < B; ++b) run_att.seqs[b] = pl.seqs[run_order[b]];
+    }
     for (int b = 0; b < B; ++b) { run_att.seqs[b].n_new = n_steps; run_att.seqs[b].row_start = b * n_steps; }
   }
   const Plan &att_pl = run_prefill ? run_att : pl;      // the rows that attend together: sequence after sequence (the kernel finds where they lie)
@@ -1489,7 +1504,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   if (attn_mfma) qtiles = build_prefill_items(att_pl, L, B, attn_waves, pp);
   const size_t seq_bytes = (ppl.seqs.size() * sizeof(SeqMeta) + 15) & ~(size_t)15;
   const size_t list_bytes = (qtiles.size() * sizeof(AttnItem) + ditems.size() * sizeof(DecItem) + 15) & ~(size_t)15;   // (both: a run of decode steps)
-  const size_t row_bytes = ((dp.rows.size() + dp.counts.size()) * sizeof(int32_t) + 15) & ~(size_t)15;                // decode: shared items' rows, records per row
+  const size_t row_bytes = ((dp.rows.size() + dp.counts.size() + run_order.size()) * sizeof(int32_t) + 15) & ~(size_t)15;      // decode: shared items' rows, records per row; runs
   const size_t work_bytes = list_bytes + row_bytes;
   const size_t scale_bytes = stack ? (((size_t)L.n_adapters * sizeof(float) + 15) & ~(size_t)15) : 0;
   const size_t meta_bytes = seq_bytes + work_bytes + scale_bytes;
@@ -1502,6 +1517,8 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   if (!ditems.empty()) memcpy(slot->host + dec_at, ditems.data(), ditems.size() * sizeof(DecItem));
   if (!dp.counts.empty()) memcpy(slot->host + seq_bytes + list_bytes, dp.counts.data(), dp.counts.size() * sizeof(int32_t));
   if (!dp.rows.empty()) memcpy(slot->host + seq_bytes + list_bytes + dp.counts.size() * sizeof(int32_t), dp.rows.data(), dp.rows.size() * sizeof(int32_t));
+  const size_t order_at = seq_bytes + list_bytes + (dp.counts.size() + dp.rows.size()) * sizeof(int32_t);
+  if (!run_order.empty()) memcpy(slot->host + order_at, run_order.data(), run_order.size() * sizeof(int32_t));
   if (scale_bytes) memcpy(slot->host + seq_bytes + work_bytes, layers[0].scale, (size_t)L.n_adapters * sizeof(float));
   const int n16 = (int)((meta_bytes + 15) / 16);
   const bool carried = ppl.B <= FEW_SEQS && n16 <= STAGE_N16 && !ctx->opt_stage_copy;      // by the call's first kernel
@@ -1520,7 +1537,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   // few row tiles and a split reduction: the workgroups are short and the prologue of split 0 would stick out
   w.lora_split = (k_splits > 1 && ctx->opt_lora_split != 2) || ctx->opt_lora_split == 1 ? 1 : 0;
   w.attn_mfma = attn_mfma;
-  if (run_prefill) { w.run_steps = n_steps; w.run_seqs = B; }
+  if (run_prefill) { w.run_steps = n_steps; w.run_seqs = B; w.run_order = run_order.empty() ? nullptr : (const int32_t *)(slot->dev + order_at); }
   w.decode_mfma = decode_mfma;
   w.attn_waves = attn_waves;
   w.qtiles = (const AttnItem *)(slot->dev + seq_bytes);

@@ -520,7 +520,7 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
 
   const int pr = wave * 32 + l32, tok = pr >> g_log2, head = (wk.g << g_log2) + (pr & ((1 << g_log2) - 1));
   const int v = row0 + min(tok, ntok - 1);
-  const int64_t row = a.steps > 0 ? v % a.steps * a.seqs + v / a.steps : v;
+  const int64_t row = a.steps > 0 ? v % a.steps * a.seqs + (a.order != nullptr ? a.order[v / a.steps] : v / a.steps) : v;
   const int pos = tok < ntok ? first_pos + tok : -1;       // -1: padding row
   u32x4 qf[8];
   {

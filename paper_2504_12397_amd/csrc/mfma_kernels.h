@@ -111,8 +111,9 @@ struct AttnArgs {
   float *partials;          // [T, n_q_heads, n_parts, head_dim + 2] (acc, max, sum), used when out == nullptr
   int compact;              // partial records in the compact form (ATTN_REC16 bytes each) that launch_attn_merge16 reads
   bf16 *out;                // [T, n_q] final output, only with n_parts == 1
-  int steps, seqs;          // steps > 0: row v of an item (sequence v / steps, its new token v % steps) is row (v % steps) * seqs + v / steps of Q,
-                            // and the records (a run of decode steps: step after step); eight waves and prescaled queries only
+  int steps, seqs;          // steps > 0: row v of an item (its new token v % steps of sequence order[v / steps], or v / steps) is row (v % steps) * seqs + that
+                            // sequence of Q and the records (a run of decode steps: step after step); eight waves and prescaled queries only
+  const int32_t *order;     // [seqs] or nullptr
 };
 constexpr int ATTN_REC16 = 272;      // 128 fp16 + (reference, row sum, scale) as fp32 + 4 bytes of padding
 bool attn_prefill_mfma_supported(const LayerDims &L);

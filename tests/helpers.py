@@ -202,6 +202,27 @@ def contexts_case(shape, C, group, own, S, k, adapter, seed):
     return case, ctx_kv
 
 
+def contexts_cache(ab, case, ctx_kv, C, group, own):
+    """The pool of a contexts_case: every sequence's own rows, then each context once."""
+    shape, n = case.shape, len(case.S)
+    cache = ab.KVCache([own[b] + case.S[b] for b in range(n)] + list(C), shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda",
+                       fill=CANARY, guard_rows=2)
+
+    def put(o, K, V):
+        for pool, rows in ((cache.k, K), (cache.v, V)):
+            pool[o:o + len(rows)] = torch.from_numpy(rows).to(shape.torch_dtype).reshape(len(rows), shape.n_kv_heads, shape.head_dim).cuda()
+
+    for i in range(len(C)):
+        put(int(cache.seq_offset[n + i]), *ctx_kv[i])
+    for b in range(n):
+        lo = C[group[b]] if group[b] >= 0 else 0
+        put(int(cache.seq_offset[b]), case.cache_K[b][lo:], case.cache_V[b][lo:])
+        cache.seq_len[b] = case.P[b]
+        if lo:
+            cache.share_prefix(b, int(cache.seq_offset[n + group[b]]), lo)
+    return cache
+
+
 def run_contexts(ab, ctx, case, ctx_kv, C, group, own, decode=False):
     shape = case.shape
     n = len(case.S)

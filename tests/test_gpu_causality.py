@@ -77,23 +77,7 @@ def test_decode_steps_before_a_non_finite_row(ab, ctx, G, steps, contexts, cache
         x[ends[b]:, b] = what
     x = x.cuda().contiguous()
 
-    def cache():
-        c = ab.KVCache([own[b] + steps for b in range(n)] + C, shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda", guard_rows=2)
-
-        def put(o, K, V):
-            for pool, rows in ((c.k, K), (c.v, V)):
-                pool[o:o + len(rows)] = torch.from_numpy(rows).to(shape.torch_dtype).reshape(len(rows), shape.n_kv_heads, shape.head_dim).cuda()
-
-        for i in range(2):
-            put(int(c.seq_offset[n + i]), *ctx_kv[i])
-        for b in range(n):
-            lo = start[b] - own[b]
-            put(int(c.seq_offset[b]), case.cache_K[b][lo:], case.cache_V[b][lo:])
-            c.seq_len[b] = start[b]
-            if contexts:
-                c.share_prefix(b, int(c.seq_offset[n + group[b]]), lo)
-        return c
-
+    cache = lambda: H.contexts_cache(ab, case, ctx_kv, C, group, own)
     layer, run, chain = H.gpu_layer(case, shape), cache(), cache()
     out = ab.alora_decode_steps(ctx, layer, run, x, case.k, case.adapter)
     want = torch.stack([ab.alora_decode(ctx, layer, chain, x[t], case.k, case.adapter) for t in range(steps)])

@@ -347,3 +347,29 @@ def test_a_stack_of_adapters_on_one_context_the_base_model_prefilled(ab, dtype):
         # size, so its layer-0 attention is partitioned differently and layer 1 sees other bf16 neighbours)
         assert e_sp <= 4 * tol, f"sequence {b}: shared and private copies of the context differ by {e_sp:.3e}"
     H.report(check="stack of adapters on one shared context", dtype=shape.dtype, err_end_to_end=worst, shared_vs_private=worst_sp)
+
+
+# sequences of one context apart in the batch, some without any, contexts that differ in length only; items of one and of several sequences
+@pytest.mark.parametrize("name,steps,opts", [("G4", 5, {}), ("G4", 40, {}), ("G1", 3, {}), ("G8", 70, {}), ("G4", 5, {"kv_splits": 2}), ("f32", 3, {})])
+def test_runs_of_decode_steps_on_contexts_in_any_order(ab, name, steps, opts):
+    shape = SHAPES[name]
+    ctx = ab.Context(0)
+    try:
+        for k_, v in opts.items():
+            ctx.set_option(k_, v)
+        C = [300, 64, 700]
+        group = [2, 0, -1, 1, 2, 0, 1, -1, 0, 2, 2]
+        own = [0, 30, 200, 0, 64, 1, 70, 0, 0, 129, 5]
+        n = len(group)
+        k = [max(0, (C[g] if g >= 0 else 0) + own[b] + b % 3 - 1) for b, g in enumerate(group)]
+        case, ctx_kv = H.contexts_case(shape, C, group, own, [steps] * n, k, [b % 4 - 1 for b in range(n)], seed=960 + steps)
+        x = torch.stack([torch.stack([case.x_new[b][t] for b in range(n)]) for t in range(steps)]).cuda().contiguous()
+        cache = H.contexts_cache(ab, case, ctx_kv, C, group, own)
+        out = ab.alora_decode_steps(ctx, H.gpu_layer(case, shape), cache, x, case.k, case.adapter)
+        torch.cuda.synchronize()
+        ref, _ = H.oracle_prefill(case)
+        for b in range(n):
+            err = H.rel_err(H.f64(out[:, b]), ref[case.cu[b]:case.cu[b + 1]])
+            assert err <= H.TOL[shape.dtype], f"sequence {b}: off by {err:.3e}"
+    finally:
+        ctx.close()
