@@ -601,7 +601,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const float *__restri
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int gi = wave + 4 * u;
-      if (GM == 1 || gi < ng) {
+      if (gi < ng) {      // (with one head three waves have none: not a loop that GM bounds)
         const float s = ps[gi * 64 + lane];
         const float mn = fmaxf(m[u], wave_max(s));
         const float p = __expf(s - mn), corr = __expf(m[u] - mn);      // (every tile holds a valid key: mn is finite)
