@@ -250,15 +250,17 @@ alora_status alora_decode_static(alora_ctx *ctx, const alora_layer_desc *layer, 
                                  const int32_t *adapter_per_seq, int32_t B, void *attn_out, void *stream);
 
 /* A run of n_steps decode steps (the short generations of an adapter: Section 3 times 16-token
- * evaluations) with the per-sequence arrays validated and staged once: the same result as n_steps
+ * evaluations) with the per-sequence arrays validated once: the same result as n_steps
  * alora_decode calls, step t reading x_steps[t] and writing attn_out[t], every sequence growing by
  * one cache row per step.  For callers that already hold the inputs of all steps (teacher forcing,
  * replay, benchmarks); a sampling loop that needs the output of step t to build step t+1 calls
  * alora_decode.  All inputs being there, the rows of up to 1024 (sequence, step) pairs are projected and appended
- * together, and a run of no more than that attends in one pass over what was cached before it; the run's own rows are
+ * together and attend in one pass over what was cached before them; their own rows are
  * read up to each row's position and no further, so that a later step reaches no earlier one whatever it holds (Inf, NaN: the
- * padding of a shorter answer).  Sums may be taken in another order than alora_decode takes them: outputs, and cache rows that
- * an adapter applies to, agree with its to rounding (cache rows of the base model bit for bit).  Where attn_out overlaps x_steps the steps are taken one at a time, in order.   x_steps DEVICE [n_steps, B, d]; attn_out DEVICE [n_steps, B, N_q];
+ * padding of a shorter answer).  Longer runs are several of these, one after the other.  Sums may be taken in another order than
+ * alora_decode takes them: outputs, and cache rows that an adapter applies to, agree with its to rounding (cache rows of the base
+ * model bit for bit).  Where attn_out overlaps x_steps the steps are taken one at a time, in order.
+ * x_steps DEVICE [n_steps, B, d]; attn_out DEVICE [n_steps, B, N_q];
  * seq_len[b] += n_steps; P_b + n_steps must fit the capacity. */
 alora_status alora_decode_steps(alora_ctx *ctx, const alora_layer_desc *layer, alora_kv_cache *cache,
                                 const void *x_steps, const int32_t *k_per_seq,

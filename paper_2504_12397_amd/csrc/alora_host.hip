@@ -1330,15 +1330,32 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   const size_t esz = layers[0].dtype == ALORA_BF16 ? 2 : 4;
   constexpr int RUN_ROWS = 1024;
   int run_steps = 1;
-  // A run of decode steps has the inputs of all of them: their rows are prepared, projected and appended RUN_ROWS at a time (one
-  // sum over K whatever the number of rows: base rows come out with the same bits as a step at a time), then every step attends to the
-  // rows up to its own.  A record per row and step stands for a sequence of one new row.  Not where an output lies where a later input
-  // does.  16 steps of 64 rows: 16 x 35 -> 115 us.
+  // A run of decode steps has the inputs of all of them: their rows are prepared, projected and appended together, RUN_ROWS at most (their
+  // workspace is bounded; one sum over K whatever the number of rows: base rows come out with the same bits as a step at a time).  A record
+  // per row and step stands for a sequence of one new row.  Not where an output lies where a later input does.  16 steps of 64 rows:
+  // 16 x 35 -> 115 us.  A longer run is several of about equal length, one after the other, each done like a short one: 17 steps of 64 rows
+  // on 16 contexts of 16384 keys 3560 -> 666 us, 64 steps 13370 -> 1491, 1025 of one row on 8192 keys 13140 -> 335.
   Plan run_pl;
   if (n_steps > 1) {
     const size_t xb = (size_t)n_steps * pl.T * L.d * esz, ob = (size_t)n_steps * pl.T * L.n_q * esz;
     const bool apart = (const char *)x + xb <= (const char *)out || (const char *)out + ob <= (const char *)x;
-    run_steps = apart ? std::max(1, std::min(n_steps, RUN_ROWS / pl.T)) : 1;
+    const int most = apart ? std::max(1, RUN_ROWS / pl.T) : 1;
+    run_steps = std::min(n_steps, most);
+    if (most > 1 && n_steps > most) {
+      st = ensure_rope(ctx, pl.max_len, L.head_dim / 2, layers[0].rope_theta, s);      // (once, not for every part)
+      if (st != ALORA_OK) return st;
+      for (int t = 0, left = (n_steps + most - 1) / most; left > 0; --left) {
+        const int n = (n_steps - t + left - 1) / left;
+        st = run(ctx, layers, 1, caches, (const char *)x + (size_t)t * pl.T * L.d * esz, cu, kps, aps, B,
+                 (char *)out + (size_t)t * pl.T * L.n_q * esz, stream, false, true, n);
+        if (st != ALORA_OK) {      // (no memory: the run's rows do not count)
+          for (int b = 0; b < B; ++b) caches[0].seq_len[b] -= (cu[b + 1] - cu[b]) * t;
+          return st;
+        }
+        t += n;
+      }
+      return ALORA_OK;
+    }
   }
   if (run_steps > 1) {
     run_pl = pl;
@@ -1362,7 +1379,7 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   // pass that masked them their values would still be multiplied, by probability 0, and a step whose row is Inf or NaN would reach
   // the steps before it.  16 steps of 64 rows on 16 contexts of 16384 keys 3412 -> 442 us, 22 of them the new keys.  (A private cache read once by the prefill kernel takes about as long as 1.4 decode steps, so this holds from two steps on.  Not
   // for the variants of the prefill kernel that the options choose.)
-  const bool run_prefill = decode && n_steps > 1 && run_steps == n_steps && layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 &&
+  const bool run_prefill = decode && run_steps > 1 && layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 &&
                            attn_waves == 8 && ctx->opt_attn_fold && attn_prefill_mfma_supported(L);
   Plan run_att;
   // sequences by prefix, so that those of one context share its items wherever they stand in the batch: two steps of 64 rows on 16 contexts of 16384
@@ -1561,17 +1578,13 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
 
   const bool bf = layers[0].dtype == ALORA_BF16;
   if (!stack) {
-    // n_steps > 1: a run of decode steps on the metadata staged once; step t sits t positions further on
+    // n_steps > 1: a run of decode steps on the metadata staged once, projected together (run_steps = n_steps) or one at a time
     auto steps = [&](auto one) {
       using T = decltype(one);
       for (int t0 = 0; t0 < n_steps; t0 += run_steps) {
-        // (the last rows of a run that run_steps does not divide: the steps that are left)
-        const int n = std::min(run_steps, n_steps - t0);
-        Plan rest;
-        if (n < run_steps) { rest = ppl; rest.T = rest.B = n * pl.T; rest.seqs.resize(rest.T); }
-        project_rows<T>(ctx, &layers[0], L, &caches[0], (const T *)x + (size_t)t0 * pl.T * L.d, n < run_steps ? rest : ppl, seqs_dev, w, true, t0, s);
+        project_rows<T>(ctx, &layers[0], L, &caches[0], (const T *)x + (size_t)t0 * pl.T * L.d, ppl, seqs_dev, w, true, t0, s);
         if (run_prefill) attend_rows<T>(ctx, L, &caches[0], att_pl, seqs_dev, w, n_splits, false, 0, 0, (T *)out, s);
-        else for (int t = 0; t < n; ++t)
+        else for (int t = 0; t < run_steps; ++t)
           attend_rows<T>(ctx, L, &caches[0], pl, seqs_dev, w, n_splits, decode, t0 + t, t * pl.T, (T *)out + (size_t)(t0 + t) * pl.T * L.n_q, s);
       }
     };

@@ -554,6 +554,24 @@ def test_runs_of_decode_steps(ab, ctx, G, steps, opts):
     assert H.rel_err(H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1), ref) <= H.TOL["bf16"]
 
 
+# beyond the 1024 rows that are projected together: parts of about equal length, each in one pass over what is cached before it
+@pytest.mark.parametrize("n,steps,parts", [(64, 16, 1), (64, 17, 2), (64, 33, 3), (3, 341, 1), (3, 342, 2), (1, 2049, 3)])
+def test_runs_of_decode_steps_in_parts(ab, ctx, n, steps, parts):
+    ctx.set_option("profile", 1)
+    shape = wl.LayerShape(d=256, n_q_heads=4, n_kv_heads=2, head_dim=128, rank=8, n_adapters=2)
+    P = [(37 * b) % 90 for b in range(n)]
+    case = H.make_case(shape, P, [steps] * n, [p + b % 5 for b, p in enumerate(P)], [b % 3 - 1 for b in range(n)], seed=3050 + n, prefix="random")
+    x = torch.stack([torch.stack([case.x_new[b][t] for b in range(n)]) for t in range(steps)]).cuda().contiguous()
+    cache = H.gpu_cache(case)
+    before_k, before_v = cache.k.cpu(), cache.v.cpu()
+    out = ab.alora_decode_steps(ctx, H.gpu_layer(case, shape), cache, x, case.k, case.adapter)
+    torch.cuda.synchronize()
+    assert {f: ctx.profile_read()[f]["launches"] for f in ("qkv_gemm", "attn_prefill", "attn_decode")} == {"qkv_gemm": parts, "attn_prefill": parts, "attn_decode": parts}
+    ref, rows = H.oracle_prefill(case)
+    H.check_cache_after(case, cache, before_k, before_v, rows, H.TOL["bf16"])
+    assert H.rel_err(H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1), ref) <= H.TOL["bf16"]
+
+
 # records from the kernel arguments (up to 16 sequences), one per thread, and more than a workgroup has threads; 3 * rank columns in tiles of 8 and of 16
 @pytest.mark.parametrize("n,rank,n_adapters", [(16, 8, 2), (17, 24, 3), (512, 8, 1), (513, 8, 2), (700, 16, 2)])
 def test_row_preparation_of_many_short_sequences(ab, ctx, n, rank, n_adapters):
