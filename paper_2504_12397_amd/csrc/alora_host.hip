@@ -899,6 +899,7 @@ struct DecodePlan {
   int range = 0;                   // keys per own range, before it is evened out (dec_cut)
   int n_device_items = 0;          // size of the device-built list: rows x head groups x n_own
   int hw = 1, kr = 1, groups = 1, cols_max = 1;
+  double us = 0;                   // what a step's attention would take (decode_cut_us)
 };
 
 // What one way of cutting the keys would take, in us: `n_of` [s] workgroups run s steps of 32 keys per wave, `records` partial records, at
@@ -1015,7 +1016,7 @@ DecodePlan plan_decode_items(const alora_ctx *ctx, const Plan &pl, const LayerDi
         records += (double)c.parts * q.rows;
       }
       const double us = decode_cut_us(n_of, n_cu, 512.0 * keys * L.n_kv_heads, kr > 1, hw < wide, records * L.n_q_heads, (int64_t)pl.T * L.n_q_heads, own + shared);
-      if (us < best) { best = us; dp.hw = hw; dp.kr = kr; range = r; }
+      if (us < best) { best = dp.us = us; dp.hw = hw; dp.kr = kr; range = r; }
     };
     for (int form = cap > 1 && wide > 2 ? 0 : 1; form < 2; ++form) {
       int hw, kr, last = 0;
@@ -1098,6 +1099,7 @@ struct PrefixRun { int64_t prefix_off; int prefix_len, row0, n_rows; };
 struct PrefillPlan {
   std::vector<PrefixRun> runs;
   int n_own = 1, n_sh = 0;
+  double tiles = 0;      // what the cut would take (prefill_cut_tiles), where anything is compared with it
 };
 // keys of a sequence behind its prefix that prefill attention walks
 int prefill_own_keys(const Plan &pl, const SeqMeta &m) { return m.P - m.prefix_len + (pl.cached_only ? 0 : m.n_new); }
@@ -1137,8 +1139,10 @@ double prefill_cut_tiles(const alora_ctx *ctx, const Plan &pl, const LayerDims &
     n += count[c] * per;
     worst = std::max(worst, std::ceil(n / cus) * (len[c] + PREFILL_ITEM_TILES));
   }
-  // (a tile is about 1.7 us; a record of 272 bytes is written and read at about 4 TB/s, and the merge is a launch)
-  if (n_own + n_sh > 1) worst += 2.0 + (double)rows * (n_own + n_sh) * L.n_q_heads * (2 * 272) / 4e6 / 1.7;
+  // (a tile is about 1.7 us; a record of 272 bytes, 520 where it is a run's, is written and read at about 4 TB/s, and the merge is a launch)
+  const int most = n_own + n_sh + (pl.cached_only ? 1 : 0);
+  if (most > 1) worst += 2.0 + (double)rows * (n_own + n_sh) * L.n_q_heads * (2 * (pl.cached_only ? 520 : 272)) / 4e6 / 1.7;
+  if (most > 16 && rows * L.n_q_heads > 512) worst += 1.6;
   return worst;
 }
 
@@ -1171,18 +1175,23 @@ PrefillPlan plan_prefill_ranges(const alora_ctx *ctx, const Plan &pl, const Laye
   // prefixes) or one (no prefix) would have them: 32 x 16 rows on four contexts of 16384 keys 249 -> 224 us with one range per unit instead
   // of two, eight sequences of 128 rows on 32768 keys 4285 -> 4228 (four layers).
   // (and at most 2^20 records of a kind: half a gigabyte)
-  const int longest = std::max(max_own, max_pfx), most = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(16, longest / 256), (1 << 20) / ((int64_t)pl.T * L.n_q_heads)));
-  if (pp.runs.empty() && tiles * L.n_kv_heads >= 4 * (int64_t)ctx->n_cu) return pp;      // more items than could be evened out by cutting them
+  // (a run of decode steps has few rows to a context, and as many ranges as a step of it: one row on 131072 keys of one kv head, two steps 175 us
+  // in 16 ranges, 62 in as many as are worth it; 67 a step at a time)
+  const int limit = pl.cached_only ? 256 : 16;
+  const int longest = std::max(max_own, max_pfx);
+  int most = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(limit, longest / 256), (1 << 20) / ((int64_t)pl.T * L.n_q_heads)));
+  if (pp.runs.empty() && tiles * L.n_kv_heads >= 4 * (int64_t)ctx->n_cu) most = 1;      // more items than could be evened out by cutting them
+  if (most == 1 && !pl.cached_only) return pp;      // (nothing to compare)
   double least = 0;
   int was_own = 0, was_sh = 0;
-  for (int n = 1; n <= most; ++n) {
+  for (int n = 1; n <= most; n += n < 16 ? 1 : n / 4) {
     const int len = std::max(4, ((longest + 63) / 64 + n - 1) / n);      // tiles of a range
-    auto ranges = [&](int keys) { return std::max(1, std::min(16, ((keys + 63) / 64 + len - 1) / len)); };
+    auto ranges = [&](int keys) { return std::max(1, std::min(limit, ((keys + 63) / 64 + len - 1) / len)); };
     const int own = max_own > 0 ? ranges(max_own) : 0, sh = pp.runs.empty() ? 0 : ranges(max_pfx);
     if (own == was_own && sh == was_sh) continue;
     was_own = own; was_sh = sh;
     const double t = prefill_cut_tiles(ctx, pl, L, tq, pp, (longest + 63) / 64, own, sh);
-    if (n == 1 || t < least) { least = t; pp.n_own = own; pp.n_sh = sh; }
+    if (n == 1 || t < least) { least = pp.tiles = t; pp.n_own = own; pp.n_sh = sh; }
   }
   return pp;
 }
@@ -1290,6 +1299,23 @@ std::vector<DecItem> build_run_items(const Plan &pl, const LayerDims &L, int n_s
   return items;
 }
 
+// What the attention of a run of decode steps would take in one pass over what was cached before it, in us: the prefill items (a workgroup has its
+// start to pay for, many of them more than the few tiles of a short cache), the decode items of the run's own keys, the records.  Against
+// n_steps * (decode_cut_us + 2.5).  Fitted to 2254 measured runs (2 to 16 steps of 1 to 500 rows on 0 to 131072 keys, 1 to 32 kv heads, private
+// and shared contexts): the way it picks takes 0.3 % longer than the better one on average and 24 % at most, the pass throughout 2.6 % and 4.7 x
+// (two steps: 64 rows of 32 kv heads on 16 keys 180 us, 55 a step at a time; 500 rows of 8 on 300 keys 354 and 301).
+double run_pass_us(const alora_ctx *ctx, const Plan &pl, const LayerDims &L, const PrefillPlan &pp, int n_steps) {
+  const int tq = attn_prefill_mfma_tokens_per_tile(L, 8);
+  int64_t items = 0;
+  for (const SeqMeta &m : pl.seqs) items += (int64_t)((n_steps + tq - 1) / tq) * (m.prefix_len > 0 ? pp.n_own : pp.n_own + pp.n_sh);
+  for (const PrefixRun &r : pp.runs) items += (int64_t)((r.n_rows + tq - 1) / tq) * pp.n_sh;
+  items *= L.n_kv_heads;
+  const int64_t own = (int64_t)pl.T * ((L.n_kv_heads + 7) / 8);
+  const double start = items > 0 ? 7.0 + 11.0 * (double)items / ctx->n_cu : 0.0;
+  return 1.6 * std::max(pp.tiles, start) + 4.0 * (double)((own + ctx->n_cu - 1) / ctx->n_cu) +
+         1.7 * (double)pl.T * L.n_q_heads * (pp.n_own + pp.n_sh + 1) * (2 * 520) / 4e6;
+}
+
 alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, alora_kv_cache *caches,
                  const void *x, const int32_t *cu, const int32_t *kps, const int32_t *aps, int B, void *out,
                  void *stream, bool stack, bool decode = false, int n_steps = 1, bool use_static = false) {
@@ -1373,34 +1399,6 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
       }
   }
   const Plan &ppl = run_steps > 1 ? run_pl : pl;      // the rows that are projected together
-  const int attn_waves = ctx->opt_attn_waves == 4 ? 4 : 8;
-  // Where the whole run is projected together, prefill attention walks the keys that were cached before it for the rows of all its steps: the
-  // cache is read once instead of once a step.  The run's own keys are for items of the decode kernel that end at each row's position: in a
-  // pass that masked them their values would still be multiplied, by probability 0, and a step whose row is Inf or NaN would reach
-  // the steps before it.  16 steps of 64 rows on 16 contexts of 16384 keys 3412 -> 442 us, 22 of them the new keys.  (A private cache read once by the prefill kernel takes about as long as 1.4 decode steps, so this holds from two steps on.  Not
-  // for the variants of the prefill kernel that the options choose.)
-  const bool run_prefill = decode && run_steps > 1 && layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 &&
-                           attn_waves == 8 && ctx->opt_attn_fold && attn_prefill_mfma_supported(L);
-  Plan run_att;
-  // sequences by prefix, so that those of one context share its items wherever they stand in the batch: two steps of 64 rows on 16 contexts of 16384
-  // keys, in turn, 977 us in the order of the batch (a step at a time 490), 368 like this
-  std::vector<int32_t> run_order;
-  if (run_prefill) {
-    run_att = pl;
-    run_att.T = pl.T * n_steps;
-    run_att.cached_only = true;
-    if (pl.any_prefix) {
-      run_order = by_prefix(pl);
-      for (int b = 0; b < B; ++b) run_att.seqs[b] = pl.seqs[run_order[b]];
-    }
-    for (int b = 0; b < B; ++b) { run_att.seqs[b].n_new = n_steps; run_att.seqs[b].row_start = b * n_steps; }
-  }
-  const Plan &att_pl = run_prefill ? run_att : pl;      // the rows that attend together: sequence after sequence (the kernel finds where they lie)
-  const bool attn_mfma = run_prefill || (layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && !decode &&
-                                         attn_prefill_mfma_supported(L));
-  int n_splits = pick_splits(ctx, pl.T, L.n_kv_heads, pl.max_len);
-  const bool decode_mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && decode && !run_prefill &&
-                           attn_decode_mfma_supported(L);
   // kernel family: MFMA for bf16 shapes it covers, plain otherwise
   const bool mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && L.d % 64 == 0 &&
                     (L.n_adapters == 0 || (L.rank % 8 == 0 && L.n_adapters <= 64)) && L.n_q % 32 == 0 &&
@@ -1430,26 +1428,60 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
   // alike: they give the same bits).  Not where the option asked for the segments: such a call is refused.
   if (decode && ctx->opt_gemm_splits == 0 && k_splits > 1 && static_bytes(1, (L.n_kv_heads + 7) / 8) > SCRATCH_BYTES) k_splits = 1;
   // work lists of the MFMA attention kernels (the number of partial records per (row, head) comes out of them)
+  const int attn_waves = ctx->opt_attn_waves == 4 ? 4 : 8;
+  int n_splits = pick_splits(ctx, pl.T, L.n_kv_heads, pl.max_len);
+  bool attn_mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && !decode && attn_prefill_mfma_supported(L);
+  bool decode_mfma = layers[0].dtype == ALORA_BF16 && ctx->opt_kernels == 0 && decode && attn_decode_mfma_supported(L);
   DecodePlan dp;
   PrefillPlan pp;
-  if (decode_mfma) {
+  auto plan_decode = [&](bool items) {
     // One long sequence among many short ones asks for many records in every row's place: bounded to about 130 MB at 32 heads,
     // and to what the static scratch array holds where one record per row fits there (both entry points cut the keys alike).
     int cap = pl.T <= 16 ? 256 : std::max(1, std::min(64, 8192 / pl.T));
     if (!pl.any_prefix && static_bytes(1, (L.n_kv_heads + 7) / 8) <= SCRATCH_BYTES)
       while (cap > 1 && static_bytes(cap, (L.n_kv_heads + 1) / 2) > SCRATCH_BYTES) --cap;
-    dp = plan_decode_items(ctx, pl, L, cap, n_steps, use_static);
-    n_splits = dp.n_own + dp.n_shared;
+    return plan_decode_items(ctx, pl, L, cap, n_steps, !items);
+  };
+  // Rows of several steps that are projected together can attend in one pass: prefill attention walks the keys that were cached before them for
+  // the rows of all steps, the cache read once instead of once a step.  The run's own keys are for items of the decode kernel that end at each
+  // row's position: in a pass that masked them their values would still be multiplied, by probability 0, and a step whose row is Inf or NaN
+  // would reach the steps before it.  16 steps of 64 rows on 16 contexts of 16384 keys 3412 -> 442 us, 22 of them the new keys.  Not for the
+  // variants of the prefill kernel that the options choose.
+  Plan run_att;
+  // sequences by prefix, so that those of one context share its items wherever they stand in the batch: two steps of 64 rows on 16 contexts of 16384
+  // keys, in turn, 977 us in the order of the batch (a step at a time 490), 368 like this
+  std::vector<int32_t> run_order;
+  bool run_prefill = decode_mfma && run_steps > 1 && attn_waves == 8 && ctx->opt_attn_fold && attn_prefill_mfma_supported(L);
+  if (run_prefill) {
+    run_att = pl;
+    run_att.T = pl.T * n_steps;
+    run_att.cached_only = true;
+    if (pl.any_prefix) {
+      run_order = by_prefix(pl);
+      for (int b = 0; b < B; ++b) run_att.seqs[b] = pl.seqs[run_order[b]];
+    }
+    for (int b = 0; b < B; ++b) { run_att.seqs[b].n_new = n_steps; run_att.seqs[b].row_start = b * n_steps; }
+    pp = plan_prefill_ranges(ctx, run_att, L, B, attn_waves);
+    // (kv_splits leaves nothing to compare, and no decode step is done in less than its round and one step of keys)
+    const double pass = run_pass_us(ctx, run_att, L, pp, n_steps);
+    run_prefill = ctx->opt_splits > 0 || pass <= n_steps * (3.76 + 4.8 + 2.5) || pass <= n_steps * (plan_decode(false).us + 2.5);
   }
-  if (attn_mfma) {
-    pp = plan_prefill_ranges(ctx, att_pl, L, B, attn_waves);
-    n_splits = pp.n_own + pp.n_sh;
-  }
-  if (run_prefill) {      // (one more record per row: the run's own keys)
+  if (run_prefill) {
+    attn_mfma = true;
+    decode_mfma = false;
+    n_splits = pp.n_own + pp.n_sh + 1;      // (one more record per row: the run's own keys)
     decode_mfma_shape(L.n_kv_heads, false, &dp.hw, &dp.kr);
     dp.cols_max = L.n_q_heads / L.n_kv_heads;
-    dp.items = build_run_items(pl, L, n_steps, dp.hw, n_splits++);
+    dp.items = build_run_items(pl, L, n_steps, dp.hw, n_splits - 1);
+  } else if (decode_mfma) {
+    run_order.clear();
+    dp = plan_decode(!use_static);
+    n_splits = dp.n_own + dp.n_shared;
+  } else if (attn_mfma) {
+    pp = plan_prefill_ranges(ctx, pl, L, B, attn_waves);
+    n_splits = pp.n_own + pp.n_sh;
   }
+  const Plan &att_pl = run_prefill ? run_att : pl;      // the rows that attend together: sequence after sequence (the kernel finds where they lie)
   const std::vector<DecItem> &ditems = dp.items;
   const int n_static_items = dp.n_device_items;
   const int dec_hw = dp.hw, dec_kr = dp.kr, dec_groups = dp.groups, dec_cols_max = dp.cols_max;

@@ -572,6 +572,27 @@ def test_runs_of_decode_steps_in_parts(ab, ctx, n, steps, parts):
     assert H.rel_err(H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1), ref) <= H.TOL["bf16"]
 
 
+# one pass over the cache or a step at a time, whichever takes less: many workgroups on short caches, a long row of one kv head, contexts between
+@pytest.mark.parametrize("n,kv,G,P,steps,one_pass", [(64, 32, 1, 16, 2, False), (500, 8, 2, 40, 2, False), (64, 32, 1, 16, 16, None), (1, 1, 8, 40000, 2, None),
+                                                     (1, 1, 8, 40000, 3, True), (4, 8, 4, 3000, 4, True), (16, 2, 4, 300, 9, True)])
+def test_runs_of_decode_steps_one_way_or_the_other(ab, ctx, n, kv, G, P, steps, one_pass):
+    ctx.set_option("profile", 1)
+    shape = wl.LayerShape(d=256, n_q_heads=kv * G, n_kv_heads=kv, head_dim=128, rank=8, n_adapters=2)
+    P = [P - b % 3 for b in range(n)]
+    case = H.make_case(shape, P, [steps] * n, [p + b % 2 for b, p in enumerate(P)], [b % 3 - 1 for b in range(n)], seed=3080 + n + steps, prefix="random")
+    x = torch.stack([torch.stack([case.x_new[b][t] for b in range(n)]) for t in range(steps)]).cuda().contiguous()
+    cache = H.gpu_cache(case)
+    before_k, before_v = cache.k.cpu(), cache.v.cpu()
+    out = ab.alora_decode_steps(ctx, H.gpu_layer(case, shape), cache, x, case.k, case.adapter)
+    torch.cuda.synchronize()
+    if one_pass is not None:
+        launches = {f: r["launches"] for f, r in ctx.profile_read().items()}
+        assert (launches.get("attn_prefill", 0), launches["attn_decode"]) == ((1, 1) if one_pass else (0, steps))
+    ref, rows = H.oracle_prefill(case)
+    H.check_cache_after(case, cache, before_k, before_v, rows, H.TOL["bf16"])
+    assert H.rel_err(H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1), ref) <= H.TOL["bf16"]
+
+
 # records from the kernel arguments (up to 16 sequences), one per thread, and more than a workgroup has threads; 3 * rank columns in tiles of 8 and of 16
 @pytest.mark.parametrize("n,rank,n_adapters", [(16, 8, 2), (17, 24, 3), (512, 8, 1), (513, 8, 2), (700, 16, 2)])
 def test_row_preparation_of_many_short_sequences(ab, ctx, n, rank, n_adapters):
