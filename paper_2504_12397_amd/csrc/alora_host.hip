@@ -238,9 +238,23 @@ struct Plan {
   int n_used = 0;            // adapters that a row of the call may use (at most 64 listed), and their scales
   uint8_t used[64] = {};
   float used_scale[64] = {};
-  int n_adapted = 0;         // rows (of the last step) that an adapter applies to
+  int adapted_tiles = 0;     // pairs of 32 rows (of the last step) and an adapter that applies to one of them
   bool cached_only = false;  // prefill attention walks the keys that were cached before the call and no others
 };
+
+// of a call that ends `more` steps later than its records say
+void count_adapted_tiles(Plan *pl, int more) {
+  pl->adapted_tiles = 0;
+  int last[64];
+  std::fill(last, last + 64, -1);
+  for (const SeqMeta &m : pl->seqs) {      // (in the order of their rows)
+    const int rows = (int)std::min<int64_t>(m.n_new, (int64_t)m.P + m.n_new + more - m.k);
+    if (m.adapter < 0 || m.adapter >= 64 || rows <= 0) continue;
+    const int lo = std::max((m.row_start + m.n_new - rows) / 32, last[m.adapter] + 1), hi = (m.row_start + m.n_new - 1) / 32;
+    pl->adapted_tiles += std::max(0, hi - lo + 1);
+    last[m.adapter] = std::max(last[m.adapter], hi);
+  }
+}
 
 alora_status check_layer(alora_ctx *ctx, const alora_layer_desc *ly, bool need_tail, LayerDims *L) {
   if (!ly) return fail(ctx, ALORA_EINVAL, "layer descriptor is NULL");
@@ -296,7 +310,6 @@ alora_status check_batch(alora_ctx *ctx, const alora_layer_desc *ly, const alora
   pl->any_adapter = false;
   pl->any_prefix = false;
   pl->n_used = 0;
-  pl->n_adapted = 0;
   uint64_t listed = 0;
   for (int b = 0; b < B; ++b) {
     const int S = cu[b + 1] - cu[b];
@@ -334,7 +347,6 @@ alora_status check_batch(alora_ctx *ctx, const alora_layer_desc *ly, const alora
     if (plen > 0) pl->any_prefix = true;
     if (aps[b] >= 0 && S > 0 && grown > kps[b]) {
       pl->any_adapter = true;
-      pl->n_adapted += (int)std::min<int64_t>(S, grown - kps[b]);
       if (aps[b] < 64 && !((listed >> aps[b]) & 1)) {
         listed |= 1ull << aps[b];
         pl->used[pl->n_used] = (uint8_t)aps[b];
@@ -344,6 +356,7 @@ alora_status check_batch(alora_ctx *ctx, const alora_layer_desc *ly, const alora
     pl->max_len = std::max(pl->max_len, (int)grown);
   }
   pl->T = cu[B];
+  count_adapted_tiles(pl, n_steps - 1);
   // The regions the sequences own must be disjoint, and nobody may write where somebody reads a shared prefix:
   // the kernels would write those cache rows concurrently, silently.
   {
@@ -518,7 +531,7 @@ void project_rows(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L
       if (rank_used) {
         pa.parts = 3;
         pa.n_used = pl.n_used;
-        pa.n_adapted = pl.n_adapted;
+        pa.adapted_tiles = pl.adapted_tiles;
         memcpy(pa.used, pl.used, sizeof pa.used);
         memcpy(pa.used_scale, pl.used_scale, sizeof pa.used_scale);
       }
@@ -681,7 +694,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     pa.T = T_rows; pa.d = K; pa.A = (const bf16 *)A_all; pa.rank = r; pa.parts = parts;
     pa.xh = (bf16 *)const_cast<void *>(z); pa.packed = packed ? 1 : 0; pa.tlow16 = (bf16 *)w.tlow; pa.rm = w.rm;
     if (K <= 8192 && prep_rows_mfma_supported(L.d, r) && t_rows_mfma_supported(pa)) {
-      pa.n_used = w.pl->n_used; pa.n_adapted = w.pl->n_adapted;
+      pa.n_used = w.pl->n_used; pa.adapted_tiles = w.pl->adapted_tiles;
       memcpy(pa.used, w.pl->used, sizeof pa.used);
       memcpy(pa.used_scale, w.pl->used_scale, sizeof pa.used_scale);
       launch_t_rows_mfma(pa, s);
@@ -1388,15 +1401,14 @@ alora_status run(alora_ctx *ctx, const alora_layer_desc *layers, int n_layers, a
     run_pl.T = run_pl.B = run_steps * pl.T;
     run_pl.seqs.clear();
     run_pl.seqs.reserve(run_pl.T);
-    run_pl.n_adapted = 0;
     for (int t = 0; t < run_steps; ++t)
       for (const SeqMeta &m : pl.seqs) {
         SeqMeta q = m;
         q.row_start += t * pl.T;
         q.P += t;
         run_pl.seqs.push_back(q);
-        if (m.adapter >= 0) ++run_pl.n_adapted;      // (at most: the last steps')
       }
+    count_adapted_tiles(&run_pl, 0);
   }
   const Plan &ppl = run_steps > 1 ? run_pl : pl;      // the rows that are projected together
   // kernel family: MFMA for bf16 shapes it covers, plain otherwise

@@ -18,7 +18,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int PREP_ROWS = 16;
 constexpr int PREP_WAVES = 8;
 constexpr int PREP_FEW = 512;      // workgroups
-constexpr int T_NARROW = 256;      // workgroups with something to do, up to which t_rows takes 32 columns each instead of 96
+constexpr int T_NARROW = 220;      // workgroups, up to which t_rows takes 32 columns each instead of 96 (launch_t_rows_mfma)
 constexpr int PREP_NARROW = 128;      // up to so many of 16 columns (half of the compute units) they take 8 columns instead
 
 // Sum of squares of a row, in ONE order for every kernel that normalises rows (a row's x_hat must not depend on
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
 // t of many rows from x_hat (or from the input of another linear with `parts` down-matrices): workgroup (x, y, z) takes 32 rows, columns 32 NB y .. of the parts * rank and adapter used[z]; it leaves at
 // once when no row of its tile uses that adapter.  What bounds it: down matrix and rows through one compute unit, which
 // loads to registers in operand order brought in at 28 bytes per ns; requests to LDS arrive at 50 to 130.  So 96 columns per workgroup
-// (1 MB) only where the adapted rows would make more workgroups of 32 columns (0.5 MB) than there are compute units: 512 rows of four
+// (1 MB) only where 32 columns (0.5 MB) would make more workgroups than the chip takes at once: 512 rows of four
 // adapters 20.5 -> 11.3 us, 1024 rows at rank 64 23 -> 17, 8131 rows of which 127 are adapted 20.5 -> 11.6; 4458 rows 24.6 with 96, 31.7 with 32.  128 values of k per
 // step, RING steps on their way; wave w multiplies the 16 values 16 w .. of a step, the eight sums are added in wave order.
 // LDS rows are 256 bytes, chunk c of row i at c ^ (i & 15); x_hat in operand order needs no rows (1 KB per 16 values of k).
@@ -372,7 +372,12 @@ static void launch_t_rows(const PrepArgs &a, hipStream_t s) {
 bool t_rows_mfma_supported(const PrepArgs &a) { return a.d % 128 == 0 && lds_aligned(a.A) && lds_aligned(a.xh); }
 
 void launch_t_rows_mfma(const PrepArgs &a, hipStream_t s) {
-  if ((a.n_adapted + 31) / 32 * ((a.parts * a.rank + 31) / 32) <= T_NARROW) launch_t_rows<1>(a, s);
+  // Those with something to do, and a fiftieth of the others (each of them holds a compute unit's LDS for a moment): the least loss over 700 products of
+  // 8 to 4458 rows, 1 to 16 adapters of rank 16 to 64, all or a tenth of the rows adapted, K 2048 to 8192: 0.3 % on average against the quicker
+  // one of the two each time, 14 % at most.  Counting adapted rows instead 0.5 % and 73 %: 1000 rows of eight rank-64 adapters are 234 workgroups
+  // with something to do and 1302 others, row preparation 33 us in 96 columns, 54 in 32.
+  const int cols = (a.parts * a.rank + 31) / 32, busy = a.adapted_tiles * cols, all = (a.T + 31) / 32 * cols * a.n_used;
+  if (busy + (all - busy) / 50 <= T_NARROW) launch_t_rows<1>(a, s);
   else launch_t_rows<3>(a, s);
 }
 

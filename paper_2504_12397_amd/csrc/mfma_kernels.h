@@ -65,7 +65,7 @@ struct PrepArgs {
   int n_used;               // the adapters that rows of this call may use ...
   uint8_t used[64];         // ... their ids and their scales s_a
   float used_scale[64];
-  int n_adapted;            // rows of the call that an adapter applies to
+  int adapted_tiles;        // pairs of 32 rows of the call and an adapter that applies to one of them
   int few;                  // one kernel for normalisation and t: 0 never, 1 few rows, 2 always
   int write_meta;
   bf16 *xh;                 // [T, d]

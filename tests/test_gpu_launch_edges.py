@@ -593,6 +593,16 @@ def test_runs_of_decode_steps_one_way_or_the_other(ab, ctx, n, kv, G, P, steps, 
     assert H.rel_err(H.f64(out).transpose(1, 0, 2).reshape(n * steps, -1), ref) <= H.TOL["bf16"]
 
 
+# row tiles of 32 that hold one adapter, two and many; few columns of the down-projection per workgroup, and many of them where most have nothing to do
+@pytest.mark.parametrize("n,rows,rank,n_adapters", [(8, 125, 64, 8), (1, 1000, 64, 1), (40, 20, 16, 5), (3, 400, 24, 3), (16, 125, 32, 16)])
+def test_down_projection_of_row_tiles_with_several_adapters(ab, ctx, n, rows, rank, n_adapters):
+    shape = wl.LayerShape(d=512, n_q_heads=2, n_kv_heads=1, head_dim=128, rank=rank, n_adapters=n_adapters)
+    P, S = [b % 3 for b in range(n)], [rows - b % 2 for b in range(n)]
+    case = H.make_case(shape, P, S, [P[b] + (S[b] // 2 if b % 3 == 2 else 0) for b in range(n)], [b % n_adapters for b in range(n)], seed=3150 + n,
+                       prefix="random")
+    check_case(ab, ctx, case)
+
+
 # records from the kernel arguments (up to 16 sequences), one per thread, and more than a workgroup has threads; 3 * rank columns in tiles of 8 and of 16
 @pytest.mark.parametrize("n,rank,n_adapters", [(16, 8, 2), (17, 24, 3), (512, 8, 1), (513, 8, 2), (700, 16, 2)])
 def test_row_preparation_of_many_short_sequences(ab, ctx, n, rank, n_adapters):
