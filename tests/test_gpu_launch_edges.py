@@ -603,6 +603,20 @@ def test_down_projection_of_row_tiles_with_several_adapters(ab, ctx, n, rows, ra
     check_case(ab, ctx, case)
 
 
+# one range of keys where the row tiles fill the chip by themselves and a merge would cost more than it evens out, several where they do not
+@pytest.mark.parametrize("T,P,merged", [(2500, 64, False), (1000, 64, False), (128, 4000, True), (1024, 4096, True)])
+def test_ranges_of_prefill_attention(ab, ctx, T, P, merged):
+    ctx.set_option("profile", 1)
+    shape = wl.LayerShape(d=256, n_q_heads=32, n_kv_heads=8, head_dim=128, rank=8, n_adapters=1)
+    case = H.make_case(shape, [P], [T], [P], [0], seed=3170, prefix="random")
+    cache = H.gpu_cache(case)
+    out = ab.alora_prefill(ctx, H.gpu_layer(case, shape), cache, case.x_packed.cuda().contiguous(), case.cu, case.k, case.adapter)
+    torch.cuda.synchronize()
+    assert ("attn_merge" in ctx.profile_read()) == merged
+    ref, _ = H.oracle_prefill(case)
+    assert H.rel_err(H.f64(out), ref) <= H.TOL["bf16"]
+
+
 # records from the kernel arguments (up to 16 sequences), one per thread, and more than a workgroup has threads; 3 * rank columns in tiles of 8 and of 16
 @pytest.mark.parametrize("n,rank,n_adapters", [(16, 8, 2), (17, 24, 3), (512, 8, 1), (513, 8, 2), (700, 16, 2)])
 def test_row_preparation_of_many_short_sequences(ab, ctx, n, rank, n_adapters):
