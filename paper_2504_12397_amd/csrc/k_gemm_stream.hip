@@ -115,6 +115,9 @@ __global__ __launch_bounds__(X::THREADS) void gemm_stream_kernel(GemmArgs g, int
   const int first = PAIRS ? cc * CB * 16 + (l32 & 15) : cc * CB * 32 + l32;
   const int srow = (CB == 1 ? min(first, COLS - 1) : first) + (PAIRS ? (l32 >> 4) * COLS : 0);
   constexpr int BLOCK = (PAIRS ? 16 : 32) * RUN;
+  // where the slot's operand of step k is: chunks 2 k and 2 k + 1 of the row, so k is bits 5 to 7 of the address.  An offset per step is kept where there
+  // are registers; eight row blocks leave none (6 and 4 of them went to scratch, gate/up of 139 rows 62.7 us) and compute it, anew in every stage
+  // (61.3; two registers of the tile of 56 pairs still wait in scratch, from one tile to the next).
   int off[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) off[i] = srow * RUN + kw * 256 + ((i * 2 + lhi) ^ (srow & 15)) * 16;
@@ -188,16 +191,18 @@ __global__ __launch_bounds__(X::THREADS) void gemm_stream_kernel(GemmArgs g, int
         fetch(i0 + j + XB - 1, xr[(j + XB - 1) % XB]);
         wave_barrier();
         if (!idle) {
-        const char *w = lds + slot * X::STAGE;
+        int at = slot * X::STAGE + off[0];
+        if constexpr (RW == 8) asm("" : "+v"(at));      // (not kept from one stage to the next)
+        auto of_step = [&](int k) { return lds + (RW == 8 ? at ^ (k * 32) : slot * X::STAGE + off[k]); };
         // (the reads run a step ahead: a wave that multiplies is alone on its SIMD, or has one neighbour)
         bf16x8 f[2][CB];
 #pragma unroll
-        for (int b = 0; b < CB; ++b) f[0][b] = *reinterpret_cast<const bf16x8 *>(w + off[0] + b * BLOCK);
+        for (int b = 0; b < CB; ++b) f[0][b] = *reinterpret_cast<const bf16x8 *>(of_step(0) + b * BLOCK);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
           if (k < 7)
 #pragma unroll
-            for (int b = 0; b < CB; ++b) f[(k + 1) & 1][b] = *reinterpret_cast<const bf16x8 *>(w + off[k + 1] + b * BLOCK);
+            for (int b = 0; b < CB; ++b) f[(k + 1) & 1][b] = *reinterpret_cast<const bf16x8 *>(of_step(k + 1) + b * BLOCK);
           if (RW < 8) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int b = 0; b < CB; ++b)
