@@ -1200,7 +1200,7 @@ PrefillPlan plan_prefill_ranges(const alora_ctx *ctx, const Plan &pl, const Laye
   const int longest = std::max(max_own, max_pfx);
   int most = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(limit, longest / 256), (1 << 20) / ((int64_t)pl.T * L.n_q_heads)));
   if (pp.runs.empty() && tiles * L.n_kv_heads >= 4 * (int64_t)ctx->n_cu) most = 1;      // more items than could be evened out by cutting them
-  if (most == 1 && !pl.cached_only) return pp;      // (nothing to compare)
+  if (most == 1 && !pl.cached_only && pp.runs.empty()) return pp;      // (nothing to compare)
   double least = 0;
   int was_own = 0, was_sh = 0;
   for (int n = 1; n <= most; n += n < 16 ? 1 : n / 4) {

@@ -373,3 +373,17 @@ def test_runs_of_decode_steps_on_contexts_in_any_order(ab, name, steps, opts):
             assert err <= H.TOL[shape.dtype], f"sequence {b}: off by {err:.3e}"
     finally:
         ctx.close()
+
+
+# contexts and own rows shorter than the shortest range: one range of each kind, nothing to choose
+@pytest.mark.parametrize("C,own,S", [([17], [200, 5], [31, 64]), ([1], [0, 0, 3], [1, 2, 1]), ([255], [0, 255], [1, 1]), ([130, 64], [0, 0, 100, 7], [15, 3, 2, 64])])
+def test_short_contexts_in_one_range(ab, C, own, S):
+    shape, n = SHAPES["G4"], len(own)
+    ctx = ab.Context(0)
+    try:
+        group = [b % len(C) for b in range(n)]
+        k = [C[g] + own[b] + b % 2 for b, g in enumerate(group)]
+        case, ctx_kv = H.contexts_case(shape, C, group, own, S, k, [b % 3 - 1 for b in range(n)], seed=980 + sum(own))
+        H.run_contexts(ab, ctx, case, ctx_kv, C, group, own)
+    finally:
+        ctx.close()
