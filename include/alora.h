@@ -152,10 +152,11 @@ const char *alora_status_string(alora_status s);
  *   "gemm_splits"     0 (default): the QKV projection is a single running sum (weights that are not 16-byte
  *                     aligned, or a hidden size that is no multiple of 128: segments fixed by the
  *                     weight shape, as with a value); the reduction axis of a stack's
- *                     other linears is cut by the shape of the weight matrix (up to 256 rows) or by what fills
- *                     the chip (more rows).  n in 1..64: QKV, W_o and W_down in n equal segments (where the
- *                     reduction length allows; 1 = a single running sum); gate and up are a single
- *                     running sum always.  See "Summation order" below.
+ *                     other linears is cut by the shape of the weight matrix (up to 256 rows; W_down of up to
+ *                     32 rows is streamed, in an order of its own) or by what fills the chip (more rows).
+ *                     n in 1..64: QKV, W_o and W_down in n equal segments (where the reduction length
+ *                     allows; 1 = a single running sum); gate and up are a single running sum always (streamed
+ *                     ones begin it where their tile begins).  See "Summation order" below.
  *   "gemm_tile"       0 (default): automatic block shape.  1: 128x128, 2: 256x128, 3: 256x256, 4: 128x64
  *                     (four waves); 5 / 6: 128x128 on eight waves of 32x64 / 64x32.  1 and 4..6 also apply to
  *                     the other linears of a stack.  A tuning experiment: with a value other than 0 the

@@ -725,8 +725,8 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     g.row_adapter = w.rm.adapter;
     g.present16 = prep_rows_mfma_supported(L.d, r) ? w.rm.present16 : nullptr;      // (the row preparation that wrote it)
   };
-  // reduction segments of a linear [N, K] where the large tiles do not take the call: fixed by the weight shape (or by the
-  // gemm_splits option), so that a row's result does not depend on the number of rows among such calls
+  // reduction segments of a linear [N, K] where neither the large tiles nor the streaming kernel takes the call: fixed by the weight shape (or by
+  // the gemm_splits option), so that a row's result does not depend on the number of rows among such calls
   auto segments_of = [&](int N, int K) {
     if (ctx->opt_gemm_splits > 0) return K % (64 * ctx->opt_gemm_splits) == 0 ? ctx->opt_gemm_splits : 1;
     return gemm_mfma_fixed_segments(N, K, ctx->n_cu);

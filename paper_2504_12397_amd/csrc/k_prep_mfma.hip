@@ -67,8 +67,8 @@ __device__ __forceinline__ void fill_row_meta(const PrepArgs &a, const SeqMeta &
 // The kernel is memory round trips and little else, so everything is requested at once: x, the gain, the sequences' records (in the kernel arguments when they are few)
 // and this adapter's down matrix, before anybody knows whether a row of the tile uses it.
 // No load stands behind a branch of its own or is a generic one (the compiler waits for all that was asked for there), and the arguments arrive
-// together: as it was compiled before, records, x with the gain, one chunk of A and the rest of A were a round trip each.  Token steps of
-// 16 layers 2488 -> 2474 us (one row), of 8 layers 1492 -> 1480 (eight rows of eight adapters), five rows of rank-8 adapters 48.8 -> 47.8.
+// together: as it was compiled before, records, x with the gain, one chunk of A and the rest of A were a round trip each.  One row of one rank-64 adapter
+// 10.2 -> 9.0 us, eight rows of eight 11.4 -> 10.5, five rows of rank-8 adapters 10.1 -> 9.2.
 // NC = 8: half the columns of the matrix operand, for calls whose 16-column workgroups would leave half of the chip idle: a compute
 // unit takes operands in this order at 28 bytes per ns, so it is
 // done sooner with half the 128 KB of 16 columns.  A one-row token step of 16 layers at rank 64 2615 -> 2589 us (1.6 a layer), five rows of

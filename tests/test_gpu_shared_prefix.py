@@ -350,7 +350,7 @@ def test_a_stack_of_adapters_on_one_context_the_base_model_prefilled(ab, dtype):
 
 
 # sequences of one context apart in the batch, some without any, contexts that differ in length only; items of one and of several sequences
-@pytest.mark.parametrize("name,steps,opts", [("G4", 5, {}), ("G4", 40, {}), ("G1", 3, {}), ("G8", 70, {}), ("G4", 5, {"kv_splits": 2}), ("f32", 3, {})])
+@pytest.mark.parametrize("name,steps,opts", [("G4", 5, {}), ("G4", 40, {}), ("G4", 100, {}), ("G1", 3, {}), ("G8", 70, {}), ("G4", 5, {"kv_splits": 2}), ("f32", 3, {})])
 def test_runs_of_decode_steps_on_contexts_in_any_order(ab, name, steps, opts):
     shape = SHAPES[name]
     ctx = ab.Context(0)
