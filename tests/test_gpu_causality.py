@@ -1,5 +1,6 @@
-"""A later row reaches no earlier one, whatever it holds.  Attention at position p reads keys and values 0 .. p (Eq.1): rows behind it
-may be padding of a shorter answer, Inf or NaN, and the rows before them come out as if they were not there."""
+"""Rows behind a row may be padding of a shorter answer, Inf or NaN (Eq.1: attention at position p reads keys and values 0 .. p).  In a run
+of decode steps nothing that a later step holds reaches an earlier one; in a prefill no later key does (a later value that is not
+finite is multiplied by probability 0 where both rows share a tile of keys, and is not tested)."""
 import pytest
 import torch
 
