@@ -508,8 +508,32 @@ void project_rows(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L
   // beyond that, where a head is 128 columns, in the one whose tiles are large in both directions (both add in one order), or in the
   // 128 x 128 block of four waves, which also adds segments.
   const bool fuse = mfma && ctx->opt_rope_fuse && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
-  const int stream_rows = qkv_stream_rows(L.n_qkv, ctx->n_cu);
   const bool lora_split = pl.any_adapter && w.lora_split;      // (in a kernel that takes partial sums)
+  GemmArgs g{};
+  if (mfma) {
+    g.A = (const bf16 *)w.xh; g.lda = L.d;
+    g.B = (const bf16 *)ly->W_qkv; g.ldb = L.d;
+    g.M = pl.T; g.N = L.n_qkv; g.K = L.d;
+    g.k_splits = w.k_splits;
+    g.k_segments = w.k_segments;
+    g.lora_split = lora_split ? 1 : 0;
+    g.tile_hint = ctx->opt_gemm_tile;
+    g.Cpart = w.Y;
+    g.tlow = pl.any_adapter ? (const bf16 *)w.tlow : nullptr;
+    g.rank = L.rank;
+    g.lr_parts = 3;
+    g.Bq = (const bf16 *)ly->B_q; g.Bk = (const bf16 *)ly->B_k; g.Bv = (const bf16 *)ly->B_v;
+    g.n_q = L.n_q; g.n_kv = L.n_kv;
+    g.row_adapter = w.rm.adapter;
+    g.present16 = prep_mfma ? w.rm.present16 : nullptr;
+    g.rope_pos = w.rm.pos; g.rope_slot = w.rm.slot; g.rope_table = w.rope; g.q_scale = q_scale;
+    g.rope_by_row = w.rope_by_row ? 1 : 0;
+    g.head_dim = L.head_dim; g.q_f32 = q_half ? 0 : 1;
+    g.Qout = (bf16 *)w.Q; g.cacheK = (bf16 *)cache->k; g.cacheV = (bf16 *)cache->v;
+  }
+  // (their tiles are the quicker way from 129 rows on: 139 rows 30.8 -> 23.5 us, 256 34.2 -> 30.1; 128 rows stream in 22.7 and take 28.9 in tiles)
+  const bool tiles = fuse && q_half && !w.rope_by_row && w.k_segments == 1 && gemm_mfma_rope_supported(g, L.head_dim) && gemm_large_supported(g, GEMM_EPI_ROPE);
+  const int stream_rows = tiles ? std::min(128, qkv_stream_rows(L.n_qkv, ctx->n_cu)) : qkv_stream_rows(L.n_qkv, ctx->n_cu);
   const bool stream = fuse && !lora_split && w.k_segments == 1 && ctx->opt_gemm_tile == 0 && pl.T <= stream_rows && qkv_stream_supported(ly->W_qkv, L.n_qkv, L.d, L.head_dim);
   auto stage_of = [&](bool first) {
     StagedCall st{};
@@ -549,32 +573,11 @@ void project_rows(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L
   {
     ProfScope p(ctx, K_QKV, s);
     if (mfma) {
-      GemmArgs g{};
-      g.A = (const bf16 *)w.xh; g.lda = L.d;
-      g.B = (const bf16 *)ly->W_qkv; g.ldb = L.d;
-      g.M = pl.T; g.N = L.n_qkv; g.K = L.d;
-      g.k_splits = w.k_splits;
-      g.k_segments = w.k_segments;
-      g.lora_split = lora_split ? 1 : 0;
-      g.tile_hint = ctx->opt_gemm_tile;
-      g.Cpart = w.Y;
-      g.tlow = pl.any_adapter ? (const bf16 *)w.tlow : nullptr;
-      g.rank = L.rank;
-      g.lr_parts = 3;
-      g.Bq = (const bf16 *)ly->B_q; g.Bk = (const bf16 *)ly->B_k; g.Bv = (const bf16 *)ly->B_v;
-      g.n_q = L.n_q; g.n_kv = L.n_kv;
-      g.row_adapter = w.rm.adapter;
-      g.present16 = prep_mfma ? w.rm.present16 : nullptr;
-      g.rope_pos = w.rm.pos; g.rope_slot = w.rm.slot; g.rope_table = w.rope; g.q_scale = q_scale;
-      g.rope_by_row = w.rope_by_row ? 1 : 0;
-      g.head_dim = L.head_dim; g.q_f32 = q_half ? 0 : 1;
-      g.Qout = (bf16 *)w.Q; g.cacheK = (bf16 *)cache->k; g.cacheV = (bf16 *)cache->v;
       if (stream) {
         launch_qkv_stream(g, ctx->n_cu, s);
         rope_fused = true;
-      } else if (fuse && q_half && !w.rope_by_row && w.k_segments == 1 && pl.T > stream_rows && gemm_mfma_rope_supported(g, L.head_dim) &&
-                 gemm_large_supported(g, GEMM_EPI_ROPE)) {
-        launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, GEMM_EPI_ROPE, ctx->n_cu, 1).tile, s);
+      } else if (tiles && pl.T > stream_rows) {
+        launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, GEMM_EPI_ROPE, ctx->n_cu, 1), s);
         rope_fused = true;
       } else if (fuse && q_half && !w.rope_by_row && ctx->opt_gemm_tile == 0 && pl.T > 256 && gemm_mfma_rope_supported(g, L.head_dim)) {
         launch_gemm_mfma(g, GEMM_EPI_ROPE, ctx->n_cu, s);
@@ -731,18 +734,19 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     if (ctx->opt_gemm_splits > 0) return K % (64 * ctx->opt_gemm_splits) == 0 ? ctx->opt_gemm_splits : 1;
     return gemm_mfma_fixed_segments(N, K, ctx->n_cu);
   };
-  // Many rows with default splits: the large-tile kernel, whose partial sums (when it takes several workgroups per output tile)
+  // More than 32 rows with default splits: the large-tile kernels, whose partial sums (when it takes several workgroups per output tile)
   // land in Y.  Returns their number, 0: not this way, 1: C is written.
   auto large = [&](GemmArgs &g) -> int {
-    if (T_rows <= 256 || ctx->opt_gemm_splits != 0 || g.tile_hint == 1 || g.tile_hint >= 4) return 0;
-    int most = 4;
+    if (T_rows <= 32 || (T_rows <= 256 && g.tile_hint != 0) || ctx->opt_gemm_splits != 0 || g.tile_hint == 1 || g.tile_hint >= 4) return 0;
+    int most = 8;
     while (most > 1 && ((size_t)most * T_rows * g.N > w.y_floats || T_rows > gemm_large_slice_rows(g.lda))) most /= 2;
-    const GemmLargePlan pn = gemm_large_plan(g.tile_hint, g, GEMM_EPI_BF16, ctx->n_cu, most);
+    const GemmLargePlan pn = T_rows <= 256 ? gemm_few_plan(g, ctx->n_cu) : gemm_large_plan(g.tile_hint, g, GEMM_EPI_BF16, ctx->n_cu, std::min(most, 4));
+    if (pn.splits == 0 || pn.splits > most) return 0;
     g.k_splits = pn.splits;
     const int epi = pn.splits > 1 ? GEMM_EPI_PARTIAL : GEMM_EPI_BF16;
     if (!gemm_large_supported(g, epi)) return 0;
     g.Cpart = w.Y;
-    launch_gemm_large(g, epi, pn.tile, s);
+    launch_gemm_large(g, epi, pn, s);
     return pn.splits;
   };
   // C = A W^T (+ R), with the gated low-rank term of (Al, Bl) when given

@@ -24,26 +24,18 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// TMH: 32-row blocks per wave and half (2: 256-row tile, 1: 128-row tile); the tile is 256 columns wide.
-// TMH = 0: the tile for calls that fill less than half of the chip with those: 128 x 128, four waves by two, a wave 32 rows by two
-// 32-column blocks.  Twelve fragments for eight matrix instructions: LDS-bound (96 KB of a k-tile at 322 bytes per ns: 0.3 us)
-// unless the reads run beside the matrix instructions, so a wave reads the next k-tile's fragments while it multiplies this one's,
-// with one barrier per k-tile and four buffers.  512 x 6144 x 4096 with adapters: 50 us in 192 workgroups, 80 in 96 of the
-// 128 x 256 tile; 1024 x 4096 x 4096: 45 us.
-template <int TMH, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-  constexpr int BM = TMH ? 128 * TMH : 128, BN = TMH ? 256 : 128, BK = 64;
-  constexpr int A_HALF = TMH ? 8192 * TMH : 8192, B_HALF = 64 * BN;      // bytes of a half-tile
-  constexpr int BUF = 2 * A_HALF + 2 * B_HALF;
-  constexpr int NBUF = TMH == 2 ? 2 : TMH == 1 ? 3 : 4;
-  constexpr int NMI = TMH ? 2 * TMH : 1;                              // 32-row blocks of a wave
-  constexpr int AH = TMH ? 2 : 1, AJ = TMH ? TMH : 2, BJ = BN / 128;     // halves of A, requests of a wave for one, for a half of B
+  constexpr int BM = 256, BN = 256, BK = 64;
+  constexpr int A_HALF = 16384, B_HALF = 16384;      // bytes of a half-tile
+  constexpr int BUF = 2 * A_HALF + 2 * B_HALF, NBUF = 2;
+  constexpr int NMI = 4;      // 32-row blocks of a wave
   extern __shared__ u32x4 smem[];
   char *lds = reinterpret_cast<char *>(smem);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, lhi = lane >> 5;
-  const int wm = TMH ? wave >> 2 : wave >> 1, wn = TMH ? wave & 3 : wave & 1;
+  const int wm = wave >> 2, wn = wave & 3;
   const int M = g.M, N = g.N, K = g.K;
 
   const int nk = K / BK / g.k_splits;
@@ -65,8 +57,8 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
     n0 = (in / gm) * BN;
   };
 
-  // ---- requests: wave w moves rows 8 TMH w .. of a half of A and rows 16 w .. of a half of B -------------------------
-  // LDS row i of a half of A is row (i / (32 TMH)) * 64 TMH + h * 32 TMH + i % (32 TMH) of the tile; LDS row i of a half of
+  // ---- requests: wave w moves rows 16 w .. of a half of A and of a half of B -------------------------
+  // LDS row i of a half of A is row (i / 64) * 128 + h * 64 + i % 64 of the tile; LDS row i of a half of
   // B is a weight row: plain n0 + 64 (i / 32) + 32 h + i % 32; rotary: the partner column c + 64 of column c in the other half;
   // SwiGLU: half 0 the gate row, half 1 the up row of the same output column.
   const i32x4 rA = make_rsrc(g.A, (uint64_t)M * g.lda * 2);
@@ -74,21 +66,21 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   const i32x4 rB1 = EPI == GEMM_EPI_SWIGLU ? make_rsrc(g.B2, (uint64_t)(N >> 1) * g.ldb * 2) : rB0;
   // byte offsets of a lane's rows (the k-tile is the scalar offset, so that a row past the end is out of range by its lane
   // offset alone); they move to the next output tile when the last requests of the current one are out
-  int va[AH][AJ], vb[2][BJ], ka[AH], kb;      // ka, kb: byte offset of the first k-tile
+  int va[2][2], vb[2][2], ka[2], kb;      // ka, kb: byte offset of the first k-tile
   auto aim_a = [&](int m0, int k0, int h) {
     ka[h] = k0;
 #pragma unroll
-    for (int j = 0; j < AJ; ++j) {
-      const int i = 8 * (AJ * wave + j) + (lane >> 3), c = (lane & 7) ^ ((i >> 1) & 7);
-      const int r = TMH ? (i / (32 * AJ)) * 64 * TMH + h * 32 * TMH + i % (32 * AJ) : i;
+    for (int j = 0; j < 2; ++j) {
+      const int i = 8 * (2 * wave + j) + (lane >> 3), c = (lane & 7) ^ ((i >> 1) & 7);
+      const int r = (i >> 6) * 128 + h * 64 + (i & 63);
       va[h][j] = ((m0 + r) * g.lda + c * 8) * 2;
     }
   };
   auto aim_b = [&](int n0, int k0) {
     kb = k0;
 #pragma unroll
-    for (int j = 0; j < BJ; ++j) {
-      const int i = 8 * (BJ * wave + j) + (lane >> 3), c = (lane & 7) ^ ((i >> 1) & 7);
+    for (int j = 0; j < 2; ++j) {
+      const int i = 8 * (2 * wave + j) + (lane >> 3), c = (lane & 7) ^ ((i >> 1) & 7);
       const int row = EPI == GEMM_EPI_SWIGLU ? (n0 >> 1) + i
                       : EPI == GEMM_EPI_ROPE ? n0 + (i >> 6) * 128 + (i & 63)
                                              : n0 + (i >> 5) * 64 + (i & 31);
@@ -98,33 +90,32 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   };
   // half h of k-tile t (of the output tile aimed at) into the buffer at LDS byte `buf`
   auto req_a = [&](int t, int buf, int h) {
-    const int dst = buf + h * A_HALF + wave * (1024 * AJ);
+    const int dst = buf + h * A_HALF + wave * 2048;
 #pragma unroll
-    for (int j = 0; j < AJ; ++j) load_to_lds(rA, va[h][j], ka[h] + t * (BK * 2), dst + j * 1024);
+    for (int j = 0; j < 2; ++j) load_to_lds(rA, va[h][j], ka[h] + t * (BK * 2), dst + j * 1024);
   };
   auto req_b = [&](int t, int buf, int h) {
-    const int dst = buf + 2 * A_HALF + h * B_HALF + wave * (1024 * BJ);
+    const int dst = buf + 2 * A_HALF + h * B_HALF + wave * 2048;
 #pragma unroll
-    for (int j = 0; j < BJ; ++j) load_to_lds(h ? rB1 : rB0, vb[h][j], kb + t * (BK * 2), dst + j * 1024);
+    for (int j = 0; j < 2; ++j) load_to_lds(h ? rB1 : rB0, vb[h][j], kb + t * (BK * 2), dst + j * 1024);
   };
   int m0, n0, k0;
   tile_at(in_run, m0, n0, k0);
   aim_a(m0, k0, 0);
-  if constexpr (TMH != 0) aim_a(m0, k0, 1);
+  aim_a(m0, k0, 1);
   aim_b(n0, k0);
-  int bo = 0;      // LDS byte of the running k-tile's buffer (three or four buffers only)
-  for (int t = 0; t < (TMH ? NBUF : 3); ++t) {      // in the order of the main loop
+  for (int t = 0; t < NBUF; ++t) {      // in the order of the main loop
     req_a(t, t * BUF, 0);
-    if (NBUF != 3 || t < 2) { req_b(t, t * BUF, 0); req_b(t, t * BUF, 1); }
-    if constexpr (TMH != 0)
-      if (t < NBUF - 1) req_a(t, t * BUF, 1);
+    req_b(t, t * BUF, 0);
+    req_b(t, t * BUF, 1);
+    if (t < NBUF - 1) req_a(t, t * BUF, 1);
   }
 
   int ra[4], rb[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const int pos = ((2 * ks + lhi) ^ ((l32 >> 1) & 7)) * 16;
-    ra[ks] = (wm * (TMH ? 32 * TMH : 32) + l32) * 128 + pos;
+    ra[ks] = (wm * 64 + l32) * 128 + pos;
     rb[ks] = 2 * A_HALF + (wn * 32 + l32) * 128 + pos;
   }
 
@@ -262,7 +253,7 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   }
 
   // ---- main loop -----------------------------------------------------------------------------------------------
-  constexpr int AR = TMH ? TMH : 1;
+  constexpr int AR = 2;
   bf16x8 fa0[AR][4], fa1[AR][4], fb0[4], fb1[4];
   auto read_a = [&](int buf, int h, bf16x8 (&f)[AR][4]) {
 #pragma unroll
@@ -299,50 +290,16 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   const bool more = in_run + per_xcd < run_n;
   int m_next = m0, n_next = n0, k_next = k0;
   if (more) tile_at(in_run + per_xcd, m_next, n_next, k_next);
-  if constexpr (TMH == 0) {
-    // fragments of the next k-tile (of the next output tile behind the last one) are read beside this one's products
-    bf16x8 fc0[4], fc1[4];
-    auto read = [&](int buf, bf16x8 (&fa)[AR][4], bf16x8 (&f0)[4], bf16x8 (&f1)[4]) {
-      read_a(buf, 0, fa);
-      read_b(buf, 0, f0);
-      read_b(buf, 1, f1);
-    };
-    auto turn = [&](int t) {      // k-tile t + 1 is there and k-tile t - 1 used up; requests k-tile t + 3
-      wait_vm<4>();
-      __builtin_amdgcn_sched_barrier(0);
-      wave_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      if (t == nk - 3) { aim_a(m_next, k_next, 0); aim_b(n_next, k_next); }
-      const int to = t + 3 < nk ? t + 3 : t + 3 - nk, prev = bo ? bo - BUF : (NBUF - 1) * BUF;
-      req_a(to, prev, 0);
-      req_b(to, prev, 0);
-      req_b(to, prev, 1);
-      bo = bo + BUF < NBUF * BUF ? bo + BUF : 0;
-    };
-    wait_vm<8>();
-    wave_barrier();
-    read(bo, fa0, fb0, fb1);
-    for (int t = 0; t < nk; t += 2) {
-      turn(t);
-      read(bo, fa1, fc0, fc1);
-      mma(fa0, fb0, 0, 0);
-      mma(fa0, fb1, 0, 1);
-      turn(t + 1);
-      read(bo, fa0, fb0, fb1);
-      mma(fa1, fc0, 0, 0);
-      mma(fa1, fc1, 0, 1);
-    }
-  } else {
-  wait_vm<NBUF == 2 ? 10 : 8>();        // A0 and B0 (B0, B1) of k-tile 0 are there
+  wait_vm<10>();        // A0 and B0 of k-tile 0 are there
   wave_barrier();
-  read_a(bo, 0, fa0);
+  read_a(0, 0, fa0);
   wait_lds();
   if (wm == 1) wave_barrier();      // the second group runs one barrier behind
   wave_barrier();
   // The last k-tiles request the first ones of the workgroup's next output tile, which then arrive under the epilogue; behind the
   // last output tile they request its own first ones again, into buffers that nobody reads any more, so that the count
   // of requests in flight is the same everywhere.
-  if constexpr (NBUF == 2) {
+  {
     auto tile = [&](int b, int t1, int t0) {      // buffer b; requests: A1 of k-tile t1, the rest of k-tile t0
       const int buf = b * BUF;
       read_b(buf, 0, fb0);
@@ -375,38 +332,8 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
     tile(0, nk - 1, 0);
     aim_a(m_next, k_next, 1);
     tile(1, 0, 1);
-  } else {
-    // half as many matrix instructions per half-tile: two phases of eight, three buffers (two k-tiles ahead)
-    auto tile = [&](int tb, int t0) {      // requests: B and A1 of k-tile tb, A0 of k-tile t0
-      const int next = bo + BUF < NBUF * BUF ? bo + BUF : 0, prev = bo ? bo - BUF : (NBUF - 1) * BUF;
-      read_b(bo, 0, fb0);
-      read_b(bo, 1, fb1);
-      req_b(tb, prev, 0);
-      req_b(tb, prev, 1);
-      ALORA_TURN(10);
-      mma(fa0, fb0, 0, 0);
-      mma(fa0, fb1, 0, 1);
-      ALORA_TURN2();
-      read_a(bo, 1, fa1);
-      read_a(next, 0, fa0);
-      req_a(tb, prev, 1);
-      req_a(t0, bo, 0);
-      ALORA_TURN(8);
-      mma(fa1, fb0, 1, 0);
-      mma(fa1, fb1, 1, 1);
-      ALORA_TURN2();
-      bo = next;
-    };
-    for (int t = 3; t < nk; ++t) tile(t - 1, t);
-    aim_a(m_next, k_next, 0);
-    tile(nk - 1, 0);
-    aim_a(m_next, k_next, 1);
-    aim_b(n_next, k_next);
-    tile(0, 1);
-    tile(1, 2);
   }
   if (wm == 0) wave_barrier();
-  }
 
 
   // ---- epilogues -------------------------------------------------------------------------------------------------
@@ -541,13 +468,13 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
   wait_vm<0>();
 }
 
-template <int TMH, int EPI>
+template <int EPI>
 static void launch_cfg(const GemmArgs &g, hipStream_t s) {
-  constexpr int BM = TMH == 2 ? 256 : 128, BN = TMH ? 256 : 128;
+  constexpr int BM = 256, BN = 256;
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const size_t smem = (TMH == 2 ? 2 : TMH == 1 ? 3 : 4) * (BM + BN) * 128 + 8 * 2048;
+  const size_t smem = 2 * (BM + BN) * 128 + 8 * 2048;
   const int all = (tiles_m * tiles_n * g.k_splits + 7) & ~7, grid = all < 256 ? all : 256;      // a workgroup per compute unit walks its tiles
-  auto kern = gemm_large_kernel<TMH, EPI>;
+  auto kern = gemm_large_kernel<EPI>;
   (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, g, tiles_m, tiles_n);
 }
@@ -565,36 +492,52 @@ bool gemm_large_supported(const GemmArgs &g, int epi) {
   return g.K % (128 * g.k_splits) == 0 && g.K >= 256 * g.k_splits && g.N % 32 == 0 && b_rows * g.ldb * 2 < (1ull << 31);
 }
 
-// Tile and workgroups per output tile for a product of M rows: the cheapest by measured times (us).  A k-tile of a
-// 256-row tile takes 1.1 with most of the chip idle and 1.5 with all of it at work (the clock gives way: 1.6 GHz at 0.83
-// matrix utilisation), one of a 128-row tile 0.65 and 1.0, one of the 128 x 128 tile 0.6 (it waits for LDS, not for the clock); a tile's prologue and epilogue
-// take about 6; partial sums cost their bytes there and back and the launch that adds them.
+// Tile and workgroups per output tile for a product of M rows: the cheapest by measured times (us).  `idle`, `busy`: a k-tile with most of the
+// chip idle and with all of it at work (the clock gives way: 1.6 GHz at 0.83 matrix utilisation); a tile's prologue and epilogue take about 6;
+// partial sums cost their bytes there and back and the launch that adds them.  Over 64 products of 139 to 4458 rows (N, K 6144, 4096; 4096, 4096;
+// 4096, 14336; gate/up 2 x 14336, 4096) what it picks is 0.6 % slower than the best of the tiles and splits on average, 10 % at most.
 GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits) {
-  GemmLargePlan best{2, 1};
+  static const struct { int rows, cols; double idle, busy; } tiles[] = {
+      {128, 64, 0.24, 0.34}, {128, 96, 0.38, 0.48}, {128, 128, 0.44, 0.53}, {128, 192, 0.62, 0.70}, {128, 256, 0.74, 0.86}, {256, 256, 1.1, 1.48}};
+  GemmLargePlan best{256, 256, 1};
   double best_us = 1e30;
-  for (int tile = 0; tile <= 2; ++tile)
+  for (const auto &t : tiles)
     for (int sp = 1; sp <= max_splits; sp *= 2) {
-      if ((hint == 2 && tile != 1) || (hint == 3 && tile != 2) || g.K % (128 * sp) != 0 || g.K < 512 * sp) continue;
-      const int rows = tile == 2 ? 256 : 128, cols = tile ? 256 : 128;
-      const int tiles = (g.M + rows - 1) / rows * ((g.N + cols - 1) / cols) * sp, rounds = (tiles + n_cu - 1) / n_cu;
-      const double load = tiles < n_cu ? (double)tiles / n_cu : 1.0;
-      const double k_tile = tile == 2 ? 1.1 + 0.4 * load : tile == 1 ? 0.65 + 0.35 * load : 0.55 + 0.05 * load;
-      double us = rounds * (k_tile * (g.K / 64 / sp) + 6.0);
+      if ((hint == 2 && (t.rows != 128 || t.cols != 256)) || (hint == 3 && t.rows != 256) || g.K % (128 * sp) != 0 || g.K < 512 * sp) continue;
+      const int n = (g.M + t.rows - 1) / t.rows * ((g.N + t.cols - 1) / t.cols) * sp, rounds = (n + n_cu - 1) / n_cu;
+      const double load = n < n_cu ? (double)n / n_cu : 1.0;
+      double us = rounds * ((t.idle + (t.busy - t.idle) * load) * (g.K / 64 / sp) + 6.0);
       if (sp > 1) us += 5.0 + (double)sp * g.M * g.N * 8.0 / 4.5e6;
-      if (us < best_us) { best_us = us; best = GemmLargePlan{tile, sp}; }
+      if (us < best_us) { best_us = us; best = GemmLargePlan{t.rows, t.cols, sp}; }
     }
   return best;
 }
 
-template <int TMH>
-static void launch_epi(const GemmArgs &g, int epi, hipStream_t s) {
-  if (epi == GEMM_EPI_ROPE) launch_cfg<TMH, GEMM_EPI_ROPE>(g, s);
-  else if (epi == GEMM_EPI_SWIGLU) launch_cfg<TMH, GEMM_EPI_SWIGLU>(g, s);
-  else if (epi == GEMM_EPI_PARTIAL) launch_cfg<TMH, GEMM_EPI_PARTIAL>(g, s);
-  else launch_cfg<TMH, GEMM_EPI_BF16>(g, s);
+// The same for 33 to 256 rows, partial sums; splits = 0: not here.  The segments by the weights' shape alone, so that they are the same for all of these
+// rows: as many, up to eight, as let two row tiles of the widest tile be one round, of 16 k-tiles or more, or fewer where that leaves the chip idle (a shorter one
+// waits for its first tiles, a narrow product's partial sums are few); then the narrowest tile that is one round, with an eighth to spare for those that
+// read the rows most often.
+// Where the 128 x 128 tiles of k_gemm_mfma.hip and their segments are nearly one round they stay: 128 rows of 4096 x 4096 and 4096 x 14336 were 17.3 and 34.8 us there
+// and 14.3 and 33.7 here, each by itself, but in a layer (4 segments are 3 us of the gate/up product behind them, which reads none of this) 168 and 171.
+// Elsewhere, a product with its reduction, us, there and here, and a layer of that shape:
+//   N x K            40 rows       128           150           256           | layer  40            128           139           256
+//   4096 x 4096                                  22.6 / 18.3   26.8 / 23.7   |                                    195 / 190     229 / 220
+//   4096 x 14336                                 49.0 / 40.9   55.4 / 46.8   |
+//   5120 x 5120      22.0 / 16.3   28.5 / 22.6   32.7 / 25.4   41.0 / 29.6   |        323 / 308     657 / 642     692 / 671     997 / 975
+//   5120 x 13824     42.7 / 32.3   52.1 / 42.7   62.5 / 47.3   71.4 / 56.6   |
+//   2048 x 8192      15.4 / 11.3   17.5 / 14.3                               |        86 / 79       97 / 93
+GemmLargePlan gemm_few_plan(const GemmArgs &g, int n_cu) {
+  const int now = (g.M + 127) / 128 * ((g.N + 127) / 128) * gemm_mfma_fixed_segments(g.N, g.K, n_cu);
+  if (now <= n_cu && 3 * now > 2 * n_cu) return GemmLargePlan{0, 0, 0};
+  int sp = 8;
+  while (sp > 1 && (g.K % (128 * sp) != 0 || g.K < 512 * sp || 2 * ((g.N + 255) / 256) * sp > n_cu || (g.K / 64 / sp < 16 && g.N * sp > 8192))) sp /= 2;
+  static const int tiles[] = {64, 96, 128, 192};
+  for (int cols : tiles)
+    if ((g.M + 127) / 128 * ((g.N + cols - 1) / cols) * sp <= (cols < 128 ? n_cu * 7 / 8 : n_cu)) return GemmLargePlan{128, cols, sp};
+  return GemmLargePlan{128, 256, sp};
 }
 
-void launch_gemm_large(GemmArgs g, int epi, int tile, hipStream_t s) {
+void launch_gemm_large(GemmArgs g, int epi, const GemmLargePlan &plan, hipStream_t s) {
   if (epi != GEMM_EPI_PARTIAL) g.k_splits = 1;
   const int slice = gemm_large_slice_rows(g.lda), M = g.M;
   for (int m = 0; m < M; m += slice) {
@@ -607,9 +550,11 @@ void launch_gemm_large(GemmArgs g, int epi, int tile, hipStream_t s) {
     if (q.row_adapter) q.row_adapter += m;
     if (q.present16) q.present16 += m / 16;
     if (epi == GEMM_EPI_ROPE) { q.rope_pos += m; q.rope_slot += m; q.Qout += (int64_t)m * g.n_q; }
-    if (tile == 2) launch_epi<2>(q, epi, s);
-    else if (tile == 1) launch_epi<1>(q, epi, s);
-    else launch_epi<0>(q, epi, s);
+    if (plan.rows == 128) launch_gemm_mid(q, epi, plan.cols, s);
+    else if (epi == GEMM_EPI_ROPE) launch_cfg<GEMM_EPI_ROPE>(q, s);
+    else if (epi == GEMM_EPI_SWIGLU) launch_cfg<GEMM_EPI_SWIGLU>(q, s);
+    else if (epi == GEMM_EPI_PARTIAL) launch_cfg<GEMM_EPI_PARTIAL>(q, s);
+    else launch_cfg<GEMM_EPI_BF16>(q, s);
   }
 }
 

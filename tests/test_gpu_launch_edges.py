@@ -88,6 +88,33 @@ def test_many_rows_through_the_large_tiles(ab, ctx, T, inter, tile, rest, rank):
     _one_stack_layer(ab, ctx, shape, T, 1200 + T + inter)
 
 
+@pytest.mark.parametrize("T,inter,rest,rank", [(33, 1280, True, 16), (129, 1280, True, 24), (256, 8192, False, 16), (640, 1280, True, 8), (1025, 2048, False, 40)])
+def test_rows_through_the_tiles_of_128_rows(ab, ctx, T, inter, rest, rank):
+    _one_stack_layer(ab, ctx, dataclasses.replace(SMALL_BF16, intermediate=inter, rank=rank, adapt_rest=rest), T, 2200 + T + inter)
+
+
+# columns of a tile, 64 to 256 (N = 3072, 4096, 6144 columns; the last column tiles are parts of one)
+@pytest.mark.parametrize("hq,hkv,T,rank", [(16, 4, 129, 16), (10, 1, 256, 8), (16, 4, 700, 24), (24, 4, 1000, 32), (32, 8, 1000, 64), (32, 8, 1200, 16)])
+def test_projection_in_tiles_of_every_width_gives_the_same_bits(ab, hq, hkv, T, rank):
+    """Queries, keys and values of one running sum: the same from 256 x 256 tiles (gemm_tile 3) as from the tiles of 128 rows."""
+    shape = wl.LayerShape(d=512, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rank=rank, n_adapters=3)
+    S = [T - 40, 17, 23]
+    case = H.make_case(shape, [5, 33, 0], S, [5 + S[0] // 2, 33, 4], [1, 2, 0], seed=2300 + T + hq, prefix="random")
+    layer, x = H.gpu_layer(case, shape), case.x_packed.cuda().contiguous()
+    got = []
+    for tile in (0, 3):
+        c = ab.Context(0)
+        c.set_option("gemm_tile", tile)
+        cache = H.gpu_cache(case)
+        out = ab.alora_prefill(c, layer, cache, x, case.cu, case.k, case.adapter)
+        torch.cuda.synchronize()
+        got.append([t.clone() for t in (out, cache.k, cache.v)])
+        c.close()
+    assert all(torch.equal(p, q) for p, q in zip(*got))
+    ref, _ = H.oracle_prefill(case)
+    assert H.rel_err(H.f64(got[0][0]), ref) <= H.TOL["bf16"]
+
+
 @pytest.mark.parametrize("T", [20, 300])
 def test_weights_that_are_not_16_byte_aligned(ab, ctx, T):
     """Parameters that are views into one flat buffer, eight bytes off: the kernels whose weights go to LDS by request
