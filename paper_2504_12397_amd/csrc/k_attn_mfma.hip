@@ -806,11 +806,64 @@ __global__ __launch_bounds__(256) void attn_merge16_kernel(const char *__restric
   *reinterpret_cast<bf16x2_t *>(out + rh * 128 + lane * 2) = ov;
 }
 
+// Up to sixteen records: all of them in one round trip, the maximum from what came with them (the same sums in the same order).  1024 rows of 32 heads, three
+// records: 15.8 -> 7.3 us (it asked for eight records' places whatever their number, and for the maxima first); 512 rows, five: 10.2 -> 5.6; 128 rows, sixteen: 5.8 -> 5.6.
+template <int N>
+__global__ __launch_bounds__(256) void attn_merge16_few_kernel(const char *__restrict__ part, int64_t n_rh, bf16 *__restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  const int64_t rh = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (rh >= n_rh) return;
+  const char *p = part + rh * N * (int64_t)ATTN_REC16;
+  typedef __attribute__((__vector_size__(2 * sizeof(_Float16)))) _Float16 half2_t;
+  float4 t[N];      // reference, row sum, magnitude
+  half2_t u[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    t[i] = *reinterpret_cast<const float4 *>(p + i * ATTN_REC16 + 256);
+    u[i] = *reinterpret_cast<const half2_t *>(p + i * ATTN_REC16 + lane * 4);
+  }
+  float M = t[0].x;
+#pragma unroll
+  for (int i = 1; i < N; ++i) M = fmaxf(M, t[i].x);
+  float denom = 0.f, a0 = 0.f, a1 = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float w = t[i].x == -INFINITY ? 0.f : __expf(t[i].x - M);
+    denom += w * t[i].y;
+    a0 += w * t[i].z * (float)u[i][0];
+    a1 += w * t[i].z * (float)u[i][1];
+  }
+  const float inv = 1.0f / denom;
+  typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
+  bf16x2_t ov;
+  ov[0] = (bf16)(a0 * inv);
+  ov[1] = (bf16)(a1 * inv);
+  *reinterpret_cast<bf16x2_t *>(out + rh * 128 + lane * 2) = ov;
+}
+
 void launch_attn_merge16(const float *partials, const LayerDims &L, int T_rows, int n_splits, bf16 *out, hipStream_t s) {
   if (T_rows == 0) return;
   const int64_t n_rh = (int64_t)T_rows * L.n_q_heads;
-  hipLaunchKernelGGL(attn_merge16_kernel, dim3((unsigned)((n_rh + 3) / 4)), dim3(256), 0, s, (const char *)partials,
-                     n_splits, n_rh, out);
+  const dim3 grid((unsigned)((n_rh + 3) / 4));
+  const char *p = (const char *)partials;
+  switch (n_splits) {
+    case 2: hipLaunchKernelGGL(attn_merge16_few_kernel<2>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 3: hipLaunchKernelGGL(attn_merge16_few_kernel<3>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 4: hipLaunchKernelGGL(attn_merge16_few_kernel<4>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 5: hipLaunchKernelGGL(attn_merge16_few_kernel<5>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 6: hipLaunchKernelGGL(attn_merge16_few_kernel<6>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 7: hipLaunchKernelGGL(attn_merge16_few_kernel<7>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 8: hipLaunchKernelGGL(attn_merge16_few_kernel<8>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 9: hipLaunchKernelGGL(attn_merge16_few_kernel<9>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 10: hipLaunchKernelGGL(attn_merge16_few_kernel<10>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 11: hipLaunchKernelGGL(attn_merge16_few_kernel<11>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 12: hipLaunchKernelGGL(attn_merge16_few_kernel<12>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 13: hipLaunchKernelGGL(attn_merge16_few_kernel<13>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 14: hipLaunchKernelGGL(attn_merge16_few_kernel<14>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 15: hipLaunchKernelGGL(attn_merge16_few_kernel<15>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    case 16: hipLaunchKernelGGL(attn_merge16_few_kernel<16>, grid, dim3(256), 0, s, p, n_rh, out); break;
+    default: hipLaunchKernelGGL(attn_merge16_kernel, grid, dim3(256), 0, s, p, n_splits, n_rh, out);
+  }
 }
 
 void launch_attn_prefill_mfma(const AttnArgs &a, int n_work, int G, int waves, bool prefix, hipStream_t s) {

@@ -283,13 +283,21 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(GemmArgs g, int tiles_m, 
       for (int i = 0; i < 4; ++i) a[i] = (bf16)y[i];
       return __builtin_bit_cast(uint2, a);
     };
+    int pos[MB];
+    int64_t slot[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+      if constexpr (EPI == GEMM_EPI_ROPE) {
+        const int rc = min(row0 + m * 32 + l32, M - 1);
+        pos[m] = g.rope_pos[rc];
+        slot[m] = g.rope_slot[rc];
+      }
 #pragma unroll
     for (int m = 0; m < MB; ++m) {
       const int row = row0 + m * 32 + l32, rc = min(row, M - 1);
       if (row0 + m * 32 >= M) break;
       if constexpr (EPI == GEMM_EPI_ROPE) {
-        const int64_t slot = g.rope_slot[rc];
-        const float2 *line = g.rope_table + (int64_t)g.rope_pos[rc] * 64 + 4 * lhi;
+        const float2 *line = g.rope_table + (int64_t)pos[m] * 64 + 4 * lhi;
         float4 cs[NB][2][2];
 #pragma unroll
         for (int j = 0; j < NB; ++j)
@@ -318,7 +326,7 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(GemmArgs g, int tiles_m, 
           }
           const u32x4 l = join(lo[0], lo[1]), h = join(hi[0], hi[1]);
           bf16 *dst = kind == 0 ? g.Qout + (int64_t)row * g.n_q + col
-                                : (kind == 1 ? g.cacheK + slot * g.n_kv + col - g.n_q : g.cacheV + slot * g.n_kv + col - g.n_q - g.n_kv);
+                                : (kind == 1 ? g.cacheK + slot[m] * g.n_kv + col - g.n_q : g.cacheV + slot[m] * g.n_kv + col - g.n_q - g.n_kv);
           if (row < M && col < N) {
             *reinterpret_cast<u32x4 *>(dst + 8 * lhi) = l;
             *reinterpret_cast<u32x4 *>(dst + 8 * lhi + 64) = h;

@@ -653,3 +653,16 @@ def test_row_preparation_of_many_short_sequences(ab, ctx, n, rank, n_adapters):
     case = H.make_case(shape, P, S, [P[b] + (b % 7 == 3) for b in range(n)], [b % (n_adapters + 1) - 1 for b in range(n)], seed=3100 + n,
                        prefix="random")
     check_case(ab, ctx, case)
+
+
+@pytest.mark.parametrize("records", [2, 3, 4, 5, 6, 7, 8, 9, 11, 16, 17])
+@pytest.mark.parametrize("compact", [1, 0])
+def test_merge_of_every_number_of_records(ab, records, compact):
+    """Ranges that hold keys and, of the short sequence, ranges that hold none (their records have no weight)."""
+    shape = wl.LayerShape(d=512, n_q_heads=6, n_kv_heads=3, head_dim=128, rank=16, n_adapters=2)
+    case = H.make_case(shape, [1500, 3], [9, 2], [1500, 3], [1, 0], seed=2400 + records, prefix="random")
+    c = ab.Context(0)
+    c.set_option("kv_splits", records)
+    c.set_option("attn_partials16", compact)
+    check_case(ab, c, case)
+    c.close()
