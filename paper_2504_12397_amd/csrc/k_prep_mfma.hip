@@ -196,6 +196,146 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   }
 }
 
+// The same for at most RT rows (RT = 2, 8): a thread has one chunk of each of them, not a lane sixteen of one row, of which lanes without a row repeat the last
+// one.  With one row that was 128 elements per lane to square, scale and convert, sixteen times over; now it is 8.  x_hat goes through LDS, chunk c of row r
+// at c ^ r, to become the matrix operand.  Sums as above, bit for bit.
+// The kernel, us, sixteen rows a tile -> so: one row of a rank-64 adapter 9.6 -> 6.6, four rows of four 9.8 -> 7.4, five of five 9.8 -> 8.6, eight of eight 10.3 -> 9.2; five
+// rows of four rank-8 adapters 9.7 -> 8.8.
+// Tree over u, neighbours first, for N rows at once: while there are several a lane keeps half of them and gives the other half for its partner's.
+template <int N, int O, int GL> __device__ __forceinline__ float tree_of_rows(const float (&v)[N], int lane, int &row) {
+  if constexpr (O >= GL) {
+    return v[0];
+  } else if constexpr (N > 1) {
+    const bool high = lane & O;
+    float k[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) k[i] = (high ? v[N / 2 + i] : v[i]) + __shfl_xor(high ? v[i] : v[N / 2 + i], O, 64);
+    row = row * 2 + (high ? 1 : 0);
+    return tree_of_rows<N / 2, O * 2, GL>(k, lane, row);
+  } else {
+    const float k[1] = {v[0] + __shfl_xor(v[0], O, 64)};
+    return tree_of_rows<1, O * 2, GL>(k, lane, row);
+  }
+}
+template <int CH, int NC, int RT>
+__global__ __launch_bounds__(512, 2) void prep_few_rows_kernel(PrepArgs a) {
+  constexpr int d = CH * 256, NCHUNK = d / 8, GL = 4 * CH;      // GL: chunks (neighbouring lanes) of one w
+  static_assert(4 * RT <= GL, "");
+  __shared__ float s_ssq[RT][PREP_WAVES];
+  __shared__ int s_adapter[PREP_ROWS];
+  __shared__ float s_scale[PREP_ROWS];
+  __shared__ unsigned long long s_present;
+  __shared__ u32x4 s_x[RT * NCHUNK];
+  __shared__ float s_part[PREP_WAVES][PREP_ROWS][17];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, kg = lane >> 4;
+  const int rank = a.rank, col0 = blockIdx.y * NC;
+  const int ad = (reinterpret_cast<const uint32_t *>(a.used)[blockIdx.z >> 2] >> (8 * (blockIdx.z & 3))) & 255;      // (a scalar load)
+  // all arguments in one round trip, not where they are used
+  asm volatile("" ::"s"(a.rm.seq), "s"(a.rm.pos), "s"(a.rm.adapter), "s"(a.rm.slot), "s"(a.rm.present16), "s"(a.xh), "s"(a.tlow16), "s"(a.gain),
+               "s"(a.packed), "s"(a.eps), "s"(a.write_meta), "s"(a.pos_shift), "s"(a.n_seqs), "s"(ad),
+               "s"(a.x), "s"(a.A), "s"(a.rank), "s"(a.T), "s"(a.st.src), "s"(a.st.dst), "s"(a.st.n16));
+  const bool lead = blockIdx.y == 0 && blockIdx.z == 0;
+  const int c = min(tid, NCHUNK - 1);
+
+  // (requests as in the kernel above: none behind a branch)
+  typedef uint32_t rec16 __attribute__((ext_vector_type(4), aligned(8)));
+  const uint64_t recs = a.st.n_few ? (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(PrepArgs, st.few) : (uint64_t)a.seqs;
+  const auto *rec = reinterpret_cast<const __attribute__((address_space(1))) rec16 *>(recs + (uint64_t)min(tid, a.n_seqs - 1) * sizeof(SeqMeta));
+  const u32x4 rec0 = rec[0], rec1 = rec[1];
+  u32x4 xr[RT], br[CH];
+#pragma unroll
+  for (int r = 0; r < RT; ++r) xr[r] = *reinterpret_cast<const u32x4 *>(a.x + (int64_t)min(r, a.T - 1) * d + c * 8);
+  const u32x4 gain = *reinterpret_cast<const u32x4 *>((a.gain != nullptr ? a.gain : a.x) + c * 8);
+  const int my_col = min(col0 + r16, 3 * rank - 1), k_lo = wave * (CH * 32) + kg * 8;
+  const auto A_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(a.A + (int64_t)ad * 3 * rank * d), 0, 3 * rank * d * 2, 0x00020000);
+  const int A_off = NC == 16 || r16 < NC ? (my_col * d + k_lo) * 2 : 0x7fff0000;
+#pragma unroll
+  for (int u = 0; u < CH; ++u) br[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(A_rsrc, A_off, 64 * u, 0));
+  uint4 staged{};
+  const bool carry = lead && a.st.src != nullptr && tid < a.st.n16;
+  if (carry) staged = a.st.src[tid];      // (host memory: behind what everybody waits for)
+
+  if (tid == 0) s_present = 0ull;
+  if (tid < PREP_ROWS) { s_adapter[tid] = -1; s_scale[tid] = 0.f; }
+  __syncthreads();
+  auto fill = [&](const SeqMeta &sm, int sq) {
+    for (int mrow = sm.row_start; mrow < min(sm.row_start + sm.n_new, a.T); ++mrow)
+      fill_row_meta(a, sm, sq, mrow, 0, a.write_meta && lead, s_adapter, s_scale, &s_present);
+  };
+  if (tid < a.n_seqs) {
+    SeqMeta sm{};
+    sm.row_start = (int)rec0[0]; sm.n_new = (int)rec0[1]; sm.P = (int)rec0[2]; sm.k = (int)rec0[3];
+    sm.adapter = (int)rec1[0]; sm.scale = __uint_as_float(rec1[1]); sm.pool_off = (int64_t)((uint64_t)rec1[3] << 32 | rec1[2]);
+    fill(sm, tid);
+  }
+  for (int sq = tid + 512; sq < a.n_seqs; sq += 512) fill(a.seqs[sq], sq);
+
+  if (a.gain != nullptr) {
+    float v[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) v[r] = chunk_ssq(xr[r]);
+    int row = 0;
+    float sum = tree_of_rows<RT, 4, GL>(v, lane, row);
+    sum += __shfl_xor(sum, 1, 64);      // tree over g
+    sum += __shfl_xor(sum, 2, 64);
+    if (tid < NCHUNK && (lane % GL & ~(4 * (RT - 1))) == 0) s_ssq[row][tid / GL] = sum;
+  }
+  __syncthreads();
+  if (lead && tid == 0 && a.rm.present16 != nullptr) a.rm.present16[0] = s_present;
+  if (a.gain != nullptr) {
+    float t = 0.f;      // of row lane % RT
+#pragma unroll
+    for (int w = 0; w < PREP_WAVES; ++w) t += s_ssq[lane % RT][w];
+    const float rinv = row_rinv(t, d, a.eps);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      xr[r] = norm_chunk(xr[r], gain, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(rinv), r)));
+    }
+  }
+  if (tid < NCHUNK) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) s_x[r * NCHUNK + (tid ^ r)] = xr[r];
+    if (lead) {
+      u32x4 *dst = reinterpret_cast<u32x4 *>(a.xh) + xh_chunk(0, tid, d, a.packed);
+      const int step = a.packed ? 1 : NCHUNK;      // (all rows are in the first block of 32)
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+        if (r < a.T) dst[r * step] = xr[r];
+    }
+  }
+  if (carry) a.st.dst[tid] = staged;
+  if (!((s_present >> ad) & 1)) return;
+  __syncthreads();
+
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool mine = s_adapter[r16] == ad;      // (no row: -1)
+  const u32x4 *xa = s_x + (r16 % RT) * NCHUNK;
+#pragma unroll
+  for (int u = 0; u < CH; ++u) {
+    const u32x4 au = mine ? xa[((k_lo >> 3) + 4 * u) ^ (r16 % RT)] : u32x4{0, 0, 0, 0};
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, au), __builtin_bit_cast(bf16x8, br[u]), acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) s_part[wave][4 * kg + v][r16] = acc[v];
+  __syncthreads();
+  if (tid < RT * 16) {
+    const int row = tid >> 4, col = tid & 15;
+    if (row < a.T && s_adapter[row] == ad && col < NC && col0 + col < 3 * rank) {
+      float t = 0.f;
+#pragma unroll
+      for (int w = 0; w < PREP_WAVES; ++w) t += s_part[w][row][col];
+      t *= s_scale[row];
+      const int p = (col0 + col) / rank, jj = (col0 + col) % rank;
+      const bf16 hi = (bf16)t;
+      bf16 *dst = a.tlow16 + (((int64_t)row * 3 + p) * 2) * rank + jj;
+      dst[0] = hi;
+      dst[rank] = (bf16)(t - (float)hi);
+    }
+  }
+}
+
 // Metadata and RMSNorm, four waves per workgroup, RW rows per wave.  A wave takes its rows whole -- every load and
 // store instruction covers 1 KB of one row -- and the only wait besides the rows themselves is the sequences' records.  One row
 // per wave (four per workgroup, so that a few hundred rows reach every compute unit: 512 rows 12 -> 8.4 us against 16 rows per workgroup), four
@@ -387,7 +527,15 @@ static void launch_prep_ch(const PrepArgs &a, hipStream_t s) {
   if (a.rank == 0 || a.A == nullptr || a.n_used == 0) {
     launch_norm<CH>(a, s);
   } else if (a.few == 2 || !lds_aligned(a.A) || (a.few == 1 && row_tiles * cols16 * a.n_used <= PREP_FEW)) {
-    if (row_tiles * cols16 * a.n_used <= PREP_NARROW)
+    const dim3 narrow(1, (3 * a.rank + 7) / 8, a.n_used);
+    const bool rows = CH >= 8 && cols16 * a.n_used <= PREP_NARROW;
+    if (rows && a.T <= 2)
+      hipLaunchKernelGGL((prep_few_rows_kernel<CH < 8 ? 8 : CH, 8, 2>), narrow, dim3(512), 0, s, a);
+    else if (rows && a.T <= 4)
+      hipLaunchKernelGGL((prep_few_rows_kernel<CH < 8 ? 8 : CH, 8, 4>), narrow, dim3(512), 0, s, a);
+    else if (rows && a.T <= 8)
+      hipLaunchKernelGGL((prep_few_rows_kernel<CH < 8 ? 8 : CH, 8, 8>), narrow, dim3(512), 0, s, a);
+    else if (row_tiles * cols16 * a.n_used <= PREP_NARROW)
       hipLaunchKernelGGL((prep_few_kernel<CH, 8>), dim3(row_tiles, (3 * a.rank + 7) / 8, a.n_used), dim3(512), 0, s, a);
     else
       hipLaunchKernelGGL((prep_few_kernel<CH, 16>), dim3(row_tiles, cols16, a.n_used), dim3(512), 0, s, a);

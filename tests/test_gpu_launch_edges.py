@@ -666,3 +666,25 @@ def test_merge_of_every_number_of_records(ab, records, compact):
     c.set_option("attn_partials16", compact)
     check_case(ab, c, case)
     c.close()
+
+
+@pytest.mark.parametrize("d,rank", [(4096, 8), (2048, 24)])
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 8, 9])
+def test_row_preparation_of_up_to_eight_rows(ab, d, rank, T):
+    """Normalised rows and t of few rows: outputs against the oracle, base rows' keys and values bit for bit those of a call of many rows."""
+    shape = wl.LayerShape(d=d, n_q_heads=4, n_kv_heads=2, head_dim=128, rank=rank, n_adapters=3)
+    S = _split(T, min(T, 3))
+    n = len(S)
+    case = H.make_case(shape, [64, 3, 40][:n], S, [64, 3, 40 + S[-1] // 2][:n], [1, 2, 0][:n], seed=2500 + T + d, prefix="random")
+    c = ab.Context(0)
+    check_case(ab, c, case)
+    x = wl.make_hidden(wl.Rng(2510 + T), "x", 40, shape).cuda()
+    layer, rows = H.gpu_layer(case, shape), []
+    for m in (T, 40):
+        cache = ab.KVCache([40], shape.n_kv_heads, shape.head_dim, shape.torch_dtype, "cuda")
+        ab.alora_prefill(c, layer, cache, x[:m].contiguous(), [0, m], [T - 1], [1])      # (the last row of the short call is an adapted one)
+        torch.cuda.synchronize()
+        rows.append([t.clone() for t in cache.rows(0, 0, T)])
+    for a, b in zip(*rows):
+        assert torch.equal(a[:T - 1].view(torch.int16), b[:T - 1].view(torch.int16))
+    c.close()
