@@ -617,8 +617,17 @@ __global__ __launch_bounds__(256) void tlow_select_kernel(const float *__restric
   const float sc = scale[a];
   for (int i = threadIdx.x; i < parts * rank; i += 256) {
     const int p = i / rank, j = i - p * rank;
+    // eight partial sums asked for together, added in order (one after the other 28 of them are 28 round trips: 8.5 -> 4.7 us)
+    const float *y = Y + (int64_t)row * N + (a * parts + p) * rank + j;
+    const int64_t step = (int64_t)M * N;
     float t = 0.f;
-    for (int sp = 0; sp < splits; ++sp) t += Y[((int64_t)sp * M + row) * N + (a * parts + p) * rank + j];
+    for (int s0 = 0; s0 < splits; s0 += 8) {
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = y[min(s0 + i, splits - 1) * step];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t += s0 + i < splits ? v[i] : 0.f;
+    }
     t *= sc;
     const bf16 hi = (bf16)t;
     bf16 *dst = tlow + (((int64_t)row * parts + p) * 2) * rank + j;
