@@ -172,6 +172,90 @@ __device__ __forceinline__ void write_result(const AttnArgs &a, int part, int64_
   }
 }
 
+// The same, whole pieces of 64 bytes of a row at a time: eight bytes of 32 rows a request are what the unit that looks up addresses takes longest for.  Each wave
+// turns 32 rows x 64 bytes at a time through 2 KB of LDS of its own; there and on the way out a lane has rows lane / 4 and 16 more, 16 bytes lane % 4 of them.
+// io_rh: (row, head) of those two rows, or -1.
+__device__ __forceinline__ void write_result_staged(const AttnArgs &a, int part, char *st, const int64_t (&io_rh)[2], int lane, float m_ref, float l_run,
+                                                    const f32x16 (&o)[4]) {
+  constexpr int H = 128;
+  typedef __attribute__((__vector_size__(4 * sizeof(_Float16)))) _Float16 half4_t;
+  typedef uint32_t w16 __attribute__((ext_vector_type(4), aligned(8)));
+  const int l32 = lane & 31, kh = lane >> 5, chunk = lane & 3;
+  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);      // the two halves of the wave hold disjoint keys
+  auto at = [&](int r, int c) { return st + r * 64 + ((c ^ ((r >> 2) & 3)) * 16); };
+  auto take = [&](int half) { return *reinterpret_cast<const u32x4 *>(at(16 * half + (lane >> 2), chunk)); };
+  const bool direct = a.out != nullptr;
+  if (direct || a.compact) {
+    float rs, amax = 0.f;
+    if (direct) {
+      rs = 1.0f / l_tot;
+    } else {      // (compact record: see write_result)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) amax = fmaxf(amax, fabsf(o[cb][v]));
+      amax = max_with_other_half(amax);
+      rs = amax > 0.f ? 1.0f / amax : 0.f;
+    }
+    const int64_t step = direct ? H * 2 : (int64_t)a.n_parts * ATTN_REC16;
+    char *base = direct ? reinterpret_cast<char *>(a.out) : reinterpret_cast<char *>(a.partials) + part * ATTN_REC16;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        uint2 w;
+        if (direct) {
+          w.x = pack_bf16x2(o[cb][4 * v4] * rs, o[cb][4 * v4 + 1] * rs);
+          w.y = pack_bf16x2(o[cb][4 * v4 + 2] * rs, o[cb][4 * v4 + 3] * rs);
+        } else {
+          half4_t hv;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) hv[i] = (_Float16)(o[cb][4 * v4 + i] * rs);
+          w = __builtin_bit_cast(uint2, hv);
+        }
+        *reinterpret_cast<uint2 *>(at(l32, v4) + 8 * kh) = w;
+      }
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const u32x4 w = take(half);
+        if (io_rh[half] >= 0) *reinterpret_cast<u32x4 *>(base + io_rh[half] * step + cb * 64 + chunk * 16) = w;
+      }
+    }
+    if (direct) return;
+    // the three numbers of a record: row l32's, to the lanes that know where its record is
+    if (kh == 0)
+      *reinterpret_cast<float4 *>(at(l32, 0)) = make_float4((l_tot == 0.f || m_ref == -INFINITY) ? -INFINITY : m_ref * LN2, l_tot, amax, 0.f);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const float4 t = *reinterpret_cast<const float4 *>(at(16 * half + (lane >> 2), 0));
+      if (chunk == 0 && io_rh[half] >= 0) *reinterpret_cast<float4 *>(base + io_rh[half] * step + 2 * H) = t;
+    }
+  } else {
+    float *base = a.partials + (int64_t)part * (H + 2);
+    const int64_t step = (int64_t)a.n_parts * (H + 2);
+#pragma unroll
+    for (int hc = 0; hc < 8; ++hc) {      // 16 columns
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int v = 8 * (hc & 1) + 4 * q;
+        *reinterpret_cast<float4 *>(at(l32, 2 * q + kh)) = make_float4(o[hc >> 1][v], o[hc >> 1][v + 1], o[hc >> 1][v + 2], o[hc >> 1][v + 3]);
+      }
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const u32x4 w = take(half);
+        // ((H + 2) floats per record keeps 8-byte, not 16-byte, alignment)
+        if (io_rh[half] >= 0) *reinterpret_cast<w16 *>(base + io_rh[half] * step + hc * 16 + chunk * 4) = w;
+      }
+    }
+    if (kh == 0) *reinterpret_cast<float2 *>(at(l32, 0)) = make_float2((l_tot == 0.f || m_ref == -INFINITY) ? -INFINITY : m_ref * LN2, l_tot);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const float2 t = *reinterpret_cast<const float2 *>(at(16 * half + (lane >> 2), 0));
+      if (chunk == 0 && io_rh[half] >= 0) *reinterpret_cast<float2 *>(base + io_rh[half] * step + H) = t;
+    }
+  }
+}
+
 // PFX: tile loads with full 64-bit address arithmetic (items whose keys lie beyond 2 GB from their first row)
 // instead of buffer loads with 32-bit offsets
 //
@@ -492,7 +576,7 @@ template <int N> using ic = std::integral_constant<int, N>;
 // one K tile (rows 16 bytes apart from a multiple of 256, so that 16 of them lie in different banks) and one V^T tile in LDS; four of each
 constexpr int PIPE_AHEAD = 4;      // operand reads run this many matrix instructions ahead
 constexpr int PIPE_KROW = 272, PIPE_K = ATT_BN * PIPE_KROW, PIPE_VT = ATT_BN * 256;
-constexpr int PIPE_V = 4 * PIPE_K, PIPE_LDS = PIPE_V + 4 * PIPE_VT;
+constexpr int PIPE_V = 4 * PIPE_K, PIPE_OUT = PIPE_V + 4 * PIPE_VT, PIPE_LDS = PIPE_OUT + 8 * 2048;      // (the last: results on their way out)
 // a value that the compiler takes as computed here (and whose parts it does not look into)
 __device__ __forceinline__ void pin(int &x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void pin(uint32_t &x) { asm volatile("" : "+v"(x)); }
@@ -518,15 +602,27 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
   const bf16 *Kp = a.K + wk.key_row0 * a.n_kv + wk.g * H;
   const bf16 *Vp = a.V + wk.key_row0 * a.n_kv + wk.g * H;
 
-  const int pr = wave * 32 + l32, tok = pr >> g_log2, head = (wk.g << g_log2) + (pr & ((1 << g_log2) - 1));
-  const int v = row0 + min(tok, ntok - 1);
-  const int64_t row = a.steps > 0 ? v % a.steps * a.seqs + (a.order != nullptr ? a.order[v / a.steps] : v / a.steps) : v;
-  const int pos = tok < ntok ? first_pos + tok : -1;       // -1: padding row
+  // this lane's packed row: its row of Q and the records (rows past the last repeat that one); other lanes' rows come from them
+  const int tok = (wave * 32 + l32) >> g_log2, pos = tok < ntok ? first_pos + tok : -1;       // -1: padding row
+  int my_row = row0 + min(tok, ntok - 1);
+  if (a.steps > 0) {      // (a run has 1024 rows at most: its sequence is exact in floats)
+    const int seq = (int)(((float)my_row + 0.5f) / (float)a.steps);
+    my_row = (my_row - seq * a.steps) * a.seqs + (a.order != nullptr ? a.order[seq] : seq);
+  }
+  const int head0 = wk.g << g_log2, in_group = (1 << g_log2) - 1;
+  auto rh_of = [&](int r) { return (int64_t)__shfl(my_row, r, 64) * a.n_q_heads + head0 + ((wave * 32 + r) & in_group); };      // (row, head) of the wave's row r
+  // The wave's 32 query rows of 256 bytes come in whole, four a request, and through LDS (in the tile buffers that are filled last) into operand order: chunk
+  // c of row r at c ^ (r & 15).  Asked for in operand order they are 32 bytes of 32 rows a request, and 64 such requests 2 us of a compute unit.
   u32x4 qf[8];
   {
-    const _Float16 *qp = a.Q + row * a.n_q + head * H + kh * 8;
+    u32x4 raw[8];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const u32x4 *>(qp + ks * 16);
+    for (int j = 0; j < 8; ++j) {
+      const int r = 4 * j + (lane >> 4);
+      raw[j] = *reinterpret_cast<const u32x4 *>(a.Q + rh_of(r) * H + ((lane & 15) ^ (r & 15)) * 8);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) qf[j] = raw[j];
   }
   f32x16 o[4], negm;
 #pragma unroll
@@ -687,6 +783,11 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
     u32x2 rv1[4];
     load_tile(0, rk, rv);
     load_tile(1, rk1, rv1);
+    const int q_at = lds + (wave < 4 ? 2 * PIPE_K + wave * 8192 : PIPE_V + 2 * PIPE_VT + (wave - 4) * 8192);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) lds_write(q_at + j * 1024 + lane * 16, qf[j]);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = lds_read<u32x4>(q_at + l32 * 256 + (((2 * ks + kh) ^ (l32 & 15)) * 16));
     wait_all_global_loads();
     k_st -= dk; v_st[0] -= dv; v_st[1] -= dv;
 #pragma unroll
@@ -733,7 +834,15 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
     }
   }
   const float m_ref = -negm[0];
-  write_result(a, wk.part, row, tok < ntok, head, kh, m_ref, l_run, o);
+  if ((wave * 32 >> g_log2) >= ntok) return;      // (no row)
+  int64_t io_rh[2];
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int r = 16 * half + (lane >> 2);
+    const int64_t rh = rh_of(r);
+    io_rh[half] = ((wave * 32 + r) >> g_log2) < ntok ? rh : -1;
+  }
+  write_result_staged(a, wk.part, reinterpret_cast<char *>(pipe_lds) + PIPE_OUT + wave * 2048, io_rh, lane, m_ref, l_run, o);
 }
 
 bool attn_prefill_mfma_supported(const LayerDims &L) {
