@@ -623,6 +623,7 @@ void attend_rows(alora_ctx *ctx, const LayerDims &L, const alora_kv_cache *cache
     a.heads_per_wg = w.dec_hw; a.ranges_per_wg = w.dec_kr; a.cols_max = w.dec_cols_max;
     a.sm_scale = folded ? 0.6931471805599453f : 1.0f / sqrtf((float)L.head_dim);
     a.partials = w.partials;
+    a.keys_max = w.run_steps > 0 ? w.run_steps : pl.max_len;
     launch_attn_decode_mfma(a, w.n_ditems, s);
   };
   if (w.attn_mfma && std::is_same<T, bf16>::value) {

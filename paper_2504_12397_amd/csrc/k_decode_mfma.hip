@@ -52,8 +52,10 @@ __device__ __forceinline__ float dec_sum2(uint32_t pair, float acc) {
 constexpr float DEC_LOG2E = 1.4426950408889634f;
 constexpr float DEC_LN2 = 0.6931471805599453f;
 
-template <int NC>
-__global__ __launch_bounds__(512, 2) void attn_decode_mfma_kernel(DecodeArgs a) {
+// SHORT: at most 32 keys an item (the own keys of a run of decode steps).  Nothing to ask for ahead: without the copies two workgroups share a
+// compute unit.  1024 rows of 1 to 16 keys: 32 -> 19 us (of these 23 -> 19 for asking for the first 16 keys only).
+template <int NC, bool SHORT = false>
+__global__ __launch_bounds__(512, SHORT ? 4 : 2) void attn_decode_mfma_kernel(DecodeArgs a) {
   constexpr int H = 128;
   extern __shared__ float s_o[];           // [wave][column < cols_max][acc..., m, l], several sub-ranges only
 
@@ -88,9 +90,15 @@ __global__ __launch_bounds__(512, 2) void attn_decode_mfma_kernel(DecodeArgs a) 
   auto row_of = [&](int rj) { return it.shared ? a.rows[it.row + rj] : it.row; };
 
   u32x4 kr[2][4], vr[2][4];      // [key block u][k-step s] and [u][n]: key 16u + 4kg + n
+  const bool one_block = SHORT && it.kend - it.kbeg <= 16;      // (the second 16 keys are then not asked for)
   auto load_k = [&](int k0) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
+      if (u == 1 && one_block) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) kr[1][s] = u32x4{0, 0, 0, 0};
+        break;
+      }
       const int kk = min(k0 + 16 * u + j, item_end - 1);
 #pragma unroll
       for (int s = 0; s < 4; ++s)
@@ -102,6 +110,7 @@ __global__ __launch_bounds__(512, 2) void attn_decode_mfma_kernel(DecodeArgs a) 
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int n = 0; n < 4; ++n) {
+        if (u == 1 && one_block) { vr[1][n] = u32x4{0, 0, 0, 0}; continue; }
         const int kv = min(k0 + 16 * u + 4 * kg + n, item_end - 1);
         vr[u][n] = *reinterpret_cast<const u32x4 *>(Vp + (int64_t)kv * a.n_kv + 8 * j);
       }
@@ -135,7 +144,7 @@ __global__ __launch_bounds__(512, 2) void attn_decode_mfma_kernel(DecodeArgs a) 
   for (int k0 = kbeg; k0 < kend; k0 += 32) {
     f32x4 sc[NC][2];
     u32x4 vc[2][4];
-    if constexpr (NC == 1) {
+    if constexpr (NC == 1 && !SHORT) {
       // consume copies of this step's registers and refill them for the next step at once: 16 KB per wave on the way
       u32x4 kc[2][4];
 #pragma unroll
@@ -166,7 +175,7 @@ __global__ __launch_bounds__(512, 2) void attn_decode_mfma_kernel(DecodeArgs a) 
             sc[nc][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, __builtin_bit_cast(f16x8, qf[nc][s]), sc[nc][u], 0, 0, 0);
         }
       }
-      load_k(k0 + 32);
+      if (!SHORT) load_k(k0 + 32);
     }
     u32x4 pf[NC];
     float alpha[NC];
@@ -201,7 +210,7 @@ __global__ __launch_bounds__(512, 2) void attn_decode_mfma_kernel(DecodeArgs a) 
       pf[nc] = u32x4{d0, d1, d2, d3};
       l_run[nc] = l_run[nc] * alpha[nc] + rs;
     }
-    u32x4 (&vs)[2][4] = NC == 1 ? vc : vr;
+    u32x4 (&vs)[2][4] = NC == 1 && !SHORT ? vc : vr;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       // column 8*j + c of the 8 keys this lane loaded: element c of each 16-byte row
@@ -217,7 +226,8 @@ __global__ __launch_bounds__(512, 2) void attn_decode_mfma_kernel(DecodeArgs a) 
         o[nc][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, vf), __builtin_bit_cast(f16x8, pf[nc]), oc, 0, 0, 0);
       }
     }
-    if constexpr (NC != 1) load_v(k0 + 32);
+    if constexpr (NC != 1 && !SHORT) load_v(k0 + 32);
+    if constexpr (SHORT) break;
   }
 
   // o[c][v] of lane (j, kg) is O[column 8*(4*kg + v) + c][head j]
@@ -300,7 +310,7 @@ void decode_mfma_shape(int n_kv_heads, bool two_heads, int *heads_per_wg, int *r
 void launch_attn_decode_mfma(const DecodeArgs &a, int n_items, hipStream_t s) {
   if (n_items == 0) return;
   const size_t smem = a.ranges_per_wg == 1 ? 0 : (size_t)8 * a.cols_max * (128 + 2) * sizeof(float);
-  auto kern = a.cols_max <= 16 ? attn_decode_mfma_kernel<1> : attn_decode_mfma_kernel<2>;
+  auto kern = a.keys_max <= 32 && a.cols_max <= 16 ? attn_decode_mfma_kernel<1, true> : a.cols_max <= 16 ? attn_decode_mfma_kernel<1> : attn_decode_mfma_kernel<2>;
   // set on every launch that needs it: a host-side attribute write, safe from any thread and on any device
   if (smem > 48 * 1024)
     (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);

@@ -158,6 +158,7 @@ struct DecodeArgs {
   int n_parts;              // partial records per (row, head)
   int heads_per_wg;         // kv heads a workgroup covers (one wave each) and ...
   int ranges_per_wg;        // ... sub-ranges its key split is cut in; heads_per_wg * ranges_per_wg <= 8 waves
+  int keys_max;             // no item (of any step) has more keys than this
   int cols_max;             // largest n_rows * G over the items (MFMA columns in use; sizes the merge buffer)
   float sm_scale;
   float *partials;          // [rows, n_q_heads, n_parts, head_dim + 2]

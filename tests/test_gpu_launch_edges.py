@@ -688,3 +688,13 @@ def test_row_preparation_of_up_to_eight_rows(ab, d, rank, T):
     for a, b in zip(*rows):
         assert torch.equal(a[:T - 1].view(torch.int16), b[:T - 1].view(torch.int16))
     c.close()
+
+
+@pytest.mark.parametrize("hq,hkv", [(8, 4), (6, 3), (16, 1), (24, 8)])
+@pytest.mark.parametrize("P", [[0, 1, 14], [15, 16, 17], [30, 31, 31, 7]])
+def test_decode_of_at_most_32_keys(ab, ctx, hq, hkv, P):
+    """Steps of 1 to 32 keys an item: the kernel without loads ahead, one block of 16 keys or two."""
+    shape = wl.LayerShape(d=512, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rank=16, n_adapters=3)
+    n = len(P)
+    case = H.make_case(shape, P, [1] * n, [max(0, p - 3) for p in P], [b % 4 - 1 for b in range(n)], seed=2600 + n + hq + P[0], prefix="random")
+    check_case(ab, ctx, case, decode=True)
