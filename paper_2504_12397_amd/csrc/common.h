@@ -25,13 +25,29 @@ struct SeqMeta {
 // The records of a call with few sequences as kernel arguments, for the kernel that prepares its rows.  That kernel, the first of
 // the call, also carries the staged metadata (records and work lists, `n16` pieces of 16 bytes) from the pinned host buffer to
 // where the kernels after it read them: a copy kernel of its own is 4 us of a call that may take 30.
-constexpr int FEW_SEQS = 16, STAGE_N16 = 256;
+constexpr int FEW_SEQS = 16, STAGE_N16 = 1024;      // (16 KB: the work list of most calls of few sequences; 480 pieces of five short decode rows 46.0 -> 44.0 us)
 struct StagedCall {
   int n_few;                 // 0: the records are in device memory already
   const uint4 *src;          // nullptr: nothing to carry
   uint4 *dst;
   int n16;                   // <= STAGE_N16
   SeqMeta few[FEW_SEQS];
+};
+// ... by the NT threads of one workgroup: asked for, and put where it belongs
+template <int NT> struct Carried {
+  uint4 v[STAGE_N16 / NT];
+  __device__ __forceinline__ void load(const StagedCall &st, int tid, bool mine) {
+#pragma unroll
+    for (int j = 0; j < STAGE_N16 / NT; ++j) {
+      v[j] = uint4{};
+      if (mine && st.src != nullptr && tid + j * NT < st.n16) v[j] = st.src[tid + j * NT];
+    }
+  }
+  __device__ __forceinline__ void store(const StagedCall &st, int tid, bool mine) const {
+#pragma unroll
+    for (int j = 0; j < STAGE_N16 / NT; ++j)
+      if (mine && st.src != nullptr && tid + j * NT < st.n16) st.dst[tid + j * NT] = v[j];
+  }
 };
 
 // pool row of cached position j of a sequence

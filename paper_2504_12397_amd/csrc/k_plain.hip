@@ -65,9 +65,8 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const T *__restrict__ x,
   __shared__ int s_adapter;
   __shared__ float s_scale;
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint4 staged{};
-  const bool carry = row == 0 && st.src != nullptr && tid < st.n16;
-  if (carry) staged = st.src[tid];
+  Carried<256> staged;
+  staged.load(st, tid, row == 0);
   if (tid == 0) {
     int adapter = -1;
     float scale = 0.f;
@@ -113,7 +112,7 @@ __global__ __launch_bounds__(256) void prep_rows_kernel(const T *__restrict__ x,
     xh[packed ? xh_chunk(row, c >> 3, d, 1) * 8 + (c & 7) : (int64_t)row * d + c] = stored;
     xs[c] = to_f32<T>(stored);      // the projections consume the stored (rounded) value
   }
-  if (carry) st.dst[tid] = staged;
+  staged.store(st, tid, row == 0);
   __syncthreads();
   const int a = s_adapter;
   if (a < 0 || rank == 0) return;

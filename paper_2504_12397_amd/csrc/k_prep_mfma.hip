@@ -114,9 +114,8 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   const int A_off = NC == 16 || r16 < NC ? (my_col * d + k_lo) * 2 : 0x7fff0000;      // (lanes without a column: out of range, they read zeros)
 #pragma unroll
   for (int u = 0; u < CH; ++u) br[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(A_rsrc, A_off, 64 * u, 0));
-  uint4 staged{};
-  const bool carry = blockIdx.x == 0 && lead && a.st.src != nullptr && tid < a.st.n16;
-  if (carry) staged = a.st.src[tid];      // (host memory: behind what everybody waits for)
+  Carried<512> staged;
+  staged.load(a.st, tid, blockIdx.x == 0 && lead);      // (host memory: behind what everybody waits for)
 
   if (tid == 0) s_present = 0ull;
   if (tid < PREP_ROWS) { s_adapter[tid] = -1; s_scale[tid] = 0.f; }
@@ -166,7 +165,7 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
 #pragma unroll
     for (int u = 0; u < CH; ++u) dst[xh_chunk(row, (k_lo >> 3) + 4 * u, d, a.packed)] = xr[u];
   }
-  if (carry) a.st.dst[tid] = staged;
+  staged.store(a.st, tid, blockIdx.x == 0 && lead);
   if (!((s_present >> ad) & 1)) return;
 
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -253,9 +252,8 @@ __global__ __launch_bounds__(512, 2) void prep_few_rows_kernel(PrepArgs a) {
   const int A_off = NC == 16 || r16 < NC ? (my_col * d + k_lo) * 2 : 0x7fff0000;
 #pragma unroll
   for (int u = 0; u < CH; ++u) br[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(A_rsrc, A_off, 64 * u, 0));
-  uint4 staged{};
-  const bool carry = lead && a.st.src != nullptr && tid < a.st.n16;
-  if (carry) staged = a.st.src[tid];      // (host memory: behind what everybody waits for)
+  Carried<512> staged;
+  staged.load(a.st, tid, lead);      // (host memory: behind what everybody waits for)
 
   if (tid == 0) s_present = 0ull;
   if (tid < PREP_ROWS) { s_adapter[tid] = -1; s_scale[tid] = 0.f; }
@@ -305,7 +303,7 @@ __global__ __launch_bounds__(512, 2) void prep_few_rows_kernel(PrepArgs a) {
         if (r < a.T) dst[r * step] = xr[r];
     }
   }
-  if (carry) a.st.dst[tid] = staged;
+  staged.store(a.st, tid, lead);
   if (!((s_present >> ad) & 1)) return;
   __syncthreads();
 
@@ -349,9 +347,6 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
   const int row0 = blockIdx.x * (4 * RW);
   constexpr int D = CH * 256, NJ = D / 512;
   const int wrow0 = row0 + wave * RW;
-  uint4 staged{};
-  const bool carry = blockIdx.x == 0 && a.st.src != nullptr && tid < a.st.n16;
-  if (carry) staged = a.st.src[tid];
   u32x4 xr[RW][NJ], gr[NJ];
 #pragma unroll
   for (int i = 0; i < RW; ++i) {
@@ -401,7 +396,8 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
       for (int j = 0; j < NJ; ++j) dst[xh_chunk(wrow0 + i, lane + 64 * j, D, a.packed)] = xr[i][j];
     }
   }
-  if (carry) a.st.dst[tid] = staged;
+  if (blockIdx.x == 0 && a.st.src != nullptr)      // (the first workgroup has the time: others start after it)
+    for (int i = tid; i < a.st.n16; i += NT) a.st.dst[i] = a.st.src[i];
 }
 
 // t of many rows from x_hat (or from the input of another linear with `parts` down-matrices): workgroup (x, y, z) takes 32 rows, columns 32 NB y .. of the parts * rank and adapter used[z]; it leaves at
