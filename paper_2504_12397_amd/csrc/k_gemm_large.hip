@@ -138,13 +138,13 @@ __global__ __launch_bounds__(512, 2) void gemm_large_kernel(GemmArgs g, int tile
 
   // ---- gated low-rank term (Eq.6), under the first tiles' way from memory ------------------------------------------
   if (g.tlow != nullptr && (EPI != GEMM_EPI_PARTIAL || k0 == 0)) {      // (split 0 carries it)
-    unsigned long long present = 0ull;
+    unsigned long long present = 0ull;      // of this wave's rows
+    const int row_end = min(M, row_base + 32 * NMI);
     if (g.present16 != nullptr) {
-      const int t_end = min((m0 + BM) / 16, (M + 15) / 16);
-      for (int t = m0 / 16; t < t_end; ++t) present |= g.present16[t];
+      for (int t = row_base / 16; t < (row_end + 15) / 16; ++t) present |= g.present16[t];
     } else {
-      for (int r = m0; r < min(M, m0 + BM); r += 64) {
-        const int a = r + lane < min(M, m0 + BM) ? g.row_adapter[r + lane] : -1;
+      for (int r = row_base; r < row_end; r += 64) {
+        const int a = r + lane < row_end ? g.row_adapter[r + lane] : -1;
         unsigned long long mine = a >= 0 ? 1ull << a : 0ull;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1)
