@@ -505,7 +505,7 @@ void project_rows(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L
   const int q_mode = q_half ? 1 : 2;
   const float q_scale = qf.scale;
   // The projection rotates and appends by itself: up to stream_rows rows in the kernel that streams the weights past all rows,
-  // beyond that, where a head is 128 columns, in the one whose tiles are large in both directions (both add in one order), or in the
+  // beyond that, where a head is 128 columns, in tiles of 128 or 256 rows (all add in one order), or in the
   // 128 x 128 block of four waves, which also adds segments.
   const bool fuse = mfma && ctx->opt_rope_fuse && ctx->opt_gemm_tile < 4 && ctx->opt_gemm_tile != 1;
   const bool lora_split = pl.any_adapter && w.lora_split;      // (in a kernel that takes partial sums)

@@ -513,8 +513,8 @@ GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, in
   return best;
 }
 
-// The same for 33 to 256 rows, partial sums; splits = 0: not here.  The segments by the weights' shape alone, so that they are the same for all of these
-// rows: as many, up to eight, as let two row tiles of the widest tile be one round, of 16 k-tiles or more, or fewer where that leaves the chip idle (a shorter one
+// The same for 33 to 256 rows, partial sums; splits = 0: not here.  The segments by the weights' shape alone, so that they are the same for all rows that
+// come here: as many, up to eight, as let two row tiles of the widest tile be one round, of 16 k-tiles or more, or fewer where that leaves the chip idle (a shorter one
 // waits for its first tiles, a narrow product's partial sums are few); then the narrowest tile that is one round, with an eighth to spare for those that
 // read the rows most often.
 // Where the 128 x 128 tiles of k_gemm_mfma.hip and their segments are nearly one round they stay: 128 rows of 4096 x 4096 and 4096 x 14336 were 17.3 and 34.8 us there

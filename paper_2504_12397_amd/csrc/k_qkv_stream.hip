@@ -1,6 +1,6 @@
 // QKV projection of a call with few rows (up to 32 CW per row tile): y = W x_hat + gated low-rank term (Eq.6), rotated and
 // appended (Eq.3) in the epilogue, ONE running sum over K per output -- the same sums in the same order as the projection of
-// many rows (k_gemm_large.hip), so a base row's keys and values are the same bits whatever call it came in, and an adapted
+// many rows (k_gemm_mid.hip, k_gemm_large.hip), so a base row's keys and values are the same bits whatever call it came in, and an adapted
 // row's where t is (the two kernels that compute t add its products over different slices of d).
 //
 // Any head size that is a multiple of 8, any reduction length that is a multiple of 128.

@@ -698,3 +698,12 @@ def test_decode_of_at_most_32_keys(ab, ctx, hq, hkv, P):
     n = len(P)
     case = H.make_case(shape, P, [1] * n, [max(0, p - 3) for p in P], [b % 4 - 1 for b in range(n)], seed=2600 + n + hq + P[0], prefix="random")
     check_case(ab, ctx, case, decode=True)
+
+
+@pytest.mark.parametrize("n,rank", [(129, 16), (200, 24)])
+def test_static_decode_of_more_rows_than_stream(ab, ctx, n, rank):
+    """The step that may allocate projects its rows in tiles, the static one streams the weights past them: the same bits."""
+    shape = wl.LayerShape(d=512, n_q_heads=8, n_kv_heads=2, head_dim=128, rank=rank, n_adapters=3)
+    P = [(7 * b) % 90 for b in range(n)]
+    case = H.make_case(shape, P, [1] * n, [max(0, p - 5) for p in P], [b % 4 - 1 for b in range(n)], seed=2700 + n, prefix="random")
+    _both(ab, ctx, case)
