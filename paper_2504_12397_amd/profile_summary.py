@@ -43,7 +43,7 @@ BENCH_WORKLOAD = {"r3pp": "r3p", "c5f": "c5"}         # summary key -> bench.py 
 KT_EXTRA = {"c5f": " --steps 3 --warmup 1"}      # of the kernel trace alone
 # kernel symbol -> the kernel family bench.py reports (only where one symbol is one family in that workload)
 FAMILY = [("attn_prefill_", "attn_prefill"), ("attn_decode_mfma_kernel", "attn_decode"),
-          ("prep_few_kernel", "prep_rows"), ("qkv_stream_kernel", "qkv_gemm"), ("rope_append_kernel", "rope_append"), ("attn_merge", "attn_merge")]
+          ("prep_few_", "prep_rows"), ("qkv_stream_kernel", "qkv_gemm"), ("rope_append_kernel", "rope_append"), ("attn_merge", "attn_merge")]
 
 
 def short(name: str) -> str:
