@@ -152,9 +152,8 @@ const char *alora_status_string(alora_status s);
  *   "gemm_splits"     0 (default): the QKV projection is a single running sum (weights that are not 16-byte
  *                     aligned, or a hidden size that is no multiple of 128: segments fixed by the
  *                     weight shape, as with a value); the reduction axis of a stack's
- *                     other linears is cut by the shape of the weight matrix (alike for all calls of up to 32
- *                     rows, of 33 to 128 and of 129 to 256; W_down of up to 32 rows is streamed, in an order of
- *                     its own) or by what fills the chip (more rows).
+ *                     other linears is cut by the shape of the weight matrix (up to 256 rows; W_down of up to
+ *                     32 rows is streamed, in an order of its own) or by what fills the chip (more rows).
  *                     n in 1..64: QKV, W_o and W_down in n equal segments (where the reduction length
  *                     allows; 1 = a single running sum); gate and up are a single running sum always (streamed
  *                     ones begin it where their tile begins).  See "Summation order" below.

@@ -745,7 +745,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     if (pn.splits == 0 || pn.splits > most) return 0;
     g.k_splits = pn.splits;
     const int epi = pn.splits > 1 ? GEMM_EPI_PARTIAL : GEMM_EPI_BF16;
-    if (!gemm_large_supported(g, epi)) return 0;
+    if (!gemm_large_supported(g, epi, T_rows <= 256 ? pn.rows : 256)) return 0;
     g.Cpart = w.Y;
     launch_gemm_large(g, epi, pn, s);
     return pn.splits;

@@ -482,59 +482,64 @@ static void launch_cfg(const GemmArgs &g, hipStream_t s) {
 // Rows of A that one launch takes: their byte offsets are 32 bits wide, tiles past the end included.
 int gemm_large_slice_rows(int lda) { return (int)(((int64_t)((1ull << 31) / ((uint64_t)lda * 2)) - 512) & ~(int64_t)255); }
 
-// (32-bit byte offsets into both operands; at least four k-tiles per split, in pairs; partial sums of one launch only: a second one
-// would put its rows where the first one's are)
-bool gemm_large_supported(const GemmArgs &g, int epi) {
+// (32-bit byte offsets into both operands; at least four k-tiles per split, in the tiles of 256 rows in pairs; partial sums of one launch only: a
+// second one would put its rows where the first one's are)
+bool gemm_large_supported(const GemmArgs &g, int epi, int tile_rows) {
   const uint64_t b_rows = epi == GEMM_EPI_SWIGLU ? g.N / 2 : g.N;
   const int slice = gemm_large_slice_rows(g.lda);
   if (!lds_aligned(g.A) || !lds_aligned(g.B) || (epi == GEMM_EPI_SWIGLU && !lds_aligned(g.B2)) || g.lda % 8 != 0 || g.ldb % 8 != 0) return false;
   if (slice < 256 || (epi == GEMM_EPI_PARTIAL && (g.lora_split || g.M > slice))) return false;
-  return g.K % (128 * g.k_splits) == 0 && g.K >= 256 * g.k_splits && g.N % 32 == 0 && b_rows * g.ldb * 2 < (1ull << 31);
+  return g.K % ((tile_rows == 128 ? 64 : 128) * g.k_splits) == 0 && g.K >= 256 * g.k_splits && g.N % 32 == 0 && b_rows * g.ldb * 2 < (1ull << 31);
 }
 
-// Tile and workgroups per output tile for a product of M rows: the cheapest by measured times (us).  `idle`, `busy`: a k-tile with most of the
-// chip idle and with all of it at work (the clock gives way: 1.6 GHz at 0.83 matrix utilisation); a tile's prologue and epilogue take about 6;
+// Measured times of the tiles, us: a k-tile with most of the chip idle and with all of it at work (the clock gives way: 1.6 GHz at 0.83 matrix
+// utilisation); a tile's prologue and epilogue take about 6.
+struct LargeTile { int rows, cols; double idle, busy; };
+static const LargeTile large_tiles[] = {
+    {128, 64, 0.24, 0.34}, {128, 96, 0.38, 0.48}, {128, 128, 0.44, 0.53}, {128, 192, 0.62, 0.70}, {128, 256, 0.74, 0.86}, {256, 256, 1.1, 1.48}};
+static double tile_us(const LargeTile &t, const GemmArgs &g, int sp, int n_cu) {
+  const int n = (g.M + t.rows - 1) / t.rows * ((g.N + t.cols - 1) / t.cols) * sp, rounds = (n + n_cu - 1) / n_cu;
+  const double load = n < n_cu ? (double)n / n_cu : 1.0;
+  return rounds * ((t.idle + (t.busy - t.idle) * load) * (g.K / 64 / sp) + 6.0);
+}
+
+// Tile and workgroups per output tile for a product of M rows: the cheapest by those times;
 // partial sums cost their bytes there and back and the launch that adds them.  Over 64 products of 139 to 4458 rows (N, K 6144, 4096; 4096, 4096;
 // 4096, 14336; gate/up 2 x 14336, 4096) what it picks is 0.6 % slower than the best of the tiles and splits on average, 10 % at most.
 GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits) {
-  static const struct { int rows, cols; double idle, busy; } tiles[] = {
-      {128, 64, 0.24, 0.34}, {128, 96, 0.38, 0.48}, {128, 128, 0.44, 0.53}, {128, 192, 0.62, 0.70}, {128, 256, 0.74, 0.86}, {256, 256, 1.1, 1.48}};
   GemmLargePlan best{256, 256, 1};
   double best_us = 1e30;
-  for (const auto &t : tiles)
+  for (const auto &t : large_tiles)
     for (int sp = 1; sp <= max_splits; sp *= 2) {
       if ((hint == 2 && (t.rows != 128 || t.cols != 256)) || (hint == 3 && t.rows != 256) || g.K % (128 * sp) != 0 || g.K < 512 * sp) continue;
-      const int n = (g.M + t.rows - 1) / t.rows * ((g.N + t.cols - 1) / t.cols) * sp, rounds = (n + n_cu - 1) / n_cu;
-      const double load = n < n_cu ? (double)n / n_cu : 1.0;
-      double us = rounds * ((t.idle + (t.busy - t.idle) * load) * (g.K / 64 / sp) + 6.0);
+      double us = tile_us(t, g, sp, n_cu);
       if (sp > 1) us += 5.0 + (double)sp * g.M * g.N * 8.0 / 4.5e6;
       if (us < best_us) { best_us = us; best = GemmLargePlan{t.rows, t.cols, sp}; }
     }
   return best;
 }
 
-// The same for 33 to 256 rows, partial sums; splits = 0: not here.  The segments by the weights' shape alone, so that they are the same for all rows that
-// come here: as many, up to eight, as let two row tiles of the widest tile be one round, of 16 k-tiles or more, or fewer where that leaves the chip idle (a shorter one
-// waits for its first tiles, a narrow product's partial sums are few); then the narrowest tile that is one round, with an eighth to spare for those that
-// read the rows most often.
-// Where the 128 x 128 tiles of k_gemm_mfma.hip and their segments are nearly one round they stay: 128 rows of 4096 x 4096 and 4096 x 14336 were 17.3 and 34.8 us there
-// and 14.3 and 33.7 here, each by itself, but in a layer (4 segments are 3 us of the gate/up product behind them, which reads none of this) 168 and 171.
-// Elsewhere, a product with its reduction, us, there and here, and a layer of that shape:
-//   N x K            40 rows       128           150           256           | layer  40            128           139           256
-//   4096 x 4096                                  22.6 / 18.3   26.8 / 23.7   |                                    195 / 190     229 / 220
-//   4096 x 14336                                 49.0 / 40.9   55.4 / 46.8   |
-//   5120 x 5120      22.0 / 16.3   28.5 / 22.6   32.7 / 25.4   41.0 / 29.6   |        323 / 308     657 / 642     692 / 671     997 / 975
-//   5120 x 13824     42.7 / 32.3   52.1 / 42.7   62.5 / 47.3   71.4 / 56.6   |
-//   2048 x 8192      15.4 / 11.3   17.5 / 14.3                               |        86 / 79       97 / 93
+// The same for 33 to 256 rows; splits = 0: not here.  The segments are those that calls of these rows are cut in whichever kernel takes them
+// (gemm_mfma_fixed_segments), so only the tile is chosen: over 220 products of 33 to 256 rows (d = 512 to 8192) 0.4 % above the best tile on average, 10 % at most.
+// Up to 64 rows and in two row tiles the tiles of 128 rows are the quicker ones, us between events, k_gemm_mfma.hip and here, with the reduction:
+//   N x K           33 rows        64             128            129            256
+//   4096 x 4096     19.0 / 17.3    19.7 / 18.5    22.3 / 22.6    25.9 / 25.5    30.9 / 29.6
+//   4096 x 14336    29.2 / 29.0    31.9 / 31.4    38.5 / 39.7    46.6 / 43.6    55.5 / 50.9
+//   4096 x 11008    35.1 / 26.5    36.6 / 27.4    40.8 / 33.5    38.7 / 33.6    42.9 / 42.4
+//   5120 x 13824    42.0 / 34.0    47.3 / 39.9    57.9 / 47.2    59.3 / 52.5    72.6 / 67.3
+//   2048 x 8192     18.6 / 14.3    19.9 / 15.6    22.1 / 18.8    21.7 / 20.7    24.6 / 24.9
+// One row tile of more than 64 rows stays with the 128 x 128 tiles of k_gemm_mfma.hip where they and their segments are nearly one round.
 GemmLargePlan gemm_few_plan(const GemmArgs &g, int n_cu) {
-  const int now = (g.M + 127) / 128 * ((g.N + 127) / 128) * gemm_mfma_fixed_segments(g.N, g.K, n_cu);
-  if (now <= n_cu && 3 * now > 2 * n_cu) return GemmLargePlan{0, 0, 0};
-  int sp = 8;
-  while (sp > 1 && (g.K % (128 * sp) != 0 || g.K < 512 * sp || 2 * ((g.N + 255) / 256) * sp > n_cu || (g.K / 64 / sp < 16 && g.N * sp > 8192))) sp /= 2;
-  static const int tiles[] = {64, 96, 128, 192};
-  for (int cols : tiles)
-    if ((g.M + 127) / 128 * ((g.N + cols - 1) / cols) * sp <= (cols < 128 ? n_cu * 7 / 8 : n_cu)) return GemmLargePlan{128, cols, sp};
-  return GemmLargePlan{128, 256, sp};
+  const int sp = gemm_mfma_fixed_segments(g.N, g.K, n_cu), there = (g.N + 127) / 128 * sp;
+  if (g.M > 64 && g.M <= 128 && there <= n_cu && 3 * there > 2 * n_cu) return GemmLargePlan{0, 0, 0};
+  GemmLargePlan best{0, 0, 0};
+  double best_us = 1e30;
+  for (const auto &t : large_tiles) {
+    if (t.rows != 128) continue;
+    const double us = tile_us(t, g, sp, n_cu);
+    if (us < best_us) { best_us = us; best = GemmLargePlan{t.rows, t.cols, sp}; }
+  }
+  return best;
 }
 
 void launch_gemm_large(GemmArgs g, int epi, const GemmLargePlan &plan, hipStream_t s) {

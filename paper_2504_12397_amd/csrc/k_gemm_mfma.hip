@@ -662,10 +662,10 @@ int gemm_mfma_pick_splits(int M, int N, int K, int n_cu) {
   return s;
 }
 
-// The number of equal segments the reduction axis of a linear with weights [N, K] is ALWAYS cut in: a function
-// of the weight shape (and the chip) alone, never of the number of rows, so that a row's result has one
-// summation order whatever else is in the call (Proposition 1 in its strong form: the rows before the
-// invocation point come out bit-identical from a long prefill, a short one and a decode step).  Enough
+// The number of equal segments the reduction axis of a linear with weights [N, K] is cut in -- W_o of up to 256 rows, W_down of 33 to
+// 256, and the QKV projection where it is not one running sum -- whichever kernel takes the call: a function
+// of the weight shape (and the chip) alone, never of the number of rows, so that a row's sum has one
+// order whatever else is in the call.  Enough
 // segments that a call with one row tile fills the chip when every segment gets a workgroup of its own.
 int gemm_mfma_fixed_segments(int N, int K, int n_cu) {
   const int tiles_n = (N + 127) / 128;

@@ -707,3 +707,45 @@ def test_static_decode_of_more_rows_than_stream(ab, ctx, n, rank):
     P = [(7 * b) % 90 for b in range(n)]
     case = H.make_case(shape, P, [1] * n, [max(0, p - 5) for p in P], [b % 4 - 1 for b in range(n)], seed=2700 + n, prefix="random")
     _both(ab, ctx, case)
+
+
+def _segments_of_a_linear(ab, which, T, d, heads, inter):
+    """In how many segments W_o or W_down sums its K products, read off the result: every product is 0 but for 2^32 at k = 0 and, in output column
+    j, -2^32 at k = j K / 8 and 64 behind that.  Summed in one segment they leave 64; where the second lies in another segment the 64 is
+    less than half a unit of its -2^32 and lost.  (All of it exact in bf16; x, its norm, the attention output and silu(gate) * up are ones.)"""
+    kv, h = heads // 4, 128
+    K = heads * h if which == "o" else inter
+    z = lambda *s: torch.zeros(s, dtype=torch.bfloat16, device="cuda")
+    t = {"W_qkv": z((heads + 2 * kv) * h, d), "W_o": z(d, heads * h), "W_gate": z(inter, d), "W_up": z(inter, d), "W_down": z(d, inter),
+         "rms_gain": torch.ones(d, dtype=torch.bfloat16, device="cuda"), "rms2_gain": torch.ones(d, dtype=torch.bfloat16, device="cuda")}
+    W = t["W_o"] if which == "o" else t["W_down"]
+    W[:, 0] = 2.0 ** 32
+    for n in range(d):
+        at = K * (n % 7 + 1) // 8
+        W[n, at], W[n, at + 32] = -(2.0 ** 32), 64.0
+    if which == "o":
+        t["W_qkv"][(heads + kv) * h:, 0] = 1.0      # values of one: so is every average of them
+    else:
+        t["W_gate"][:, 0], t["W_up"][:, 0] = 32.0, 1 / 32      # silu(32) = 32 in fp32
+    layer = ab.Layer(t, heads, kv, h, 1e-5, 10000.0, inter)
+    x = torch.ones((T, d), dtype=torch.bfloat16, device="cuda")
+    c = ab.Context(0)
+    out = ab.alora_stack_prefill(c, [layer], [ab.KVCache([T], kv, h, torch.bfloat16, "cuda")], x, [0, T], [T], [-1])
+    torch.cuda.synchronize()
+    c.close()
+    out = out.float().cpu()
+    kept = out[0, :7] == 65.0
+    assert torch.equal(out, torch.where(kept.repeat(d // 7 + 1)[:d], 65.0, 1.0).expand(T, d)), out
+    segments = {7: 1, 3: 2, 1: 4, 0: 8}[int(kept.sum())]
+    assert all(bool(kept[j - 1]) == (j * segments < 8) for j in range(1, 8)), kept
+    return segments
+
+
+# d x K: tiles that fill a round, short ones, a segment of an odd number of k-tiles
+@pytest.mark.parametrize("which,d,heads,inter,segments", [("o", 1536, 32, 128, 8), ("down", 1536, 4, 4096, 8), ("down", 1280, 4, 6912, 4),
+                                                          ("o", 1024, 8, 128, 2), ("down", 512, 4, 512, 1)])
+def test_segments_of_up_to_256_rows_are_those_of_the_weights(ab, which, d, heads, inter, segments):
+    """W_o of 1 to 256 rows and W_down of 33 to 256 (fewer are streamed) are cut by the shape of the weights alone: a row's sum does not
+    depend on how many rows the call has."""
+    for T in ([1, 8, 32] if which == "o" else []) + [33, 64, 65, 128, 129, 200, 256]:
+        assert _segments_of_a_linear(ab, which, T, d, heads, inter) == segments, T
