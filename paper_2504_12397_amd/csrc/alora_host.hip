@@ -577,7 +577,7 @@ void project_rows(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L
         launch_qkv_stream(g, ctx->n_cu, s);
         rope_fused = true;
       } else if (tiles && pl.T > stream_rows) {
-        launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, GEMM_EPI_ROPE, ctx->n_cu, 1), s);
+        launch_gemm_large(g, GEMM_EPI_ROPE, gemm_large_plan(ctx->opt_gemm_tile, g, ctx->n_cu, 1), s);
         rope_fused = true;
       } else if (fuse && q_half && !w.rope_by_row && ctx->opt_gemm_tile == 0 && pl.T > 256 && gemm_mfma_rope_supported(g, L.head_dim)) {
         launch_gemm_mfma(g, GEMM_EPI_ROPE, ctx->n_cu, s);
@@ -741,7 +741,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
     if (T_rows <= 32 || (T_rows <= 256 && g.tile_hint != 0) || ctx->opt_gemm_splits != 0 || g.tile_hint == 1 || g.tile_hint >= 4) return 0;
     int most = 8;
     while (most > 1 && ((size_t)most * T_rows * g.N > w.y_floats || T_rows > gemm_large_slice_rows(g.lda))) most /= 2;
-    const GemmLargePlan pn = T_rows <= 256 ? gemm_few_plan(g, ctx->n_cu) : gemm_large_plan(g.tile_hint, g, GEMM_EPI_BF16, ctx->n_cu, std::min(most, 4));
+    const GemmLargePlan pn = T_rows <= 256 ? gemm_few_plan(g, ctx->n_cu) : gemm_large_plan(g.tile_hint, g, ctx->n_cu, std::min(most, 4));
     if (pn.splits == 0 || pn.splits > most) return 0;
     g.k_splits = pn.splits;
     const int epi = pn.splits > 1 ? GEMM_EPI_PARTIAL : GEMM_EPI_BF16;

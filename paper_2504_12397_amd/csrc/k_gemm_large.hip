@@ -503,19 +503,35 @@ static double tile_us(const LargeTile &t, const GemmArgs &g, int sp, int n_cu) {
   return rounds * ((t.idle + (t.busy - t.idle) * load) * (g.K / 64 / sp) + 6.0);
 }
 
-// Tile and workgroups per output tile for a product of M rows: the cheapest by those times;
-// partial sums cost their bytes there and back and the launch that adds them.  Over 64 products of 139 to 4458 rows (N, K 6144, 4096; 4096, 4096;
-// 4096, 14336; gate/up 2 x 14336, 4096) what it picks is 0.6 % slower than the best of the tiles and splits on average, 10 % at most.
-GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits) {
-  GemmLargePlan best{256, 256, 1};
+// Segments of the reduction (workgroups per output tile) of a product of more than 256 rows.  They are part of what a call returns -- the order in which a row's
+// products are added -- so they do not follow the tiles' times when those change: they are the cheapest by the times of `tiles` here, those of when the
+// rule was made.  Partial sums cost their bytes there and back and the launch that adds them.
+// With the best tile for them W_o (its norm included) and W_down of 257 to 5000 rows are 2.7 % above the best of all cuts and tiles (159 of each, d = 512 to 5120); cut by the times above
+// 5.8 % (us, so and as here: 512 rows of 4096 x 4096 39.2 and 36.3, its reduction normalises too; 640 rows of 4096 x 14336 99.5 and 90.0; but 4200 rows 490 and 517).
+static int large_segments(int hint, const GemmArgs &g, int n_cu, int most) {
+  static const LargeTile tiles[] = {{128, 128, 0.55, 0.60}, {128, 256, 0.65, 1.0}, {256, 256, 1.1, 1.5}};
+  int best = 1;
   double best_us = 1e30;
-  for (const auto &t : large_tiles)
-    for (int sp = 1; sp <= max_splits; sp *= 2) {
+  for (const auto &t : tiles)
+    for (int sp = 1; sp <= most; sp *= 2) {
       if ((hint == 2 && (t.rows != 128 || t.cols != 256)) || (hint == 3 && t.rows != 256) || g.K % (128 * sp) != 0 || g.K < 512 * sp) continue;
       double us = tile_us(t, g, sp, n_cu);
       if (sp > 1) us += 5.0 + (double)sp * g.M * g.N * 8.0 / 4.5e6;
-      if (us < best_us) { best_us = us; best = GemmLargePlan{t.rows, t.cols, sp}; }
+      if (us < best_us) { best_us = us; best = sp; }
     }
+  return best;
+}
+
+// Tile and segments for a product of M rows: for those segments the cheapest tile by its times.
+GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int n_cu, int max_splits) {
+  const int sp = max_splits > 1 ? large_segments(hint, g, n_cu, max_splits) : 1;
+  GemmLargePlan best{256, 256, sp};
+  double best_us = 1e30;
+  for (const auto &t : large_tiles) {
+    if ((hint == 2 && (t.rows != 128 || t.cols != 256)) || (hint == 3 && t.rows != 256) || g.K % (128 * sp) != 0 || g.K < 512 * sp) continue;
+    const double us = tile_us(t, g, sp, n_cu);
+    if (us < best_us) { best_us = us; best = GemmLargePlan{t.rows, t.cols, sp}; }
+  }
   return best;
 }
 

@@ -708,7 +708,7 @@ void launch_gemm_mfma(GemmArgs g, int epi, int n_cu, hipStream_t s) {
     GemmArgs q = g;
     q.k_splits = 1;
     if (gemm_large_supported(q, epi)) {
-      launch_gemm_large(q, epi, gemm_large_plan(g.tile_hint, q, epi, n_cu, 1), s);
+      launch_gemm_large(q, epi, gemm_large_plan(g.tile_hint, q, n_cu, 1), s);
       return;
     }
   }

@@ -185,7 +185,7 @@ void launch_gemm_stream(const GemmArgs &g, int epi, int n_cu, hipStream_t s);
 // many rows: tiles of 256 x 256 or of 128 x 64, 96, 128, 192, 256, one running sum over K
 struct GemmLargePlan { int rows, cols, splits; };      // tile; workgroups per output tile (> 1: PARTIAL)
 GemmLargePlan gemm_few_plan(const GemmArgs &g, int n_cu);      // 33 to 256 rows, segments by the weights' shape alone; splits = 0: none of them
-GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int epi, int n_cu, int max_splits);      // hint 2 / 3: 128 x 256 / 256 x 256
+GemmLargePlan gemm_large_plan(int hint, const GemmArgs &g, int n_cu, int max_splits);      // hint 2 / 3: 128 x 256 / 256 x 256
 bool gemm_large_supported(const GemmArgs &g, int epi, int tile_rows = 256);
 int gemm_large_slice_rows(int lda);      // more rows than this take several launches (and no PARTIAL)
 void launch_gemm_large(GemmArgs g, int epi, const GemmLargePlan &plan, hipStream_t s);

@@ -749,3 +749,10 @@ def test_segments_of_up_to_256_rows_are_those_of_the_weights(ab, which, d, heads
     depend on how many rows the call has."""
     for T in ([1, 8, 32] if which == "o" else []) + [33, 64, 65, 128, 129, 200, 256]:
         assert _segments_of_a_linear(ab, which, T, d, heads, inter) == segments, T
+
+
+# rows -> segments of a W_down of 1024 x 4096 and of 512 x 2048
+@pytest.mark.parametrize("d,inter,segments", [(1024, 4096, {257: 4, 640: 4, 1024: 4, 1281: 2, 2049: 1}), (512, 2048, {257: 4, 1024: 4, 2049: 2, 5000: 1})])
+def test_segments_of_more_than_256_rows(ab, d, inter, segments):
+    """The cut of the reduction is part of the result: it stays when tiles get quicker."""
+    assert {T: _segments_of_a_linear(ab, "down", T, d, 4, inter) for T in segments} == segments
