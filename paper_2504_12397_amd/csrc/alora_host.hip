@@ -679,7 +679,7 @@ void layer_tail(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L, 
   const int r = L.rank, n_ad = L.n_adapters;
   // Few rows with default options: gate/up, W_down and the adapters' down-projections in the kernel that streams weights past all rows
   auto streamed = [&](const GemmArgs &g, int epi) {
-    return mfma && ctx->opt_gemm_splits == 0 && ctx->opt_gemm_tile == 0 && gemm_stream_supported(g, epi);
+    return mfma && ctx->opt_gemm_splits == 0 && ctx->opt_gemm_tile == 0 && gemm_stream_supported(g, epi, ctx->n_cu);
   };
   auto linear = [&](const void *W, const void *W2, int N, int K) {
     GemmArgs g{};
@@ -1890,7 +1890,7 @@ alora_status alora_lm_head(alora_ctx *ctx, alora_dtype dtype, int32_t d, int32_t
       g.k_splits = 1;
       g.k_segments = 1;
       g.Cpart = lg;
-      if (ctx->opt_gemm_splits == 0 && ctx->opt_gemm_tile == 0 && gemm_stream_supported(g, GEMM_EPI_PARTIAL))
+      if (ctx->opt_gemm_splits == 0 && ctx->opt_gemm_tile == 0 && gemm_stream_supported(g, GEMM_EPI_PARTIAL, ctx->n_cu))
         launch_gemm_stream(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);
       else
         launch_gemm_mfma(g, GEMM_EPI_PARTIAL, ctx->n_cu, s);

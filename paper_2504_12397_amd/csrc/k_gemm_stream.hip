@@ -293,10 +293,13 @@ static int best_tile(int n_cols, int n_cu, const int *choice, int n) {
   return best;
 }
 
-// gate/up up to 192 rows (200 rows: 65.5 us here, 64.6 in tiles of 128 x 256; 256 rows: 70.7 and 66.0; 139 rows: 58.5 and 60.5), W_down only up to 32 rows and where the reduction comes in whole kilobytes (see above)
-bool gemm_stream_supported(const GemmArgs &g, int epi) {
+// W_down only up to 32 rows and where the reduction comes in whole kilobytes (see above).  gate/up of more than 192 rows where its tiles are one round of more than the smallest:
+// us, here / in tiles of 128 rows, 193 rows and 256: 2 x 14336 x 4096 65.7 / 68.5 and 71.8 / 72.7, 2 x 13824 x 5120 78.2 / 96.2 and 84.9 / 101.2, 2 x 6912 x 2560 29.8 / 33.0 and 31.4 / 35.9,
+// 2 x 8192 x 2048 27.1 / 26.9 and 29.1 / 29.5; several rounds, 2 x 28672 x 8192: 242 / 236 and 265 / 234 (160 rows 212 / 214); the smallest tiles, 2 x 4096 x 1024: 13.3 / 11.8 and 14.2 / 13.1.
+bool gemm_stream_supported(const GemmArgs &g, int epi, int n_cu) {
   const int n_cols = epi == GEMM_EPI_SWIGLU ? g.N >> 1 : g.N;
-  return g.M >= 1 && g.M <= (epi == GEMM_EPI_BF16 ? 32 : epi == GEMM_EPI_SWIGLU ? 192 : STREAM_ROWS) && g.K % (epi == GEMM_EPI_BF16 ? 512 : 128) == 0 && n_cols % 4 == 0 &&
+  const int rows = epi == GEMM_EPI_BF16 ? 32 : epi == GEMM_EPI_SWIGLU && (n_cols <= 16 * n_cu || n_cols > 64 * n_cu) ? 192 : STREAM_ROWS;
+  return g.M >= 1 && g.M <= rows && g.K % (epi == GEMM_EPI_BF16 ? 512 : 128) == 0 && n_cols % 4 == 0 &&
          g.rank % 8 == 0 && lds_aligned(g.B) && (epi != GEMM_EPI_SWIGLU || lds_aligned(g.B2)) && g.ldb == g.K &&
          (uint64_t)n_cols * g.K * 2 < (1ull << 31);
 }

@@ -179,7 +179,7 @@ bool qkv_stream_supported(const void *W, int N, int K, int head_dim);
 void launch_qkv_stream(const GemmArgs &g, int n_cu, hipStream_t s);
 // few rows: SWIGLU, BF16 (unsplit) or PARTIAL, weights streamed past all rows
 constexpr int STREAM_ROWS = 256;
-bool gemm_stream_supported(const GemmArgs &g, int epi);
+bool gemm_stream_supported(const GemmArgs &g, int epi, int n_cu);
 int gemm_stream_segments(const GemmArgs &g, int n_cu, int most);      // PARTIAL: how many
 void launch_gemm_stream(const GemmArgs &g, int epi, int n_cu, hipStream_t s);
 // many rows: tiles of 256 x 256 or of 128 x 64, 96, 128, 192, 256, one running sum over K

@@ -491,7 +491,10 @@ def test_prefill_attention_around_tiles_of_keys(ab, ctx, G, splits):
 # rows around the row blocks; adapters on every linear with ranks that are no multiple of 16
 @pytest.mark.parametrize("T,inter,d,rest,rank", [(1, 1280, 512, False, 16), (32, 8192, 512, True, 8), (33, 12224, 256, False, 16), (31, 14336, 512, True, 24),
                                                  (64, 14336, 256, False, 8), (65, 16320, 256, True, 40), (128, 14336, 256, False, 16), (129, 8192, 256, True, 8),
-                                                 (200, 14336, 256, True, 16), (256, 20032, 256, False, 16), (7, 20032, 640, True, 16), (3, 7168, 1152, True, 16)])
+                                                 (200, 14336, 256, True, 16), (256, 20032, 256, False, 16), (7, 20032, 640, True, 16), (3, 7168, 1152, True, 16),
+                                                 # more than 192 rows: streamed in one round of tiles wider than the smallest, else in tiles of 128 rows
+                                                 (192, 4096, 256, False, 16), (193, 4096, 256, True, 8), (193, 4160, 256, True, 24), (256, 16384, 256, False, 8),
+                                                 (192, 16448, 256, True, 16), (193, 16448, 256, False, 16)])
 def test_few_rows_through_the_streaming_linears(ab, ctx, T, inter, d, rest, rank):
     shape = wl.LayerShape(d=d, n_q_heads=4, n_kv_heads=1, head_dim=128, rank=rank, n_adapters=3, intermediate=inter, adapt_rest=rest)
     _one_stack_layer(ab, ctx, shape, T, 1700 + T + inter)
