@@ -531,9 +531,12 @@ void project_rows(alora_ctx *ctx, const alora_layer_desc *ly, const LayerDims &L
     g.head_dim = L.head_dim; g.q_f32 = q_half ? 0 : 1;
     g.Qout = (bf16 *)w.Q; g.cacheK = (bf16 *)cache->k; g.cacheV = (bf16 *)cache->v;
   }
-  // (their tiles are the quicker way from 129 rows on: 139 rows 30.8 -> 23.5 us, 256 34.2 -> 30.1; 128 rows stream in 22.7 and take 28.9 in tiles)
+  // The tiles are the quicker way from 129 rows on, unless even those of 64 columns leave more than three fifths of the chip idle: preparation and projection, us, streamed / in
+  // tiles, 129 rows and 256: N x K 6144 x 4096 50.9 / 45.6 and 64.8 / 60.0, 7680 x 5120 102.6 / 93.1 and 105.9 / 103.0, 3840 x 2560 56.1 / 54.7 and 59.5 / 60.5,
+  // 3072 x 2048 29.1 / 28.9 and 37.1 / 37.5 (224 rows 30.3 / 32.0), 1536 x 1024 21.0 / 22.0 and 24.0 / 25.3.  (128 rows of 6144 x 4096: 22.7 / 28.9, the projection alone.)
   const bool tiles = fuse && q_half && !w.rope_by_row && w.k_segments == 1 && gemm_mfma_rope_supported(g, L.head_dim) && gemm_large_supported(g, GEMM_EPI_ROPE);
-  const int stream_rows = tiles ? std::min(128, qkv_stream_rows(L.n_qkv, ctx->n_cu)) : qkv_stream_rows(L.n_qkv, ctx->n_cu);
+  const bool tiles_fill = 5 * ((L.n_qkv + 63) / 64) >= ctx->n_cu;
+  const int stream_rows = tiles && tiles_fill ? std::min(128, qkv_stream_rows(L.n_qkv, ctx->n_cu)) : qkv_stream_rows(L.n_qkv, ctx->n_cu);
   const bool stream = fuse && !lora_split && w.k_segments == 1 && ctx->opt_gemm_tile == 0 && pl.T <= stream_rows && qkv_stream_supported(ly->W_qkv, L.n_qkv, L.d, L.head_dim);
   auto stage_of = [&](bool first) {
     StagedCall st{};

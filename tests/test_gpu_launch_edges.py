@@ -37,7 +37,9 @@ def _split(T, n):
 
 # heads / kv heads give 6, 20, 32 columns of 256: tiles of 8, 12 and 16 rotation pairs, the 12-pair ones crossing heads and kinds
 @pytest.mark.parametrize("hq,hkv,rank,T", [(8, 2, 8, 1), (8, 2, 24, 33), (32, 4, 64, 32), (32, 4, 8, 65), (32, 16, 16, 129),
-                                           (32, 16, 40, 256), (32, 4, 16, 255)])
+                                           (32, 16, 40, 256), (32, 4, 16, 255),
+                                           # more than 128 rows are streamed where tiles would leave most of the chip idle (up to 3200 columns)
+                                           (16, 4, 16, 129), (8, 2, 24, 255), (16, 8, 8, 256)])
 def test_few_rows_through_the_streaming_projection(ab, ctx, hq, hkv, rank, T):
     shape = wl.LayerShape(d=512, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rank=rank, n_adapters=4)
     n = min(T, 5)
