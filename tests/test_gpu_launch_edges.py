@@ -95,10 +95,23 @@ def test_rows_through_the_tiles_of_128_rows(ab, ctx, T, inter, rest, rank):
     _one_stack_layer(ab, ctx, dataclasses.replace(SMALL_BF16, intermediate=inter, rank=rank, adapt_rest=rest), T, 2200 + T + inter)
 
 
-# columns of a tile, 64 to 256 (N = 3072, 4096, 6144 columns; the last column tiles are parts of one)
-@pytest.mark.parametrize("hq,hkv,T,rank", [(16, 4, 129, 16), (10, 1, 256, 8), (16, 4, 700, 24), (24, 4, 1000, 32), (32, 8, 1000, 64), (32, 8, 1200, 16)])
+# W_o and W_down (d x heads * 128 and d x inter) in tiles of 96, 128, 192, 256 columns, as fp32 partial sums of 8 or 4 segments and whole with
+# the residual; 96 of 1280 and 1024 columns and 192 of 2560 and 1024 end inside a wave's part of the last tile.  The last: gate/up in 192 columns, three tiles a workgroup.
+@pytest.mark.parametrize("T,d,heads,kv,inter,rest,rank", [(129, 1280, 32, 8, 4096, True, 16), (129, 2048, 32, 8, 4096, False, 8), (139, 2560, 32, 8, 4096, True, 24),
+                                                          (150, 4096, 32, 8, 4096, True, 16),
+                                                          (513, 1024, 16, 4, 2048, True, 16), (700, 1024, 16, 4, 2048, False, 8), (1100, 1024, 32, 8, 4096, True, 16), (1300, 1024, 4, 1, 5120, True, 24),
+                                                          (1600, 1280, 4, 1, 512, True, 16), (2100, 1536, 4, 1, 512, False, 8), (1600, 2560, 4, 1, 512, True, 16), (2100, 3072, 4, 1, 512, True, 8),
+                                                          (400, 512, 4, 1, 16448, True, 16)])
+def test_linears_in_tiles_of_every_width(ab, ctx, T, d, heads, kv, inter, rest, rank):
+    shape = wl.LayerShape(d=d, n_q_heads=heads, n_kv_heads=kv, head_dim=128, rank=rank, n_adapters=3, intermediate=inter, adapt_rest=rest)
+    _one_stack_layer(ab, ctx, shape, T, 2800 + T + d)
+
+
+# columns of a tile: 64, 64, 96, 96 (the last tile is part of one), 128, 192 (part of one), 256; 192 and three tiles a workgroup; 96, 128, 192 of 6144 columns
+@pytest.mark.parametrize("hq,hkv,T,rank", [(16, 8, 129, 16), (8, 2, 257, 8), (32, 8, 257, 64), (64, 8, 129, 24), (32, 16, 257, 8), (64, 8, 400, 16), (64, 8, 513, 32), (32, 32, 1500, 16),
+                                           (16, 4, 700, 24), (32, 8, 1000, 64), (32, 8, 1200, 16)])
 def test_projection_in_tiles_of_every_width_gives_the_same_bits(ab, hq, hkv, T, rank):
-    """Queries, keys and values of one running sum: the same from 256 x 256 tiles (gemm_tile 3) as from the tiles of 128 rows."""
+    """Queries, keys and values of one running sum: the same from 256 x 256 tiles (gemm_tile 3) as from the tiles of 128 rows.  Both rotate and append by themselves."""
     shape = wl.LayerShape(d=512, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rank=rank, n_adapters=3)
     S = [T - 40, 17, 23]
     case = H.make_case(shape, [5, 33, 0], S, [5 + S[0] // 2, 33, 4], [1, 2, 0], seed=2300 + T + hq, prefix="random")
@@ -107,9 +120,11 @@ def test_projection_in_tiles_of_every_width_gives_the_same_bits(ab, hq, hkv, T, 
     for tile in (0, 3):
         c = ab.Context(0)
         c.set_option("gemm_tile", tile)
+        c.set_option("profile", 1)
         cache = H.gpu_cache(case)
         out = ab.alora_prefill(c, layer, cache, x, case.cu, case.k, case.adapter)
         torch.cuda.synchronize()
+        assert "rope_append" not in c.profile_read()      # (what takes over where the tiles cannot)
         got.append([t.clone() for t in (out, cache.k, cache.v)])
         c.close()
     assert all(torch.equal(p, q) for p, q in zip(*got))
@@ -708,7 +723,7 @@ def test_decode_of_at_most_32_keys(ab, ctx, hq, hkv, P):
 @pytest.mark.parametrize("n,rank", [(129, 16), (200, 24)])
 def test_static_decode_of_more_rows_than_stream(ab, ctx, n, rank):
     """The step that may allocate projects its rows in tiles, the static one streams the weights past them: the same bits."""
-    shape = wl.LayerShape(d=512, n_q_heads=8, n_kv_heads=2, head_dim=128, rank=rank, n_adapters=3)
+    shape = wl.LayerShape(d=512, n_q_heads=16, n_kv_heads=8, head_dim=128, rank=rank, n_adapters=3)      # (4096 columns: fewer than 3201 are always streamed)
     P = [(7 * b) % 90 for b in range(n)]
     case = H.make_case(shape, P, [1] * n, [max(0, p - 5) for p in P], [b % 4 - 1 for b in range(n)], seed=2700 + n, prefix="random")
     _both(ab, ctx, case)
