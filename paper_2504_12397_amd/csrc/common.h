@@ -25,7 +25,9 @@ struct SeqMeta {
 // The records of a call with few sequences as kernel arguments, for the kernel that prepares its rows.  That kernel, the first of
 // the call, also carries the staged metadata (records and work lists, `n16` pieces of 16 bytes) from the pinned host buffer to
 // where the kernels after it read them: a copy kernel of its own is 4 us of a call that may take 30.
-constexpr int FEW_SEQS = 16, STAGE_N16 = 1024;      // (16 KB: the work list of most calls of few sequences; 480 pieces of five short decode rows 46.0 -> 44.0 us)
+// 16 KB: the work list of most calls of few sequences.  Calls of 1 to 16 sequences, 142 to 816 pieces, by a copy kernel -> so: 1.5 to 4 us less, except 800 pieces of 1600 to 2000 rows (equal);
+// 480 pieces of five short decode rows 46.0 -> 44.0 us, 816 of 16 sequences of 4 rows 56.7 -> 55.2.
+constexpr int FEW_SEQS = 16, STAGE_N16 = 1024;
 struct StagedCall {
   int n_few;                 // 0: the records are in device memory already
   const uint4 *src;          // nullptr: nothing to carry

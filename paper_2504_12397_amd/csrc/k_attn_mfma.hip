@@ -614,15 +614,10 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
   // The wave's 32 query rows of 256 bytes come in whole, four a request, and through LDS (in the tile buffers that are filled last) into operand order: chunk
   // c of row r at c ^ (r & 15).  Asked for in operand order they are 32 bytes of 32 rows a request, and 64 such requests 2 us of a compute unit.
   u32x4 qf[8];
-  {
-    u32x4 raw[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int r = 4 * j + (lane >> 4);
-      raw[j] = *reinterpret_cast<const u32x4 *>(a.Q + rh_of(r) * H + ((lane & 15) ^ (r & 15)) * 8);
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) qf[j] = raw[j];
+  for (int j = 0; j < 8; ++j) {
+    const int r = 4 * j + (lane >> 4);
+    qf[j] = *reinterpret_cast<const u32x4 *>(a.Q + rh_of(r) * H + ((lane & 15) ^ (r & 15)) * 8);
   }
   f32x16 o[4], negm;
 #pragma unroll

@@ -1,17 +1,17 @@
 // bf16 MFMA GEMM of 128-row tiles:  C[M,N] = A[M,K] B[N,K]^T for calls whose 256 x 256 tiles (k_gemm_large.hip) would leave much of
-// the chip idle.  Tiles of 128 x 96, 128, 192 or 256, one running sum over K: every accumulator starts from the gated low-rank term and adds its
-// k-steps of 16 in ascending order, as the other projection kernels do.
+// the chip idle, or all but a little of a further round.  Tiles of 128 x 64, 96, 128, 192 or 256, one running sum over K (or over a segment of it): every accumulator starts
+// from the gated low-rank term and adds its k-steps of 16 in ascending order, as the other projection kernels do.  A workgroup walks its tiles one after the other.
 //
-// What bounds it: LDS.  Four waves multiply, one per SIMD, a wave 64 x 64, 96 or 128 (32 x 96 in the tile of 96): 96 KB of fragments for a
+// What bounds it: LDS.  Four waves multiply, one per SIMD, a wave 64 x 64, 96 or 128 (32 x 64 and 32 x 96 in the tiles of 64 and 96): 96 KB of fragments for a
 // k-tile (64 wide) of 128 x 256 where eight waves of 64 x 64 read 128, at about 140 bytes per clock and compute unit.  A wave is alone on its SIMD, so
 // the reads of a k-step run beside the matrix instructions of the one before, over the barrier too: a k-tile's last fragments are in registers
 // when its buffer is handed back, and the next one's first are read under the last products.  Four more waves only move tiles from memory to LDS
-// (buffer_load ... lds), two to four k-tiles ahead.  Apart, because a wave's loads complete in order: the low-rank term's loads would wait for
+// (buffer_load ... lds), two (256 columns) to five (64) k-tiles ahead.  Apart, because a wave's loads complete in order: the low-rank term's loads would wait for
 // the tiles.  (Lines of k-tiles further ahead asked for by a wave of their own, for the L2: up to 1.5 x slower, its scattered requests cost more
 // than the misses.)
 // Against the tiles of eight waves of 128 x 128 and 128 x 256 that it replaces (kernel trace, us): QKV with rotation and append, 1024 rows of eight rank-64 adapters
 // 78 -> 62 (256 tiles of 192 columns where 192 of 256 left a quarter of the chip idle), 1024 rows of four rank-32 adapters in turn 90 -> 71, 512 rows 54 -> 43;
-// W_o of 1024 rows 43 both.  Against the kernels of few rows: 139 rows of QKV 33 -> 25, of W_down 44 -> 39, of W_o 20 -> 17 and half the partial sums.
+// W_o of 1024 rows 43 both.  Against the kernels of few rows: 139 rows of QKV 33 -> 25; W_o and W_down in as many segments: see gemm_few_plan.
 //
 // LDS: rows of 128 bytes (8 chunks of 16), chunk c of row i at position c ^ ((i >> 1) & 7): the rows that a fragment read serves together lie in
 // different banks.

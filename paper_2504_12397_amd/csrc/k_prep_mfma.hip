@@ -195,11 +195,6 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   }
 }
 
-// The same for at most RT rows (RT = 2, 8): a thread has one chunk of each of them, not a lane sixteen of one row, of which lanes without a row repeat the last
-// one.  With one row that was 128 elements per lane to square, scale and convert, sixteen times over; now it is 8.  x_hat goes through LDS, chunk c of row r
-// at c ^ r, to become the matrix operand.  Sums as above, bit for bit.
-// The kernel, us, sixteen rows a tile -> so: one row of a rank-64 adapter 9.6 -> 6.6, four rows of four 9.8 -> 7.4, five of five 9.8 -> 8.6, eight of eight 10.3 -> 9.2; five
-// rows of four rank-8 adapters 9.7 -> 8.8.
 // Tree over u, neighbours first, for N rows at once: while there are several a lane keeps half of them and gives the other half for its partner's.
 template <int N, int O, int GL> __device__ __forceinline__ float tree_of_rows(const float (&v)[N], int lane, int &row) {
   if constexpr (O >= GL) {
@@ -216,6 +211,11 @@ template <int N, int O, int GL> __device__ __forceinline__ float tree_of_rows(co
     return tree_of_rows<1, O * 2, GL>(k, lane, row);
   }
 }
+// The same for at most RT rows (RT = 2, 4, 8): a thread has one chunk of each of them, not a lane sixteen of one row, of which lanes without a row repeat the last
+// one.  With one row that was 128 elements per lane to square, scale and convert, sixteen times over; now it is 8.  x_hat goes through LDS, chunk c of row r
+// at c ^ r, to become the matrix operand.  Sums as above, bit for bit.
+// The kernel, us, sixteen rows a tile -> so: one row of a rank-64 adapter 9.6 -> 6.6, four rows of four 9.8 -> 7.4, five of five 9.8 -> 8.6, eight of eight 10.3 -> 9.2; five
+// rows of four rank-8 adapters 9.7 -> 8.8.
 template <int CH, int NC, int RT>
 __global__ __launch_bounds__(512, 2) void prep_few_rows_kernel(PrepArgs a) {
   constexpr int d = CH * 256, NCHUNK = d / 8, GL = 4 * CH;      // GL: chunks (neighbouring lanes) of one w
@@ -494,7 +494,7 @@ bool prep_rows_mfma_supported(int d, int rank) {
 
 template <int CH>
 static void launch_norm(const PrepArgs &a, hipStream_t s) {
-  // (us, one row a wave / four: 2500 rows 17.2 / 21.6, 4458 17.3 / 21.6, 6000 25.8 / 23.7, 8131 33 / 30)
+  // (us, one row a wave / four: d = 4096: 2500 rows 17.2 / 21.6, 4458 17.3 / 21.6, 6000 25.8 / 23.7, 8131 33 / 30; 2049 and 5000 rows of d = 2048 7.7 / 9.9 and 10.3 / 13.3, of 1024 6.6 / 7.3 and 7.5 / 9.2, of 512 alike)
   if (a.T <= 5000) hipLaunchKernelGGL((norm_rows_kernel<CH, 1>), dim3((a.T + 3) / 4), dim3(256), 0, s, a);
   else hipLaunchKernelGGL((norm_rows_kernel<CH, 4>), dim3((a.T + 15) / 16), dim3(256), 0, s, a);
 }
