@@ -344,7 +344,16 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
   __shared__ unsigned long long s_present;
   constexpr int NT = 256;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row0 = blockIdx.x * (4 * RW);
+  // Staged metadata comes from host memory: a workgroup of its own, the first, carries it beside the others' rows (one row 6.7 -> 5.4 us against the rows' first workgroup doing
+  // so behind them, 8 KB for one row 6.5 -> 4.1).
+  const int carries = a.st.src != nullptr ? 1 : 0;
+  if (carries && blockIdx.x == 0) {
+    Carried<NT> staged;
+    staged.load(a.st, tid, true);
+    staged.store(a.st, tid, true);
+    return;
+  }
+  const int row0 = ((int)blockIdx.x - carries) * (4 * RW);
   constexpr int D = CH * 256, NJ = D / 512;
   const int wrow0 = row0 + wave * RW;
   u32x4 xr[RW][NJ], gr[NJ];
@@ -396,8 +405,6 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
       for (int j = 0; j < NJ; ++j) dst[xh_chunk(wrow0 + i, lane + 64 * j, D, a.packed)] = xr[i][j];
     }
   }
-  if (blockIdx.x == 0 && a.st.src != nullptr)      // (the first workgroup has the time: others start after it)
-    for (int i = tid; i < a.st.n16; i += NT) a.st.dst[i] = a.st.src[i];
 }
 
 // t of many rows from x_hat (or from the input of another linear with `parts` down-matrices): workgroup (x, y, z) takes 32 rows, columns 32 NB y .. of the parts * rank and adapter used[z]; it leaves at
@@ -495,8 +502,9 @@ bool prep_rows_mfma_supported(int d, int rank) {
 template <int CH>
 static void launch_norm(const PrepArgs &a, hipStream_t s) {
   // (us, one row a wave / four: d = 4096: 2500 rows 17.2 / 21.6, 4458 17.3 / 21.6, 6000 25.8 / 23.7, 8131 33 / 30; 2049 and 5000 rows of d = 2048 7.7 / 9.9 and 10.3 / 13.3, of 1024 6.6 / 7.3 and 7.5 / 9.2, of 512 alike)
-  if (a.T <= 5000) hipLaunchKernelGGL((norm_rows_kernel<CH, 1>), dim3((a.T + 3) / 4), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((norm_rows_kernel<CH, 4>), dim3((a.T + 15) / 16), dim3(256), 0, s, a);
+  const int carries = a.st.src != nullptr ? 1 : 0;
+  if (a.T <= 5000) hipLaunchKernelGGL((norm_rows_kernel<CH, 1>), dim3((a.T + 3) / 4 + carries), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((norm_rows_kernel<CH, 4>), dim3((a.T + 15) / 16 + carries), dim3(256), 0, s, a);
 }
 
 template <int NB>
