@@ -830,6 +830,12 @@ __global__ __launch_bounds__(512) void attn_prefill_pipe_kernel(AttnArgs a, int 
   }
   const float m_ref = -negm[0];
   if ((wave * 32 >> g_log2) >= ntok) return;      // (no row)
+  // The rows of one wave: as they lie in its registers, without the way through LDS, which takes longer than one wave's requests.  One row on 40 keys, us, before results went
+  // through LDS / all of them / so: 32 groups of one head 6.6 / 7.4 / 5.9, 4 of two 6.4 / 6.8 / 6.0, 8 of four 7.8 / 7.4 / 6.7; 64 x 16 rows of 32 groups of one 43.5 / 51.1 / 46.2.
+  if ((ntok << g_log2) <= 32) {
+    write_result(a, wk.part, my_row, tok < ntok, head0 + ((wave * 32 + l32) & in_group), kh, m_ref, l_run, o);
+    return;
+  }
   int64_t io_rh[2];
 #pragma unroll
   for (int half = 0; half < 2; ++half) {

@@ -344,8 +344,8 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(PrepArgs a) {
   __shared__ unsigned long long s_present;
   constexpr int NT = 256;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // Staged metadata comes from host memory: a workgroup of its own, the first, carries it beside the others' rows (one row 6.7 -> 5.4 us against the rows' first workgroup doing
-  // so behind them, 8 KB for one row 6.5 -> 4.1).
+  // Staged metadata comes from host memory: a workgroup of its own, the first, carries it beside the others' rows (one row of 4096 6.7 -> 4.7 us against the rows' first workgroup doing
+  // so behind them; of 512 4.2 -> 3.3, with 9 KB 7.8 -> 3.4).
   const int carries = a.st.src != nullptr ? 1 : 0;
   if (carries && blockIdx.x == 0) {
     Carried<NT> staged;

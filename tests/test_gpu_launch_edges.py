@@ -776,3 +776,25 @@ def test_segments_of_up_to_256_rows_are_those_of_the_weights(ab, which, d, heads
 def test_segments_of_more_than_256_rows(ab, d, inter, segments):
     """The cut of the reduction is part of the result: it stays when tiles get quicker."""
     assert {T: _segments_of_a_linear(ab, "down", T, d, 4, inter) for T in segments} == segments
+
+
+# packed rows of an item: one wave's 32 or less (results straight from registers), 33 and more (through LDS), a last wave with one row
+@pytest.mark.parametrize("hq,hkv,S", [(4, 4, [1, 32, 33]), (6, 3, [1, 16, 17]), (8, 2, [3, 8, 9]), (16, 2, [1, 4, 5]), (3, 3, [31, 64, 65])])
+@pytest.mark.parametrize("splits,compact", [(1, 1), (3, 1), (3, 0)])
+def test_prefill_items_of_one_wave_and_of_more(ab, hq, hkv, S, splits, compact):
+    shape = wl.LayerShape(d=512, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, rank=16, n_adapters=2)
+    case = H.make_case(shape, [700, 0, 200], S, [700, S[1] // 2, 200], [1, 0, -1], seed=2900 + hq + S[0], prefix="random")
+    c = ab.Context(0)
+    c.set_option("kv_splits", splits)
+    c.set_option("attn_partials16", compact)
+    check_case(ab, c, case)
+    c.close()
+
+
+@pytest.mark.parametrize("n,cached", [(1, 20), (3, 2000), (16, 900), (17, 40)])
+def test_metadata_carried_beside_base_rows(ab, ctx, n, cached):
+    """Calls without adapters, whose first workgroup carries the staged metadata (few sequences) or does not (17)."""
+    shape = wl.LayerShape(d=512, n_q_heads=8, n_kv_heads=2, head_dim=128, rank=16, n_adapters=2)
+    for S in (1, 5):
+        case = H.make_case(shape, [cached + 3 * b for b in range(n)], [S] * n, [0] * n, [-1] * n, seed=2950 + n + S, prefix="random")
+        check_case(ab, ctx, case)
