@@ -60,8 +60,9 @@ __device__ __forceinline__ void fill_row_meta(const PrepArgs &a, const SeqMeta &
   if (adapter >= 0) atomicOr(s_present, 1ull << adapter);
 }
 
-// Few rows with adapters (up to PREP_FEW workgroups): workgroup (x, y, z) takes row tile x (16 rows), columns NC y .. of the 3 * rank
-// columns of t and adapter used[z]; the first of a tile also writes x_hat and the row metadata.  Eight waves split the hidden dimension; a lane
+// Few rows with adapters (up to PREP_FEW workgroups): workgroup (x, y) takes row tile x % tiles (16 rows), columns NC (x / tiles) .. of the 3 * rank
+// columns of t and adapter used[y]; the first of a tile also writes x_hat and the row metadata.  Where there is staged metadata, x begins at 1 and workgroup (0, 0) carries it: in the first
+// tile's workgroup its registers left one workgroup a compute unit of d = 2048 instead of two (300 rows of four rank-32 adapters 17 us, before that and so 14.5 and 15; 16 rows of eight rank-64 adapters of d = 4096 13.7, so 11.6).  Eight waves split the hidden dimension; a lane
 // owns 8 consecutive elements of one row at a time, which is both the 16-byte global access and the operand layout of
 // v_mfma_f32_16x16x32_bf16 (lane l: row l % 16, k = 8 * (l / 16) ..).  CH = d / 256: chunks of its row a lane holds.
 // The kernel is memory round trips and little else, so everything is requested at once: x, the gain, the sequences' records (in the kernel arguments when they are few)
@@ -84,15 +85,31 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kg = lane >> 4;
-  const int row0 = blockIdx.x * PREP_ROWS;
+  const int carries = a.st.src != nullptr ? 1 : 0;
+  if (carries && blockIdx.x == 0) {      // (one of each adapter's)
+    if (blockIdx.y == 0) {
+      Carried<512> staged;
+      staged.load(a.st, tid, true);
+      staged.store(a.st, tid, true);
+    }
+    return;
+  }
+  const int tiles = (a.T + PREP_ROWS - 1) / PREP_ROWS;
+  int tile = 0, part = (int)blockIdx.x - carries;      // row tile, columns
+  if (tiles > 1) {
+    const int at = part;
+    part = at / tiles;
+    tile = at - part * tiles;
+  }
+  const int row0 = tile * PREP_ROWS;
   constexpr int d = CH * 256;
-  const int rank = a.rank, col0 = blockIdx.y * NC;
-  const int ad = (reinterpret_cast<const uint32_t *>(a.used)[blockIdx.z >> 2] >> (8 * (blockIdx.z & 3))) & 255;      // (a scalar load)
+  const int rank = a.rank, col0 = part * NC;
+  const int ad = (reinterpret_cast<const uint32_t *>(a.used)[blockIdx.y >> 2] >> (8 * (blockIdx.y & 3))) & 255;      // (a scalar load)
   // all arguments in one round trip, not where they are used
   asm volatile("" ::"s"(a.rm.seq), "s"(a.rm.pos), "s"(a.rm.adapter), "s"(a.rm.slot), "s"(a.rm.present16), "s"(a.xh), "s"(a.tlow16), "s"(a.gain),
                "s"(a.packed), "s"(a.eps), "s"(a.write_meta), "s"(a.pos_shift), "s"(a.n_seqs), "s"(ad),
                "s"(a.x), "s"(a.A), "s"(a.rank), "s"(a.T), "s"(a.st.src), "s"(a.st.dst), "s"(a.st.n16));
-  const bool lead = blockIdx.y == 0 && blockIdx.z == 0;
+  const bool lead = part == 0 && blockIdx.y == 0;
   const int row = min(row0 + r16, a.T - 1);
   const bool row_ok = row0 + r16 < a.T;
   const int k_lo = wave * (CH * 32) + kg * 8;  // this lane's first element; chunk u is at k_lo + 32 u
@@ -114,8 +131,6 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
   const int A_off = NC == 16 || r16 < NC ? (my_col * d + k_lo) * 2 : 0x7fff0000;      // (lanes without a column: out of range, they read zeros)
 #pragma unroll
   for (int u = 0; u < CH; ++u) br[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(A_rsrc, A_off, 64 * u, 0));
-  Carried<512> staged;
-  staged.load(a.st, tid, blockIdx.x == 0 && lead);      // (host memory: behind what everybody waits for)
 
   if (tid == 0) s_present = 0ull;
   if (tid < PREP_ROWS) { s_adapter[tid] = -1; s_scale[tid] = 0.f; }
@@ -151,7 +166,7 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
     if (tid < d / 8) s_gain[tid] = gown;
   }
   __syncthreads();
-  if (lead && tid == 0 && a.rm.present16 != nullptr) a.rm.present16[blockIdx.x] = s_present;
+  if (lead && tid == 0 && a.rm.present16 != nullptr) a.rm.present16[tile] = s_present;
   if (a.gain != nullptr) {
     float t = 0.f;
 #pragma unroll
@@ -165,7 +180,6 @@ __global__ __launch_bounds__(512, 2) void prep_few_kernel(PrepArgs a) {
 #pragma unroll
     for (int u = 0; u < CH; ++u) dst[xh_chunk(row, (k_lo >> 3) + 4 * u, d, a.packed)] = xr[u];
   }
-  staged.store(a.st, tid, blockIdx.x == 0 && lead);
   if (!((s_present >> ad) & 1)) return;
 
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -532,6 +546,7 @@ static void launch_prep_ch(const PrepArgs &a, hipStream_t s) {
   if (a.rank == 0 || a.A == nullptr || a.n_used == 0) {
     launch_norm<CH>(a, s);
   } else if (a.few == 2 || !lds_aligned(a.A) || (a.few == 1 && row_tiles * cols16 * a.n_used <= PREP_FEW)) {
+    const int carries = a.st.src != nullptr ? 1 : 0;      // (prep_few_kernel only)
     const dim3 narrow(1, (3 * a.rank + 7) / 8, a.n_used);
     const bool rows = CH >= 8 && cols16 * a.n_used <= PREP_NARROW;
     if (rows && a.T <= 2)
@@ -541,9 +556,9 @@ static void launch_prep_ch(const PrepArgs &a, hipStream_t s) {
     else if (rows && a.T <= 8)
       hipLaunchKernelGGL((prep_few_rows_kernel<CH < 8 ? 8 : CH, 8, 8>), narrow, dim3(512), 0, s, a);
     else if (row_tiles * cols16 * a.n_used <= PREP_NARROW)
-      hipLaunchKernelGGL((prep_few_kernel<CH, 8>), dim3(row_tiles, (3 * a.rank + 7) / 8, a.n_used), dim3(512), 0, s, a);
+      hipLaunchKernelGGL((prep_few_kernel<CH, 8>), dim3(row_tiles * ((3 * a.rank + 7) / 8) + carries, a.n_used), dim3(512), 0, s, a);
     else
-      hipLaunchKernelGGL((prep_few_kernel<CH, 16>), dim3(row_tiles, cols16, a.n_used), dim3(512), 0, s, a);
+      hipLaunchKernelGGL((prep_few_kernel<CH, 16>), dim3(row_tiles * cols16 + carries, a.n_used), dim3(512), 0, s, a);
   } else {
     launch_norm<CH>(a, s);
     launch_t_rows_mfma(a, s);
