@@ -42,14 +42,15 @@ __global__ __launch_bounds__(512) void gemm_mid_kernel(GemmArgs g, int tiles_m, 
   const int M = g.M, N = g.N;
   const int nk = g.K / 64 / g.k_splits;
   const int n_out = tiles_m * tiles_n, n_tiles = n_out * g.k_splits;      // (PARTIAL only: several workgroups per output tile)
-  // as in k_gemm_large.hip: an XCD takes a contiguous run of tiles, in patches of four row tiles by all column tiles
+  // As in k_gemm_large.hip: an XCD takes a contiguous run of tiles, in patches of eight row tiles (1024 rows, as there) by all column tiles.  Every patch reads the weights, which from
+  // about 240 MB on no cache holds until the next one does: gate/up of 513 rows in patches of four / so, us: 2 x 13824 x 5120 203 / 174, 2 x 28672 x 8192 595 / 523, 2 x 14336 x 4096 152 / 135.
   const int xcd = blockIdx.x & 7, per_xcd = gridDim.x >> 3;
   const int run0 = xcd * (n_tiles >> 3) + min(xcd, n_tiles & 7), run_n = (n_tiles >> 3) + (xcd < (n_tiles & 7) ? 1 : 0);
   const int in_run = blockIdx.x >> 3;
   if (in_run >= run_n) return;
   struct At { int m0, n0, split; };
   auto tile_at = [&](int i) {
-    constexpr int GM = 4;
+    constexpr int GM = 8;
     const int split = EPI == GEMM_EPI_PARTIAL ? (run0 + i) / n_out : 0, t = run0 + i - split * n_out;
     const int patch = t / (GM * tiles_n), first = patch * GM, gm = min(GM, tiles_m - first), in = t - patch * GM * tiles_n;
     return At{(first + in % gm) * BM, (in / gm) * BN, split};
